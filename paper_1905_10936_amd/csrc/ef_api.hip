@@ -17,7 +17,7 @@ struct ef_plan {
     int max_workers;
     int device;
     int spin_limit;
-    ef::CallState *d_state;         // calls made so far and the tags of the scratch sets: advanced on the device
+    ef::CallState *d_state;         // [2]: calls made so far and the tags of the scratch sets, advanced on the device; a call's snapshot of it
     std::vector<int64_t> offs_host;
     std::vector<int32_t> fb_host, lb_host;
     // What depends on the one-pass limit, which differs between the kernels (each is bounded by what
@@ -54,7 +54,7 @@ struct ef_plan {
     int32_t *d_tile_lb;
     unsigned long long *d_part;
     unsigned long long *d_ready;
-    unsigned int *d_list_cnt;       // [8]: defer_cnt[2], fin_cnt[2], ticket[2] (alternating between calls), done, unused
+    unsigned int *d_list_cnt;       // [6]: defer_cnt[2], fin_cnt[2], ticket[2] (alternating between calls)
     int worker_grid;                // workgroups of the persistent worker kernel
     int persistent;                 // worker: 1 pipelined persistent kernel, 0 one workgroup per tile
     int persistent_auto;            // what plan creation chose for this layout
@@ -338,7 +338,7 @@ int build_device(ef_plan *p)
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
     EF_HIP(hipMalloc(&p->d_ready, sizeof(unsigned long long) * ef::READY_STRIDE * (size_t)ntiles * nsets));
     EF_HIP(hipMemset(p->d_ready, 0, sizeof(unsigned long long) * ef::READY_STRIDE * (size_t)ntiles * nsets));
-    EF_HIP(hipMalloc(&p->d_list_cnt, sizeof(unsigned int) * 8));
+    EF_HIP(hipMalloc(&p->d_list_cnt, sizeof(unsigned int) * 6));
     EF_HIP(hipMalloc(&p->d_defer_list, sizeof(unsigned long long) * 2 * (size_t)ntiles * nsets));
     EF_HIP(hipMalloc(&p->d_fin_list, sizeof(unsigned long long) * max_cross * nsets));
     for (auto &r : p->role) {
@@ -367,9 +367,9 @@ int build_device(ef_plan *p)
         p->L.mixed_tiles = p->d_mixed;
         p->L.uniform_tiles = p->d_uniform;
     }
-    EF_HIP(hipMemset(p->d_list_cnt, 0, sizeof(unsigned int) * 8));
-    EF_HIP(hipMalloc(&p->d_state, sizeof(ef::CallState)));
-    EF_HIP(hipMemset(p->d_state, 0, sizeof(ef::CallState)));     // the zeroed partial words carry tag 0
+    EF_HIP(hipMemset(p->d_list_cnt, 0, sizeof(unsigned int) * 6));
+    EF_HIP(hipMalloc(&p->d_state, 2 * sizeof(ef::CallState)));
+    EF_HIP(hipMemset(p->d_state, 0, 2 * sizeof(ef::CallState)));     // the zeroed partial words carry tag 0
     p->L.offs = p->d_offs;
     p->L.tile_fb = p->d_tile_fb;
     p->L.tile_lb = p->d_tile_lb;
@@ -379,6 +379,7 @@ int build_device(ef_plan *p)
     p->X.fin_list = p->d_fin_list;
     p->X.list_cnt = p->d_list_cnt;
     p->X.state = p->d_state;
+    p->X.snapshot = p->d_state + 1;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
     // A block finishes in one pass if its tiles fit twice over into the

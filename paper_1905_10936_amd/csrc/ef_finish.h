@@ -93,7 +93,6 @@ __device__ __forceinline__ void advance_call(CallState *state, const Scratch &X,
     X.next_cnt[0] = 0u;
     X.next_cnt[2] = 0u;
     X.next_cnt[4] = 0u;
-    *X.done = 0u;
     state->calls = state->calls + 1u;
     if (X.set_base == 0) {
         state->worker_tags ^= used;
@@ -113,13 +112,17 @@ __device__ __forceinline__ void advance_call(CallState *state, const Scratch &X,
 //                        blocks with whole tiles have in mixed tiles);
 //   DEFER_WGS workgroups the same two jobs for what the main kernels gave up on at run time
 //                        (a gather or a wait that ran out): normally nothing.
-// Each workgroup strides over its list.  The last workgroup to finish steps the plan's call
-// state to the next call (no workgroup reads it after its first instructions).
+// Each workgroup strides over its list.  The first one also steps the plan's call state to the next
+// call: the others do not look at it, they go by the main kernel's snapshot.  (They used to count
+// themselves out on one word for that, at about 84 atomic adds per microsecond: with a workgroup for
+// each of 2000 parked segments the count alone took two thirds of this kernel's 36 us.)
 __global__ __launch_bounds__(THREADS) void k_tail(Layout L, ScratchRef R, TailArgs T)
 {
+    R.state = R.snapshot;
     const Scratch X = open_call(R);
     __shared__ SyncShared S;
     const int wg = blockIdx.x;
+    if (wg == 0 && threadIdx.x == 0) advance_call(T.state, X, T.nsets, T.lazy);
     if (wg < T.fin_wgs) {
         const int n = T.n_late * T.nsets;
         for (int i = wg; i < n; i += T.fin_wgs) {
@@ -183,18 +186,11 @@ __global__ __launch_bounds__(THREADS) void k_tail(Layout L, ScratchRef R, TailAr
             residual_segment(L, tile, which, T.err + (int64_t)(set - X.set_base) * T.err_stride, s);
         }
     }
-    // last one out steps the call state
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned before = atomicAdd(X.done, 1u);
-        if (before + 1u == gridDim.x) advance_call(T.state, X, T.nsets, T.lazy);
-    }
 }
 
 // A long per-layout list of parked segments (the whole tiles of blocks larger than fuse_limit when
 // the correction is not deferred) streams faster with one workgroup per item, dispatched in list
-// order, than through the strided loop of k_tail, and a grid of that size is too large for that
-// kernel's count of finished workgroups.  So this kernel runs after k_tail, with the scales taken
+// order, than through the strided loop of k_tail.  So this kernel runs after k_tail, with the scales taken
 // from the call's finished scale arrays.  One workgroup per (item, set).
 __global__ __launch_bounds__(THREADS) void k_residual_static(Layout L, const uint32_t *items, int n_items, float *err,
                                                              int64_t err_stride, const float *scales,

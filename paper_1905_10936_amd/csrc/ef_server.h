@@ -225,6 +225,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
     } else if constexpr (MIXED) {
         server_mixed_tile(L, X, A, tile, set, n_valid, S);
     }
+    snapshot_call(R);
 }
 
 }  // namespace ef

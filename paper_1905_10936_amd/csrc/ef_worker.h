@@ -263,6 +263,7 @@ void k_worker_uniform(Layout L, ScratchRef R, WorkerArgs A, int n_workers)
     prod.A = A;
     prod.X = &X;
     persistent_uniform(L, X, prod, n_workers, S, stage);
+    snapshot_call(R);
 }
 
 // All tiles of all workers in one launch, one workgroup per (tile, worker): the mixed tiles first
@@ -358,6 +359,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     } else if constexpr (MIXED) {
         worker_mixed_tile<MOM, QUAL>(L, X, A, Q, tile, worker, n_valid, S);
     }
+    snapshot_call(R);
 }
 
 }  // namespace ef
