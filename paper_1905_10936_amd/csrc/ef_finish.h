@@ -250,7 +250,7 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
     const uint32_t *s32 = reinterpret_cast<const uint32_t *>(signs);
     const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
     const int64_t n_hw = 2 * L.W;
-    const int *seg = reinterpret_cast<const int *>(S.val);
+    const uint16_t *seg = reinterpret_cast<const uint16_t *>(S.val);
     float4 xv4[SUBROWS], mv4[SUBROWS];
     load_tile(xt, xv4, n_valid);
     if (WD) load_tile(mtt, mv4, n_valid);

@@ -16,76 +16,149 @@ __device__ __forceinline__ float mean_of(float acc, float Mf, float Minv)
 
 constexpr int SERVER_CHUNK = 8;     // workers whose sign words are in flight together
 constexpr int SCALE_GROUP = 4;      // mixed tiles: workers whose scales are staged in LDS together ...
-constexpr int SCALE_STAGE = 2048;   // ... in this many floats
+constexpr int SCALE_STAGE = TILE / 2;   // ... in this many floats
+
+typedef unsigned vu4 __attribute__((ext_vector_type(4)));
+
+// Bit matrix transpose: h[u] holds worker u's sign bits of 16 consecutive elements (bit e: element
+// e); byte e of the result (element 0 in the lowest byte of .x) holds element e's bits of the eight
+// workers (bit u: worker u).  The bytes are gathered into two 8x8 bit matrices, each transposed by
+// swapping 1x1, 2x2 and 4x4 blocks across the diagonal.
+__device__ __forceinline__ vu4 transpose_signs(const unsigned (&h)[SERVER_CHUNK])
+{
+    unsigned lo[2], hi[2];          // [half]: rows 0-3 and rows 4-7 of the matrix of elements 8*half .. 8*half+7
+    {
+        // v_perm_b32: selector values 0-3 take bytes of the second operand, 4-7 of the first
+        const unsigned a = __builtin_amdgcn_perm(h[1], h[0], 0x05010400u), b = __builtin_amdgcn_perm(h[3], h[2], 0x05010400u);
+        const unsigned c = __builtin_amdgcn_perm(h[5], h[4], 0x05010400u), d = __builtin_amdgcn_perm(h[7], h[6], 0x05010400u);
+        lo[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+        lo[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        hi[0] = __builtin_amdgcn_perm(d, c, 0x05040100u);
+        hi[1] = __builtin_amdgcn_perm(d, c, 0x07060302u);
+    }
+    unsigned out[4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        unsigned x = lo[q], y = hi[q], t;
+        t = (x ^ (x >> 7)) & 0x00AA00AAu;
+        x ^= t ^ (t << 7);
+        t = (y ^ (y >> 7)) & 0x00AA00AAu;
+        y ^= t ^ (t << 7);
+        t = (x ^ (x >> 14)) & 0x0000CCCCu;
+        x ^= t ^ (t << 14);
+        t = (y ^ (y >> 14)) & 0x0000CCCCu;
+        y ^= t ^ (t << 14);
+        out[2 * q] = (x & 0x0F0F0F0Fu) | ((y & 0x0F0F0F0Fu) << 4);
+        out[2 * q + 1] = ((x >> 4) & 0x0F0F0F0Fu) | (y & 0xF0F0F0F0u);
+    }
+    return vu4{out[0], out[1], out[2], out[3]};
+}
+
+// LDS of server_values_whole, laid over TileShared::val.
+constexpr int SUM_TABLE = 256;                          // floats: one sum per pattern of eight signs
+constexpr int EXCHANGE_AT = SUM_TABLE;                  // 1 KiB per wavefront
+constexpr int NIBBLE_AT = EXCHANGE_AT + NWAVES * 256;   // SERVER_CHUNK x 16 float4
+static_assert(NIBBLE_AT + SERVER_CHUNK * 64 <= TILE, "fits into TileShared::val");
 
 // p~ of a tile that lies inside one block b (Algorithm 4, server: decode and add the M payloads
-// in worker order, divide by M, add the rescaled server residual tv).  The sign words of
-// SERVER_CHUNK workers are loaded together (one 32-bit word per worker and sub-row holds this
-// lane's 4 bits), the block's M scales come through scalar loads.  Decoding goes through a
-// small table in LDS: entry (u, nibble) holds the four values +-s_u that the nibble stands for,
-// so a lane gets its four addends of worker u with one bit-field extract and one 128-bit LDS
-// read (16 entries of 16 bytes cover the 64 banks once: no conflicts) instead of shifting and
-// selecting bit by bit (measured 0.57 -> 0.55 ms at M = 8, 0.70 -> 0.64 ms at M = 16 on 2^28
-// elements).  Called by every thread of the workgroup; S.val is free again on return.
+// in worker order, divide by M, add the rescaled server residual tv).  Inside a block every element's
+// sum over the first eight workers is one of 256 values, so the workgroup forms those 256 sums
+// once, thread t the one of sign pattern t (in worker order from +0, divided by M if that is all of
+// them: the operations Algorithm 4 writes, hence the same bits), and an element costs one LDS read.
+// The pattern of an element is a byte: a lane loads each worker's bits of 16 consecutive elements,
+// transposes the 8 x 16 bit matrix in registers and passes the bytes through LDS to the lanes that hold
+// the elements (inside the wavefront).  Per 16 elements about 90 vector instructions, whatever M <= 8,
+// where decoding worker by worker took 6 per four elements and worker and a division per element
+// (2^28 elements in blocks of 2^20, same occupancy: M = 8 515 -> 491 us, M = 7 510 -> 478).
+// Workers beyond the eighth are added one by one, eight at a time: entry (u, nibble) of a second table
+// holds the four values +-s_u that a nibble of worker u's bits stands for, so four addends cost
+// one bit-field extract and one 128-bit LDS read.
+// Called by every thread of the workgroup; S.val is free again on return.
 __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t tile_start, int32_t b,
                                                     const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], TileShared &S)
 {
     float acc[SUBROWS][4];
-#pragma unroll
-    for (int k = 0; k < SUBROWS; ++k)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
-
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(A.signs_in);
-    const int64_t in_hw = 2 * A.in_signs_stride;
-    const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
-    // half-word index of sub-row k for this lane: consecutive sub-rows are 8 half-words apart
-    const int64_t hw0 = (tile_start + local_base(0)) >> 5;
-
-    for (int i0 = 0; i0 < A.M; i0 += SERVER_CHUNK) {
-        uint32_t word[SERVER_CHUNK][SUBROWS];
+    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
+    const int64_t in_half = 4 * A.in_signs_stride;
+    const int64_t half0 = (tile_start >> 4) + threadIdx.x;      // this lane's 16 elements: 16 * threadIdx.x of the tile
+    const float r = A.r, Mf = A.Mf, Minv = A.Minv;
+    unsigned *exchange = reinterpret_cast<unsigned *>(S.val) + EXCHANGE_AT + wave_id() * 256;
+    {
+        unsigned h[SERVER_CHUNK];
         float sc[SERVER_CHUNK];
 #pragma unroll
         for (int u = 0; u < SERVER_CHUNK; ++u) {
-            const int i = min(i0 + u, A.M - 1);          // past M: a valid address whose value is not used
+            const int i = min(u, A.M - 1);               // past M: a valid address whose value is not used
+            h[u] = s16[(int64_t)i * in_half + half0];
             sc[u] = A.scales_in[(int64_t)i * A.in_scales_stride + b];
-#pragma unroll
-            for (int k = 0; k < SUBROWS; ++k) word[u][k] = s32[(int64_t)i * in_hw + hw0 + 8 * k];
         }
-        // table[u][nibble] = the four values (+-s_u) a nibble of worker u's sign bits stands for
-        float4 *table = reinterpret_cast<float4 *>(S.val);
-        if (i0 > 0) __syncthreads();
-        if (threadIdx.x < SERVER_CHUNK * 16) {
-            const int u = threadIdx.x >> 4, nib = threadIdx.x & 15;
-            float su = sc[0];
+        float sum = 0.0f;
 #pragma unroll
-            for (int q = 1; q < SERVER_CHUNK; ++q) su = (u == q) ? sc[q] : su;
-            table[threadIdx.x] = make_float4(signed_scale(su, nib & 1), signed_scale(su, nib & 2),
-                                             signed_scale(su, nib & 4), signed_scale(su, nib & 8));
-        }
+        for (int u = 0; u < SERVER_CHUNK; ++u)
+            if (u < A.M) sum = sum + signed_scale(sc[u], (threadIdx.x >> u) & 1u);
+        S.val[threadIdx.x] = A.M <= SERVER_CHUNK ? mean_of(sum, Mf, Minv) : sum;
+        *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) = transpose_signs(h);
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < SERVER_CHUNK; ++u) {
-            if (i0 + u < A.M) {
+        for (int k = 0; k < SUBROWS; ++k) {
+            const unsigned pat = exchange[64 * k + lane_id()];
 #pragma unroll
-                for (int k = 0; k < SUBROWS; ++k) {
-                    const float4 dv = table[u * 16 + ((word[u][k] >> sh) & 15u)];
-                    acc[k][0] = acc[k][0] + dv.x;
-                    acc[k][1] = acc[k][1] + dv.y;
-                    acc[k][2] = acc[k][2] + dv.z;
-                    acc[k][3] = acc[k][3] + dv.w;
+            for (int c = 0; c < 4; ++c) acc[k][c] = S.val[(pat >> (8 * c)) & 255u];
+        }
+    }
+    if (A.M > SERVER_CHUNK) {
+        float4 *table = reinterpret_cast<float4 *>(S.val + NIBBLE_AT);
+        const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
+        for (int i0 = SERVER_CHUNK; i0 < A.M; i0 += SERVER_CHUNK) {
+            unsigned h[SERVER_CHUNK];
+            float sc[SERVER_CHUNK];
+#pragma unroll
+            for (int u = 0; u < SERVER_CHUNK; ++u) {
+                const int i = min(i0 + u, A.M - 1);
+                h[u] = s16[(int64_t)i * in_half + half0];
+                sc[u] = A.scales_in[(int64_t)i * A.in_scales_stride + b];
+            }
+            if (i0 > SERVER_CHUNK) __syncthreads();      // the table is read no more
+            if (threadIdx.x < SERVER_CHUNK * 16) {
+                const int u = threadIdx.x >> 4, nib = threadIdx.x & 15;
+                float su = sc[0];
+#pragma unroll
+                for (int q = 1; q < SERVER_CHUNK; ++q) su = (u == q) ? sc[q] : su;
+                table[threadIdx.x] = make_float4(signed_scale(su, nib & 1), signed_scale(su, nib & 2),
+                                                 signed_scale(su, nib & 4), signed_scale(su, nib & 8));
+            }
+            *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) =
+                vu4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) {
+                // elements 256k + 4*lane .. +3 of the wavefront: half-word 16k + lane/4, nibble lane%4
+                const vu4 w = *reinterpret_cast<const vu4 *>(exchange + 4 * (16 * k + (lane_id() >> 2)));
+#pragma unroll
+                for (int u = 0; u < SERVER_CHUNK; ++u) {
+                    if (i0 + u < A.M) {
+                        const unsigned two = w[u >> 1];
+                        const float4 dv = table[u * 16 + ((two >> (sh + 16 * (u & 1))) & 15u)];
+                        acc[k][0] = acc[k][0] + dv.x;
+                        acc[k][1] = acc[k][1] + dv.y;
+                        acc[k][2] = acc[k][2] + dv.z;
+                        acc[k][3] = acc[k][3] + dv.w;
+                    }
                 }
             }
         }
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] = mean_of(acc[k][c], Mf, Minv);
     }
-    __syncthreads();            // the table's space is free again
-    const float r = A.r, Mf = A.Mf, Minv = A.Minv;
+    __syncthreads();            // S.val is free again
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
-        p[k].x = mean_of(acc[k][0], Mf, Minv) + r * tv[k].x;
-        p[k].y = mean_of(acc[k][1], Mf, Minv) + r * tv[k].y;
-        p[k].z = mean_of(acc[k][2], Mf, Minv) + r * tv[k].z;
-        p[k].w = mean_of(acc[k][3], Mf, Minv) + r * tv[k].w;
+        p[k].x = acc[k][0] + r * tv[k].x;
+        p[k].y = acc[k][1] + r * tv[k].y;
+        p[k].z = acc[k][2] + r * tv[k].z;
+        p[k].w = acc[k][3] + r * tv[k].w;
     }
 }
 
@@ -111,11 +184,11 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
 
     const int nseg = lb - fb + 1;
     build_segment_index(L, tile, n_valid, fb, nseg, S);
-    const int4 *seg4 = reinterpret_cast<const int4 *>(S.val);
+    const ushort4 *seg4 = reinterpret_cast<const ushort4 *>(S.val);
     // The scales of the tile's segments are staged in LDS, SCALE_GROUP workers at a time where
     // they fit (one coalesced read per worker instead of a gather per element), and looked up
     // there; a tile with more segments than the stage holds gathers them from global memory.
-    __shared__ float seg_scale[SCALE_STAGE];
+    float *seg_scale = S.val + TILE / 2;            // the index takes the first half
     const int group = nseg * SCALE_GROUP <= SCALE_STAGE ? SCALE_GROUP : nseg <= SCALE_STAGE ? 1 : 0;
     if (group) {
         for (int i0 = 0; i0 < A.M; i0 += group) {
@@ -142,7 +215,7 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
 #pragma unroll
                     for (int k = 0; k < SUBROWS; ++k) {
                         const unsigned nibble = (word[u][k] >> sh) & 0xFu;
-                        const int4 sg = seg4[local_base(k) >> 2];
+                        const ushort4 sg = seg4[local_base(k) >> 2];
                         acc[k][0] = acc[k][0] + signed_scale(sc_u[sg.x], nibble & 1u);
                         acc[k][1] = acc[k][1] + signed_scale(sc_u[sg.y], nibble & 2u);
                         acc[k][2] = acc[k][2] + signed_scale(sc_u[sg.z], nibble & 4u);
@@ -159,7 +232,7 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
                 const int64_t hw = hw0 + 8 * k;
                 const uint32_t word = (hw < n_hw) ? s32[(int64_t)i * in_hw + hw] : 0u;
                 const unsigned nibble = (word >> sh) & 0xFu;
-                const int4 sg = seg4[local_base(k) >> 2];
+                const ushort4 sg = seg4[local_base(k) >> 2];
                 acc[k][0] = acc[k][0] + signed_scale(sc_i[sg.x], nibble & 1u);
                 acc[k][1] = acc[k][1] + signed_scale(sc_i[sg.y], nibble & 2u);
                 acc[k][2] = acc[k][2] + signed_scale(sc_i[sg.z], nibble & 4u);
@@ -197,10 +270,13 @@ __device__ __forceinline__ void server_mixed_tile(const Layout &L, const Scratch
 // compressed like a worker's p; the workgroup of a whole tile waits in the kernel for its
 // block's scale.
 // MIXED = false: the layout has only whole tiles, and the code for the others is left out.
-// Six workgroups per CU (80 VGPRs): measured 0.58 ms against 0.63 ms at five and 0.73 ms at eight
-// (where a third of the tile spills) on 2^28 elements and 8 workers.
+// Bound by HBM and, where blocks wait for their scale, by the workgroups resident meanwhile.  Layouts of
+// whole tiles run eight workgroups per CU (64 VGPRs, 2^28 elements, 8 workers, blocks of 2^20: 457 us against
+// 465 at seven and 491 at six), the others seven: at eight the mixed tiles spill 39 registers (one
+// worker-payload set of the ResNet-50 layout, 7 workers: 80 us against 66 at seven and 67 at six; 354 M
+// elements in transformer blocks, 16 workers: 1180 us against 1017 and 1047).
 template <bool MIXED>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED ? 7 : 8, 8)))
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
     const Scratch X = open_call(R);

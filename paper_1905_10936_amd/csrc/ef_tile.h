@@ -924,13 +924,13 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const Layout &L, c
     }
 }
 
-// Fill S.val (read as int) with the segment index of every element of a mixed
-// tile (0 past the end of the vector), so that element j can look up scale[fb + seg].
+// Fill the first half of S.val (read as 16-bit integers) with the segment index of every element of a
+// mixed tile (0 past the end of the vector), so that element j can look up scale[fb + seg].
 __device__ __forceinline__ void build_segment_index(const Layout &L, int32_t tile, int n_valid, int32_t fb,
                                                     int nseg, TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
-    int *seg = reinterpret_cast<int *>(S.val);
+    uint16_t *seg = reinterpret_cast<uint16_t *>(S.val);
     if (threadIdx.x == 0) S.n_long = 0;
     __syncthreads();
     for (int j = n_valid + (int)threadIdx.x; j < TILE; j += THREADS) seg[j] = 0;
@@ -941,7 +941,7 @@ __device__ __forceinline__ void build_segment_index(const Layout &L, int32_t til
             S.long_list[atomicAdd(&S.n_long, 1)] = sg;
             continue;
         }
-        for (int j = lo; j < hi; ++j) seg[j] = sg;
+        for (int j = lo; j < hi; ++j) seg[j] = (uint16_t)sg;
     }
     __syncthreads();
     const int n_long = S.n_long;
@@ -949,7 +949,7 @@ __device__ __forceinline__ void build_segment_index(const Layout &L, int32_t til
         const int sg = S.long_list[q];
         const int lo = (int)max(L.offs[fb + sg] - tile_start, (int64_t)0);
         const int hi = (int)min(L.offs[fb + sg + 1] - tile_start, (int64_t)n_valid);
-        for (int j = lo + lane_id(); j < hi; j += 64) seg[j] = sg;
+        for (int j = lo + lane_id(); j < hi; j += 64) seg[j] = (uint16_t)sg;
     }
     __syncthreads();
 }
