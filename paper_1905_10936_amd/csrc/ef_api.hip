@@ -38,6 +38,7 @@ struct ef_plan {
     int sync_group;                 // tiles of a large block that are written out in step (ef_plan_set_sync_group)
     int lazy;                       // deferred correction on (ef_plan_set_lazy)
     ef_state *state;                // the library-held state that lives on this plan, if any
+    bool held;                      // a library-held state is, or is being, created
     // Host-side guard of the deferred mode: the residual buffers (workers, server) the last calls
     // left waiting for their correction, so that a call with other buffers is refused.  The
     // device-side CallState is what the kernels go by; this only catches misuse at the boundary.
@@ -66,6 +67,12 @@ struct ef_plan {
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
     double *d_qtile, *d_qpart;      // [max_workers][ntiles][2], [max_workers][2*ntiles][2]
+    // launches that fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
+    // counters, in one allocation (null: this layout has none)
+    int small_wgs;                  // workgroups of those kernels that are resident at once
+    void *d_small;
+    ef::SmallArgs small;
+    bool worker_kernel_auto;        // ef_plan_set_persistent has not been used to pick one
 };
 
 // Scratch of ef_compressor_quality_static: device memory that exists from the moment the library
@@ -188,6 +195,7 @@ void destroy_device(ef_plan *p)
     if (p->d_cross) (void)hipFree(p->d_cross);
     if (p->d_qtile) (void)hipFree(p->d_qtile);
     if (p->d_qpart) (void)hipFree(p->d_qpart);
+    if (p->d_small) (void)hipFree(p->d_small);
 }
 
 int64_t tiles_of_block(const ef_plan *p, int64_t b)
@@ -276,7 +284,9 @@ int refresh_limits_unguarded(ef_plan *p)
         // Layout::sync_group.  Both worker roles get the same limit: the buffers a call leaves
         // behind must fit the lists of whichever worker call comes next.
         ticket.fuse_limit = tiles.fuse_limit = p->persistent_forced ? 0 : LAZY_WAIT_LIMIT;
-        server.fuse_limit = 0;
+        // A layout of few tiles whose server residual the caller never sees is finished in one launch,
+        // where waiting is cheap.
+        server.fuse_limit = p->d_small && p->held ? ef::SMALL_SPAN : 0;
     } else {
         ticket.fuse_limit = clamp(p->lim_persistent);
         server.fuse_limit = clamp(p->lim_server);
@@ -299,6 +309,82 @@ int refresh_limits(ef_plan *p)
     } catch (const std::bad_alloc &) {
         return EF_ERR_ARG;
     }
+}
+
+// Records, start words and counters of the kernels for launches that fit on the GPU all at once, if the
+// layout has calls for them: few enough tiles, and no block of more tiles than a wavefront adds up.
+int build_small(ef_plan *p)
+{
+    int occ = 0, occ_s = 0;
+    EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
+    EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_s, ef::k_server_small, ef::SMALL_THREADS, 0));
+    int cus = 0;
+    EF_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    p->small_wgs = cus * (occ < occ_s ? occ : occ_s);
+    const int32_t ntiles = p->L.ntiles;
+    if (ntiles > p->small_wgs) return EF_OK;
+    const int64_t *o = p->offs_host.data();
+    const int64_t d = p->L.d;
+    for (int64_t b = 0; b < p->L.B; ++b)
+        if (tiles_of_block(p, b) > ef::SMALL_SPAN) return EF_OK;
+    std::vector<ef::SmallTile> tiles((size_t)ntiles);
+    std::vector<uint32_t> starts;
+    std::vector<uint16_t> rank;
+    for (int32_t t = 0; t < ntiles; ++t) {
+        const int64_t start = (int64_t)t * ef::TILE, end = start + ef::TILE;
+        const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
+        ef::SmallTile &r = tiles[(size_t)t];
+        r = ef::SmallTile();
+        r.fb = fb;
+        r.nseg = lb - fb + 1;
+        r.words = -1;
+        if (o[fb] < start || o[fb + 1] > end) {
+            r.flags |= ef::SMALL_HEAD;
+            r.head_t0 = (int32_t)(o[fb] / ef::TILE);
+            r.head_n = (int32_t)tiles_of_block(p, fb);
+            r.head_db = o[fb + 1] - o[fb];
+            if (o[fb] % ef::TILE) r.flags |= ef::SMALL_HEAD_SLOT;
+            if (o[fb + 1] <= end) r.flags |= ef::SMALL_WRITES_HEAD;
+        }
+        if (lb != fb && o[lb + 1] > end) {
+            r.flags |= ef::SMALL_TAIL;
+            r.tail_n = (int32_t)tiles_of_block(p, lb);
+            r.tail_db = o[lb + 1] - o[lb];
+        }
+        if (fb == lb && end <= d) continue;
+        r.words = (int32_t)(starts.size() / ef::SMALL_WORDS);
+        starts.resize(starts.size() + ef::SMALL_WORDS, 0u);
+        rank.resize(starts.size());
+        uint32_t *w = starts.data() + starts.size() - ef::SMALL_WORDS;
+        w[0] = 1u;
+        for (int32_t b = fb + 1; b <= lb; ++b) {
+            const int j = (int)(o[b] - start);
+            w[j >> 5] |= 1u << (j & 31);
+        }
+        unsigned before = 0;
+        for (int i = 0; i < ef::SMALL_WORDS; ++i) {
+            rank[starts.size() - ef::SMALL_WORDS + (size_t)i] = (uint16_t)before;
+            before += (unsigned)__builtin_popcount(w[i]);
+        }
+    }
+    const size_t at_done = sizeof(ef::SmallTile) * tiles.size();
+    const size_t at_starts = at_done + sizeof(unsigned) * (ef::DONE_GROUPS + 1) * ef::DONE_STRIDE;
+    const size_t at_rank = at_starts + sizeof(uint32_t) * starts.size();
+    std::vector<char> all(at_rank + sizeof(uint16_t) * rank.size(), 0);
+    memcpy(all.data(), tiles.data(), at_done);
+    if (!starts.empty()) {
+        memcpy(all.data() + at_starts, starts.data(), at_rank - at_starts);
+        memcpy(all.data() + at_rank, rank.data(), all.size() - at_rank);
+    }
+    EF_HIP(hipMalloc(&p->d_small, all.size()));
+    EF_HIP(hipMemcpy(p->d_small, all.data(), all.size(), hipMemcpyHostToDevice));
+    char *base = static_cast<char *>(p->d_small);
+    p->small.tiles = reinterpret_cast<const ef::SmallTile *>(base);
+    p->small.done = reinterpret_cast<unsigned *>(base + at_done);
+    p->small.starts = reinterpret_cast<const uint32_t *>(base + at_starts);
+    p->small.rank = reinterpret_cast<const uint16_t *>(base + at_rank);
+    p->small.state = p->d_state;
+    return EF_OK;
 }
 
 int build_device(ef_plan *p)
@@ -440,6 +526,10 @@ int build_device(ef_plan *p)
         EF_HIP(hipMalloc(&p->d_qtile, sizeof(double) * 2 * nt * nv));
     }
     {
+        int rc_small = build_small(p);
+        if (rc_small) return rc_small;
+    }
+    {
         double *unused = nullptr;       // the static scratch of this device, looked up once, ahead of the first call that needs it
         int rc_scratch = static_scratch(p->device, &unused);
         if (rc_scratch) return rc_scratch;
@@ -467,6 +557,25 @@ int worker_role(const ef_plan *plan, bool has_mom)
     const bool ticketed = plan->L.n_uniform && plan->persistent &&
                           (plan->lazy ? plan->persistent_forced != 0 : (has_mom || plan->persistent_forced));
     return ticketed ? ROLE_TICKET : ROLE_TILES;
+}
+
+// Does a call over nsets sets go to the kernels of ef_small.h?  Its workgroups have to be resident together, and no
+// block may be left for a second pass (a limit set by the caller, or that of the deferred mode).
+bool small_call(const ef_plan *plan, int role, int nsets)
+{
+    return plan->d_small && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs && plan->role[role].n_late == 0;
+}
+
+ef::SmallArgs small_args(const ef_plan *plan, int nsets, float *err, int64_t err_stride, float *scales, int64_t scales_stride)
+{
+    ef::SmallArgs Z = plan->small;
+    Z.nsets = nsets;
+    Z.lazy = plan->lazy;
+    Z.err = err;
+    Z.err_stride = err_stride;
+    Z.scales = scales;
+    Z.scales_stride = scales_stride;
+    return Z;
 }
 
 // Scratch argument of one call over the sets [set_base, set_base + nsets).  Everything that
@@ -575,6 +684,7 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
     p->d_lazy_scales = nullptr;
     p->lazy = 0;
     p->state = nullptr;
+    p->held = false;
     p->sync_group = 16;
     p->lazy_buf[0] = p->lazy_buf[1] = nullptr;
     p->lazy_stride_seen = 0;
@@ -592,6 +702,8 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
     p->d_cross = nullptr;
     p->n_cross = 0;
     p->d_qtile = p->d_qpart = nullptr;
+    p->d_small = nullptr;
+    p->worker_kernel_auto = true;
 
     try {
         p->offs_host.assign(block_offsets_host, block_offsets_host + B + 1);
@@ -749,6 +861,7 @@ int ef_plan_set_persistent(ef_plan *plan, int on)
     if (pending) return EF_ERR_ARG;
     plan->persistent = on < 0 ? plan->persistent_auto : (on ? 1 : 0);
     plan->persistent_forced = on > 0 ? 1 : 0;
+    plan->worker_kernel_auto = on < 0;
     return refresh_limits(plan);
 }
 
@@ -879,6 +992,16 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         if (n_workers > plan->lazy_sets_seen) plan->lazy_sets_seen = n_workers;
     }
     const CallScratch c = next_call(plan, 0, n_workers);
+    if (!quality && plan->worker_kernel_auto && small_call(plan, ROLE_TILES, n_workers)) {
+        const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::SMALL_THREADS);
+        const ef::SmallArgs Z = small_args(plan, n_workers, err, state_stride, scales, scales_stride);
+        if (has_mom)
+            hipLaunchKernelGGL(ef::k_worker_small<true>, grid, block, 0, s, plan->L, c.X, A, Z);
+        else
+            hipLaunchKernelGGL(ef::k_worker_small<false>, grid, block, 0, s, plan->L, c.X, A, Z);
+        EF_HIP(hipGetLastError());
+        return EF_OK;
+    }
     const int role = quality ? (int)ROLE_TILES : worker_role(plan, has_mom);
     const ef::Layout L = role_layout(plan, role);
     if (quality) {
@@ -984,6 +1107,13 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
         plan->lazy_buf[1] = server_err;
     }
     const CallScratch c = next_call(plan, plan->max_workers, 1);
+    if (small_call(plan, ROLE_SERVER, 1)) {
+        const ef::SmallArgs Z = small_args(plan, 1, server_err, 0, out_scales, 0);
+        hipLaunchKernelGGL(ef::k_server_small, dim3((unsigned)plan->L.ntiles), dim3(ef::SMALL_THREADS), 0, s, plan->L, c.X, A, Z,
+                           plan->max_workers);
+        EF_HIP(hipGetLastError());
+        return EF_OK;
+    }
     const ef::Layout L = role_layout(plan, ROLE_SERVER);
     if (L.n_mixed)
         hipLaunchKernelGGL(ef::k_server_tiles<true>, dim3((unsigned)L.ntiles), dim3(ef::THREADS), 0, s, L, c.X, A,
@@ -1017,7 +1147,11 @@ int ef_apply(const ef_plan *plan, float *params, const uint64_t *packed_signs, c
     if (!aligned(params, 16) || !aligned(packed_signs, 8) || !aligned(scales, 4)) return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    hipLaunchKernelGGL(ef::k_apply, grid, dim3(ef::THREADS), 0, s, plan->L, params, packed_signs, scales, eta);
+    if (plan->d_small)
+        hipLaunchKernelGGL(ef::k_apply_small<false>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
+                           (float *)nullptr, packed_signs, scales, eta, 0.0f, 0.0f);
+    else
+        hipLaunchKernelGGL(ef::k_apply, grid, dim3(ef::THREADS), 0, s, plan->L, params, packed_signs, scales, eta);
     EF_HIP(hipGetLastError());
     return EF_OK;
 }
@@ -1034,8 +1168,12 @@ int ef_apply_wd(const ef_plan *plan, float *params, float *decay_mom, const uint
         return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    hipLaunchKernelGGL(ef::k_apply_wd, grid, dim3(ef::THREADS), 0, s, plan->L, params, decay_mom, packed_signs,
-                       scales, eta, mu, lambda);
+    if (plan->d_small)
+        hipLaunchKernelGGL(ef::k_apply_small<true>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
+                           decay_mom, packed_signs, scales, eta, mu, lambda);
+    else
+        hipLaunchKernelGGL(ef::k_apply_wd, grid, dim3(ef::THREADS), 0, s, plan->L, params, decay_mom, packed_signs,
+                           scales, eta, mu, lambda);
     EF_HIP(hipGetLastError());
     return EF_OK;
 }
@@ -1098,10 +1236,15 @@ int ef_state_create(ef_plan *plan, int n_workers, ef_state **out, void *stream)
     *out = nullptr;
     if (n_workers < 1 || n_workers > plan->max_workers || plan->state) return EF_ERR_ARG;
     { const int rc_dev = on_plan_device(plan); if (rc_dev) return rc_dev; }
+    plan->held = true;
     int rc = set_lazy(plan, 1);             // refused (EF_ERR_ARG) while caller-owned buffers wait for a correction
-    if (rc) return rc;
-    ef_state *st = new (std::nothrow) ef_state();
-    if (!st) return EF_ERR_ARG;
+    ef_state *st = rc ? nullptr : new (std::nothrow) ef_state();
+    if (!st) {
+        plan->held = false;
+        if (rc) return rc;
+        (void)set_lazy(plan, 0);
+        return EF_ERR_ARG;
+    }
     st->plan = plan;
     st->n_workers = n_workers;
     st->stride = (plan->L.d + 3) / 4 * 4;
@@ -1121,6 +1264,7 @@ int ef_state_create(ef_plan *plan, int n_workers, ef_state **out, void *stream)
         if (st->err) (void)hipFree(st->err);
         if (st->server_err) (void)hipFree(st->server_err);
         delete st;
+        plan->held = false;
         (void)set_lazy(plan, 0);
         return hip_fail(e);
     }
@@ -1145,6 +1289,7 @@ int ef_state_destroy(ef_state *state)
     EF_HIP(hipGetLastError());
     plan->lazy_buf[0] = plan->lazy_buf[1] = nullptr;
     plan->lazy_sets_seen = 0;
+    plan->held = false;
     return set_lazy(plan, 0);
 }
 

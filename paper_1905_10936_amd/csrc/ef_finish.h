@@ -238,6 +238,24 @@ __global__ void k_flush_done(CallState *state, int set_base, int nsets)
 //   mt <- mu*mt + lambda*x ;  x <- x - eta*((Delta~ + mu*mt) + lambda*x),
 // one fp32 rounding per operation in the order written.
 template <bool WD>
+__device__ __forceinline__ void update_element(float &x, float &m, float delta, float eta, float mu, float lambda)
+{
+    if (WD) {
+        const float lx = lambda * x;
+        const float a = mu * m;
+        m = a + lx;
+        const float b = mu * m;
+        const float u1 = delta + b;
+        const float u = u1 + lx;
+        const float step = eta * u;
+        x = x - step;
+    } else {
+        const float u = eta * delta;
+        x = x - u;
+    }
+}
+
+template <bool WD>
 __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt, const uint64_t *signs,
                                            const float *scales, float eta, float mu, float lambda, TileShared &S)
 {
@@ -276,19 +294,7 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
             float s = s_uniform;
             if (fb != lb) s = scales[fb + ((j < n_valid) ? seg[j] : 0)];
             const float delta = signed_scale(s, (nibble >> c) & 1u);
-            if (WD) {
-                const float lx = lambda * xv[c];
-                const float a = mu * mv[c];
-                mv[c] = a + lx;
-                const float b = mu * mv[c];
-                const float u1 = delta + b;
-                const float u = u1 + lx;
-                const float step = eta * u;
-                xv[c] = xv[c] - step;
-            } else {
-                const float u = eta * delta;
-                xv[c] = xv[c] - u;
-            }
+            update_element<WD>(xv[c], mv[c], delta, eta, mu, lambda);
         }
         xv4[k] = make_float4(xv[0], xv[1], xv[2], xv[3]);
         if (WD) mv4[k] = make_float4(mv[0], mv[1], mv[2], mv[3]);

@@ -1,0 +1,457 @@
+// Kernels for launches that fit on the GPU all at once: see ef_tile.h for the tile scheme.
+//
+// A launch of a few hundred tiles is over before HBM or the vector units matter: its time is one
+// workgroup's chain of dependent memory round trips (about 0.5 to 1 us each), plus that of every kernel that
+// has to follow.  These kernels do the same work as k_worker_tiles / k_server_tiles / k_apply with a shorter
+// chain:
+//   * what a tile needs to know about its blocks comes in one record (SmallTile) and two words per 32
+//     elements (SmallArgs), written at plan creation, instead of tile -> block -> offsets lookups and an
+//     index built in LDS;
+//   * 1024 threads to a tile, four elements each;
+//   * every workgroup is resident (the host checks that), so all tiles of a block, mixed ones included,
+//     can wait for it in place; and they do not wait for a gatherer's answer, each adds up the block's partial
+//     sums itself (at most SMALL_SPAN of them: one wavefront, four words a lane);
+//   * no kernel follows: the last workgroup to finish steps the call state (and sees to the segments
+//     whose bounded wait ran out, normally none).
+#pragma once
+#include "ef_tile.h"
+#include "ef_worker.h"
+#include "ef_server.h"
+#include "ef_finish.h"
+
+namespace ef {
+
+constexpr int SMALL_THREADS = 1024;
+constexpr int SMALL_WAVES = SMALL_THREADS / 64;
+constexpr int SMALL_SPAN = 256;         // most tiles of a block that spans tiles
+constexpr int SMALL_WORDS = TILE / 32;  // start words per tile
+constexpr int DONE_GROUPS = 8;          // workgroups count themselves out on this many words ...
+constexpr int DONE_STRIDE = 32;         // ... a cache line apart, and these on one more
+
+struct SmallTile {
+    int32_t fb, nseg;           // first block and number of segments
+    int32_t words;              // which set of start words; < 0: a whole tile
+    int32_t flags;
+    int32_t head_t0, head_n;    // tiles of the first segment's block, if it is open (SMALL_HEAD)
+    int32_t tail_n;             // tiles of the last segment's block, if that one is (SMALL_TAIL): it starts in this tile
+    int32_t unused;
+    int64_t head_db, tail_db;   // elements of those blocks
+};
+enum {
+    SMALL_HEAD = 1,         // the first segment is open (a whole tile has no other)
+    SMALL_TAIL = 2,         // the last segment is open, and is not the first
+    SMALL_HEAD_SLOT = 4,    // the head block's partial in its first tile is in slot 1 (it starts inside that tile)
+    SMALL_WRITES_HEAD = 8,  // this tile is the head block's last: it writes the block's scale
+};
+
+struct SmallArgs {
+    const SmallTile *tiles;     // [ntiles]
+    const uint32_t *starts;     // [..][SMALL_WORDS] bit j: a segment starts at element j (the tile's first always does)
+    const uint16_t *rank;       // [..][SMALL_WORDS] starts before the word
+    unsigned *done;             // [DONE_GROUPS + 1][DONE_STRIDE], zero between calls
+    CallState *state;
+    int nsets;
+    int lazy;
+    float *err;                 // what advance_call and the segments left over need, as in TailArgs
+    int64_t err_stride;
+    float *scales;
+    int64_t scales_stride;
+};
+
+struct SmallShared {
+    double sum[TILE];           // segment sums; a whole tile: one row sum per thread
+    float scale[TILE];          // segment scales
+    double row_total[SMALL_WAVES];
+    int row_any[SMALL_WAVES];
+    int parked[2];              // head, tail: the wait ran out
+    double total;
+};
+
+// This thread's four elements among the tile's segments.
+struct SmallPlace {
+    unsigned starts;            // bit c: a segment starts at element c
+    int seg;                    // segment in progress before element 0 (-1: none)
+};
+__device__ __forceinline__ SmallPlace small_place(const SmallArgs &Z, const SmallTile &T)
+{
+    SmallPlace q;
+    const int i = T.words * SMALL_WORDS + (int)(threadIdx.x >> 3);
+    const unsigned word = Z.starts[i], sh = (threadIdx.x & 7u) * 4u;
+    q.starts = (word >> sh) & 15u;
+    q.seg = (int)Z.rank[i] + __popc(word & ((1u << sh) - 1u)) - 1;
+    return q;
+}
+
+__device__ __forceinline__ float4 small_load4(const float *base, int n_valid)
+{
+    const int j = 4 * (int)threadIdx.x;
+    return n_valid == TILE ? stream_load4(base + j) : guarded_load4(base, j, n_valid);
+}
+__device__ __forceinline__ void small_store4(float *base, int n_valid, float4 v)
+{
+    const int j = 4 * (int)threadIdx.x;
+    if (n_valid == TILE)
+        stream_store4(base + j, v);
+    else
+        guarded_store4(base, j, n_valid, v);
+}
+
+// Sign words (as store_signs): 16 lanes make one.
+__device__ __forceinline__ void small_signs(float4 p, int n_valid, uint64_t *signs, int64_t tile_start, int64_t W)
+{
+    const int l16 = lane_id() & 15, j = 4 * (int)threadIdx.x;
+    unsigned nib = (p.x >= 0.f ? 1u : 0u) | (p.y >= 0.f ? 2u : 0u) | (p.z >= 0.f ? 4u : 0u) | (p.w >= 0.f ? 8u : 0u);
+    if (j + 4 > n_valid) nib &= j < n_valid ? (1u << (n_valid - j)) - 1u : 0u;
+    const unsigned sh = (unsigned)(l16 & 7) * 4u;
+    unsigned lo = (l16 < 8) ? (nib << sh) : 0u, hi = (l16 >= 8) ? (nib << sh) : 0u;
+    lo |= row_move<EF_DPP_XOR1>(lo);
+    hi |= row_move<EF_DPP_XOR1>(hi);
+    lo |= row_move<EF_DPP_XOR2>(lo);
+    hi |= row_move<EF_DPP_XOR2>(hi);
+    lo |= row_move<EF_DPP_HALF_MIRROR>(lo);
+    hi |= row_move<EF_DPP_HALF_MIRROR>(hi);
+    lo |= row_move<EF_DPP_MIRROR>(lo);
+    hi |= row_move<EF_DPP_MIRROR>(hi);
+    const int64_t w = tile_start / 64 + (threadIdx.x >> 4);
+    if (l16 == 0 && w < W) signs[w] = ((uint64_t)hi << 32) | (uint64_t)lo;
+}
+
+// The block's partial sums as one wavefront sees them: lane i is in charge of tiles i, i + 64, ...
+struct SmallSpan {
+    int64_t t0;
+    int n, slot;                // slot of the first tile's word
+};
+__device__ __forceinline__ const unsigned long long *small_part(const unsigned long long *part, const SmallSpan &s, int i)
+{
+    return part + 2 * (s.t0 + i) + (i == 0 ? s.slot : 0);
+}
+// The order of sum_block_partials, which has 256 threads.
+__device__ __forceinline__ double small_total(const double (&v)[4])
+{
+    const double a = wave_sum(v[0]), b = wave_sum(v[1]), c = wave_sum(v[2]), d = wave_sum(v[3]);
+    return ((a + b) + c) + d;
+}
+// Waits (bounded) for the partials of all the block's tiles and adds them up.  One wavefront; own: the
+// word this workgroup has posted, whose value need not be fetched.
+__device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double own_value, const unsigned long long *part,
+                                             unsigned long long tag, int spin_limit, double *total)
+{
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned have = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = lane_id() + 64 * q;
+        if (i >= s.n) have |= 1u << q;
+        if (i == own) {
+            have |= 1u << q;
+            v[q] = own_value;
+        }
+    }
+    bool ok = false;
+    for (int it = 0; it < spin_limit; ++it) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!((have >> q) & 1u)) {
+                const unsigned long long w = __hip_atomic_load(small_part(part, s, lane_id() + 64 * q), __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+                if ((w >> 63) == tag) {
+                    v[q] = __longlong_as_double((long long)(w & ~TAG_BIT));
+                    have |= 1u << q;
+                }
+            }
+        }
+        if (__all(have == 15u)) {
+            ok = true;
+            break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    if (ok) *total = small_total(v);
+    return ok;
+}
+
+// A call that ran out of patience somewhere: scales not written and segments parked as p, seen to by the
+// first wavefront of the workgroup that finishes last (every partial sum has been posted by then).
+__device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &X, const SmallArgs &Z)
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    for (int kind = 0; kind < 2; ++kind) {
+        const unsigned n = __hip_atomic_load(kind ? X.defer_cnt : X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (unsigned i = 0; i < n; ++i) {
+            const unsigned long long it = kind ? X.defer_list[i] : X.fin_list[i];
+            const int set = kind ? (int)(it >> 33) : (int)(it >> 32);
+            const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
+            const int which = (int)(it & 1ull);
+            const int64_t b = kind ? (which ? L.tile_lb[tile] : L.tile_fb[tile]) : (int64_t)(it & 0xffffffffull);
+            const BlockSpan sp = block_span(L, b);
+            const unsigned long long *part = set_part(X, L, set);
+            double v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j = lane_id() + 64 * q;
+                v[q] = j < sp.n ? __longlong_as_double((long long)(part[part_index(sp.t0 + j, sp)] & ~TAG_BIT)) : 0.0;
+            }
+            const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
+            const int w = set - X.set_base;
+            if (!kind) {
+                if (lane_id() == 0) Z.scales[(int64_t)w * Z.scales_stride + b] = s;
+                continue;
+            }
+            const int64_t lo = max(sp.bs, (int64_t)tile * TILE), hi = min(sp.be, ((int64_t)tile + 1) * TILE);
+            float *e = Z.err + (int64_t)w * Z.err_stride;
+            for (int64_t j = lo + lane_id(); j < hi; j += 64) e[j] = residual(e[j], s);
+        }
+    }
+}
+
+// The workgroup is done (its wavefront 0 calls this): the last one to get here ends the call.
+__device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, const SmallArgs &Z)
+{
+    int last = 0;
+    if (lane_id() == 0) {
+        const unsigned n = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x, g = me % DONE_GROUPS;
+        const unsigned in_group = (n + DONE_GROUPS - 1 - g) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
+        if (atomicAdd(Z.done + g * DONE_STRIDE, 1u) + 1u == in_group) {
+            Z.done[g * DONE_STRIDE] = 0u;
+            if (atomicAdd(Z.done + DONE_GROUPS * DONE_STRIDE, 1u) + 1u == groups) {
+                Z.done[DONE_GROUPS * DONE_STRIDE] = 0u;
+                last = 1;
+            }
+        }
+    }
+    if (!__any(last)) return;
+    if (__hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+        __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        small_left_over(L, X, Z);
+    if (lane_id() == 0) advance_call(Z.state, X, Z.nsets, Z.lazy);
+}
+
+// Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
+// of the blocks that end here, e' = p - Delta.  db: elements of the block of segment threadIdx.x.
+__device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallArgs &Z, const SmallTile &T,
+                                               const SmallPlace &at, int64_t db, int n_valid, uint64_t *signs, float *scales_out,
+                                               float *err_tile, const Scratch &X, int set, SmallShared &S)
+{
+    const int32_t tile = blockIdx.x;
+    const int lane = lane_id(), wave = wave_id();
+    small_signs(p, n_valid, signs, (int64_t)tile * TILE, L.W);
+    const int j0 = 4 * (int)threadIdx.x;
+    const bool whole = T.words < 0;
+    const double a[4] = {j0 + 0 < n_valid ? fabsf(p.x) : 0.f, j0 + 1 < n_valid ? fabsf(p.y) : 0.f,
+                         j0 + 2 < n_valid ? fabsf(p.z) : 0.f, j0 + 3 < n_valid ? fabsf(p.w) : 0.f};
+    const unsigned long long tag = set_tag(X, set);
+    unsigned long long *part = set_part(X, L, set);
+    if (threadIdx.x < 2) S.parked[threadIdx.x] = 0;
+    if (whole) {
+        S.sum[threadIdx.x] = ((a[0] + a[1]) + a[2]) + a[3];
+        __syncthreads();
+        if (wave == 0) {
+            // the order of abs_sum and block_sum: a lane's four rows, the 64 lanes, the four quarters
+            double q[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                q[w] = ((S.sum[256 * w + lane] + S.sum[256 * w + 64 + lane]) + S.sum[256 * w + 128 + lane]) + S.sum[256 * w + 192 + lane];
+            S.total = small_total(q);
+        }
+    } else {
+        // Segmented sums.  r[c]: the sum from element 0, or the last start, to element c; T: the same from
+        // the last start of the row of 256 elements that this wavefront has.
+        const unsigned st = at.starts;
+        double r[4];
+        r[0] = a[0];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) r[c] = ((st >> c) & 1u) ? a[c] : r[c - 1] + a[c];
+        const unsigned long long any = __ballot(st != 0u);
+        const double t = segment_scan(r[3], any);
+        double carry = wave_shift(t);
+        if (lane == 63) {
+            S.row_total[wave] = t;
+            S.row_any[wave] = any != 0ull;
+        }
+        __syncthreads();
+        const int l16 = lane & 15;
+        const double rows = segment_scan16(S.row_total[l16], (unsigned)__ballot(S.row_any[l16]) & 0xffffu);
+        // read by all lanes, outside any branch: the lane that is read from has to have formed its value
+        const double below = read_lane(rows, (int)uniform_u32(wave ? wave - 1 : 0));
+        carry += (wave && !(any & ((1ull << lane) - 1ull))) ? below : 0.0;
+        int seg = at.seg;
+        double before = carry;
+        bool started = false;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if ((st >> c) & 1u) {
+                if (seg >= 0) S.sum[seg] = before;
+                ++seg;
+                started = true;
+            }
+            before = started ? r[c] : carry + r[c];
+        }
+        if (threadIdx.x == SMALL_THREADS - 1) S.sum[seg] = before;
+    }
+    __syncthreads();
+    // the open segments' sums go out first, then the closed segments' scales are formed while others post
+    const bool head = T.flags & SMALL_HEAD, tail = T.flags & SMALL_TAIL;
+    const double head_sum = whole ? S.total : S.sum[0], tail_sum = whole ? 0.0 : S.sum[T.nseg - 1];
+    const SmallSpan hs = {T.head_t0, T.head_n, (T.flags & SMALL_HEAD_SLOT) ? 1 : 0};
+    const SmallSpan ts = {tile, T.tail_n, 1};
+    if (head) store_partial(head_sum, 0, tile, L, X, set);
+    if (tail) store_partial(tail_sum, 1, tile, L, X, set);
+    for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
+        if ((sg == 0 && head) || (sg == T.nseg - 1 && tail)) continue;
+        if (sg >= SMALL_THREADS) db = L.offs[T.fb + sg + 1] - L.offs[T.fb + sg];
+        const float sc = (float)((whole ? S.total : S.sum[sg]) / (double)db);
+        S.scale[sg] = sc;
+        scales_out[T.fb + sg] = sc;
+    }
+    if ((wave == 0 && head) || (wave == 1 && tail)) {
+        const SmallSpan &sp = wave ? ts : hs;
+        double total = 0.0;
+        const bool ok = small_gather(sp, tile - (int)sp.t0, wave ? tail_sum : head_sum, part, tag, X.spin_limit, &total);
+        const int sg = wave ? T.nseg - 1 : 0;
+        if (lane == 0) {
+            const float sc = (float)(total / (double)(wave ? T.tail_db : T.head_db));
+            S.scale[sg] = sc;
+            S.parked[wave] = !ok;
+            if (wave == 0 && (T.flags & SMALL_WRITES_HEAD)) {
+                if (ok)
+                    scales_out[T.fb] = sc;
+                else
+                    X.fin_list[atomicAdd(X.fin_cnt, 1u)] = ((unsigned long long)set << 32) | (unsigned long long)T.fb;
+            }
+            if (!ok)
+                X.defer_list[atomicAdd(X.defer_cnt, 1u)] =
+                    ((unsigned long long)set << 33) | ((unsigned long long)tile << 1) | (unsigned)(sg > 0 ? 1 : 0);
+        }
+    }
+    __syncthreads();
+    const int park_head = S.parked[0], park_tail = S.parked[1];
+    int seg = whole ? 0 : at.seg;
+    float v[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        seg += (int)((at.starts >> c) & 1u);     // a whole tile has no start bits
+        const float e = residual(v[c], S.scale[seg]);
+        const bool keep = (park_head && seg == 0) || (park_tail && seg == T.nseg - 1);
+        v[c] = keep ? v[c] : e;
+    }
+    small_store4(err_tile, n_valid, make_float4(v[0], v[1], v[2], v[3]));
+    if (park_head | park_tail) {
+        // whoever ends the call reads what was parked, and the list entry
+        __threadfence();
+        __syncthreads();
+        __threadfence();
+    }
+    if (wave == 0) small_finish(L, X, Z);
+}
+
+template <bool MOM>
+__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
+{
+    __shared__ SmallShared S;
+    const Scratch X = open_call(R);
+    const int32_t tile = blockIdx.x;
+    const int worker = blockIdx.y;
+    const SmallTile T = Z.tiles[tile];
+    const int n_valid = tile_valid(L, tile);
+    const int64_t start = (int64_t)tile * TILE;
+    float *mt = MOM ? A.mom + (int64_t)worker * A.state_stride + start : nullptr;
+    float *et = A.err + (int64_t)worker * A.state_stride + start;
+    const float4 g = small_load4(A.grad + (int64_t)worker * A.grad_stride + start, n_valid);
+    float4 m = g, e = small_load4(et, n_valid);
+    if (MOM) m = small_load4(mt, n_valid);
+    SmallPlace at = {0u, -1};
+    int64_t db = 1;
+    if (T.words >= 0) at = small_place(Z, T);
+    if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
+    worker_values4<MOM>(g, m, e, A.mu, A.r);
+    if (MOM) small_store4(mt, n_valid, m);
+    small_compress(e, L, Z, T, at, db, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+                   A.scales + (int64_t)worker * A.scales_stride, et, X, worker, S);
+}
+
+constexpr int SMALL_CHUNK = 4;      // workers whose payloads are in flight together
+
+__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
+{
+    __shared__ SmallShared S;
+    const Scratch X = open_call(R);
+    const int32_t tile = blockIdx.x;
+    const SmallTile T = Z.tiles[tile];
+    const int n_valid = tile_valid(L, tile);
+    const int64_t start = (int64_t)tile * TILE;
+    float *et = A.err + start;
+    const float4 te = small_load4(et, n_valid);
+    SmallPlace at = {0u, -1};
+    int64_t db = 1;
+    if (T.words >= 0) at = small_place(Z, T);
+    if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
+    int seg[4];
+    {
+        int sg = T.words >= 0 ? at.seg : 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) seg[c] = sg += (int)((at.starts >> c) & 1u);
+    }
+    // this thread's four sign bits are in half-word hw of every payload
+    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(A.signs_in);
+    const int64_t hw = (start >> 5) + (threadIdx.x >> 3);
+    const bool in = hw < 2 * L.W;
+    const unsigned sh = (threadIdx.x & 7u) * 4u;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
+        uint32_t word[SMALL_CHUNK];
+        float sc[SMALL_CHUNK][4];
+#pragma unroll
+        for (int u = 0; u < SMALL_CHUNK; ++u) {
+            const int i = min(i0 + u, A.M - 1);              // past M: loaded, not used
+            const float *sc_i = A.scales_in + (int64_t)i * A.in_scales_stride + T.fb;
+            word[u] = in ? s32[2 * (int64_t)i * A.in_signs_stride + hw] : 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sc[u][c] = sc_i[seg[c]];
+        }
+#pragma unroll
+        for (int u = 0; u < SMALL_CHUNK; ++u)
+            if (i0 + u < A.M) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[u][c], (word[u] >> (sh + c)) & 1u);
+            }
+    }
+    float4 p;
+    p.x = mean_of(acc[0], A.Mf, A.Minv) + A.r * te.x;
+    p.y = mean_of(acc[1], A.Mf, A.Minv) + A.r * te.y;
+    p.z = mean_of(acc[2], A.Mf, A.Minv) + A.r * te.z;
+    p.w = mean_of(acc[3], A.Mf, A.Minv) + A.r * te.w;
+    small_compress(p, L, Z, T, at, db, n_valid, A.signs, A.scales, et, X, set, S);
+}
+
+// Parameter update (see apply_tile), one workgroup of 1024 threads per tile.
+template <bool WD>
+__global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallArgs Z, float *x, float *mt, const uint64_t *signs,
+                                                               const float *scales, float eta, float mu, float lambda)
+{
+    const int32_t tile = blockIdx.x;
+    const SmallTile T = Z.tiles[tile];
+    const int n_valid = tile_valid(L, tile);
+    const int64_t start = (int64_t)tile * TILE;
+    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(signs);
+    const int64_t hw = (start >> 5) + (threadIdx.x >> 3);
+    const float4 x4 = small_load4(x + start, n_valid);
+    const uint32_t word = hw < 2 * L.W ? s32[hw] : 0u;
+    float4 m4 = x4;
+    if (WD) m4 = small_load4(mt + start, n_valid);
+    SmallPlace at = {0u, 0};
+    if (T.words >= 0) at = small_place(Z, T);
+    float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
+    int seg = at.seg;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        seg += (int)((at.starts >> c) & 1u);
+        const float delta = signed_scale(scales[T.fb + seg], (word >> ((threadIdx.x & 7u) * 4u + c)) & 1u);
+        update_element<WD>(xv[c], mv[c], delta, eta, mu, lambda);
+    }
+    small_store4(x + start, n_valid, make_float4(xv[0], xv[1], xv[2], xv[3]));
+    if (WD) small_store4(mt + start, n_valid, make_float4(mv[0], mv[1], mv[2], mv[3]));
+}
+
+}  // namespace ef

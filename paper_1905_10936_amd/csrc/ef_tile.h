@@ -327,6 +327,68 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// Segmented sums along lanes.  t: a lane's sum since the last start among its own elements (all of
+// them if none of its elements starts a segment); `any`: the lanes with a start.  Returns the sum since the
+// last start at or before the lane's last element, from lane 0 on if there is none, as a fixed tree
+// over the lanes: Hillis-Steele steps, in which a lane takes in the value `off` lanes below only if no start
+// lies in between.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double row_fetch(double v)      // 0 where there is no such lane, or in rows not in ROWS
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+#define EF_DPP_ROW_SHR(n) (0x110 + (n))     // lane i <- lane i-n of its row of 16
+#define EF_DPP_WAVE_SHR1 0x138              // lane i <- lane i-1
+#define EF_DPP_BCAST15 0x142                // a row <- the last lane of the row below
+#define EF_DPP_BCAST31 0x143                // lanes 32-63 <- lane 31
+__device__ __forceinline__ double segment_scan16(double t, unsigned any)    // over each row of 16 lanes by itself
+{
+    const int l = lane_id() & 15;
+    const unsigned le = any & ((2u << l) - 1u);
+    const int dist = le ? l - (31 - __clz((int)le)) : 16;      // lanes back to the last start
+    double n;
+    n = row_fetch<EF_DPP_ROW_SHR(1), 0xf>(t);
+    t += dist >= 1 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(2), 0xf>(t);
+    t += dist >= 2 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(4), 0xf>(t);
+    t += dist >= 4 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(8), 0xf>(t);
+    t += dist >= 8 ? n : 0.0;
+    return t;
+}
+__device__ __forceinline__ double segment_scan(double t, unsigned long long any)
+{
+    const int l = lane_id();
+    const unsigned long long le = any & (~0ull >> (63 - l));
+    const int dist = le ? l - (63 - __clzll((long long)le)) : 64;
+    double n;
+    n = row_fetch<EF_DPP_ROW_SHR(1), 0xf>(t);
+    t += dist >= 1 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(2), 0xf>(t);
+    t += dist >= 2 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(4), 0xf>(t);
+    t += dist >= 4 ? n : 0.0;
+    n = row_fetch<EF_DPP_ROW_SHR(8), 0xf>(t);
+    t += dist >= 8 ? n : 0.0;
+    n = row_fetch<EF_DPP_BCAST15, 0xa>(t);          // rows 1 and 3 take in the row below whole
+    t += dist > (l & 15) ? n : 0.0;
+    n = row_fetch<EF_DPP_BCAST31, 0xc>(t);          // the upper half takes in the lower
+    t += dist > (l & 31) ? n : 0.0;
+    return t;
+}
+__device__ __forceinline__ double wave_shift(double t) { return row_fetch<EF_DPP_WAVE_SHR1, 0xf>(t); }
+__device__ __forceinline__ double read_lane(double v, int lane)             // lane: the same in all lanes
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Workgroup sum in a fixed order; every thread gets the same bits.
 __device__ __forceinline__ double block_sum(double v, double *red)
 {
@@ -392,7 +454,7 @@ __device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_va
     }
 }
 
-// fp64 sum of |p| over the thread's valid elements
+// fp64 sum of |p| over the thread's valid elements, sub-row by sub-row
 __device__ __forceinline__ double abs_sum(const float4 (&p)[SUBROWS], int n_valid)
 {
     double acc = 0.0;
@@ -400,8 +462,10 @@ __device__ __forceinline__ double abs_sum(const float4 (&p)[SUBROWS], int n_vali
     for (int k = 0; k < SUBROWS; ++k) {
         const int lb0 = local_base(k);
         const float a[4] = {fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w)};
+        double row = 0.0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc += (n_valid == TILE || lb0 + c < n_valid) ? (double)a[c] : 0.0;
+        for (int c = 0; c < 4; ++c) row += (n_valid == TILE || lb0 + c < n_valid) ? (double)a[c] : 0.0;
+        acc += row;
     }
     return acc;
 }

@@ -12,30 +12,30 @@ namespace ef {
 // with the new momentum, e with p.  !MOM (Algorithm 3, no momentum buffer):
 // p = g + r*e; m is not touched.
 template <bool MOM>
+__device__ __forceinline__ void worker_values4(const float4 &g, float4 &m, float4 &e, float mu, float r)
+{
+    if (!MOM) {
+        e.x = g.x + r * e.x;
+        e.y = g.y + r * e.y;
+        e.z = g.z + r * e.z;
+        e.w = g.w + r * e.w;
+        return;
+    }
+    m.x = mu * m.x + g.x;
+    m.y = mu * m.y + g.y;
+    m.z = mu * m.z + g.z;
+    m.w = mu * m.w + g.w;
+    e.x = (mu * m.x + g.x) + r * e.x;
+    e.y = (mu * m.y + g.y) + r * e.y;
+    e.z = (mu * m.z + g.z) + r * e.z;
+    e.w = (mu * m.w + g.w) + r * e.w;
+}
+template <bool MOM>
 __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4 (&m)[SUBROWS], float4 (&e)[SUBROWS],
                                               float mu, float r)
 {
-    if (!MOM) {
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) {
-            e[k].x = g[k].x + r * e[k].x;
-            e[k].y = g[k].y + r * e[k].y;
-            e[k].z = g[k].z + r * e[k].z;
-            e[k].w = g[k].w + r * e[k].w;
-        }
-        return;
-    }
-#pragma unroll
-    for (int k = 0; k < SUBROWS; ++k) {
-        m[k].x = mu * m[k].x + g[k].x;
-        m[k].y = mu * m[k].y + g[k].y;
-        m[k].z = mu * m[k].z + g[k].z;
-        m[k].w = mu * m[k].w + g[k].w;
-        e[k].x = (mu * m[k].x + g[k].x) + r * e[k].x;
-        e[k].y = (mu * m[k].y + g[k].y) + r * e[k].y;
-        e[k].z = (mu * m[k].z + g[k].z) + r * e[k].z;
-        e[k].w = (mu * m[k].w + g[k].w) + r * e[k].w;
-    }
+    for (int k = 0; k < SUBROWS; ++k) worker_values4<MOM>(g[k], m[k], e[k], mu, r);
 }
 
 // Mixed tiles of all workers, one workgroup per (tile, worker).  Runs before

@@ -1,0 +1,128 @@
+"""Calls whose workgroups fit on the GPU all at once run kernels of their own (csrc/ef_small.h).  They are
+the plan's choice, so nothing is forced here.  Same bar as the other parity tests: the oracle, stage by stage."""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_10936_amd as ef
+from tests.parity_util import F, GpuState, synced_step
+from tests.test_parity_gpu import LAYOUTS, _offs
+
+pytestmark = pytest.mark.gpu
+
+T = 4096
+# 256 tiles is the longest block those kernels take; 512 workgroups is what a GPU of 256 units keeps resident
+EDGES = {
+    "span_256": [100, 255 * T + 50, 3],
+    "span_257": [100, 256 * T + 50, 3],
+    "span_65": [7, 64 * T + 9, T - 3],
+    "span_129_aligned": [129 * T, 5],
+    "wgs_170x3": [3 * T + 1] * 56 + [1000],
+    "wgs_171x3": [3 * T + 1] * 57 + [100],
+    "rows_of_256": [255, 1, 256, 257, 1023, 1, 1, 3, 60, 64, 65, 2 * T, 769],
+    "last_tile_ragged": [2 * T, 4094],
+}
+ALL = dict(LAYOUTS, **EDGES)
+
+
+@pytest.mark.parametrize("spin", [None, 0])
+@pytest.mark.parametrize("name", list(ALL))
+def test_small_launches_against_the_oracle(name, spin):
+    """spin = 0: every wait gives up, so the last workgroup finishes every open segment."""
+    offs = _offs(ALL[name])
+    d, M = int(offs[-1]), 3
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    st = GpuState(offs, M, x0=rng.standard_normal(d).astype(F), pad=1)
+    st.plan.set_persistent(None)
+    if spin is not None:
+        st.plan.tune(spin_limit=spin)
+    eta_prev, stats = 0.0, {}
+    for t, eta in enumerate([0.1, 0.05]):
+        g = rng.standard_normal((M, d)).astype(F)
+        g[rng.random((M, d)) < 0.05] = 0.0
+        st.set_grads(g)
+        synced_step(st, 0.9, eta_prev, eta, stats, "%s step %d" % (name, t))
+        parked, late = st.plan.last_fallbacks()
+        spanning = ((offs[1:] - 1) // T > offs[:-1] // T).any()
+        assert (parked > 0 and late > 0) if spin == 0 and spanning else spin == 0 or (parked, late) == (0, 0)
+        eta_prev = eta
+    assert stats["scales_not_bit_equal"] == 0
+
+
+@pytest.mark.parametrize("M", [1, 2, 4, 5, 9, 64])
+def test_small_server_worker_counts_and_fused_messages(M):
+    offs = _offs(EDGES["rows_of_256"])
+    d = int(offs[-1])
+    rng = np.random.default_rng(M)
+    st = GpuState(offs, M, fused=M % 2 == 1)
+    st.plan.set_persistent(None)
+    for t, eta in enumerate([0.1, 0.2]):
+        st.set_grads(rng.standard_normal((M, d)).astype(F))
+        synced_step(st, 0.5, 0.1 * t, eta, None, "M=%d step %d" % (M, t))
+
+
+def test_small_and_general_kernels_share_a_plan():
+    """Calls on one plan alternate between the two families (the choice of the worker kernel is changed in
+    between), and replays of a captured iteration stand between them."""
+    offs = _offs(LAYOUTS["mixed_tiny_and_big"])
+    d, M = int(offs[-1]), 2
+    rng = np.random.default_rng(3)
+    st = GpuState(offs, M)
+    st.plan.set_persistent(None)
+
+    def step(eta_prev, eta):
+        ef.ef_worker_step(st.plan, st.g, st.m, st.e, 0.9, eta_prev, eta, st.ws, st.wc)
+        ef.ef_server_step(st.plan, M, st.ws, st.wc, st.te, eta_prev, eta, st.ss, st.sc)
+        ef.ef_apply(st.plan, st.x, st.ss, st.sc, eta)
+
+    def fresh():
+        st.set_grads(rng.standard_normal((M, d)).astype(F))
+
+    fresh()
+    synced_step(st, 0.9, 0.0, 0.1, None, "first")
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        step(0.1, 0.1)
+    for k, choice in enumerate([None, False, None, True, None]):
+        fresh()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        st.plan.set_persistent(choice)
+        fresh()
+        synced_step(st, 0.9, 0.1, 0.1, None, "choice %s after replay %d" % (choice, k))
+    # the replay itself against the eager calls of another plan
+    other = GpuState(offs, M)
+    other.plan.set_persistent(False)
+    for name in ("g", "m", "e", "te", "x"):
+        getattr(other, name).copy_(getattr(st, name))
+    graph.replay()
+    synced_step(other, 0.9, 0.1, 0.1, None, "beside the replay")
+    torch.cuda.synchronize()
+    for name in ("ws", "wc", "ss", "sc", "m", "e", "te", "x"):
+        assert torch.equal(getattr(st, name), getattr(other, name)), name
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+def test_small_update_with_weight_decay_and_the_momentum_free_worker(mu):
+    import oracle
+    offs = _offs(EDGES["rows_of_256"])
+    d = int(offs[-1])
+    rng = np.random.default_rng(8)
+    st = GpuState(offs, 1)
+    st.plan.set_persistent(None)
+    st.set_grads(rng.standard_normal((1, d)).astype(F))
+    e0 = rng.standard_normal(d).astype(F)
+    st.e[0, :d].copy_(torch.as_tensor(e0))
+    ef.ef_worker_step_sgd(st.plan, st.g, st.e, 0.1, 0.2, st.ws, st.wc)
+    e_ref = e0.copy()
+    s_ref, c_ref = oracle.worker_step_sgd(st.g[0, :d].cpu().numpy(), e_ref, offs, F(0.1), F(0.2))
+    assert np.array_equal(st.ws[0].cpu().numpy().view(np.uint64), s_ref)
+    assert np.array_equal(st.wc[0].cpu().numpy(), c_ref) and np.array_equal(st.e[0, :d].cpu().numpy(), e_ref)
+    x, m = rng.standard_normal(d).astype(F), rng.standard_normal(d).astype(F)
+    xd, md = torch.as_tensor(x).cuda(), torch.as_tensor(m).cuda()
+    ef.ef_apply_wd(st.plan, xd, md, st.ws[0], st.wc[0], 0.1, mu, 1e-3)
+    oracle.apply_wd(x, m, s_ref, c_ref, offs, F(0.1), F(mu), F(1e-3))
+    assert np.array_equal(xd.cpu().numpy(), x) and np.array_equal(md.cpu().numpy(), m)
