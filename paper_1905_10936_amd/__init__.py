@@ -40,6 +40,9 @@ DEBUG_SYMBOLS = (
 )
 
 
+_Tensor, _f32, _f64, _u8 = torch.Tensor, torch.float32, torch.float64, torch.uint8
+
+
 class EfError(RuntimeError):
     def __init__(self, code, text):
         super().__init__("libef error %d: %s" % (code, text))
@@ -135,24 +138,33 @@ def ef_strerror(code):
 
 
 def _check(rc):
-    if rc != EF_OK:
+    if rc:
         raise EfError(rc, ef_strerror(rc))
 
 
+# The raw handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object
+# through half a dozen Python calls (2.5 us), which three calls an iteration would feel on a small layout.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(_current_device())
 
 
 def _ptr(t, dtype, name):
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    """Address of a contiguous device tensor of that type (ctypes turns the integer into the pointer argument)."""
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA/HIP torch tensor" % name)
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError("%s must have dtype %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise TypeError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stride(t, d, name):
@@ -240,12 +252,12 @@ def ef_flush(plan, err=None, server_err=None, stream=None):
     if err is not None:
         n = 1 if err.dim() == 1 else err.shape[0]
         ss = _stride(err, plan.d, "err")
-        ep = _ptr(err, torch.float32, "err")
+        ep = _ptr(err, _f32, "err")
     sp = None
     if server_err is not None:
         if server_err.numel() != plan.d:
             raise TypeError("server_err must hold d entries")
-        sp = _ptr(server_err, torch.float32, "server_err")
+        sp = _ptr(server_err, _f32, "server_err")
     _check(lib().ef_flush(plan._h, n, ep, ss, sp, _stream_ptr(stream)))
 
 
@@ -262,11 +274,11 @@ def ef_worker_step(plan, grad, mom, err, mu, eta_prev, eta, packed_signs, scales
         raise TypeError("mom and err must share shape and stride")
     if packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B:
         raise TypeError("packed_signs must hold n*W words and scales n*B floats")
-    rc = lib().ef_worker_step(plan._h, n, _ptr(grad, torch.float32, "grad"), gs,
-                              _ptr(mom, torch.float32, "mom"), _ptr(err, torch.float32, "err"), ss,
+    rc = lib().ef_worker_step(plan._h, n, _ptr(grad, _f32, "grad"), gs,
+                              _ptr(mom, _f32, "mom"), _ptr(err, _f32, "err"), ss,
                               float(mu), float(eta_prev), float(eta),
                               _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                              _ptr(scales, torch.float32, "scales"), _stream_ptr(stream))
+                              _ptr(scales, _f32, "scales"), _stream_ptr(stream))
     _check(rc)
 
 
@@ -279,11 +291,11 @@ def ef_worker_step_quality(plan, grad, mom, err, mu, eta_prev, eta, packed_signs
         raise TypeError("mom and err must share shape and stride")
     if packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B or quality.numel() != 2 * n:
         raise TypeError("packed_signs must hold n*W words, scales n*B floats, quality 2*n doubles")
-    rc = lib().ef_worker_step_quality(plan._h, n, _ptr(grad, torch.float32, "grad"), gs,
-                                      _ptr(mom, torch.float32, "mom"), _ptr(err, torch.float32, "err"), ss,
+    rc = lib().ef_worker_step_quality(plan._h, n, _ptr(grad, _f32, "grad"), gs,
+                                      _ptr(mom, _f32, "mom"), _ptr(err, _f32, "err"), ss,
                                       float(mu), float(eta_prev), float(eta),
                                       _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                                      _ptr(scales, torch.float32, "scales"), _ptr(quality, torch.float64, "quality"),
+                                      _ptr(scales, _f32, "scales"), _ptr(quality, _f64, "quality"),
                                       _stream_ptr(stream))
     _check(rc)
 
@@ -295,19 +307,19 @@ def ef_server_step(plan, M, packed_signs, scales, server_err, eta_prev, eta, out
     if server_err.numel() != plan.d or out_signs.numel() != plan.W or out_scales.numel() != plan.B:
         raise TypeError("server_err/out_signs/out_scales must hold d/W/B entries")
     rc = lib().ef_server_step(plan._h, int(M), _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                              _ptr(scales, torch.float32, "scales"),
-                              _ptr(server_err, torch.float32, "server_err"), float(eta_prev), float(eta),
+                              _ptr(scales, _f32, "scales"),
+                              _ptr(server_err, _f32, "server_err"), float(eta_prev), float(eta),
                               _ptr(out_signs, out_signs.dtype, "out_signs"),
-                              _ptr(out_scales, torch.float32, "out_scales"), _stream_ptr(stream))
+                              _ptr(out_scales, _f32, "out_scales"), _stream_ptr(stream))
     _check(rc)
 
 
 def ef_apply(plan, params, packed_signs, scales, eta, stream=None):
     if params.numel() != plan.d or packed_signs.numel() != plan.W or scales.numel() != plan.B:
         raise TypeError("params/packed_signs/scales must hold d/W/B entries")
-    rc = lib().ef_apply(plan._h, _ptr(params, torch.float32, "params"),
+    rc = lib().ef_apply(plan._h, _ptr(params, _f32, "params"),
                         _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                        _ptr(scales, torch.float32, "scales"), float(eta), _stream_ptr(stream))
+                        _ptr(scales, _f32, "scales"), float(eta), _stream_ptr(stream))
     _check(rc)
 
 
@@ -315,10 +327,10 @@ def ef_apply_wd(plan, params, decay_mom, packed_signs, scales, eta, mu, lam, str
     if (params.numel() != plan.d or decay_mom.numel() != plan.d or packed_signs.numel() != plan.W
             or scales.numel() != plan.B):
         raise TypeError("params/decay_mom/packed_signs/scales must hold d/d/W/B entries")
-    rc = lib().ef_apply_wd(plan._h, _ptr(params, torch.float32, "params"),
-                           _ptr(decay_mom, torch.float32, "decay_mom"),
+    rc = lib().ef_apply_wd(plan._h, _ptr(params, _f32, "params"),
+                           _ptr(decay_mom, _f32, "decay_mom"),
                            _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                           _ptr(scales, torch.float32, "scales"), float(eta), float(mu), float(lam),
+                           _ptr(scales, _f32, "scales"), float(eta), float(mu), float(lam),
                            _stream_ptr(stream))
     _check(rc)
 
@@ -335,7 +347,7 @@ def _messages(t, n, plan, name):
     """A uint8 buffer of n fused messages (Section 4.2: one message per worker)."""
     if t.numel() != n * ef_payload_bytes(plan):
         raise TypeError("%s must hold %d messages of %d bytes" % (name, n, ef_payload_bytes(plan)))
-    return _ptr(t, torch.uint8, name)
+    return _ptr(t, _u8, name)
 
 
 def ef_worker_step_fused(plan, grad, mom, err, mu, eta_prev, eta, payloads, stream=None):
@@ -343,8 +355,8 @@ def ef_worker_step_fused(plan, grad, mom, err, mu, eta_prev, eta, payloads, stre
     gs, ss = _stride(grad, plan.d, "grad"), _stride(mom, plan.d, "mom")
     if _stride(err, plan.d, "err") != ss or mom.shape != err.shape:
         raise TypeError("mom and err must share shape and stride")
-    rc = lib().ef_worker_step_fused(plan._h, n, _ptr(grad, torch.float32, "grad"), gs,
-                                    _ptr(mom, torch.float32, "mom"), _ptr(err, torch.float32, "err"), ss,
+    rc = lib().ef_worker_step_fused(plan._h, n, _ptr(grad, _f32, "grad"), gs,
+                                    _ptr(mom, _f32, "mom"), _ptr(err, _f32, "err"), ss,
                                     float(mu), float(eta_prev), float(eta), _messages(payloads, n, plan, "payloads"),
                                     _stream_ptr(stream))
     _check(rc)
@@ -353,8 +365,8 @@ def ef_worker_step_fused(plan, grad, mom, err, mu, eta_prev, eta, payloads, stre
 def ef_server_step_fused(plan, M, payloads, server_err, eta_prev, eta, out_payload, stream=None):
     if payloads.numel() < M * ef_payload_bytes(plan) or server_err.numel() != plan.d:
         raise TypeError("payloads must hold M messages and server_err d floats")
-    rc = lib().ef_server_step_fused(plan._h, int(M), _ptr(payloads, torch.uint8, "payloads"),
-                                    _ptr(server_err, torch.float32, "server_err"), float(eta_prev), float(eta),
+    rc = lib().ef_server_step_fused(plan._h, int(M), _ptr(payloads, _u8, "payloads"),
+                                    _ptr(server_err, _f32, "server_err"), float(eta_prev), float(eta),
                                     _messages(out_payload, 1, plan, "out_payload"), _stream_ptr(stream))
     _check(rc)
 
@@ -362,7 +374,7 @@ def ef_server_step_fused(plan, M, payloads, server_err, eta_prev, eta, out_paylo
 def ef_apply_fused(plan, params, payload, eta, stream=None):
     if params.numel() != plan.d:
         raise TypeError("params must hold d floats")
-    rc = lib().ef_apply_fused(plan._h, _ptr(params, torch.float32, "params"), _messages(payload, 1, plan, "payload"),
+    rc = lib().ef_apply_fused(plan._h, _ptr(params, _f32, "params"), _messages(payload, 1, plan, "payload"),
                               float(eta), _stream_ptr(stream))
     _check(rc)
 
@@ -373,10 +385,10 @@ def ef_worker_step_sgd(plan, grad, err, eta_prev, eta, packed_signs, scales, str
     gs, ss = _stride(grad, plan.d, "grad"), _stride(err, plan.d, "err")
     if packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B:
         raise TypeError("packed_signs must hold n*W words and scales n*B floats")
-    rc = lib().ef_worker_step_sgd(plan._h, n, _ptr(grad, torch.float32, "grad"), gs,
-                                  _ptr(err, torch.float32, "err"), ss, float(eta_prev), float(eta),
+    rc = lib().ef_worker_step_sgd(plan._h, n, _ptr(grad, _f32, "grad"), gs,
+                                  _ptr(err, _f32, "err"), ss, float(eta_prev), float(eta),
                                   _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                                  _ptr(scales, torch.float32, "scales"), _stream_ptr(stream))
+                                  _ptr(scales, _f32, "scales"), _stream_ptr(stream))
     _check(rc)
 
 
@@ -387,7 +399,7 @@ def ef_compressor_quality(plan, v, out, stream=None, static_scratch=False):
     if out.numel() != 2 * n:
         raise TypeError("out must hold 2 doubles per vector")
     fn = lib().ef_compressor_quality_static if static_scratch else lib().ef_compressor_quality
-    rc = fn(plan._h, n, _ptr(v, torch.float32, "v"), _stride(v, plan.d, "v"), _ptr(out, torch.float64, "out"),
+    rc = fn(plan._h, n, _ptr(v, _f32, "v"), _stride(v, plan.d, "v"), _ptr(out, _f64, "out"),
             _stream_ptr(stream))
     _check(rc)
 
@@ -429,10 +441,10 @@ def ef_worker_step_state(plan, state, grad, mu, eta_prev, eta, packed_signs, sca
     n = 1 if grad.dim() == 1 else grad.shape[0]
     if n != state.n or packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B:
         raise TypeError("grad must hold the state's workers; packed_signs n*W words, scales n*B floats")
-    rc = lib().ef_worker_step_state(plan._h, state._h, _ptr(grad, torch.float32, "grad"), _stride(grad, plan.d, "grad"),
+    rc = lib().ef_worker_step_state(plan._h, state._h, _ptr(grad, _f32, "grad"), _stride(grad, plan.d, "grad"),
                                     float(mu), float(eta_prev), float(eta),
                                     _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                                    _ptr(scales, torch.float32, "scales"), _stream_ptr(stream))
+                                    _ptr(scales, _f32, "scales"), _stream_ptr(stream))
     _check(rc)
 
 
@@ -442,9 +454,9 @@ def ef_server_step_state(plan, state, M, packed_signs, scales, eta_prev, eta, ou
     if out_signs.numel() != plan.W or out_scales.numel() != plan.B:
         raise TypeError("out_signs/out_scales must hold W/B entries")
     rc = lib().ef_server_step_state(plan._h, state._h, int(M), _ptr(packed_signs, packed_signs.dtype, "packed_signs"),
-                                    _ptr(scales, torch.float32, "scales"), float(eta_prev), float(eta),
+                                    _ptr(scales, _f32, "scales"), float(eta_prev), float(eta),
                                     _ptr(out_signs, out_signs.dtype, "out_signs"),
-                                    _ptr(out_scales, torch.float32, "out_scales"), _stream_ptr(stream))
+                                    _ptr(out_scales, _f32, "out_scales"), _stream_ptr(stream))
     _check(rc)
 
 
@@ -459,7 +471,7 @@ def _state_copy(fn, plan, state, mom, err, server_err, stream):
         raise TypeError("mom and err must share their row stride")
     if server_err is not None and server_err.numel() != plan.d:
         raise TypeError("server_err must hold d entries")
-    p = [None if t is None else _ptr(t, torch.float32, n) for t, n in ((mom, "mom"), (err, "err"), (server_err, "server_err"))]
+    p = [None if t is None else _ptr(t, _f32, n) for t, n in ((mom, "mom"), (err, "err"), (server_err, "server_err"))]
     _check(fn(plan._h, state._h, p[0], p[1], stride, p[2], _stream_ptr(stream)))
 
 

@@ -67,9 +67,9 @@ struct ef_plan {
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
     double *d_qtile, *d_qpart;      // [max_workers][ntiles][2], [max_workers][2*ntiles][2]
-    // launches that fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
+    // launches that (nearly) fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
     // counters, in one allocation (null: this layout has none)
-    int small_wgs;                  // workgroups of those kernels that are resident at once
+    int small_wgs;                  // most workgroups such a launch may have
     void *d_small;
     ef::SmallArgs small;
     bool worker_kernel_auto;        // ef_plan_set_persistent has not been used to pick one
@@ -320,7 +320,11 @@ int build_small(ef_plan *p)
     EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_s, ef::k_server_small, ef::SMALL_THREADS, 0));
     int cus = 0;
     EF_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    p->small_wgs = cus * (occ < occ_s ? occ : occ_s);
+    // Up to twice what is resident: a block's tiles are at most half of that and are dispatched in order, as the
+    // other one-pass kernels assume.  Measured, worker calls in blocks of 30 000 elements, these kernels against
+    // k_worker_tiles + k_tail: 64 workgroups 7.7 / 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3;
+    // server calls with 4 workers, against k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
+    p->small_wgs = 2 * cus * (occ < occ_s ? occ : occ_s);
     const int32_t ntiles = p->L.ntiles;
     if (ntiles > p->small_wgs) return EF_OK;
     const int64_t *o = p->offs_host.data();
@@ -559,7 +563,7 @@ int worker_role(const ef_plan *plan, bool has_mom)
     return ticketed ? ROLE_TICKET : ROLE_TILES;
 }
 
-// Does a call over nsets sets go to the kernels of ef_small.h?  Its workgroups have to be resident together, and no
+// Does a call over nsets sets go to the kernels of ef_small.h?  It has to be small enough, and no
 // block may be left for a second pass (a limit set by the caller, or that of the deferred mode).
 bool small_call(const ef_plan *plan, int role, int nsets)
 {

@@ -1,4 +1,4 @@
-// Kernels for launches that fit on the GPU all at once: see ef_tile.h for the tile scheme.
+// Kernels for launches that (nearly) fit on the GPU all at once: see ef_tile.h for the tile scheme.
 //
 // A launch of a few hundred tiles is over before HBM or the vector units matter: its time is one
 // workgroup's chain of dependent memory round trips (about 0.5 to 1 us each), plus that of every kernel that
@@ -8,8 +8,8 @@
 //     elements (SmallArgs), written at plan creation, instead of tile -> block -> offsets lookups and an
 //     index built in LDS;
 //   * 1024 threads to a tile, four elements each;
-//   * every workgroup is resident (the host checks that), so all tiles of a block, mixed ones included,
-//     can wait for it in place; and they do not wait for a gatherer's answer, each adds up the block's partial
+//   * all workgroups, or half of them, are resident at once, so all tiles of a block, mixed ones
+//     included, can wait for it in place; and they do not wait for a gatherer's answer, each adds up the block's partial
 //     sums itself (at most SMALL_SPAN of them: one wavefront, four words a lane);
 //   * no kernel follows: the last workgroup to finish steps the call state (and sees to the segments
 //     whose bounded wait ran out, normally none).

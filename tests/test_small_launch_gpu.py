@@ -1,4 +1,4 @@
-"""Calls whose workgroups fit on the GPU all at once run kernels of their own (csrc/ef_small.h).  They are
+"""Calls whose workgroups (nearly) fit on the GPU all at once run kernels of their own (csrc/ef_small.h).  They are
 the plan's choice, so nothing is forced here.  Same bar as the other parity tests: the oracle, stage by stage."""
 import zlib
 
@@ -13,14 +13,14 @@ from tests.test_parity_gpu import LAYOUTS, _offs
 pytestmark = pytest.mark.gpu
 
 T = 4096
-# 256 tiles is the longest block those kernels take; 512 workgroups is what a GPU of 256 units keeps resident
+# 256 tiles is the longest block those kernels take; 1024 workgroups is twice what 256 units keep resident
 EDGES = {
     "span_256": [100, 255 * T + 50, 3],
     "span_257": [100, 256 * T + 50, 3],
     "span_65": [7, 64 * T + 9, T - 3],
     "span_129_aligned": [129 * T, 5],
-    "wgs_170x3": [3 * T + 1] * 56 + [1000],
-    "wgs_171x3": [3 * T + 1] * 57 + [100],
+    "wgs_341x3": [3 * T + 1] * 113 + [7000],
+    "wgs_342x3": [3 * T + 1] * 114,
     "rows_of_256": [255, 1, 256, 257, 1023, 1, 1, 3, 60, 64, 65, 2 * T, 769],
     "last_tile_ragged": [2 * T, 4094],
 }
