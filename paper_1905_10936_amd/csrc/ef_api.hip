@@ -27,12 +27,12 @@ struct ef_plan {
         int32_t fuse_limit;
         uint32_t n_static;          // segments whose p the first kernels always park
         uint32_t n_late;            // blocks whose scale the first kernels never write
-        uint32_t *d_static;         // [2*ntiles] capacity
-        int32_t *d_late;            // [min(B, 2*ntiles)] capacity
-        // deferred correction: position of every block in d_late if it is larger than fuse_limit, else -1;
-        // the whole tiles of those blocks (left out of d_static while the mode is on)
+        uint32_t *d_static;         // [n_static]
+        int32_t *d_late;            // [n_late]
+        // deferred correction: position of every block in d_late if it is larger than fuse_limit, else -1 (written
+        // while the mode is on); the whole tiles of those blocks (left out of d_static while the mode is on)
         int32_t *d_late_index;      // [B]
-        int32_t *d_lazy_tiles;      // [ntiles] capacity
+        int32_t *d_lazy_tiles;      // [n_lazy_tiles]
         uint32_t n_lazy_tiles;
     } role[3];
     int sync_group;                 // tiles of a large block that are written out in step (ef_plan_set_sync_group)
@@ -49,7 +49,9 @@ struct ef_plan {
     int lazy_stride;
     int32_t lim_persistent, lim_direct, lim_server;   // automatic limits
     int32_t user_fuse_limit;        // >= 0: set through ef_plan_tune, overrides the automatic limits
-    // device allocations owned by the plan
+    // device memory owned by the plan: one allocation, and where its parts are
+    void *d_arena;
+    uint32_t *d_lists;              // the roles' d_static, d_late and d_lazy_tiles, one after the other
     int64_t *d_offs;
     int32_t *d_tile_fb;
     int32_t *d_tile_lb;
@@ -68,9 +70,9 @@ struct ef_plan {
     int32_t n_cross;
     double *d_qtile, *d_qpart;      // [max_workers][ntiles][2], [max_workers][2*ntiles][2]
     // launches that (nearly) fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
-    // counters, in one allocation (null: this layout has none)
+    // counters, null: this layout has none)
     int small_wgs;                  // most workgroups such a launch may have
-    void *d_small;
+    bool has_small;                 // this layout has such launches
     ef::SmallArgs small;
     bool worker_kernel_auto;        // ef_plan_set_persistent has not been used to pick one
 };
@@ -174,28 +176,92 @@ bool good_eta(float eta_prev, float eta)
 
 void destroy_device(ef_plan *p)
 {
-    if (p->d_offs) (void)hipFree(p->d_offs);
-    if (p->d_tile_fb) (void)hipFree(p->d_tile_fb);
-    if (p->d_tile_lb) (void)hipFree(p->d_tile_lb);
-    if (p->d_part) (void)hipFree(p->d_part);
-    if (p->d_ready) (void)hipFree(p->d_ready);
-    if (p->d_list_cnt) (void)hipFree(p->d_list_cnt);
-    if (p->d_state) (void)hipFree(p->d_state);
-    if (p->d_lazy_scales) (void)hipFree(p->d_lazy_scales);
-    if (p->d_defer_list) (void)hipFree(p->d_defer_list);
-    if (p->d_fin_list) (void)hipFree(p->d_fin_list);
-    for (auto &r : p->role) {
-        if (r.d_static) (void)hipFree(r.d_static);
-        if (r.d_late) (void)hipFree(r.d_late);
-        if (r.d_late_index) (void)hipFree(r.d_late_index);
-        if (r.d_lazy_tiles) (void)hipFree(r.d_lazy_tiles);
+    if (p->d_arena) (void)hipFree(p->d_arena);
+}
+
+// The parts of a plan's device memory: one allocation, one copy for the small tables and one for each
+// large one, one fill (a plan used to make 30 allocations and 20 copies).
+class Arena {
+public:
+    enum Fill { COPY, ZERO, LEAVE };
+    template <class T>
+    void add(T **where, size_t n, Fill fill, const T *from = nullptr)
+    {
+        parts_.push_back({reinterpret_cast<void **>(where), n * sizeof(T), fill, from});
     }
-    if (p->d_mixed) (void)hipFree(p->d_mixed);
-    if (p->d_uniform) (void)hipFree(p->d_uniform);
-    if (p->d_cross) (void)hipFree(p->d_cross);
-    if (p->d_qtile) (void)hipFree(p->d_qtile);
-    if (p->d_qpart) (void)hipFree(p->d_qpart);
-    if (p->d_small) (void)hipFree(p->d_small);
+    // Allocates (the caller frees *base, also after an error) and sets every *where.
+    int make(void **base)
+    {
+        const size_t align = 256, stage_max = 1u << 18;
+        size_t total = 0, staged = 0, zero_from = 0, zero_to = 0;
+        std::vector<Part *> order;
+        for (int pass = 0; pass < 4; ++pass) {          // small tables, large tables, zeroed, the rest
+            for (Part &q : parts_) {
+                const int mine = q.fill == COPY ? (q.bytes <= stage_max ? 0 : 1) : q.fill == ZERO ? 2 : 3;
+                if (mine != pass) continue;
+                q.at = total;
+                total += (q.bytes + align - 1) / align * align;
+                order.push_back(&q);
+            }
+            if (pass == 0) staged = total;
+            if (pass == 1) zero_from = total;
+            if (pass == 2) zero_to = total;
+        }
+        std::vector<char> stage(staged, 0);
+        EF_HIP(hipMalloc(base, total ? total : align));
+        char *b = static_cast<char *>(*base);
+        for (Part *q : order) {
+            *q->where = b + q->at;
+            if (q->fill != COPY || !q->bytes) continue;
+            if (q->at < staged)
+                memcpy(stage.data() + q->at, q->from, q->bytes);
+            else
+                EF_HIP(hipMemcpy(b + q->at, q->from, q->bytes, hipMemcpyHostToDevice));
+        }
+        if (staged) EF_HIP(hipMemcpy(b, stage.data(), staged, hipMemcpyHostToDevice));
+        if (zero_to > zero_from) EF_HIP(hipMemset(b + zero_from, 0, zero_to - zero_from));
+        return EF_OK;
+    }
+
+private:
+    struct Part {
+        void **where;
+        size_t bytes;
+        Fill fill;
+        const void *from;
+        size_t at = 0;
+        Part(void **w, size_t n, Fill f, const void *p) : where(w), bytes(n), fill(f), from(p) {}
+    };
+    std::vector<Part> parts_;
+};
+
+// What plan creation asks the runtime about a device, once per device and process.
+struct DeviceFacts {
+    bool known;
+    int cus;                                    // compute units
+    int uniform, tiles, server, small;          // workgroups per unit of the kernels of these names
+};
+DeviceFacts g_facts[MAX_DEVICES];
+
+int device_facts(int device, DeviceFacts *out)
+{
+    if (device < 0 || device >= MAX_DEVICES) return EF_ERR_ARG;
+    std::lock_guard<std::mutex> lock(g_scratch_mutex);
+    DeviceFacts &f = g_facts[device];
+    if (!f.known) {
+        int small_s = 0;
+        EF_HIP(hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, device));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, true, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server, ef::k_server_tiles<true>, ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
+        if (small_s < f.small) f.small = small_s;
+        if (f.uniform < 1) f.uniform = 1;
+        f.known = true;
+    }
+    *out = f;
+    return EF_OK;
 }
 
 int64_t tiles_of_block(const ef_plan *p, int64_t b)
@@ -222,15 +288,16 @@ bool finishes_with_mixed(const ef_plan *p, const ef_plan::Role &r, int64_t b)
 // blocks larger than fuse_limit, and the residual of every open segment that is not finished
 // where it is computed (the segments of those large blocks, and the segments that blocks with
 // whole tiles have in mixed tiles).
-int upload_static_list(ef_plan *p, ef_plan::Role &r)
+int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
 {
     std::vector<uint32_t> items;
-    std::vector<int32_t> late, late_index((size_t)p->L.B, -1), lazy_tiles;
+    std::vector<int32_t> late, late_index, lazy_tiles;
+    if (p->lazy) late_index.assign((size_t)p->L.B, -1);
     const int64_t *o = p->offs_host.data();
     for (int64_t b = 0; b < p->L.B; ++b) {
         const int64_t n = tiles_of_block(p, b);
         if (n < 2 || n <= r.fuse_limit) continue;
-        if (has_uniform_tile(p, b)) late_index[(size_t)b] = (int32_t)late.size();
+        if (p->lazy && has_uniform_tile(p, b)) late_index[(size_t)b] = (int32_t)late.size();
         late.push_back((int32_t)b);
     }
     for (int32_t t = 0; t < p->L.ntiles; ++t) {
@@ -255,12 +322,14 @@ int upload_static_list(ef_plan *p, ef_plan::Role &r)
     r.n_late = (uint32_t)late.size();
     r.n_static = (uint32_t)items.size();
     r.n_lazy_tiles = (uint32_t)lazy_tiles.size();
-    EF_HIP(hipMemcpy(r.d_late_index, late_index.data(), sizeof(int32_t) * late_index.size(), hipMemcpyHostToDevice));
-    if (!lazy_tiles.empty())
-        EF_HIP(hipMemcpy(r.d_lazy_tiles, lazy_tiles.data(), sizeof(int32_t) * lazy_tiles.size(), hipMemcpyHostToDevice));
-    if (!late.empty()) EF_HIP(hipMemcpy(r.d_late, late.data(), sizeof(int32_t) * late.size(), hipMemcpyHostToDevice));
-    if (!items.empty())
-        EF_HIP(hipMemcpy(r.d_static, items.data(), sizeof(uint32_t) * items.size(), hipMemcpyHostToDevice));
+    if (p->lazy)
+        EF_HIP(hipMemcpy(r.d_late_index, late_index.data(), sizeof(int32_t) * late_index.size(), hipMemcpyHostToDevice));
+    r.d_static = p->d_lists + all.size();
+    all.insert(all.end(), items.begin(), items.end());
+    r.d_late = reinterpret_cast<int32_t *>(p->d_lists + all.size());
+    all.insert(all.end(), late.begin(), late.end());
+    r.d_lazy_tiles = reinterpret_cast<int32_t *>(p->d_lists + all.size());
+    all.insert(all.end(), lazy_tiles.begin(), lazy_tiles.end());
     return EF_OK;
 }
 
@@ -286,17 +355,19 @@ int refresh_limits_unguarded(ef_plan *p)
         ticket.fuse_limit = tiles.fuse_limit = p->persistent_forced ? 0 : LAZY_WAIT_LIMIT;
         // A layout of few tiles whose server residual the caller never sees is finished in one launch,
         // where waiting is cheap.
-        server.fuse_limit = p->d_small && p->held ? ef::SMALL_SPAN : 0;
+        server.fuse_limit = p->has_small && p->held ? ef::SMALL_SPAN : 0;
     } else {
         ticket.fuse_limit = clamp(p->lim_persistent);
         server.fuse_limit = clamp(p->lim_server);
         tiles.fuse_limit = clamp(p->lim_direct);
     }
     p->L.fuse_limit = p->role[0].fuse_limit;
+    std::vector<uint32_t> all;
     for (auto &r : p->role) {
-        int rc = upload_static_list(p, r);
+        int rc = static_list(p, r, all);
         if (rc) return rc;
     }
+    if (!all.empty()) EF_HIP(hipMemcpy(p->d_lists, all.data(), sizeof(uint32_t) * all.size(), hipMemcpyHostToDevice));
     return EF_OK;
 }
 
@@ -311,33 +382,30 @@ int refresh_limits(ef_plan *p)
     }
 }
 
-// Records, start words and counters of the kernels for launches that fit on the GPU all at once, if the
+// Records and start words of the kernels for launches that (nearly) fit on the GPU all at once, if the
 // layout has calls for them: few enough tiles, and no block of more tiles than a wavefront adds up.
-int build_small(ef_plan *p)
+struct SmallTables {
+    std::vector<ef::SmallTile> tiles;
+    std::vector<uint32_t> starts;
+    std::vector<uint16_t> rank;
+};
+
+void small_tables(ef_plan *p, SmallTables &out)
 {
-    int occ = 0, occ_s = 0;
-    EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
-    EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_s, ef::k_server_small, ef::SMALL_THREADS, 0));
-    int cus = 0;
-    EF_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    // Up to twice what is resident: a block's tiles are at most half of that and are dispatched in order, as the
-    // other one-pass kernels assume.  Measured, worker calls in blocks of 30 000 elements, these kernels against
-    // k_worker_tiles + k_tail: 64 workgroups 7.7 / 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3;
-    // server calls with 4 workers, against k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
-    p->small_wgs = 2 * cus * (occ < occ_s ? occ : occ_s);
     const int32_t ntiles = p->L.ntiles;
-    if (ntiles > p->small_wgs) return EF_OK;
+    if (ntiles > p->small_wgs) return;
     const int64_t *o = p->offs_host.data();
     const int64_t d = p->L.d;
     for (int64_t b = 0; b < p->L.B; ++b)
-        if (tiles_of_block(p, b) > ef::SMALL_SPAN) return EF_OK;
-    std::vector<ef::SmallTile> tiles((size_t)ntiles);
-    std::vector<uint32_t> starts;
-    std::vector<uint16_t> rank;
+        if (tiles_of_block(p, b) > ef::SMALL_SPAN) return;
+    std::vector<uint32_t> &starts = out.starts;
+    std::vector<uint16_t> &rank = out.rank;
+    out.tiles.resize((size_t)ntiles);
+    p->has_small = true;
     for (int32_t t = 0; t < ntiles; ++t) {
         const int64_t start = (int64_t)t * ef::TILE, end = start + ef::TILE;
         const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
-        ef::SmallTile &r = tiles[(size_t)t];
+        ef::SmallTile &r = out.tiles[(size_t)t];
         r = ef::SmallTile();
         r.fb = fb;
         r.nseg = lb - fb + 1;
@@ -371,24 +439,6 @@ int build_small(ef_plan *p)
             before += (unsigned)__builtin_popcount(w[i]);
         }
     }
-    const size_t at_done = sizeof(ef::SmallTile) * tiles.size();
-    const size_t at_starts = at_done + sizeof(unsigned) * (ef::DONE_GROUPS + 1) * ef::DONE_STRIDE;
-    const size_t at_rank = at_starts + sizeof(uint32_t) * starts.size();
-    std::vector<char> all(at_rank + sizeof(uint16_t) * rank.size(), 0);
-    memcpy(all.data(), tiles.data(), at_done);
-    if (!starts.empty()) {
-        memcpy(all.data() + at_starts, starts.data(), at_rank - at_starts);
-        memcpy(all.data() + at_rank, rank.data(), all.size() - at_rank);
-    }
-    EF_HIP(hipMalloc(&p->d_small, all.size()));
-    EF_HIP(hipMemcpy(p->d_small, all.data(), all.size(), hipMemcpyHostToDevice));
-    char *base = static_cast<char *>(p->d_small);
-    p->small.tiles = reinterpret_cast<const ef::SmallTile *>(base);
-    p->small.done = reinterpret_cast<unsigned *>(base + at_done);
-    p->small.starts = reinterpret_cast<const uint32_t *>(base + at_starts);
-    p->small.rank = reinterpret_cast<const uint16_t *>(base + at_rank);
-    p->small.state = p->d_state;
-    return EF_OK;
 }
 
 int build_device(ef_plan *p)
@@ -415,51 +465,70 @@ int build_device(ef_plan *p)
         }
     }
     EF_HIP(hipGetDevice(&p->device));
-    EF_HIP(hipMalloc(&p->d_offs, sizeof(int64_t) * (B + 1)));
-    EF_HIP(hipMalloc(&p->d_tile_fb, sizeof(int32_t) * ntiles));
-    EF_HIP(hipMalloc(&p->d_tile_lb, sizeof(int32_t) * ntiles));
-    EF_HIP(hipMalloc(&p->d_part, sizeof(unsigned long long) * 2 * (size_t)ntiles * nsets));
-    EF_HIP(hipMemcpy(p->d_offs, p->offs_host.data(), sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice));
-    EF_HIP(hipMemcpy(p->d_tile_fb, fb.data(), sizeof(int32_t) * ntiles, hipMemcpyHostToDevice));
-    EF_HIP(hipMemcpy(p->d_tile_lb, lb.data(), sizeof(int32_t) * ntiles, hipMemcpyHostToDevice));
-    EF_HIP(hipMemset(p->d_part, 0, sizeof(unsigned long long) * 2 * (size_t)ntiles * nsets));
+    DeviceFacts facts;
+    { const int rc_facts = device_facts(p->device, &facts); if (rc_facts) return rc_facts; }
+    // A block finishes in one pass if its tiles fit twice over into the tiles a kernel's workgroups hold at
+    // once: grid x (PIPE_DEPTH + STAGE_DEPTH) for the persistent kernel, the resident workgroups for the
+    // kernels that run one workgroup per tile (dispatched in grid order).  Larger limits were measured slower:
+    // a block that fills most of the machine makes its first tiles wait for its last.
+    p->worker_grid = facts.cus * facts.uniform;
+    p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
+    p->lim_direct = (int32_t)((int64_t)facts.cus * facts.tiles / 2);
+    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server / 2);
+    // Launches that (nearly) fit on the GPU all at once: up to twice what is resident.  A block's tiles are at
+    // most half of that and are dispatched in order, as the other one-pass kernels assume.  Measured, worker
+    // calls in blocks of 30 000 elements, these kernels against k_worker_tiles + k_tail: 64 workgroups 7.7 /
+    // 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3; server calls with 4 workers, against
+    // k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
+    p->small_wgs = 2 * facts.cus * facts.small;
+    SmallTables small;
+    small_tables(p, small);
+
+    std::vector<int32_t> mixed, uniform, cross;
+    for (int32_t t = 0; t < ntiles; ++t) {
+        const bool full = ((int64_t)t + 1) * ef::TILE <= d;
+        (fb[t] == lb[t] && full ? uniform : mixed).push_back(t);
+    }
+    p->L.n_mixed = (int32_t)mixed.size();
+    p->L.n_uniform = (int32_t)uniform.size();
+    // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
+    for (int64_t b = 0; b < B; ++b)
+        if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);
+    p->n_cross = (int32_t)cross.size();
+
+    const size_t nt = (size_t)ntiles, ns = (size_t)nsets, nv = (size_t)p->max_workers;
     // a block that crosses a tile boundary owns at least one of the 2*ntiles open segments
     const size_t max_cross = (size_t)(2 * (int64_t)ntiles < B ? 2 * (int64_t)ntiles : B);
-    // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
-    EF_HIP(hipMalloc(&p->d_ready, sizeof(unsigned long long) * ef::READY_STRIDE * (size_t)ntiles * nsets));
-    EF_HIP(hipMemset(p->d_ready, 0, sizeof(unsigned long long) * ef::READY_STRIDE * (size_t)ntiles * nsets));
-    EF_HIP(hipMalloc(&p->d_list_cnt, sizeof(unsigned int) * 6));
-    EF_HIP(hipMalloc(&p->d_defer_list, sizeof(unsigned long long) * 2 * (size_t)ntiles * nsets));
-    EF_HIP(hipMalloc(&p->d_fin_list, sizeof(unsigned long long) * max_cross * nsets));
-    for (auto &r : p->role) {
-        EF_HIP(hipMalloc(&r.d_static, sizeof(uint32_t) * 2 * (size_t)ntiles));
-        EF_HIP(hipMalloc(&r.d_late, sizeof(int32_t) * max_cross));
-        EF_HIP(hipMalloc(&r.d_late_index, sizeof(int32_t) * (size_t)B));
-        EF_HIP(hipMalloc(&r.d_lazy_tiles, sizeof(int32_t) * (size_t)ntiles));
-    }
     p->lazy_stride = (int)max_cross;
-    EF_HIP(hipMalloc(&p->d_lazy_scales, sizeof(float) * max_cross * nsets));
-    EF_HIP(hipMemset(p->d_lazy_scales, 0, sizeof(float) * max_cross * nsets));
-    {
-        std::vector<int32_t> mixed, uniform;
-        for (int32_t t = 0; t < ntiles; ++t) {
-            const bool full = ((int64_t)t + 1) * ef::TILE <= d;
-            (fb[t] == lb[t] && full ? uniform : mixed).push_back(t);
-        }
-        p->L.n_mixed = (int32_t)mixed.size();
-        p->L.n_uniform = (int32_t)uniform.size();
-        EF_HIP(hipMalloc(&p->d_mixed, sizeof(int32_t) * (mixed.size() + 1)));
-        EF_HIP(hipMalloc(&p->d_uniform, sizeof(int32_t) * (uniform.size() + 1)));
-        if (!mixed.empty())
-            EF_HIP(hipMemcpy(p->d_mixed, mixed.data(), sizeof(int32_t) * mixed.size(), hipMemcpyHostToDevice));
-        if (!uniform.empty())
-            EF_HIP(hipMemcpy(p->d_uniform, uniform.data(), sizeof(int32_t) * uniform.size(), hipMemcpyHostToDevice));
-        p->L.mixed_tiles = p->d_mixed;
-        p->L.uniform_tiles = p->d_uniform;
+    Arena mem;
+    mem.add(&p->d_offs, (size_t)B + 1, Arena::COPY, p->offs_host.data());
+    mem.add(&p->d_tile_fb, nt, Arena::COPY, fb.data());
+    mem.add(&p->d_tile_lb, nt, Arena::COPY, lb.data());
+    mem.add(&p->d_mixed, mixed.size(), Arena::COPY, mixed.data());
+    mem.add(&p->d_uniform, uniform.size(), Arena::COPY, uniform.data());
+    mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
+    mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
+    // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
+    mem.add(&p->d_ready, (size_t)ef::READY_STRIDE * nt * ns, Arena::ZERO);
+    mem.add(&p->d_list_cnt, 6, Arena::ZERO);
+    mem.add(&p->d_state, 2, Arena::ZERO);
+    mem.add(&p->d_lazy_scales, max_cross * ns, Arena::ZERO);
+    mem.add(&p->d_defer_list, 2 * nt * ns, Arena::LEAVE);
+    mem.add(&p->d_fin_list, max_cross * ns, Arena::LEAVE);
+    mem.add(&p->d_lists, 3 * (3 * nt + max_cross), Arena::LEAVE);
+    for (auto &r : p->role) mem.add(&r.d_late_index, (size_t)B, Arena::LEAVE);
+    mem.add(&p->d_qpart, 4 * nt * nv, Arena::LEAVE);
+    mem.add(&p->d_qtile, 2 * nt * nv, Arena::LEAVE);
+    if (p->has_small) {
+        mem.add(const_cast<ef::SmallTile **>(&p->small.tiles), small.tiles.size(), Arena::COPY, small.tiles.data());
+        mem.add(const_cast<uint32_t **>(&p->small.starts), small.starts.size(), Arena::COPY, small.starts.data());
+        mem.add(const_cast<uint16_t **>(&p->small.rank), small.rank.size(), Arena::COPY, small.rank.data());
+        mem.add(&p->small.done, (size_t)(ef::DONE_GROUPS + 1) * ef::DONE_STRIDE, Arena::ZERO);
     }
-    EF_HIP(hipMemset(p->d_list_cnt, 0, sizeof(unsigned int) * 6));
-    EF_HIP(hipMalloc(&p->d_state, 2 * sizeof(ef::CallState)));
-    EF_HIP(hipMemset(p->d_state, 0, 2 * sizeof(ef::CallState)));     // the zeroed partial words carry tag 0
+    { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
+    p->small.state = p->d_state;
+    p->L.mixed_tiles = p->d_mixed;
+    p->L.uniform_tiles = p->d_uniform;
     p->L.offs = p->d_offs;
     p->L.tile_fb = p->d_tile_fb;
     p->L.tile_lb = p->d_tile_lb;
@@ -472,26 +541,6 @@ int build_device(ef_plan *p)
     p->X.snapshot = p->d_state + 1;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
-    // A block finishes in one pass if its tiles fit twice over into the
-    // workgroups resident at once (see ef_tile.h).
-    {
-        hipDeviceProp_t prop;
-        EF_HIP(hipGetDeviceProperties(&prop, p->device));
-        int occ_w = 0, occ_s = 0;
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_w, ef::k_worker_uniform<true>, ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_s, ef::k_server_tiles<true>, ef::THREADS, 0));
-        if (occ_w < 1) occ_w = 1;
-        p->worker_grid = prop.multiProcessorCount * occ_w;
-        // one-pass blocks must fit twice over into the tiles a kernel's workgroups hold at once:
-        // grid x (PIPE_DEPTH + STAGE_DEPTH) for the persistent kernel, the resident workgroups for the kernels that
-        // run one workgroup per tile (dispatched in grid order).  Larger limits were measured slower:
-        // a block that fills most of the machine makes its first tiles wait for its last.
-        int occ_d = 0;
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_d, (ef::k_worker_tiles<true, true, false>), ef::THREADS, 0));
-        p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
-        p->lim_direct = (int32_t)((int64_t)prop.multiProcessorCount * occ_d / 2);
-        p->lim_server = (int32_t)((int64_t)prop.multiProcessorCount * occ_s / 2);
-    }
     p->user_fuse_limit = -1;
     // Which worker kernel for this layout.  The persistent kernel needs enough tiles per workgroup
     // to fill its pipeline; beyond that the choice follows the measured cost per tile of each
@@ -515,23 +564,6 @@ int build_device(ef_plan *p)
         // 16 tiles per workgroup on, a small one only once the pipeline is well filled
         p->persistent_auto = ((tiles_per_wg >= 64 && cost_persistent < cost_direct) ||
                               (tiles_per_wg >= 16 && cost_persistent < 0.9 * cost_direct)) ? 1 : 0;
-    }
-    {
-        // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
-        std::vector<int32_t> cross;
-        for (int64_t b = 0; b < B; ++b)
-            if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);
-        const size_t nt = (size_t)ntiles, nv = (size_t)p->max_workers;
-        EF_HIP(hipMalloc(&p->d_cross, sizeof(int32_t) * (cross.size() + 1)));
-        if (!cross.empty())
-            EF_HIP(hipMemcpy(p->d_cross, cross.data(), sizeof(int32_t) * cross.size(), hipMemcpyHostToDevice));
-        p->n_cross = (int32_t)cross.size();
-        EF_HIP(hipMalloc(&p->d_qpart, sizeof(double) * 4 * nt * nv));
-        EF_HIP(hipMalloc(&p->d_qtile, sizeof(double) * 2 * nt * nv));
-    }
-    {
-        int rc_small = build_small(p);
-        if (rc_small) return rc_small;
     }
     {
         double *unused = nullptr;       // the static scratch of this device, looked up once, ahead of the first call that needs it
@@ -567,7 +599,7 @@ int worker_role(const ef_plan *plan, bool has_mom)
 // block may be left for a second pass (a limit set by the caller, or that of the deferred mode).
 bool small_call(const ef_plan *plan, int role, int nsets)
 {
-    return plan->d_small && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs && plan->role[role].n_late == 0;
+    return plan->has_small && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs && plan->role[role].n_late == 0;
 }
 
 ef::SmallArgs small_args(const ef_plan *plan, int nsets, float *err, int64_t err_stride, float *scales, int64_t scales_stride)
@@ -679,13 +711,7 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
     p->L.d = block_offsets_host[B];
     p->L.W = (p->L.d + 63) / 64;
     p->L.ntiles = (int32_t)((p->L.d + ef::TILE - 1) / ef::TILE);
-    p->d_offs = nullptr;
-    p->d_tile_fb = p->d_tile_lb = nullptr;
-    p->d_part = nullptr;
-    p->d_ready = nullptr;
-    p->d_list_cnt = nullptr;
-    p->d_state = nullptr;
-    p->d_lazy_scales = nullptr;
+    p->d_arena = nullptr;
     p->lazy = 0;
     p->state = nullptr;
     p->held = false;
@@ -693,20 +719,11 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
     p->lazy_buf[0] = p->lazy_buf[1] = nullptr;
     p->lazy_stride_seen = 0;
     p->lazy_sets_seen = 0;
-    p->d_defer_list = nullptr;
-    p->d_fin_list = nullptr;
     for (auto &r : p->role) {
-        r.d_static = nullptr;
-        r.d_late = nullptr;
-        r.d_late_index = r.d_lazy_tiles = nullptr;
         r.n_static = r.n_late = r.n_lazy_tiles = 0;
         r.fuse_limit = 0;
     }
-    p->d_mixed = p->d_uniform = nullptr;
-    p->d_cross = nullptr;
-    p->n_cross = 0;
-    p->d_qtile = p->d_qpart = nullptr;
-    p->d_small = nullptr;
+    p->has_small = false;
     p->worker_kernel_auto = true;
 
     try {
@@ -1151,7 +1168,7 @@ int ef_apply(const ef_plan *plan, float *params, const uint64_t *packed_signs, c
     if (!aligned(params, 16) || !aligned(packed_signs, 8) || !aligned(scales, 4)) return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    if (plan->d_small)
+    if (plan->has_small)
         hipLaunchKernelGGL(ef::k_apply_small<false>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
                            (float *)nullptr, packed_signs, scales, eta, 0.0f, 0.0f);
     else
@@ -1172,7 +1189,7 @@ int ef_apply_wd(const ef_plan *plan, float *params, float *decay_mom, const uint
         return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    if (plan->d_small)
+    if (plan->has_small)
         hipLaunchKernelGGL(ef::k_apply_small<true>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
                            decay_mom, packed_signs, scales, eta, mu, lambda);
     else
