@@ -64,7 +64,8 @@ struct ef_plan {
     int persistent_forced;          // 1 after ef_plan_set_persistent(plan, 1): also for the momentum-free worker
     unsigned long long *d_defer_list;
     unsigned long long *d_fin_list;
-    int32_t *d_mixed, *d_uniform;   // tile lists
+    int32_t *d_mixed;               // tile lists
+    ef::WholeTile *d_whole;
     // compressor-quality diagnostics
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
@@ -484,13 +485,19 @@ int build_device(ef_plan *p)
     SmallTables small;
     small_tables(p, small);
 
-    std::vector<int32_t> mixed, uniform, cross;
+    std::vector<int32_t> mixed, cross;
+    std::vector<ef::WholeTile> whole;
+    whole.reserve((size_t)ntiles);
     for (int32_t t = 0; t < ntiles; ++t) {
         const bool full = ((int64_t)t + 1) * ef::TILE <= d;
-        (fb[t] == lb[t] && full ? uniform : mixed).push_back(t);
+        if (fb[t] == lb[t] && full)
+            whole.push_back({t, fb[t], p->offs_host[(size_t)fb[t]], p->offs_host[(size_t)fb[t] + 1], 0});
+        else
+            mixed.push_back(t);
     }
     p->L.n_mixed = (int32_t)mixed.size();
-    p->L.n_uniform = (int32_t)uniform.size();
+    p->L.n_uniform = (int32_t)whole.size();
+    if (whole.empty()) whole.push_back(ef::WholeTile());    // the kernels read a record before they look whether there is one
     // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
     for (int64_t b = 0; b < B; ++b)
         if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);
@@ -505,7 +512,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_tile_fb, nt, Arena::COPY, fb.data());
     mem.add(&p->d_tile_lb, nt, Arena::COPY, lb.data());
     mem.add(&p->d_mixed, mixed.size(), Arena::COPY, mixed.data());
-    mem.add(&p->d_uniform, uniform.size(), Arena::COPY, uniform.data());
+    mem.add(&p->d_whole, whole.size(), Arena::COPY, whole.data());
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
@@ -528,7 +535,7 @@ int build_device(ef_plan *p)
     { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
     p->small.state = p->d_state;
     p->L.mixed_tiles = p->d_mixed;
-    p->L.uniform_tiles = p->d_uniform;
+    p->L.whole_tiles = p->d_whole;
     p->L.offs = p->d_offs;
     p->L.tile_fb = p->d_tile_fb;
     p->L.tile_lb = p->d_tile_lb;

@@ -80,7 +80,7 @@ __device__ __forceinline__ float tail_scale(const Layout &L, const Scratch &X, i
 {
     const BlockSpan sp = block_span(L, b);
     float s = 0.f;
-    if (sp.n > 2 * THREADS && wait_ready(b, 0ull, L, X, set, S, &s)) return s;
+    if (sp.n > 2 * THREADS && wait_ready(sp, 0ull, L, X, set, S, &s)) return s;
     const double total = sum_block_partials(L, b, set_part(X, L, set), S.red);
     return (float)(total / (double)(sp.be - sp.bs));
 }
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(THREADS) void k_tail(Layout L, ScratchRef R, TailAr
             if (threadIdx.x == 0) {
                 const float sc = (float)(total / (double)(L.offs[b + 1] - L.offs[b]));
                 T.scales[(int64_t)w * T.scales_stride + b] = sc;
-                __hip_atomic_store(ready_word(X, L, set, b),
+                __hip_atomic_store(ready_word(X, L, set, block_span(L, b)),
                                    ((unsigned long long)X.epoch << 32) | (unsigned long long)__float_as_uint(sc),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 // remembered for the deferred correction of the block's residual
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(THREADS) void k_tail(Layout L, ScratchRef R, TailAr
             if (threadIdx.x == 0) {
                 const float sc = (float)(total / (double)(L.offs[b + 1] - L.offs[b]));
                 T.scales[(int64_t)(set - X.set_base) * T.scales_stride + b] = sc;
-                __hip_atomic_store(ready_word(X, L, set, b),
+                __hip_atomic_store(ready_word(X, L, set, block_span(L, b)),
                                    ((unsigned long long)X.epoch << 32) | (unsigned long long)__float_as_uint(sc),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(THREADS) void k_flush(Layout L, ScratchRef R, const
     float4 v[SUBROWS];
     if (!((X.pending >> blockIdx.y) & 1ull)) return;
     load_tile(e, v, TILE);
-    correct_loaded_residual(v, loaded_correction(L, tile, X, set));
+    correct_loaded_residual(v, loaded_correction(L, L.tile_fb[tile], X, set));
     store_tile(e, v, TILE);
 }
 

@@ -279,25 +279,30 @@ template <bool MIXED>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED ? 7 : 8, 8)))
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
-    const Scratch X = open_call(R);
     __shared__ TileShared S;
+    float4 tv[SUBROWS], p[SUBROWS];
+    if (!MIXED) {
+        // whole tile i is tile i: its residual is asked for before anything is looked up
+        load_tile(A.err + (int64_t)blockIdx.x * TILE, tv, TILE);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const Scratch X = open_call(R);
     const bool whole = !MIXED || (int)blockIdx.x >= L.n_mixed;
-    // without mixed tiles the list of whole tiles is 0, 1, 2, ...: one dependent load less
-    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? L.uniform_tiles[blockIdx.x - L.n_mixed] : L.mixed_tiles[blockIdx.x];
+    const WholeTile w = L.whole_tiles[!MIXED ? blockIdx.x : whole ? blockIdx.x - L.n_mixed : 0];
+    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? w.tile : L.mixed_tiles[blockIdx.x];
     const int n_valid = whole ? TILE : tile_valid(L, tile);
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int32_t b = L.tile_fb[tile];
     float *te = A.err + tile_start;
-    float4 tv[SUBROWS], p[SUBROWS];
     if (whole) {
         Posted P;
-        const LoadedCorrection corr = loaded_correction(L, tile, X, set);
-        load_tile(te, tv, TILE);
+        const BlockSpan sp = span_of(w.bs, w.be);
+        const LoadedCorrection corr = loaded_correction(L, w.b, X, set);
+        if (MIXED) load_tile(te, tv, TILE);
         correct_loaded_residual(tv, corr);
-        server_values_whole(A, tile_start, b, tv, p, S);
-        const int kind = compress_uniform(p, L, tile, TILE, A.signs, A.scales, te, X, set, S, P);
+        server_values_whole(A, tile_start, w.b, tv, p, S);
+        const int kind = compress_uniform(p, L, tile, w.b, sp, TILE, A.signs, A.scales, te, X, set, S, P);
         resolve_posted(P, L, X, set, A.scales, S);
-        if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, b, 0ull, te, L, X, set, S);
+        if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
     } else if constexpr (MIXED) {
         server_mixed_tile(L, X, A, tile, set, n_valid, S);
     }

@@ -81,6 +81,15 @@ constexpr int PIPE_DEPTH = EF_PIPE_DEPTH;     // tiles a persistent workgroup ke
 constexpr unsigned long long TAG_BIT = 1ull << 63;
 constexpr int FUSE_LIMIT_MAX = 4096;                     // most tiles a one-pass block may be given through ef_plan_tune
 
+// What the kernels need to know about a whole tile (one that lies inside one block), in one record: looked up
+// piece by piece (tile, its block, the block's ends) it is three dependent loads before the first scale
+// can be asked for, and two more between a tile's sum and its posting.
+struct alignas(32) WholeTile {
+    int32_t tile, b;
+    int64_t bs, be;             // the block's element range
+    int64_t unused;
+};
+
 struct Layout {
     int64_t d;                  // elements
     int64_t B;                  // blocks
@@ -92,7 +101,7 @@ struct Layout {
     const int32_t *tile_fb;     // [ntiles] block holding the tile's first element
     const int32_t *tile_lb;     // [ntiles] block holding the tile's last valid element
     const int32_t *mixed_tiles;   // [n_mixed] ascending
-    const int32_t *uniform_tiles; // [n_uniform] ascending
+    const WholeTile *whole_tiles; // [n_uniform] ascending
     // Deferred correction (see Scratch::lazy_scales): on or off, and for every block its position
     // among the blocks larger than fuse_limit (-1 for the others).
     int32_t lazy;
@@ -503,15 +512,16 @@ struct BlockSpan {
     int n;                      // tiles
 };
 
-__device__ __forceinline__ BlockSpan block_span(const Layout &L, int64_t b)
+__device__ __forceinline__ BlockSpan span_of(int64_t bs, int64_t be)
 {
     BlockSpan s;
-    s.bs = L.offs[b];
-    s.be = L.offs[b + 1];
-    s.t0 = s.bs / TILE;
-    s.n = (int)((s.be - 1) / TILE - s.t0 + 1);
+    s.bs = bs;
+    s.be = be;
+    s.t0 = bs / TILE;
+    s.n = (int)((be - 1) / TILE - s.t0 + 1);
     return s;
 }
+__device__ __forceinline__ BlockSpan block_span(const Layout &L, int64_t b) { return span_of(L.offs[b], L.offs[b + 1]); }
 
 // Does the block own a whole tile?  Its first tile is shared (or ragged) if it
 // starts inside it, its last tile if it ends inside it; the tiles between are
@@ -563,15 +573,16 @@ __device__ __forceinline__ int64_t gatherer_tile(const Layout &L, const BlockSpa
 // time on blocks of 16 to 64 tiles (worker 9.0 -> 6.7 ms, server 0.81 -> 0.44 ms on 2^28 elements
 // in blocks of 2^16) and a few percent on blocks of 256 tiles.
 constexpr int READY_STRIDE = 16;    // 64-bit words
-__device__ __forceinline__ unsigned long long *ready_word(const Scratch &X, const Layout &L, int set, int64_t b)
+__device__ __forceinline__ unsigned long long *ready_word(const Scratch &X, const Layout &L, int set, const BlockSpan &sp)
 {
-    return X.ready + ((int64_t)set * L.ntiles + gatherer_tile(L, block_span(L, b))) * READY_STRIDE;
+    return X.ready + ((int64_t)set * L.ntiles + gatherer_tile(L, sp)) * READY_STRIDE;
 }
 
 // What a uniform tile has to follow up on after posting its partial: the block
 // whose scale it must form (it is that block's last whole tile), or -1.
 struct Posted {
     int gather;
+    BlockSpan sp;               // of that block
 };
 
 __device__ __forceinline__ void clear_posted(Posted &P) { P.gather = -1; }
@@ -606,10 +617,9 @@ __device__ __forceinline__ double sum_block_partials(const Layout &L, int64_t b,
 // the same arguments; returns the same answer to all of them.
 constexpr int GATHER_KEEP = 4;      // partial words per thread whose values are kept while polling
 
-__device__ __forceinline__ bool gather_scale(int64_t b, const Layout &L, const Scratch &X, int set, SyncShared &S,
+__device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &L, const Scratch &X, int set, SyncShared &S,
                                              float *s)
 {
-    const BlockSpan sp = block_span(L, b);
     const unsigned long long *part = set_part(X, L, set);
     const unsigned long long tag = set_tag(X, set);
     // Thread t is in charge of tiles t, t + 256, ...  All of them are polled in every round, so
@@ -667,15 +677,15 @@ __device__ __forceinline__ bool gather_scale(int64_t b, const Layout &L, const S
 // other tile of the block was handed out earlier), writes it out and posts it
 // for the block's other tiles.  Called by every thread of that workgroup;
 // returns to all of them whether the scale could be formed, and the scale.
-__device__ __forceinline__ bool finish_block(int64_t b, const Layout &L, const Scratch &X, int set,
+__device__ __forceinline__ bool finish_block(int64_t b, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
                                              float *scales_out, SyncShared &S, float *scale)
 {
     float s = 0.f;
-    const bool ok = gather_scale(b, L, X, set, S, &s);
+    const bool ok = gather_scale(sp, L, X, set, S, &s);
     if (threadIdx.x == 0) {
         if (ok) {
             scales_out[b] = s;
-            __hip_atomic_store(ready_word(X, L, set, b),
+            __hip_atomic_store(ready_word(X, L, set, sp),
                                ((unsigned long long)X.epoch << 32) | (unsigned long long)__float_as_uint(s),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
@@ -693,7 +703,7 @@ __device__ __forceinline__ void resolve_posted(const Posted &P, const Layout &L,
                                                float *scales_out, SyncShared &S)
 {
     float s;
-    if (P.gather >= 0) (void)finish_block(P.gather, L, X, set, scales_out, S, &s);
+    if (P.gather >= 0) (void)finish_block(P.gather, P.sp, L, X, set, scales_out, S, &s);
 }
 
 // Thread 0's early look at the ready word of block b (b < 0: none).
@@ -701,18 +711,18 @@ __device__ __forceinline__ unsigned long long peek_ready(int b, const Layout &L,
 {
     unsigned long long w = 0ull;           // epoch 0 is never used
     if (threadIdx.x == 0 && b >= 0)
-        w = __hip_atomic_load(ready_word(X, L, set, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w = __hip_atomic_load(ready_word(X, L, set, block_span(L, b)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return w;
 }
 
-// Wait (bounded) until the block's gatherer has posted block b's scale of this call.
+// Wait (bounded) until the block's gatherer has posted its scale of this call.
 // `peeked` is thread 0's earlier look at the word (see peek_ready).  Called by
 // every thread of the workgroup; same answer to all of them.
-__device__ __forceinline__ bool wait_ready(int64_t b, unsigned long long peeked, const Layout &L, const Scratch &X,
+__device__ __forceinline__ bool wait_ready(const BlockSpan &sp, unsigned long long peeked, const Layout &L, const Scratch &X,
                                            int set, SyncShared &S, float *s)
 {
     if (threadIdx.x == 0) {
-        const unsigned long long *word = ready_word(X, L, set, b);
+        const unsigned long long *word = ready_word(X, L, set, sp);
         unsigned long long w = peeked;
         int found = ((unsigned)(w >> 32) == X.epoch) ? 1 : 0;
         for (int it = 0; !found && it < X.spin_limit; ++it) {
@@ -821,11 +831,11 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
     float s_head = 0.f, s_tail = 0.f;
     bool fin_head = false, fin_tail = false;
     if (head_open && finishes_with_mixed(L, block_span(L, fb))) {
-        fin_head = finish_block(fb, L, X, set, scales_out, S, &s_head);
+        fin_head = finish_block(fb, block_span(L, fb), L, X, set, scales_out, S, &s_head);
         if (!fin_head) defer_segment(tile, 0, X, set);
     }
     if (tail_open && finishes_with_mixed(L, block_span(L, lb))) {
-        fin_tail = wait_ready(lb, 0ull, L, X, set, S, &s_tail);
+        fin_tail = wait_ready(block_span(L, lb), 0ull, L, X, set, S, &s_tail);
         if (!fin_tail) defer_segment(tile, 1, X, set);
     }
 #pragma unroll
@@ -855,18 +865,18 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
 // tile's block is larger than fuse_limit and the set's last call left p in the buffer, what that
 // call's payload stood for is subtracted.  The scale is looked up before the tile's loads are
 // issued (two dependent scalar loads that then overlap with them) and applied once they are in.
-// Called by every thread with the same tile and set.
+// Called by every thread with the same block and set.
 struct LoadedCorrection {
     float s;
     bool on;
 };
-__device__ __forceinline__ LoadedCorrection loaded_correction(const Layout &L, int32_t tile, const Scratch &X, int set)
+__device__ __forceinline__ LoadedCorrection loaded_correction(const Layout &L, int32_t b, const Scratch &X, int set)
 {
     LoadedCorrection c;
     c.s = 0.f;
     c.on = false;
     if (!L.lazy || !((X.pending >> (set - X.set_base)) & 1ull)) return c;
-    const int32_t li = L.late_index[L.tile_fb[tile]];
+    const int32_t li = L.late_index[b];
     if (li < 0) return c;
     c.s = X.lazy_scales[(int64_t)set * X.lazy_stride + li];
     c.on = true;
@@ -890,17 +900,15 @@ __device__ __forceinline__ void correct_loaded_residual(float4 (&e)[SUBROWS], co
 //               after sync_group_wait.
 enum { UNI_DONE = 0, UNI_PARKED = 1, UNI_PENDING = 2, UNI_HELD = 3 };
 
-__device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layout &L, int32_t tile, int n_valid,
-                                                uint64_t *signs, float *scales_out, float *err_tile,
-                                                const Scratch &X, int set, SyncShared &S, Posted &P,
+__device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layout &L, int32_t tile, int32_t b,
+                                                const BlockSpan &sp, int n_valid, uint64_t *signs, float *scales_out,
+                                                float *err_tile, const Scratch &X, int set, SyncShared &S, Posted &P,
                                                 bool hold = false)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int32_t b = L.tile_fb[tile];
     clear_posted(P);
     store_signs(p, n_valid, signs, tile_start, L.W);
     const double total = block_sum(abs_sum(p, n_valid), S.red);
-    const BlockSpan sp = block_span(L, b);
     if (sp.bs >= tile_start && sp.be <= tile_start + TILE) {
         const float s = (float)(total / (double)(sp.be - sp.bs));
         if (threadIdx.x == 0) scales_out[b] = s;
@@ -915,19 +923,22 @@ __device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layo
         store_tile(err_tile, p, n_valid);
         return UNI_PARKED;
     }
-    if ((int64_t)tile == gatherer_tile(L, sp)) P.gather = b;
+    if ((int64_t)tile == gatherer_tile(L, sp)) {
+        P.gather = b;
+        P.sp = sp;
+    }
     return UNI_PENDING;
 }
 
 // Write the residual of a uniform tile of counted block b whose p was kept
 // (e_{t+1} = p_t - Delta_t, Algorithm 4), waiting (bounded) for the scale; if
 // the wait runs out, p is parked and the segment deferred.
-__device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t tile, int n_valid, int b,
+__device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t tile, int n_valid, const BlockSpan &sp,
                                                unsigned long long peeked, float *err_tile, const Layout &L,
                                                const Scratch &X, int set, SyncShared &S, bool may_wait = true)
 {
     float s = 0.f;
-    const bool ok = may_wait && wait_ready(b, peeked, L, X, set, S, &s);
+    const bool ok = may_wait && wait_ready(sp, peeked, L, X, set, S, &s);
     if (ok) {
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) residual4(p[k], s);
@@ -950,9 +961,9 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
 // the others look for it.  Both waits are bounded, and nothing depends on their outcome:
 // whoever runs out of patience just writes.
 // Called by every thread of the workgroup, after compress_uniform returned UNI_HELD.
-__device__ __forceinline__ void sync_group_wait(int32_t tile, const Layout &L, const Scratch &X, int set, SyncShared &S)
+__device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
+                                                SyncShared &S)
 {
-    const BlockSpan sp = block_span(L, L.tile_fb[tile]);
     const int64_t first_whole = sp.t0 + ((sp.bs % TILE) != 0 ? 1 : 0);
     const int64_t last_whole = last_whole_tile(sp);
     const int64_t g0 = first_whole + ((int64_t)tile - first_whole) / L.sync_group * L.sync_group;

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(THREADS) void k_worker_mixed(Layout L, ScratchRef R
 // fuse_limit rules out, and it is bounded by spin_limit in any case.
 //
 // What is streamed comes from a producer (Algorithm 4 or Algorithm 3 worker):
-//   issue(L, idx, tile)        start the tile's loads (idx: which worker)
+//   issue(L, idx, whole tile)  start the tile's loads (idx: which worker)
 //   produce(L, idx, tile, p)   the corrected values p of Algorithm 4 (and the role's other stores)
 //   signs(L, idx), scales(L, idx), err_tile(idx, tile)   where that participant's outputs go
 struct HeldTile {
@@ -148,11 +148,12 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
         if (t >= total) break;
         if (threadIdx.x == 0) tk_next = atomicAdd(X.ticket, 1u);   // the answer is read at the next tile
         const int idx = (int)(t / per_part);
-        const int32_t tile = L.uniform_tiles[t % per_part];
+        const WholeTile w = L.whole_tiles[t % per_part];
+        const int32_t tile = w.tile;
         const int set = X.set_base + idx;
 
         // ---- this tile's loads go out first
-        prod.issue(L, idx, tile);
+        prod.issue(L, idx, w);
 
         // ---- while they fly: follow up on the previous tile's post, write out the oldest tile held
         const int old_b = staged[0].b;
@@ -164,10 +165,10 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
             // The block of the oldest tile cannot complete while this workgroup sits on a tile of
             // the same block that is not posted yet (the new one): then do not wait, park p and
             // leave the tile to the second pass.
-            const bool may_wait = !(old_idx == idx && L.tile_fb[tile] == old_b);
+            const bool may_wait = !(old_idx == idx && w.b == old_b);
             float4 pv_old[SUBROWS];
             stage_load(stage, staged[0].slot, pv_old);
-            finish_uniform(pv_old, old_tile, TILE, old_b, peeked, prod.err_tile(old_idx, old_tile), L, X,
+            finish_uniform(pv_old, old_tile, TILE, block_span(L, old_b), peeked, prod.err_tile(old_idx, old_tile), L, X,
                            X.set_base + old_idx, S, may_wait);
         }
         {
@@ -189,7 +190,7 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
         float4 pv[SUBROWS];
         prod.produce(L, idx, tile, pv);
         HeldTile &slot = held[PIPE_DEPTH - 1];
-        const int kind = compress_uniform(pv, L, tile, TILE, prod.signs(L, idx), prod.scales(L, idx),
+        const int kind = compress_uniform(pv, L, tile, w.b, span_of(w.bs, w.be), TILE, prod.signs(L, idx), prod.scales(L, idx),
                                           prod.err_tile(idx, tile), X, set, S, posted);
         posted_idx = idx;
         slot.b = -1;
@@ -198,7 +199,7 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
             for (int k = 0; k < SUBROWS; ++k) slot.p[k] = pv[k];
             slot.tile = tile;
             slot.idx = idx;
-            slot.b = L.tile_fb[tile];
+            slot.b = w.b;
         }
     }
 
@@ -209,14 +210,14 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
         if (staged[q].b >= 0) {
             float4 pv_old[SUBROWS];
             stage_load(stage, staged[q].slot, pv_old);
-            finish_uniform(pv_old, staged[q].tile, TILE, staged[q].b, 0ull, prod.err_tile(staged[q].idx, staged[q].tile),
+            finish_uniform(pv_old, staged[q].tile, TILE, block_span(L, staged[q].b), 0ull, prod.err_tile(staged[q].idx, staged[q].tile),
                            L, X, X.set_base + staged[q].idx, S);
         }
     }
 #pragma unroll
     for (int q = 0; q < PIPE_DEPTH; ++q) {
         if (held[q].b >= 0)
-            finish_uniform(held[q].p, held[q].tile, TILE, held[q].b, 0ull, prod.err_tile(held[q].idx, held[q].tile), L,
+            finish_uniform(held[q].p, held[q].tile, TILE, block_span(L, held[q].b), 0ull, prod.err_tile(held[q].idx, held[q].tile), L,
                            X, X.set_base + held[q].idx, S);
     }
 }
@@ -234,10 +235,10 @@ struct WorkerProducer {
     {
         return A.err + (int64_t)idx * A.state_stride + (int64_t)tile * TILE;
     }
-    __device__ __forceinline__ void issue(const Layout &L, int idx, int32_t tile)
+    __device__ __forceinline__ void issue(const Layout &L, int idx, const WholeTile &w)
     {
-        const int64_t tile_start = (int64_t)tile * TILE;
-        corr = loaded_correction(L, tile, *X, X->set_base + idx);
+        const int64_t tile_start = (int64_t)w.tile * TILE;
+        corr = loaded_correction(L, w.b, *X, X->set_base + idx);
         load_tile(A.grad + (int64_t)idx * A.grad_stride + tile_start, gv, TILE);
         if (MOM) load_tile(A.mom + (int64_t)idx * A.state_stride + tile_start, mv, TILE);
         load_tile(A.err + (int64_t)idx * A.state_stride + tile_start, ev, TILE);
@@ -319,26 +320,40 @@ template <bool MOM, bool MIXED, bool QUAL>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
-    const Scratch X = open_call(R);
     __shared__ typename TilesShared<MIXED || QUAL>::type S;
-    const bool whole = !MIXED || (int)blockIdx.x >= L.n_mixed;
-    // without mixed tiles the list of whole tiles is 0, 1, 2, ...: one dependent load less
-    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? L.uniform_tiles[blockIdx.x - L.n_mixed] : L.mixed_tiles[blockIdx.x];
     const int worker = blockIdx.y;
-    const int n_valid = whole ? TILE : tile_valid(L, tile);
-    const int64_t tile_start = (int64_t)tile * TILE;
-    const float *g = A.grad + (int64_t)worker * A.grad_stride + tile_start;
-    float *m = MOM ? A.mom + (int64_t)worker * A.state_stride + tile_start : nullptr;
-    float *e = A.err + (int64_t)worker * A.state_stride + tile_start;
+    const float *g = A.grad + (int64_t)worker * A.grad_stride;
+    float *m = MOM ? A.mom + (int64_t)worker * A.state_stride : nullptr;
+    float *e = A.err + (int64_t)worker * A.state_stride;
     float *scales_out = A.scales + (int64_t)worker * A.scales_stride;
     uint64_t *signs = A.signs + (int64_t)worker * A.signs_stride;
     float4 gv[SUBROWS], mv[SUBROWS], pv[SUBROWS];
+    if (!MIXED) {
+        // whole tile i is tile i: its loads go out before anything is looked up
+        const int64_t start = (int64_t)blockIdx.x * TILE;
+        load_tile(g + start, gv, TILE);
+        if (MOM) load_tile(m + start, mv, TILE);
+        load_tile(e + start, pv, TILE);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const Scratch X = open_call(R);
+    const bool whole = !MIXED || (int)blockIdx.x >= L.n_mixed;
+    const WholeTile w = L.whole_tiles[!MIXED ? blockIdx.x : whole ? blockIdx.x - L.n_mixed : 0];
+    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? w.tile : L.mixed_tiles[blockIdx.x];
+    const int n_valid = whole ? TILE : tile_valid(L, tile);
+    const int64_t tile_start = (int64_t)tile * TILE;
+    g += tile_start;
+    if (MOM) m += tile_start;
+    e += tile_start;
     if (whole) {
         Posted P;
-        const LoadedCorrection corr = loaded_correction(L, tile, X, worker);
-        load_tile(g, gv, TILE);
-        if (MOM) load_tile(m, mv, TILE);
-        load_tile(e, pv, TILE);
+        const BlockSpan sp = span_of(w.bs, w.be);
+        const LoadedCorrection corr = loaded_correction(L, w.b, X, worker);
+        if (MIXED) {
+            load_tile(g, gv, TILE);
+            if (MOM) load_tile(m, mv, TILE);
+            load_tile(e, pv, TILE);
+        }
         correct_loaded_residual(pv, corr);
         worker_values<MOM>(gv, mv, pv, A.mu, A.r);
         if (MOM) store_tile(m, mv, TILE);
@@ -348,12 +363,12 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
             quality_of_tile(a, L, Q, tile, worker, TILE, S);
         }
-        const int kind = compress_uniform(pv, L, tile, TILE, signs, scales_out, e, X, worker, S, P, true);
+        const int kind = compress_uniform(pv, L, tile, w.b, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
         resolve_posted(P, L, X, worker, scales_out, S);
         if (kind == UNI_PENDING) {
-            finish_uniform(pv, tile, TILE, L.tile_fb[tile], 0ull, e, L, X, worker, S);
+            finish_uniform(pv, tile, TILE, sp, 0ull, e, L, X, worker, S);
         } else if (kind == UNI_HELD) {
-            sync_group_wait(tile, L, X, worker, S);
+            sync_group_wait(tile, sp, L, X, worker, S);
             store_tile(e, pv, TILE);
         }
     } else if constexpr (MIXED) {
