@@ -240,7 +240,7 @@ private:
 struct DeviceFacts {
     bool known;
     int cus;                                    // compute units
-    int uniform, tiles, server, small;          // workgroups per unit of the kernels of these names
+    int uniform, tiles, server[2], small;       // workgroups per unit of the kernels of these names (server: without, with mixed tiles)
 };
 DeviceFacts g_facts[MAX_DEVICES];
 
@@ -254,7 +254,8 @@ int device_facts(int device, DeviceFacts *out)
         EF_HIP(hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, device));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, true, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server, ef::k_server_tiles<true>, ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], ef::k_server_tiles<false>, ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], ef::k_server_tiles<true>, ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
         if (small_s < f.small) f.small = small_s;
@@ -475,7 +476,6 @@ int build_device(ef_plan *p)
     p->worker_grid = facts.cus * facts.uniform;
     p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
     p->lim_direct = (int32_t)((int64_t)facts.cus * facts.tiles / 2);
-    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server / 2);
     // Launches that (nearly) fit on the GPU all at once: up to twice what is resident.  A block's tiles are at
     // most half of that and are dispatched in order, as the other one-pass kernels assume.  Measured, worker
     // calls in blocks of 30 000 elements, these kernels against k_worker_tiles + k_tail: 64 workgroups 7.7 /
@@ -497,6 +497,9 @@ int build_device(ef_plan *p)
     }
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
+    // the server's limit is that of the kernel this layout runs (2^28 elements in blocks of 1024 tiles, 8 workers:
+    // 560 us in one pass, 755 in two)
+    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[p->L.n_mixed ? 1 : 0] / 2);
     if (whole.empty()) whole.push_back(ef::WholeTile());    // the kernels read a record before they look whether there is one
     // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
     for (int64_t b = 0; b < B; ++b)
