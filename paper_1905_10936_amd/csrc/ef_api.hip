@@ -65,7 +65,11 @@ struct ef_plan {
     unsigned long long *d_defer_list;
     unsigned long long *d_fin_list;
     int32_t *d_mixed;               // tile lists
-    ef::WholeTile *d_whole;
+    int32_t *d_whole;
+    ef::TileRec *d_tiles, *d_in_order;
+    ef::StartWord *d_words;         // [n_mixed][TILE_WORDS]
+    int32_t *d_dense;
+    std::vector<char> dense_host;   // [ntiles] is the tile a dense one?
     // compressor-quality diagnostics
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
@@ -100,6 +104,7 @@ namespace {
 enum { ROLE_TICKET = 0, ROLE_SERVER = 1, ROLE_TILES = 2 };
 
 constexpr int MAX_DEVICES = 64;
+constexpr int FEW_LEAD = 256;           // see build_device
 std::mutex g_scratch_mutex;
 double *g_scratch_ptr[MAX_DEVICES];     // [device] address of `scratch` on that device, once looked up
 
@@ -253,9 +258,9 @@ int device_facts(int device, DeviceFacts *out)
         int small_s = 0;
         EF_HIP(hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, device));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, true, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], ef::k_server_tiles<false>, ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], ef::k_server_tiles<true>, ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<true, true>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
         if (small_s < f.small) f.small = small_s;
@@ -288,8 +293,8 @@ bool finishes_with_mixed(const ef_plan *p, const ef_plan::Role &r, int64_t b)
 
 // What the main kernels of a call always leave to the kernel that ends it: the scales of the
 // blocks larger than fuse_limit, and the residual of every open segment that is not finished
-// where it is computed (the segments of those large blocks, and the segments that blocks with
-// whole tiles have in mixed tiles).
+// where it is computed (the segments of those large blocks and, before the persistent worker kernel, the segments
+// that blocks with whole tiles have in mixed tiles).
 int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
 {
     std::vector<uint32_t> items;
@@ -302,6 +307,11 @@ int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
         if (p->lazy && has_uniform_tile(p, b)) late_index[(size_t)b] = (int32_t)late.size();
         late.push_back((int32_t)b);
     }
+    // are a block's segments in mixed tiles finished by the main kernels?
+    const bool in_place = &r != &p->role[ROLE_TICKET];
+    auto finished = [&](int64_t b, int32_t t) {
+        return in_place && !p->dense_host[(size_t)t] ? tiles_of_block(p, b) <= r.fuse_limit : finishes_with_mixed(p, r, b);
+    };
     for (int32_t t = 0; t < p->L.ntiles; ++t) {
         const int64_t start = (int64_t)t * ef::TILE, end = start + ef::TILE;
         const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
@@ -317,8 +327,8 @@ int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
             }
         } else {
             // a tile the mixed-tile code handles (several blocks, or the ragged end of the vector)
-            if (o[fb] < start && !finishes_with_mixed(p, r, fb)) items.push_back(((uint32_t)t << 1) | 0u);
-            if (o[lb + 1] > end && !finishes_with_mixed(p, r, lb)) items.push_back(((uint32_t)t << 1) | 1u);
+            if (o[fb] < start && !finished(fb, t)) items.push_back(((uint32_t)t << 1) | 0u);
+            if (o[lb + 1] > end && !finished(lb, t)) items.push_back(((uint32_t)t << 1) | 1u);
         }
     }
     r.n_late = (uint32_t)late.size();
@@ -384,15 +394,9 @@ int refresh_limits(ef_plan *p)
     }
 }
 
-// Records and start words of the kernels for launches that (nearly) fit on the GPU all at once, if the
+// Records of the kernels for launches that (nearly) fit on the GPU all at once, if the
 // layout has calls for them: few enough tiles, and no block of more tiles than a wavefront adds up.
-struct SmallTables {
-    std::vector<ef::SmallTile> tiles;
-    std::vector<uint32_t> starts;
-    std::vector<uint16_t> rank;
-};
-
-void small_tables(ef_plan *p, SmallTables &out)
+void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
 {
     const int32_t ntiles = p->L.ntiles;
     if (ntiles > p->small_wgs) return;
@@ -400,14 +404,13 @@ void small_tables(ef_plan *p, SmallTables &out)
     const int64_t d = p->L.d;
     for (int64_t b = 0; b < p->L.B; ++b)
         if (tiles_of_block(p, b) > ef::SMALL_SPAN) return;
-    std::vector<uint32_t> &starts = out.starts;
-    std::vector<uint16_t> &rank = out.rank;
-    out.tiles.resize((size_t)ntiles);
+    out.resize((size_t)ntiles);
     p->has_small = true;
+    int32_t words = 0;
     for (int32_t t = 0; t < ntiles; ++t) {
         const int64_t start = (int64_t)t * ef::TILE, end = start + ef::TILE;
         const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
-        ef::SmallTile &r = out.tiles[(size_t)t];
+        ef::SmallTile &r = out[(size_t)t];
         r = ef::SmallTile();
         r.fb = fb;
         r.nseg = lb - fb + 1;
@@ -425,21 +428,7 @@ void small_tables(ef_plan *p, SmallTables &out)
             r.tail_n = (int32_t)tiles_of_block(p, lb);
             r.tail_db = o[lb + 1] - o[lb];
         }
-        if (fb == lb && end <= d) continue;
-        r.words = (int32_t)(starts.size() / ef::SMALL_WORDS);
-        starts.resize(starts.size() + ef::SMALL_WORDS, 0u);
-        rank.resize(starts.size());
-        uint32_t *w = starts.data() + starts.size() - ef::SMALL_WORDS;
-        w[0] = 1u;
-        for (int32_t b = fb + 1; b <= lb; ++b) {
-            const int j = (int)(o[b] - start);
-            w[j >> 5] |= 1u << (j & 31);
-        }
-        unsigned before = 0;
-        for (int i = 0; i < ef::SMALL_WORDS; ++i) {
-            rank[starts.size() - ef::SMALL_WORDS + (size_t)i] = (uint16_t)before;
-            before += (unsigned)__builtin_popcount(w[i]);
-        }
+        if (fb != lb || end > d) r.words = words++;
     }
 }
 
@@ -482,25 +471,60 @@ int build_device(ef_plan *p)
     // 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3; server calls with 4 workers, against
     // k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
     p->small_wgs = 2 * facts.cus * facts.small;
-    SmallTables small;
+    std::vector<ef::SmallTile> small;
     small_tables(p, small);
 
-    std::vector<int32_t> mixed, cross;
-    std::vector<ef::WholeTile> whole;
-    whole.reserve((size_t)ntiles);
+    std::vector<int32_t> mixed, whole, cross;
+    std::vector<ef::TileRec> tiles((size_t)ntiles);
     for (int32_t t = 0; t < ntiles; ++t) {
-        const bool full = ((int64_t)t + 1) * ef::TILE <= d;
-        if (fb[t] == lb[t] && full)
-            whole.push_back({t, fb[t], p->offs_host[(size_t)fb[t]], p->offs_host[(size_t)fb[t] + 1], 0});
-        else
-            mixed.push_back(t);
+        const bool full = ((int64_t)t + 1) * ef::TILE <= d, one = fb[t] == lb[t] && full;
+        const int64_t last_end = p->offs_host[(size_t)lb[t] + 1];
+        const bool goes_on = lb[t] != fb[t] && last_end > ((int64_t)t + 1) * ef::TILE;
+        const int32_t tail = goes_on ? (int32_t)(2 * tiles_of_block(p, lb[t]) + (last_end % ef::TILE != 0 ? 1 : 0)) : 0;
+        const int64_t bs = p->offs_host[(size_t)fb[t]], be = p->offs_host[(size_t)fb[t] + 1];
+        tiles[(size_t)t] = {t, fb[t], lb[t] - fb[t] + 1, one ? -1 : (int32_t)mixed.size(), tail, (int32_t)(bs / ef::TILE),
+                            (int32_t)tiles_of_block(p, fb[t]), (int16_t)(bs % ef::TILE), (int16_t)(be % ef::TILE)};
+        (one ? whole : mixed).push_back(t);
+    }
+    // Which mixed tiles run in a kernel of their own: those of many segments, and with one of them every tile
+    // that a block without whole tiles shares with it, so that such a block is finished in one kernel.
+    std::vector<int32_t> dense;
+    p->dense_host.assign((size_t)ntiles, 0);
+    for (int32_t t : mixed) p->dense_host[(size_t)t] = tiles[(size_t)t].nseg > ef::FEW_SEGS;
+    auto joined = [&](int32_t t) {              // does a block without whole tiles go from tile t into t + 1?
+        const int64_t b = lb[t];
+        return t + 1 < ntiles && fb[t + 1] == b && tiles_of_block(p, b) == 2 && !has_uniform_tile(p, b);
+    };
+    for (int32_t t = 0; t + 1 < ntiles; ++t)
+        if (p->dense_host[(size_t)t] && joined(t)) p->dense_host[(size_t)t + 1] = 1;
+    for (int32_t t = ntiles - 1; t > 0; --t)
+        if (p->dense_host[(size_t)t] && joined(t - 1)) p->dense_host[(size_t)t - 1] = 1;
+    for (int32_t t : mixed)
+        if (p->dense_host[(size_t)t]) {
+            tiles[(size_t)t].nseg = -tiles[(size_t)t].nseg;
+            dense.push_back(t);
+        }
+    p->L.n_dense = (int32_t)dense.size();
+    // The order in which the kernels with one workgroup per tile take the tiles: ascending, but a mixed tile FEW_LEAD
+    // places ahead of where it is (or, if a block with whole tiles ends in it, of that block's first): it takes
+    // longer than a whole tile, and its blocks wait for it, as the call does at its end.
+    std::vector<ef::TileRec> in_order;
+    if (!mixed.empty()) {
+        in_order.reserve((size_t)ntiles);
+        size_t w = 0;
+        for (int32_t t : mixed) {
+            const ef::TileRec &r = tiles[(size_t)t];
+            const int64_t at = (r.n > 2 || (r.n == 2 && r.from == 0) ? r.t0 : t) - (int64_t)FEW_LEAD;
+            while (w < whole.size() && whole[w] < at) in_order.push_back(tiles[(size_t)whole[w++]]);
+            in_order.push_back(r);
+        }
+        while (w < whole.size()) in_order.push_back(tiles[(size_t)whole[w++]]);
     }
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
     // the server's limit is that of the kernel this layout runs (2^28 elements in blocks of 1024 tiles, 8 workers:
     // 560 us in one pass, 755 in two)
     p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[p->L.n_mixed ? 1 : 0] / 2);
-    if (whole.empty()) whole.push_back(ef::WholeTile());    // the kernels read a record before they look whether there is one
     // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
     for (int64_t b = 0; b < B; ++b)
         if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);
@@ -516,6 +540,10 @@ int build_device(ef_plan *p)
     mem.add(&p->d_tile_lb, nt, Arena::COPY, lb.data());
     mem.add(&p->d_mixed, mixed.size(), Arena::COPY, mixed.data());
     mem.add(&p->d_whole, whole.size(), Arena::COPY, whole.data());
+    mem.add(&p->d_tiles, nt, Arena::COPY, tiles.data());
+    mem.add(&p->d_in_order, in_order.size(), Arena::COPY, in_order.data());
+    mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
+    mem.add(&p->d_dense, dense.size(), Arena::COPY, dense.data());
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
@@ -530,15 +558,17 @@ int build_device(ef_plan *p)
     mem.add(&p->d_qpart, 4 * nt * nv, Arena::LEAVE);
     mem.add(&p->d_qtile, 2 * nt * nv, Arena::LEAVE);
     if (p->has_small) {
-        mem.add(const_cast<ef::SmallTile **>(&p->small.tiles), small.tiles.size(), Arena::COPY, small.tiles.data());
-        mem.add(const_cast<uint32_t **>(&p->small.starts), small.starts.size(), Arena::COPY, small.starts.data());
-        mem.add(const_cast<uint16_t **>(&p->small.rank), small.rank.size(), Arena::COPY, small.rank.data());
+        mem.add(const_cast<ef::SmallTile **>(&p->small.tiles), small.size(), Arena::COPY, small.data());
         mem.add(&p->small.done, (size_t)(ef::DONE_GROUPS + 1) * ef::DONE_STRIDE, Arena::ZERO);
     }
     { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
     p->small.state = p->d_state;
     p->L.mixed_tiles = p->d_mixed;
     p->L.whole_tiles = p->d_whole;
+    p->L.tiles = p->d_tiles;
+    p->L.grid_tiles = in_order.empty() ? p->d_tiles : p->d_in_order;
+    p->L.words = p->d_words;
+    p->L.dense_tiles = p->d_dense;
     p->L.offs = p->d_offs;
     p->L.tile_fb = p->d_tile_fb;
     p->L.tile_lb = p->d_tile_lb;
@@ -551,6 +581,10 @@ int build_device(ef_plan *p)
     p->X.snapshot = p->d_state + 1;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
+    if (p->L.n_mixed) {
+        hipLaunchKernelGGL(ef::k_start_words, dim3((unsigned)p->L.n_mixed), dim3(ef::THREADS), 0, nullptr, p->L, p->d_words);
+        EF_HIP(hipGetLastError());
+    }
     p->user_fuse_limit = -1;
     // Which worker kernel for this layout.  The persistent kernel needs enough tiles per workgroup
     // to fill its pipeline; beyond that the choice follows the measured cost per tile of each
@@ -1045,9 +1079,11 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         if (plan->L.n_mixed) {
             const dim3 grid((unsigned)plan->L.n_mixed, (unsigned)n_workers);
             if (has_mom)
-                hipLaunchKernelGGL(ef::k_worker_mixed<true>, grid, dim3(ef::THREADS), 0, s, L, c.X, A);
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs(),
+                                   (const int32_t *)plan->d_mixed);
             else
-                hipLaunchKernelGGL(ef::k_worker_mixed<false>, grid, dim3(ef::THREADS), 0, s, L, c.X, A);
+                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs(),
+                                   (const int32_t *)plan->d_mixed);
             EF_HIP(hipGetLastError());
         }
         int64_t wgs = (int64_t)plan->L.n_uniform * n_workers;
@@ -1059,7 +1095,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
             hipLaunchKernelGGL(ef::k_worker_uniform<false>, grid, block, 0, s, L, c.X, A, n_workers);
         EF_HIP(hipGetLastError());
     } else {
-        // every tile in one launch, the mixed tiles first
+        // every tile in one launch
         const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::THREADS);
         const bool mixed = plan->L.n_mixed != 0;
         ef::QualityArgs Q;
@@ -1068,10 +1104,18 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         Q.tile_sums = plan->d_qtile;
         Q.part_sums = plan->d_qpart;
         Q.out = quality;
-        if (quality && has_mom)
+        if (plan->L.n_dense) {
+            const dim3 dense((unsigned)plan->L.n_dense, (unsigned)n_workers);
+            if (quality)
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, true>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
+            else if (has_mom)
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
+            else
+                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
+            EF_HIP(hipGetLastError());
+        }
+        if (quality)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, true, true>), grid, block, 0, s, L, c.X, A, Q);
-        else if (quality)
-            hipLaunchKernelGGL((ef::k_worker_tiles<false, true, true>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom && mixed)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, true, false>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom)
@@ -1146,12 +1190,21 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
         return EF_OK;
     }
     const ef::Layout L = role_layout(plan, ROLE_SERVER);
-    if (L.n_mixed)
-        hipLaunchKernelGGL(ef::k_server_tiles<true>, dim3((unsigned)L.ntiles), dim3(ef::THREADS), 0, s, L, c.X, A,
+    if (L.n_dense) {
+        hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_dense), dim3(ef::THREADS), 0, s, L, c.X, A, L.dense_tiles,
                            plan->max_workers);
+        EF_HIP(hipGetLastError());
+    }
+    const dim3 grid((unsigned)L.ntiles), block(ef::THREADS);
+    const bool many = M > ef::SERVER_CHUNK;
+    if (L.n_mixed && many)
+        hipLaunchKernelGGL((ef::k_server_tiles<true, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+    else if (L.n_mixed)
+        hipLaunchKernelGGL((ef::k_server_tiles<true, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+    else if (many)
+        hipLaunchKernelGGL((ef::k_server_tiles<false, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else
-        hipLaunchKernelGGL(ef::k_server_tiles<false>, dim3((unsigned)L.ntiles), dim3(ef::THREADS), 0, s, L, c.X, A,
-                           plan->max_workers);
+        hipLaunchKernelGGL((ef::k_server_tiles<false, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     EF_HIP(hipGetLastError());
     return launch_tail(plan, ROLE_SERVER, c, 1, server_err, (int64_t)0, out_scales, (int64_t)0, s);
 }

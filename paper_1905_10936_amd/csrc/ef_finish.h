@@ -257,23 +257,23 @@ __device__ __forceinline__ void update_element(float &x, float &m, float delta, 
 
 template <bool WD>
 __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt, const uint64_t *signs,
-                                           const float *scales, float eta, float mu, float lambda, TileShared &S)
+                                           const float *scales, float eta, float mu, float lambda)
 {
     const int32_t tile = blockIdx.x;
     const int n_valid = tile_valid(L, tile);
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int32_t fb = L.tile_fb[tile], lb = L.tile_lb[tile];
     float *xt = x + tile_start;
     float *mtt = WD ? mt + tile_start : nullptr;
     const uint32_t *s32 = reinterpret_cast<const uint32_t *>(signs);
     const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
     const int64_t n_hw = 2 * L.W;
-    const uint16_t *seg = reinterpret_cast<const uint16_t *>(S.val);
     float4 xv4[SUBROWS], mv4[SUBROWS];
     load_tile(xt, xv4, n_valid);
     if (WD) load_tile(mtt, mv4, n_valid);
-    if (fb != lb) build_segment_index(L, tile, n_valid, fb, lb - fb + 1, S);
-    const float s_uniform = scales[fb];
+    const TileRec T = L.tiles[tile];
+    TilePlace at;
+    if (T.words >= 0) at = tile_place(L, T);
+    const float s_uniform = scales[T.fb];
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
         const int lb0 = local_base(k);
@@ -282,6 +282,7 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
         const unsigned nibble = (word >> sh) & 0xFu;
         float xv[4] = {xv4[k].x, xv4[k].y, xv4[k].z, xv4[k].w};
         float mv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        int seg = T.words >= 0 ? at.seg(k) : 0;
         if (WD) {
             mv[0] = mv4[k].x;
             mv[1] = mv4[k].y;
@@ -290,9 +291,11 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int j = lb0 + c;
             float s = s_uniform;
-            if (fb != lb) s = scales[fb + ((j < n_valid) ? seg[j] : 0)];
+            if (T.words >= 0) {
+                seg += (int)((at.starts(k) >> c) & 1u);
+                s = scales[T.fb + seg];
+            }
             const float delta = signed_scale(s, (nibble >> c) & 1u);
             update_element<WD>(xv[c], mv[c], delta, eta, mu, lambda);
         }
@@ -306,15 +309,13 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
 __global__ __launch_bounds__(THREADS) void k_apply(Layout L, float *x, const uint64_t *signs,
                                                    const float *scales, float eta)
 {
-    __shared__ TileShared S;
-    apply_tile<false>(L, x, nullptr, signs, scales, eta, 0.0f, 0.0f, S);
+    apply_tile<false>(L, x, nullptr, signs, scales, eta, 0.0f, 0.0f);
 }
 
 __global__ __launch_bounds__(THREADS) void k_apply_wd(Layout L, float *x, float *mt, const uint64_t *signs,
                                                       const float *scales, float eta, float mu, float lambda)
 {
-    __shared__ TileShared S;
-    apply_tile<true>(L, x, mt, signs, scales, eta, mu, lambda, S);
+    apply_tile<true>(L, x, mt, signs, scales, eta, mu, lambda);
 }
 
 }  // namespace ef

@@ -15,8 +15,8 @@ __device__ __forceinline__ float mean_of(float acc, float Mf, float Minv)
 }
 
 constexpr int SERVER_CHUNK = 8;     // workers whose sign words are in flight together
-constexpr int SCALE_GROUP = 4;      // mixed tiles: workers whose scales are staged in LDS together ...
-constexpr int SCALE_STAGE = TILE / 2;   // ... in this many floats
+constexpr int SCALE_GROUP = 4;      // mixed tiles: workers whose scales and sign bits are staged in LDS together ...
+constexpr int SCALE_STAGE = TILE;    // ... in this many floats (as many as a tile can have segments)
 
 typedef unsigned vu4 __attribute__((ext_vector_type(4)));
 
@@ -54,11 +54,11 @@ __device__ __forceinline__ vu4 transpose_signs(const unsigned (&h)[SERVER_CHUNK]
     return vu4{out[0], out[1], out[2], out[3]};
 }
 
-// LDS of server_values_whole, laid over TileShared::val.
+// LDS of server_values_whole.
 constexpr int SUM_TABLE = 256;                          // floats: one sum per pattern of eight signs
 constexpr int EXCHANGE_AT = SUM_TABLE;                  // 1 KiB per wavefront
 constexpr int NIBBLE_AT = EXCHANGE_AT + NWAVES * 256;   // SERVER_CHUNK x 16 float4
-static_assert(NIBBLE_AT + SERVER_CHUNK * 64 <= TILE, "fits into TileShared::val");
+constexpr int SERVER_LDS = NIBBLE_AT + SERVER_CHUNK * 64;      // floats
 
 // p~ of a tile that lies inside one block b (Algorithm 4, server: decode and add the M payloads
 // in worker order, divide by M, add the rescaled server residual tv).  Inside a block every element's
@@ -73,16 +73,17 @@ static_assert(NIBBLE_AT + SERVER_CHUNK * 64 <= TILE, "fits into TileShared::val"
 // Workers beyond the eighth are added one by one, eight at a time: entry (u, nibble) of a second table
 // holds the four values +-s_u that a nibble of worker u's bits stands for, so four addends cost
 // one bit-field extract and one 128-bit LDS read.
-// Called by every thread of the workgroup; S.val is free again on return.
+// Called by every thread of the workgroup; lds (SERVER_LDS floats) is free again on return.
+template <bool MANY>
 __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t tile_start, int32_t b,
-                                                    const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], TileShared &S)
+                                                    const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], float *lds)
 {
     float acc[SUBROWS][4];
     const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
     const int64_t in_half = 4 * A.in_signs_stride;
     const int64_t half0 = (tile_start >> 4) + threadIdx.x;      // this lane's 16 elements: 16 * threadIdx.x of the tile
     const float r = A.r, Mf = A.Mf, Minv = A.Minv;
-    unsigned *exchange = reinterpret_cast<unsigned *>(S.val) + EXCHANGE_AT + wave_id() * 256;
+    unsigned *exchange = reinterpret_cast<unsigned *>(lds) + EXCHANGE_AT + wave_id() * 256;
     {
         unsigned h[SERVER_CHUNK];
         float sc[SERVER_CHUNK];
@@ -96,18 +97,18 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
 #pragma unroll
         for (int u = 0; u < SERVER_CHUNK; ++u)
             if (u < A.M) sum = sum + signed_scale(sc[u], (threadIdx.x >> u) & 1u);
-        S.val[threadIdx.x] = A.M <= SERVER_CHUNK ? mean_of(sum, Mf, Minv) : sum;
+        lds[threadIdx.x] = MANY ? sum : mean_of(sum, Mf, Minv);
         *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) = transpose_signs(h);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) {
             const unsigned pat = exchange[64 * k + lane_id()];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[k][c] = S.val[(pat >> (8 * c)) & 255u];
+            for (int c = 0; c < 4; ++c) acc[k][c] = lds[(pat >> (8 * c)) & 255u];
         }
     }
-    if (A.M > SERVER_CHUNK) {
-        float4 *table = reinterpret_cast<float4 *>(S.val + NIBBLE_AT);
+    if constexpr (MANY) {
+        float4 *table = reinterpret_cast<float4 *>(lds + NIBBLE_AT);
         const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
         for (int i0 = SERVER_CHUNK; i0 < A.M; i0 += SERVER_CHUNK) {
             unsigned h[SERVER_CHUNK];
@@ -152,7 +153,7 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[k][c] = mean_of(acc[k][c], Mf, Minv);
     }
-    __syncthreads();            // S.val is free again
+    __syncthreads();            // lds is free again
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
         p[k].x = acc[k][0] + r * tv[k].x;
@@ -162,82 +163,64 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
     }
 }
 
-// The same for a tile where several blocks meet (or the ragged end of the vector): a
-// per-element segment index in LDS selects each worker's scale.  te: the tile of the server residual.
-__device__ __forceinline__ void server_values_mixed(const Layout &L, const ServerArgs &A, int32_t tile, int n_valid,
-                                                    const float *te, float4 (&p)[SUBROWS], TileShared &S)
+// The same for a tile where several blocks meet (or the ragged end of the vector).  The scales of the tile's
+// segments are staged in LDS, up to SCALE_GROUP workers at a time (one coalesced read per worker instead of a
+// gather per element), and looked up there by segment.  te: the tile of the server residual.
+__device__ __forceinline__ void server_values_mixed(const Layout &L, const ServerArgs &A, int32_t tile, const TileRec &T,
+                                                    const TilePlace &at, int n_valid, const float *te, float4 (&p)[SUBROWS],
+                                                    TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int32_t fb = L.tile_fb[tile], lb = L.tile_lb[tile];
     float acc[SUBROWS][4];
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
 
-    // this lane's 4 sign bits of sub-row k live in the 32-bit half-word hw0 + 8k
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(A.signs_in);
-    const int64_t hw0 = (tile_start + local_base(0)) >> 5;
-    const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
-    const int64_t n_hw = 2 * L.W;
-    const int64_t in_hw = 2 * A.in_signs_stride;
-
-    const int nseg = lb - fb + 1;
-    build_segment_index(L, tile, n_valid, fb, nseg, S);
-    const ushort4 *seg4 = reinterpret_cast<const ushort4 *>(S.val);
-    // The scales of the tile's segments are staged in LDS, SCALE_GROUP workers at a time where
-    // they fit (one coalesced read per worker instead of a gather per element), and looked up
-    // there; a tile with more segments than the stage holds gathers them from global memory.
-    float *seg_scale = S.val + TILE / 2;            // the index takes the first half
-    const int group = nseg * SCALE_GROUP <= SCALE_STAGE ? SCALE_GROUP : nseg <= SCALE_STAGE ? 1 : 0;
-    if (group) {
-        for (int i0 = 0; i0 < A.M; i0 += group) {
-            uint32_t word[SCALE_GROUP][SUBROWS];
+    // A lane loads each worker's bits of 16 consecutive elements and finds those of its own four through LDS, as
+    // in server_values_whole.
+    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
+    const int64_t half0 = (tile_start >> 4) + threadIdx.x;
+    const bool in = half0 < 4 * L.W;
+    unsigned *exchange = S.half + wave_id() * 128;
+    const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
+    const int nseg = abs(T.nseg), group = min(SCALE_GROUP, SCALE_STAGE / nseg);
+    for (int i0 = 0; i0 < A.M; i0 += group) {
+        unsigned h[SCALE_GROUP];
 #pragma unroll
-            for (int u = 0; u < SCALE_GROUP; ++u) {
-                const int i = min(i0 + u, A.M - 1);      // past the group or M: loaded, not used
+        for (int u = 0; u < SCALE_GROUP; ++u) {
+            const int i = min(i0 + u, A.M - 1);          // past the group or M: loaded, not used
+            h[u] = in ? s16[(int64_t)i * 4 * A.in_signs_stride + half0] : 0u;
+        }
+        if (i0 > 0) __syncthreads();                     // the stage is read no more
+        for (int u = 0; u < group && i0 + u < A.M; ++u) {
+            const float *sc_i = A.scales_in + (int64_t)(i0 + u) * A.in_scales_stride + T.fb;
+            for (int j = threadIdx.x; j < nseg; j += THREADS) S.val[u * nseg + j] = sc_i[j];
+        }
+        exchange[2 * lane_id()] = h[0] | (h[1] << 16);
+        exchange[2 * lane_id() + 1] = h[2] | (h[3] << 16);
+        __syncthreads();
 #pragma unroll
-                for (int k = 0; k < SUBROWS; ++k) {
-                    const int64_t hw = hw0 + 8 * k;
-                    word[u][k] = (hw < n_hw) ? s32[(int64_t)i * in_hw + hw] : 0u;
-                }
-            }
-            if (i0 > 0) __syncthreads();                 // the stage is read no more
-            for (int u = 0; u < group && i0 + u < A.M; ++u) {
-                const float *sc_i = A.scales_in + (int64_t)(i0 + u) * A.in_scales_stride + fb;
-                for (int j = threadIdx.x; j < nseg; j += THREADS) seg_scale[u * nseg + j] = sc_i[j];
-            }
-            __syncthreads();
+        for (int k = 0; k < SUBROWS; ++k) {
+            // opaque: the sixteen segment numbers would otherwise be formed once, before the loop, and spilled
+            unsigned place = at.row[k];
+            asm volatile("" : "+v"(place));
+            int seg[4], s0 = (int)(place >> 4) - 1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) seg[c] = s0 += (int)((place >> c) & 1u);
+            // elements 256k + 4*lane .. +3 of the wavefront: half-word 16k + lane/4, nibble lane%4
+            const int e = 2 * (16 * k + (lane_id() >> 2));
+            const unsigned two[2] = {exchange[e] >> sh, exchange[e + 1] >> sh};
 #pragma unroll
             for (int u = 0; u < SCALE_GROUP; ++u) {
                 if (u < group && i0 + u < A.M) {
-                    const float *sc_u = seg_scale + u * nseg;
+                    const float *sc_u = S.val + u * nseg;
+                    const unsigned nibble = two[u >> 1] >> (16 * (u & 1));
 #pragma unroll
-                    for (int k = 0; k < SUBROWS; ++k) {
-                        const unsigned nibble = (word[u][k] >> sh) & 0xFu;
-                        const ushort4 sg = seg4[local_base(k) >> 2];
-                        acc[k][0] = acc[k][0] + signed_scale(sc_u[sg.x], nibble & 1u);
-                        acc[k][1] = acc[k][1] + signed_scale(sc_u[sg.y], nibble & 2u);
-                        acc[k][2] = acc[k][2] + signed_scale(sc_u[sg.z], nibble & 4u);
-                        acc[k][3] = acc[k][3] + signed_scale(sc_u[sg.w], nibble & 8u);
-                    }
+                    for (int c = 0; c < 4; ++c) acc[k][c] = acc[k][c] + signed_scale(sc_u[seg[c]], (nibble >> c) & 1u);
                 }
             }
-        }
-    } else {
-        for (int i = 0; i < A.M; ++i) {
-            const float *sc_i = A.scales_in + (int64_t)i * A.in_scales_stride + fb;
-#pragma unroll
-            for (int k = 0; k < SUBROWS; ++k) {
-                const int64_t hw = hw0 + 8 * k;
-                const uint32_t word = (hw < n_hw) ? s32[(int64_t)i * in_hw + hw] : 0u;
-                const unsigned nibble = (word >> sh) & 0xFu;
-                const ushort4 sg = seg4[local_base(k) >> 2];
-                acc[k][0] = acc[k][0] + signed_scale(sc_i[sg.x], nibble & 1u);
-                acc[k][1] = acc[k][1] + signed_scale(sc_i[sg.y], nibble & 2u);
-                acc[k][2] = acc[k][2] + signed_scale(sc_i[sg.z], nibble & 4u);
-                acc[k][3] = acc[k][3] + signed_scale(sc_i[sg.w], nibble & 8u);
-            }
+            __builtin_amdgcn_sched_barrier(0);      // one sub-row after the other: few registers
         }
     }
     __syncthreads();            // S.val is free again
@@ -253,20 +236,128 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
     }
 }
 
-// One mixed tile of the server.  The residual tile is loaded after the payloads have been added up,
-// and the segment indices stay in LDS: both keep the registers of this path within what the whole
-// tiles, which are nearly all of the work, need anyway.
-__device__ __forceinline__ void server_mixed_tile(const Layout &L, const Scratch &X, const ServerArgs &A, int32_t tile,
-                                               int set, int n_valid, TileShared &S)
+// The dense mixed tiles, before the kernel that has the others.  The residual tile is loaded after the payloads
+// have been added up, which keeps the registers down.
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, const int32_t *tiles, int set)
 {
+    const Scratch X = open_call(R);
+    __shared__ TileShared S;
+    const int32_t tile = tiles[blockIdx.x];
+    const TileRec T = L.tiles[tile];
+    const int n_valid = tile_valid(L, tile);
     float *te = A.err + (int64_t)tile * TILE;
     float4 p[SUBROWS];
-    server_values_mixed(L, A, tile, n_valid, te, p, S);
-    compress_mixed(p, L, tile, n_valid, A.signs, A.scales, te, X, set, S);
+    const TilePlace at = tile_place(L, T);
+    server_values_mixed(L, A, tile, T, at, n_valid, te, p, S);
+    compress_mixed(p, L, T, at, tile, n_valid, A.signs, A.scales, te, X, set, S);
 }
 
-// Server part of Algorithm 4, all tiles in one launch, one workgroup per tile: the mixed tiles
-// first, then the whole tiles in ascending order (see k_worker_tiles).  p~ as above, then
+// p~ of a tile of a few segments (see compress_few): as server_values_whole, with a table of sums for one segment
+// after the other and every thread's elements masked by the segment's range.
+template <bool MANY>
+__device__ __forceinline__ void server_values_few(const Layout &L, const ServerArgs &A, const TileRec &T, int64_t tile_start,
+                                                  const float *te, int n_valid, float4 (&p)[SUBROWS], float *lds, const int *bound)
+{
+    float acc[SUBROWS][4];
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
+    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
+    const int64_t in_half = 4 * A.in_signs_stride, half0 = (tile_start >> 4) + threadIdx.x;
+    const bool in = half0 < 4 * L.W;                     // the ragged end
+    const float r = A.r, Mf = A.Mf, Minv = A.Minv;
+    unsigned *exchange = reinterpret_cast<unsigned *>(lds) + EXCHANGE_AT + wave_id() * 256;
+    float4 *nibbles = reinterpret_cast<float4 *>(lds + NIBBLE_AT);
+#pragma unroll 1
+    for (int i0 = 0; i0 < (MANY ? A.M : 1); i0 += SERVER_CHUNK) {
+        const int mine = min(i0 + (lane_id() & (SERVER_CHUNK - 1)), A.M - 1);
+        const float *sc_i = A.scales_in + (int64_t)mine * A.in_scales_stride + T.fb;
+        float sc = sc_i[0];                              // lane u: the segment's scale from worker i0 + u
+        {
+            unsigned h[SERVER_CHUNK];
+#pragma unroll
+            for (int u = 0; u < SERVER_CHUNK; ++u)
+                h[u] = in ? s16[(int64_t)min(i0 + u, A.M - 1) * in_half + half0] : 0u;
+            const vu4 row = !MANY || i0 == 0 ? transpose_signs(h)
+                                    : vu4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+            *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) = row;
+        }
+        __syncthreads();                                 // (the first time: the bounds are there)
+#pragma unroll 1
+        for (int sg = 0; sg < T.nseg; ++sg) {
+            const int lo = few_bound(bound, sg), hi = few_bound(bound, sg + 1);
+            const unsigned n = (unsigned)(hi - lo);
+            const float now = sc;
+            if (sg + 1 < T.nseg) sc = sc_i[sg + 1];
+            if (!MANY || i0 == 0) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int u = 0; u < SERVER_CHUNK; ++u) {
+                    const float s = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(now), u));
+                    if (u < A.M) sum = sum + signed_scale(s, (threadIdx.x >> u) & 1u);
+                }
+                lds[threadIdx.x] = MANY ? sum : mean_of(sum, Mf, Minv);
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < SUBROWS; ++k) {
+                    if (!few_touches(k, lo, hi)) continue;
+                    const unsigned pat = exchange[64 * k + lane_id()];
+                    const int j = local_base(k) - lo;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float v = lds[(pat >> (8 * c)) & 255u];
+                        acc[k][c] = (unsigned)(j + c) < n ? v : acc[k][c];
+                    }
+                }
+            } else {
+                const float su = __shfl(now, (int)(threadIdx.x >> 4) & (SERVER_CHUNK - 1));
+                if (threadIdx.x < SERVER_CHUNK * 16) {
+                    const unsigned nib = threadIdx.x & 15u;
+                    nibbles[threadIdx.x] = make_float4(signed_scale(su, nib & 1u), signed_scale(su, nib & 2u),
+                                                       signed_scale(su, nib & 4u), signed_scale(su, nib & 8u));
+                }
+                __syncthreads();
+                const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
+#pragma unroll
+                for (int k = 0; k < SUBROWS; ++k) {
+                    if (!few_touches(k, lo, hi)) continue;
+                    const vu4 w = *reinterpret_cast<const vu4 *>(exchange + 4 * (16 * k + (lane_id() >> 2)));
+                    const int j = local_base(k) - lo;
+#pragma unroll
+                    for (int u = 0; u < SERVER_CHUNK; ++u) {
+                        if (i0 + u < A.M) {
+                            const float4 dv = nibbles[u * 16 + ((w[u >> 1] >> (sh + 16 * (u & 1))) & 15u)];
+                            acc[k][0] = (unsigned)(j + 0) < n ? acc[k][0] + dv.x : acc[k][0];
+                            acc[k][1] = (unsigned)(j + 1) < n ? acc[k][1] + dv.y : acc[k][1];
+                            acc[k][2] = (unsigned)(j + 2) < n ? acc[k][2] + dv.z : acc[k][2];
+                            acc[k][3] = (unsigned)(j + 3) < n ? acc[k][3] + dv.w : acc[k][3];
+                        }
+                    }
+                }
+            }
+            __syncthreads();                             // the table, and after the last segment the exchange, are free
+        }
+    }
+    if (MANY) {
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] = mean_of(acc[k][c], Mf, Minv);
+    }
+    float4 tv[SUBROWS];             // loaded only now: few registers
+    load_tile(te, tv, n_valid);
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k) {
+        p[k].x = acc[k][0] + r * tv[k].x;
+        p[k].y = acc[k][1] + r * tv[k].y;
+        p[k].z = acc[k][2] + r * tv[k].z;
+        p[k].w = acc[k][3] + r * tv[k].w;
+    }
+}
+
+// Server part of Algorithm 4, all tiles in one launch, one workgroup per tile in ascending order (see k_worker_tiles).  p~ as above, then
 // compressed like a worker's p; the workgroup of a whole tile waits in the kernel for its
 // block's scale.
 // MIXED = false: the layout has only whole tiles, and the code for the others is left out.
@@ -275,36 +366,42 @@ __device__ __forceinline__ void server_mixed_tile(const Layout &L, const Scratch
 // 465 at seven and 491 at six), the others seven: at eight the mixed tiles spill 39 registers (one
 // worker-payload set of the ResNet-50 layout, 7 workers: 80 us against 66 at seven and 67 at six; 354 M
 // elements in transformer blocks, 16 workers: 1180 us against 1017 and 1047).
-template <bool MIXED>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED ? 7 : 8, 8)))
+// MANY: more than SERVER_CHUNK workers.
+template <bool MIXED, bool MANY>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED || MANY ? 7 : 8, 8)))
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
-    __shared__ TileShared S;
+    __shared__ SyncShared S;
+    __shared__ float lds[SERVER_LDS];
     float4 tv[SUBROWS], p[SUBROWS];
     if (!MIXED) {
-        // whole tile i is tile i: its residual is asked for before anything is looked up
+        // tile i is workgroup i's: its residual is asked for before anything is looked up
         load_tile(A.err + (int64_t)blockIdx.x * TILE, tv, TILE);
         __builtin_amdgcn_sched_barrier(0);
     }
     const Scratch X = open_call(R);
-    const bool whole = !MIXED || (int)blockIdx.x >= L.n_mixed;
-    const WholeTile w = L.whole_tiles[!MIXED ? blockIdx.x : whole ? blockIdx.x - L.n_mixed : 0];
-    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? w.tile : L.mixed_tiles[blockIdx.x];
-    const int n_valid = whole ? TILE : tile_valid(L, tile);
+    const TileRec T = MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
+    const int32_t tile = MIXED ? T.tile : (int32_t)blockIdx.x;
     const int64_t tile_start = (int64_t)tile * TILE;
+    const int n_valid = MIXED ? tile_valid(L, tile) : TILE;
     float *te = A.err + tile_start;
-    if (whole) {
-        Posted P;
-        const BlockSpan sp = span_of(w.bs, w.be);
-        const LoadedCorrection corr = loaded_correction(L, w.b, X, set);
+    if (!MIXED || T.words < 0) {
         if (MIXED) load_tile(te, tv, TILE);
+        Posted P;
+        const BlockSpan sp = span_of(T.bs(), T.be());
+        const LoadedCorrection corr = loaded_correction(L, T.fb, X, set);
         correct_loaded_residual(tv, corr);
-        server_values_whole(A, tile_start, w.b, tv, p, S);
-        const int kind = compress_uniform(p, L, tile, w.b, sp, TILE, A.signs, A.scales, te, X, set, S, P);
+        server_values_whole<MANY>(A, tile_start, T.fb, tv, p, lds);
+        const int kind = compress_uniform(p, L, tile, T.fb, sp, TILE, A.signs, A.scales, te, X, set, S, P);
         resolve_posted(P, L, X, set, A.scales, S);
         if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
     } else if constexpr (MIXED) {
-        server_mixed_tile(L, X, A, tile, set, n_valid, S);
+        __shared__ FewShared F;
+        if (T.nseg > 0) {               // else a dense tile: finished by the kernel before
+            few_bounds(L, T, tile_start, n_valid, F.bound);
+            server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
+            compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F);
+        }
     }
     snapshot_call(R);
 }

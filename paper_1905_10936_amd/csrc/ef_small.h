@@ -4,9 +4,7 @@
 // workgroup's chain of dependent memory round trips (about 0.5 to 1 us each), plus that of every kernel that
 // has to follow.  These kernels do the same work as k_worker_tiles / k_server_tiles / k_apply with a shorter
 // chain:
-//   * what a tile needs to know about its blocks comes in one record (SmallTile) and two words per 32
-//     elements (SmallArgs), written at plan creation, instead of tile -> block -> offsets lookups and an
-//     index built in LDS;
+//   * what a tile needs to know about both its open blocks comes in one record (SmallTile);
 //   * 1024 threads to a tile, four elements each;
 //   * all workgroups, or half of them, are resident at once, so all tiles of a block, mixed ones
 //     included, can wait for it in place; and they do not wait for a gatherer's answer, each adds up the block's partial
@@ -24,13 +22,12 @@ namespace ef {
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_WAVES = SMALL_THREADS / 64;
 constexpr int SMALL_SPAN = 256;         // most tiles of a block that spans tiles
-constexpr int SMALL_WORDS = TILE / 32;  // start words per tile
 constexpr int DONE_GROUPS = 8;          // workgroups count themselves out on this many words ...
 constexpr int DONE_STRIDE = 32;         // ... a cache line apart, and these on one more
 
 struct SmallTile {
     int32_t fb, nseg;           // first block and number of segments
-    int32_t words;              // which set of start words; < 0: a whole tile
+    int32_t words;              // as in TileRec
     int32_t flags;
     int32_t head_t0, head_n;    // tiles of the first segment's block, if it is open (SMALL_HEAD)
     int32_t tail_n;             // tiles of the last segment's block, if that one is (SMALL_TAIL): it starts in this tile
@@ -46,8 +43,6 @@ enum {
 
 struct SmallArgs {
     const SmallTile *tiles;     // [ntiles]
-    const uint32_t *starts;     // [..][SMALL_WORDS] bit j: a segment starts at element j (the tile's first always does)
-    const uint16_t *rank;       // [..][SMALL_WORDS] starts before the word
     unsigned *done;             // [DONE_GROUPS + 1][DONE_STRIDE], zero between calls
     CallState *state;
     int nsets;
@@ -72,13 +67,13 @@ struct SmallPlace {
     unsigned starts;            // bit c: a segment starts at element c
     int seg;                    // segment in progress before element 0 (-1: none)
 };
-__device__ __forceinline__ SmallPlace small_place(const SmallArgs &Z, const SmallTile &T)
+__device__ __forceinline__ SmallPlace small_place(const Layout &L, const SmallTile &T)
 {
     SmallPlace q;
-    const int i = T.words * SMALL_WORDS + (int)(threadIdx.x >> 3);
-    const unsigned word = Z.starts[i], sh = (threadIdx.x & 7u) * 4u;
-    q.starts = (word >> sh) & 15u;
-    q.seg = (int)Z.rank[i] + __popc(word & ((1u << sh) - 1u)) - 1;
+    const StartWord w = L.words[T.words * TILE_WORDS + (int)(threadIdx.x >> 3)];
+    const unsigned sh = (threadIdx.x & 7u) * 4u;
+    q.starts = (w.starts >> sh) & 15u;
+    q.seg = (int)w.rank + __popc(w.starts & ((1u << sh) - 1u)) - 1;
     return q;
 }
 
@@ -362,7 +357,7 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
     if (MOM) m = small_load4(mt, n_valid);
     SmallPlace at = {0u, -1};
     int64_t db = 1;
-    if (T.words >= 0) at = small_place(Z, T);
+    if (T.words >= 0) at = small_place(L, T);
     if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
     worker_values4<MOM>(g, m, e, A.mu, A.r);
     if (MOM) small_store4(mt, n_valid, m);
@@ -385,7 +380,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
     const float4 te = small_load4(et, n_valid);
     SmallPlace at = {0u, -1};
     int64_t db = 1;
-    if (T.words >= 0) at = small_place(Z, T);
+    if (T.words >= 0) at = small_place(L, T);
     if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
     int seg[4];
     {
@@ -441,7 +436,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallAr
     float4 m4 = x4;
     if (WD) m4 = small_load4(mt + start, n_valid);
     SmallPlace at = {0u, 0};
-    if (T.words >= 0) at = small_place(Z, T);
+    if (T.words >= 0) at = small_place(L, T);
     float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
     int seg = at.seg;
 #pragma unroll

@@ -40,15 +40,16 @@
 //     writes the scale and posts (call number, scale) in the block's "ready"
 //     word -- no counter, hence no read-modify-write on a shared address;
 //   * the others look at the ready word when they come to write the tile.
-// Mixed tiles are handed out before the whole tiles (first in the grid of the
-// kernel that runs one workgroup per tile; in a kernel of their own before the
-// persistent worker kernel), so their partial sums are there when a block's
-// last whole tile comes to form the scale.  They never wait for a whole tile:
-// a block without whole tiles is finished among the mixed tiles themselves
-// (its last tile forms its scale, the others wait for it), while the segments
-// that a block with whole tiles has in mixed tiles get p parked in the
-// residual buffer.  Parked p (those segments, all tiles of blocks larger than
-// fuse_limit, any tile whose bounded wait ran out) is finished by one kernel
+// The kernels that run one workgroup per tile take the mixed tiles of a few
+// segments in their place among the whole ones, and their open segments wait like
+// whole tiles do.  The "dense" ones, of many segments, and before the persistent
+// worker kernel all mixed tiles, run in a kernel of their own ahead of the whole
+// tiles, so their partial sums are there when a block's last whole tile comes to form the
+// scale; there they never wait for a whole tile: a block without whole tiles is
+// finished among the mixed tiles themselves (its last tile forms its scale, the
+// others wait for it), while the segments that a block with whole tiles has in
+// mixed tiles get p parked in the residual buffer.  Parked p (those segments, all
+// tiles of blocks larger than fuse_limit, any tile whose bounded wait ran out) is finished by one kernel
 // after the main one, which also computes the scales still missing and steps
 // the plan to its next call.
 //
@@ -68,8 +69,12 @@ constexpr int TILE = 4096;      // elements per workgroup and step
 constexpr int THREADS = 256;    // 4 wavefronts
 constexpr int NWAVES = THREADS / 64;
 constexpr int SUBROWS = 4;      // float4 per thread
-constexpr int SMALL_SEG = 64;   // segments up to this length are summed by one thread
+constexpr int SMALL_SEG = 64;   // quality sums: segments up to this length are summed by one thread
 constexpr int MAX_LONG = TILE / SMALL_SEG;
+constexpr int TILE_WORDS = TILE / 32;
+constexpr int ROWS = TILE / 256;        // a wavefront's sub-rows of 256 elements in a tile
+constexpr int FEW_SEGS = 6;             // most segments of a tile that is taken among the whole ones (see compress_few)
+constexpr int SEG_ROUND = 384;          // segments of a mixed tile that are finished in one round (their sums lie in LDS)
 constexpr int DEFER_WGS = 16;   // workgroups that serve the run-time lists in the kernel that ends a call
 constexpr int FIN_WGS_MAX = 512;    // most workgroups that kernel gives to the scales of blocks larger than fuse_limit ...
 constexpr int RES_WGS_MAX = 2048;   // ... and to the segments whose p was parked
@@ -81,13 +86,25 @@ constexpr int PIPE_DEPTH = EF_PIPE_DEPTH;     // tiles a persistent workgroup ke
 constexpr unsigned long long TAG_BIT = 1ull << 63;
 constexpr int FUSE_LIMIT_MAX = 4096;                     // most tiles a one-pass block may be given through ef_plan_tune
 
-// What the kernels need to know about a whole tile (one that lies inside one block), in one record: looked up
-// piece by piece (tile, its block, the block's ends) it is three dependent loads before the first scale
-// can be asked for, and two more between a tile's sum and its posting.
-struct alignas(32) WholeTile {
-    int32_t tile, b;
-    int64_t bs, be;             // the block's element range
-    int64_t unused;
+// What the kernels need to know about a tile, in one record: looked up piece by piece (tile, its block, the
+// block's ends) it is three dependent loads before the first scale can be asked for, and two more between
+// a tile's sum and its posting.
+struct alignas(32) TileRec {
+    int32_t tile;
+    int32_t fb;                 // first block
+    int32_t nseg;               // segments; < 0: that many, and they run in the dense tiles' own kernel
+    int32_t words;              // < 0: a whole tile; else which set of start words (its place among the mixed tiles)
+    int32_t tail;               // 0, or, if the last of several segments goes on past the tile: its block's tiles * 2,
+                                // + 1 if the block ends inside its last tile
+    int32_t t0, n;              // tiles of the first block
+    int16_t from, to;           // where it starts in its first tile, and ends in its last (0: at the tile's end)
+    __host__ __device__ int64_t bs() const { return (int64_t)t0 * TILE + from; }
+    __host__ __device__ int64_t be() const { return (int64_t)(t0 + n - 1) * TILE + (to ? to : TILE); }
+};
+// Where the segments of a mixed tile start, 32 elements to a word; written at plan creation.
+struct StartWord {
+    uint32_t starts;            // bit j: a segment starts at element j of the 32 (the tile's first always does)
+    uint32_t rank;              // starts before the word
 };
 
 struct Layout {
@@ -101,7 +118,12 @@ struct Layout {
     const int32_t *tile_fb;     // [ntiles] block holding the tile's first element
     const int32_t *tile_lb;     // [ntiles] block holding the tile's last valid element
     const int32_t *mixed_tiles;   // [n_mixed] ascending
-    const WholeTile *whole_tiles; // [n_uniform] ascending
+    const int32_t *whole_tiles;   // [n_uniform] ascending
+    const TileRec *tiles;         // [ntiles]
+    const TileRec *grid_tiles;    // the same in the order in which the kernels with one workgroup per tile take them
+    const StartWord *words;       // [n_mixed][TILE_WORDS]
+    int32_t n_dense;
+    const int32_t *dense_tiles;   // [n_dense] the mixed tiles of many segments, ascending
     // Deferred correction (see Scratch::lazy_scales): on or off, and for every block its position
     // among the blocks larger than fuse_limit (-1 for the others).
     int32_t lazy;
@@ -252,24 +274,38 @@ __device__ __forceinline__ void stream_store4(float *p, float4 a)
     __builtin_nontemporal_store(v, reinterpret_cast<vf4 *>(p));
 }
 
+// Elements past the end are 0.  (Clamped addresses instead of branches: the code for the one ragged tile of a
+// vector lies in front of everybody's, and twelve branches with a tile's loads in flight spilled there.)
 __device__ __forceinline__ float4 guarded_load4(const float *base, int local, int n_valid)
 {
-    if (local + 4 <= n_valid) return stream_load4(base + local);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (local + 0 < n_valid) v.x = base[local + 0];
-    if (local + 1 < n_valid) v.y = base[local + 1];
-    if (local + 2 < n_valid) v.z = base[local + 2];
-    return v;                   // local + 3 < n_valid would have taken the vector path
+    float v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = base[min(local + c, n_valid - 1)];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = local + c < n_valid ? v[c] : 0.f;
+    return make_float4(v[0], v[1], v[2], v[3]);
 }
 
 __device__ __forceinline__ void guarded_store4(float *base, int local, int n_valid, float4 v)
 {
-    if (local + 4 <= n_valid) { stream_store4(base + local, v); return; }
     if (local + 0 < n_valid) base[local + 0] = v.x;
     if (local + 1 < n_valid) base[local + 1] = v.y;
     if (local + 2 < n_valid) base[local + 2] = v.z;
+    if (local + 3 < n_valid) base[local + 3] = v.w;
 }
 
+// Turns a register array by one place.  Where only few tiles pass, loops over a thread's sub-rows are not
+// unrolled, to keep the registers of kernels that also stream the whole tiles down; a register array
+// cannot be indexed by a loop counter, so such a loop works on element 0 and turns.
+template <class T>
+__device__ __forceinline__ void turn(T (&v)[SUBROWS])
+{
+    const T first = v[0];
+    v[0] = v[1];
+    v[1] = v[2];
+    v[2] = v[3];
+    v[3] = first;
+}
 // A thread's four float4 of one tile.  Only the last tile of a vector can be
 // ragged; the test is uniform over the workgroup, so full tiles run straight
 // through 128-bit accesses with no per-access branch.
@@ -280,7 +316,10 @@ __device__ __forceinline__ void load_tile(const float *base, float4 (&v)[SUBROWS
         for (int k = 0; k < SUBROWS; ++k) v[k] = stream_load4(base + local_base(k));
     } else {
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) v[k] = guarded_load4(base, local_base(k), n_valid);
+        for (int k = 0; k < SUBROWS; ++k) {
+            v[k] = guarded_load4(base, local_base(k), n_valid);
+            __builtin_amdgcn_sched_barrier(0);      // one after the other: few registers
+        }
     }
 }
 
@@ -487,8 +526,14 @@ struct SyncShared {
 };
 // ... and what the kernels that cut a tile into segments need on top of it.
 struct TileShared : SyncShared {
-    float val[TILE];            // |p| per element, then the element's scale (closed segments)
-    double open_sum[2];
+    float val[TILE];            // the tile's p, or what the kernel needs before it has p
+    union {
+        double sum[SEG_ROUND];      // segment sums ...
+        float scale[2 * SEG_ROUND]; // ... then, in the even places, scales
+        unsigned half[SEG_ROUND * 2];
+    };
+    double row_total[ROWS];
+    int row_any[ROWS];
     int long_list[MAX_LONG];
     int n_long;
 };
@@ -607,8 +652,17 @@ __device__ __forceinline__ double sum_block_partials(const Layout &L, int64_t b,
 {
     const BlockSpan sp = block_span(L, b);
     double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < sp.n; i += THREADS)
-        acc += __longlong_as_double((long long)(part[part_index(sp.t0 + i, sp)] & ~TAG_BIT));
+    // eight words in flight a thread: a block of 12 565 tiles is 49 of them, one after the other 25 us
+    for (int64_t i0 = threadIdx.x; i0 < sp.n; i0 += 8 * THREADS) {
+        unsigned long long w[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t i = i0 + q * THREADS;
+            w[q] = i < sp.n ? part[part_index(sp.t0 + i, sp)] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += __longlong_as_double((long long)(w[q] & ~TAG_BIT));
+    }
     return block_sum(acc, red);
 }
 
@@ -718,11 +772,10 @@ __device__ __forceinline__ unsigned long long peek_ready(int b, const Layout &L,
 // Wait (bounded) until the block's gatherer has posted its scale of this call.
 // `peeked` is thread 0's earlier look at the word (see peek_ready).  Called by
 // every thread of the workgroup; same answer to all of them.
-__device__ __forceinline__ bool wait_ready(const BlockSpan &sp, unsigned long long peeked, const Layout &L, const Scratch &X,
-                                           int set, SyncShared &S, float *s)
+__device__ __forceinline__ bool wait_ready_at(const unsigned long long *word, unsigned long long peeked, const Scratch &X,
+                                              SyncShared &S, float *s)
 {
     if (threadIdx.x == 0) {
-        const unsigned long long *word = ready_word(X, L, set, sp);
         unsigned long long w = peeked;
         int found = ((unsigned)(w >> 32) == X.epoch) ? 1 : 0;
         for (int it = 0; !found && it < X.spin_limit; ++it) {
@@ -741,6 +794,12 @@ __device__ __forceinline__ bool wait_ready(const BlockSpan &sp, unsigned long lo
     return ok;
 }
 
+__device__ __forceinline__ bool wait_ready(const BlockSpan &sp, unsigned long long peeked, const Layout &L, const Scratch &X,
+                                           int set, SyncShared &S, float *s)
+{
+    return wait_ready_at(ready_word(X, L, set, sp), peeked, X, S, s);
+}
+
 // Leave a segment whose p gets parked in the residual buffer to the kernels
 // that run after this one.
 __device__ __forceinline__ void defer_segment(int32_t tile, int which, const Scratch &X, int set)
@@ -753,112 +812,176 @@ __device__ __forceinline__ void defer_segment(int32_t tile, int which, const Scr
 
 // ------------------------------------------------------- tile compression ---
 
-// Mixed tile (several blocks meet, or the ragged end of the vector): sign words;
-// segmented fp64 sums through LDS; scales and residuals e' = p - Delta of the
-// closed segments; partial sums of the (at most two) open segments posted, and
-// their residuals finished too where the block's scale forms inside this kernel
-// (bounded waits), else their elements stored as p for the kernel that ends the
-// call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of Algorithm 4.)
-__device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layout &L, int32_t tile, int n_valid,
-                                               uint64_t *signs, float *scales_out, float *err_tile,
-                                               const Scratch &X, int set, TileShared &S)
+// A thread's elements among the segments of a mixed tile, sub-row by sub-row: bits 0-3: a segment starts at
+// element c; above: segments started before element 0 (so the segment in progress there, plus one).
+struct TilePlace {
+    unsigned row[SUBROWS];
+    __device__ __forceinline__ unsigned starts(int k) const { return row[k] & 15u; }
+    __device__ __forceinline__ int seg(int k) const { return (int)(row[k] >> 4) - 1; }
+};
+__device__ __forceinline__ TilePlace tile_place(const Layout &L, const TileRec &T)
+{
+    TilePlace q;
+    const unsigned sh = (threadIdx.x & 7u) * 4u;
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k) {
+        const StartWord w = L.words[(int64_t)T.words * TILE_WORDS + (local_base(k) >> 5)];
+        q.row[k] = ((w.starts >> sh) & 15u) | ((w.rank + (unsigned)__popc(w.starts & ((1u << sh) - 1u))) << 4);
+    }
+    return q;
+}
+__device__ __forceinline__ int64_t seg_length(const Layout &L, const TileRec &T, int sg)
+{
+    return sg < abs(T.nseg) ? L.offs[T.fb + sg + 1] - L.offs[T.fb + sg] : 1;
+}
+
+// Inclusive sums of a thread's four |p| of one sub-row since the last start among them.
+__device__ __forceinline__ void row_sums(const float4 &p, unsigned starts, int valid, double (&r)[4])
+{
+    const double a[4] = {valid > 0 ? fabsf(p.x) : 0.f, valid > 1 ? fabsf(p.y) : 0.f, valid > 2 ? fabsf(p.z) : 0.f,
+                         valid > 3 ? fabsf(p.w) : 0.f};
+    r[0] = a[0];
+#pragma unroll
+    for (int c = 1; c < 4; ++c) r[c] = ((starts >> c) & 1u) ? a[c] : r[c - 1] + a[c];
+}
+
+// Mixed tile (several blocks meet, or the ragged end of the vector): sign words; segmented sums; scales and
+// residuals e' = p - Delta of the closed segments; partial sums of the (at most two) open segments posted, and
+// their residuals finished where the block's scale forms inside this kernel (bounded waits), else their
+// elements stored as p for the kernel that ends the call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of
+// Algorithm 4.)
+//
+// The sums are a segmented scan over the elements: four to a lane, the 64 lanes of a sub-row, the tile's 16
+// sub-rows; the lane that holds the next segment's start (the last lane for the last segment) leaves a
+// segment's sum in LDS.  No step depends on how long the segments are: the loops over a segment's
+// elements that this replaces ran at the length of the longest in a wavefront (25 M elements in blocks
+// of 3000, with 256, with 33: worker call, one worker, 96.8 / 92.4 / 97.5 us before).
+//
+// The kernels this runs in come before the one with the whole tiles, and only blocks that have none are
+// finished here (the last tile of such a block forms its scale); a block with whole tiles gets its
+// partial sums from here and its segments' p parked.
+__device__ __forceinline__ void compress_mixed(const float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, const TilePlace &at,
+                                               int32_t tile, int n_valid, uint64_t *signs, float *scales_out,
+                                               float *err_tile, const Scratch &X, int set, TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int32_t fb = L.tile_fb[tile], lb = L.tile_lb[tile];
+    const int lane = lane_id(), wave = wave_id(), nseg = abs(T.nseg);
+    const int64_t db0 = seg_length(L, T, (int)threadIdx.x);         // asked for early
+    const BlockSpan hs = span_of(T.bs(), T.be());
+    const bool head_open = hs.bs < tile_start || hs.be > tile_start + TILE;
+    const bool tail_open = T.tail != 0;
     store_signs(p, n_valid, signs, tile_start, L.W);
-
-    const int nseg = lb - fb + 1;
+    // every lane reads back only what it writes here
 #pragma unroll
+    for (int k = 0; k < SUBROWS; ++k) *reinterpret_cast<float4 *>(&S.val[local_base(k)]) = p[k];
+    TilePlace q = at;
+    double carry[SUBROWS];          // the sum since the last start before this thread's four elements
+#pragma unroll 1
     for (int k = 0; k < SUBROWS; ++k) {
-        float4 a = make_float4(fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w));
-        *reinterpret_cast<float4 *>(&S.val[local_base(k)]) = a;
-    }
-    if (threadIdx.x == 0) S.n_long = 0;
-    __syncthreads();
-    const bool head_open = L.offs[fb] < tile_start;
-    const bool tail_open = L.offs[lb + 1] > tile_start + TILE;
-    for (int sg = threadIdx.x; sg < nseg; sg += THREADS) {
-        const int64_t b = fb + sg;
-        const int64_t bs = L.offs[b], be = L.offs[b + 1];
-        const int lo = (int)max(bs - tile_start, (int64_t)0);
-        const int hi = (int)min(be - tile_start, (int64_t)n_valid);
-        if (hi - lo > SMALL_SEG) {
-            S.long_list[atomicAdd(&S.n_long, 1)] = sg;
-            continue;
+        double r[4];
+        row_sums(*reinterpret_cast<const float4 *>(&S.val[local_base(k)]), q.starts(0), n_valid - local_base(k), r);
+        const unsigned long long any = __ballot(q.starts(0) != 0u);
+        const double t = segment_scan(r[3], any);
+        carry[0] = wave_shift(t);
+        if (lane == 63) {
+            S.row_total[4 * wave + k] = t;
+            S.row_any[4 * wave + k] = any != 0ull;
         }
-        double acc = 0.0;
-        for (int j = lo; j < hi; ++j) acc += (double)S.val[j];
-        const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
-        if (open) {
-            S.open_sum[sg == 0 ? 0 : 1] = acc;
-        } else {
-            const float sc = (float)(acc / (double)(be - bs));
-            scales_out[b] = sc;
-            for (int j = lo; j < hi; ++j) S.val[j] = sc;
-        }
+        turn(q.row);
+        turn(carry);
     }
     __syncthreads();
-    const int n_long = S.n_long;
-    for (int q = wave_id(); q < n_long; q += NWAVES) {
-        const int sg = S.long_list[q];
-        const int64_t b = fb + sg;
-        const int64_t bs = L.offs[b], be = L.offs[b + 1];
-        const int lo = (int)max(bs - tile_start, (int64_t)0);
-        const int hi = (int)min(be - tile_start, (int64_t)n_valid);
-        double acc = 0.0;
-        for (int j = lo + lane_id(); j < hi; j += 64) acc += (double)S.val[j];
-        acc = wave_sum(acc);
-        const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
-        if (open) {
-            if (lane_id() == 0) S.open_sum[sg == 0 ? 0 : 1] = acc;
-        } else {
-            const float sc = (float)(acc / (double)(be - bs));
-            if (lane_id() == 0) scales_out[b] = sc;
-            for (int j = lo + lane_id(); j < hi; j += 64) S.val[j] = sc;
-        }
-    }
-    __syncthreads();
-    const int head_end = head_open ? (int)min(L.offs[fb + 1] - tile_start, (int64_t)n_valid) : 0;
-    const int tail_begin = tail_open ? (int)(L.offs[lb] - tile_start) : TILE;
-    if (head_open) store_partial(S.open_sum[0], 0, tile, L, X, set);
-    if (tail_open) store_partial(S.open_sum[1], 1, tile, L, X, set);
-    // An open segment whose block has no whole tile is finished in place: all tiles of such a
-    // block are mixed ones, handed out before any whole tile and in ascending order.  The first
-    // segment's block ends in this tile, which makes this workgroup the one that forms its scale;
-    // the last segment's block goes on, and its scale comes from the next mixed tile.  The segments
-    // of other blocks, and any whose wait runs out, keep p in the residual buffer for the kernel
-    // that ends the call.
-    float s_head = 0.f, s_tail = 0.f;
-    bool fin_head = false, fin_tail = false;
-    if (head_open && finishes_with_mixed(L, block_span(L, fb))) {
-        fin_head = finish_block(fb, block_span(L, fb), L, X, set, scales_out, S, &s_head);
-        if (!fin_head) defer_segment(tile, 0, X, set);
-    }
-    if (tail_open && finishes_with_mixed(L, block_span(L, lb))) {
-        fin_tail = wait_ready(block_span(L, lb), 0ull, L, X, set, S, &s_tail);
-        if (!fin_tail) defer_segment(tile, 1, X, set);
-    }
+    const double rows = segment_scan16(S.row_total[lane & 15], (unsigned)__ballot(S.row_any[lane & 15] != 0) & 0xffffu);
+    for (int base = 0; base < nseg; base += SEG_ROUND) {
+        const int end = min(nseg, base + SEG_ROUND);
+        if (base) __syncthreads();
+#pragma unroll 1
+        for (int k = 0; k < SUBROWS; ++k) {
+            if (base == 0) {
+                // read by all lanes, outside any branch: the lane that is read from has to have formed its value
+                const int row = (int)uniform_u32((unsigned)(4 * wave + k));
+                const double below = read_lane(rows, row > 0 ? row - 1 : 0);
+                const unsigned long long any = __ballot(q.starts(0) != 0u);
+                carry[0] += (row > 0 && !(any & ((1ull << lane) - 1ull))) ? below : 0.0;
+            }
+            double r[4], before = carry[0];
+            row_sums(*reinterpret_cast<const float4 *>(&S.val[local_base(k)]), q.starts(0), n_valid - local_base(k), r);
+            int seg = q.seg(0);
+            bool started = false;
 #pragma unroll
-    for (int k = 0; k < SUBROWS; ++k) {
-        const int lb0 = local_base(k);
-        const float4 sc = *reinterpret_cast<const float4 *>(&S.val[lb0]);
-        const float pv[4] = {p[k].x, p[k].y, p[k].z, p[k].w};
-        const float sv[4] = {sc.x, sc.y, sc.z, sc.w};
-        float ev[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int j = lb0 + c;
-            if (j < head_end)
-                ev[c] = fin_head ? residual(pv[c], s_head) : pv[c];
-            else if (j >= tail_begin)
-                ev[c] = fin_tail ? residual(pv[c], s_tail) : pv[c];
-            else
-                ev[c] = residual(pv[c], sv[c]);
+            for (int c = 0; c < 4; ++c) {
+                if ((q.starts(0) >> c) & 1u) {
+                    if (seg >= base && seg < end) S.sum[seg - base] = before;
+                    ++seg;
+                    started = true;
+                }
+                before = started ? r[c] : carry[0] + r[c];
+            }
+            if (k == SUBROWS - 1 && threadIdx.x == THREADS - 1 && end == nseg) S.sum[seg - base] = before;
+            turn(q.row);
+            turn(carry);
         }
-        p[k] = make_float4(ev[0], ev[1], ev[2], ev[3]);
+        __syncthreads();
+        // the open segments' sums go out first
+        if (base == 0 && head_open) store_partial(S.sum[0], 0, tile, L, X, set);
+        if (end == nseg && tail_open) store_partial(S.sum[nseg - 1 - base], 1, tile, L, X, set);
+        for (int sg = base + (int)threadIdx.x; sg < end; sg += THREADS) {
+            if ((sg == 0 && head_open) || (sg == nseg - 1 && tail_open)) continue;
+            const int64_t db = sg == (int)threadIdx.x ? db0 : seg_length(L, T, sg);
+            const float sc = (float)(S.sum[sg - base] / (double)db);
+            scales_out[T.fb + sg] = sc;
+            S.scale[2 * (sg - base)] = sc;          // over the sum, which no other thread reads
+        }
+        float s_head = 0.f, s_tail = 0.f;
+        bool fin_head = false, fin_tail = false;
+        if (base == 0 && head_open) {
+            if (finishes_with_mixed(L, hs)) {
+                fin_head = (int64_t)tile == gatherer_tile(L, hs) ? finish_block(T.fb, hs, L, X, set, scales_out, S, &s_head)
+                                                                 : wait_ready(hs, 0ull, L, X, set, S, &s_head);
+                if (!fin_head) defer_segment(tile, 0, X, set);
+            }
+        }
+        if (end == nseg && tail_open) {
+            // the block starts in this tile: its whole tiles, if any, are the ones between this and its last
+            const int n = T.tail >> 1, whole = n - 1 - (T.tail & 1);
+            if (n <= L.fuse_limit && whole == 0) {
+                const int64_t gatherer = (int64_t)tile + n - 1;
+                fin_tail = wait_ready_at(X.ready + ((int64_t)set * L.ntiles + gatherer) * READY_STRIDE, 0ull, X, S, &s_tail);
+                if (!fin_tail) defer_segment(tile, 1, X, set);
+            }
+        }
+        __syncthreads();
+        // values, no longer variables whose address was taken: a choice between them and LDS would become a
+        // choice of pointers
+        const float from_head = __uint_as_float(uniform_u32(__float_as_uint(s_head)));
+        const float from_tail = __uint_as_float(uniform_u32(__float_as_uint(s_tail)));
+#pragma unroll 1
+        for (int k = 0; k < SUBROWS; ++k) {
+            float4 &row = *reinterpret_cast<float4 *>(&S.val[local_base(k)]);
+            const float4 pk = row;
+            float v[4] = {pk.x, pk.y, pk.z, pk.w};
+            int seg = q.seg(0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                seg += (int)((q.starts(0) >> c) & 1u);
+                if (seg >= base && seg < end) {
+                    const bool head = head_open && seg == 0, tail = tail_open && seg == nseg - 1;
+                    const float own = S.scale[2 * (seg - base)], s = head ? from_head : tail ? from_tail : own;
+                    const bool keep = (head && !fin_head) || (tail && !fin_tail);
+                    v[c] = keep ? v[c] : residual(v[c], s);
+                }
+            }
+            const float4 ev = make_float4(v[0], v[1], v[2], v[3]);
+            row = ev;                               // other segments' elements may be due in a later round
+            if (end == nseg) {
+                if (n_valid == TILE)
+                    stream_store4(err_tile + local_base(k), ev);
+                else
+                    guarded_store4(err_tile, local_base(k), n_valid, ev);
+            }
+            turn(q.row);
+        }
     }
-    store_tile(err_tile, p, n_valid);
-    __syncthreads();            // S.val is free again
 }
 
 // Deferred correction of a uniform tile's residual as loaded (see Scratch::lazy_scales): if the
@@ -948,6 +1071,123 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
     store_tile(err_tile, p, n_valid);
 }
 
+// A tile where at most FEW_SEGS blocks meet, or the ragged end of the vector, taken among the whole tiles: the
+// ends of large blocks with the small ones between them (weights, then biases and norms), which is what
+// the mixed tiles of a network's layout are.  The segments are summed one after the other, every thread's
+// elements masked by the segment's range, in the registers the whole tiles need anyway and without LDS
+// arrays; an open segment waits for its block's scale like a whole tile does.  (Mixed tiles at the head of the
+// grid, with the segment code for any number of segments, cost the kernel registers, its first
+// workgroups 20 us, and the segments of blocks with whole tiles a pass of their own in the kernel that
+// ends the call: 25 M elements in blocks of 64 tiles and 7 elements, server call with 7 workers 65 us
+// against 48 for blocks of 64 tiles.)
+// bound[i]: local index of the end of segment i-1 = start of segment i, in LDS.
+struct FewShared {
+    int bound[FEW_SEGS + 1];
+    float scale[FEW_SEGS];      // of the segments; 0 leaves p as it is
+};
+// Called by the whole workgroup early; a barrier comes before the first use.
+__device__ __forceinline__ void few_bounds(const Layout &L, const TileRec &T, int64_t tile_start, int n_valid, int *bound)
+{
+    if ((int)threadIdx.x <= T.nseg) {
+        const int64_t at = L.offs[T.fb + (int)threadIdx.x] - tile_start;
+        bound[threadIdx.x] = (int)min(max(at, (int64_t)0), (int64_t)n_valid);
+    }
+}
+__device__ __forceinline__ int few_bound(const int *bound, int i) { return (int)uniform_u32((unsigned)bound[i]); }
+// Does this wavefront's sub-row k have elements of [lo, hi)?  Most segments touch one or two of a tile's 16.
+__device__ __forceinline__ bool few_touches(int k, int lo, int hi)
+{
+    const int first = (int)uniform_u32(threadIdx.x >> 6) * 1024 + k * 256;
+    return first < hi && first + 256 > lo;
+}
+__device__ __forceinline__ double abs_sum_range(const float4 (&p)[SUBROWS], int lo, int hi)
+{
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k) {
+        if (!few_touches(k, lo, hi)) continue;
+        const int j = local_base(k) - lo;
+        const unsigned n = (unsigned)(hi - lo);
+        const float a[4] = {fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w)};
+        double row = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) row += (unsigned)(j + c) < n ? (double)a[c] : 0.0;
+        acc += row;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc;
+}
+__device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
+                                             uint64_t *signs, float *scales_out, float *err_tile, const Scratch &X, int set,
+                                             SyncShared &S, FewShared &F)
+{
+    const int64_t tile_start = (int64_t)tile * TILE;
+    const int nseg = T.nseg;
+    const BlockSpan hs = span_of(T.bs(), T.be());
+    const bool head_open = hs.bs < tile_start || hs.be > tile_start + TILE, tail_open = T.tail != 0;
+    store_signs(p, n_valid, signs, tile_start, L.W);
+    __syncthreads();                // the bounds are there
+#pragma unroll 1
+    for (int i = 0; i < nseg; ++i) {
+        // the first segment, the last, then those between: what others may wait for goes out first
+        const int sg = i == 0 ? 0 : i == 1 ? nseg - 1 : i - 1;
+        const int lo = few_bound(F.bound, sg), hi = few_bound(F.bound, sg + 1);
+        const double total = block_sum(abs_sum_range(p, lo, hi), S.red);
+        if (sg == 0 && head_open) {
+            store_partial(total, 0, tile, L, X, set);
+        } else if (sg == nseg - 1 && tail_open) {
+            store_partial(total, 1, tile, L, X, set);
+        } else if (threadIdx.x == 0) {
+            const float s = (float)(total / (double)(hi - lo));
+            scales_out[T.fb + sg] = s;
+            F.scale[sg] = s;
+        }
+    }
+    if (head_open) {
+        float s = 0.f;
+        if (is_counted(L, hs)) {
+            const bool ok = (int64_t)tile == gatherer_tile(L, hs) ? finish_block(T.fb, hs, L, X, set, scales_out, S, &s)
+                                                                  : wait_ready(hs, 0ull, L, X, set, S, &s);
+            if (!ok) {
+                s = 0.f;
+                defer_segment(tile, 0, X, set);
+            }
+        }
+        if (threadIdx.x == 0) F.scale[0] = s;
+    }
+    if (tail_open) {
+        float s = 0.f;
+        const int n = T.tail >> 1, whole = n - 1 - (T.tail & 1);
+        if (n <= L.fuse_limit) {
+            // the block starts in this tile: its whole tiles, if any, are the ones between this and its last
+            const int64_t gatherer = (int64_t)tile + (whole > 0 ? whole : n - 1);
+            if (!wait_ready_at(X.ready + ((int64_t)set * L.ntiles + gatherer) * READY_STRIDE, 0ull, X, S, &s)) {
+                s = 0.f;
+                defer_segment(tile, 1, X, set);
+            }
+        }
+        if (threadIdx.x == 0) F.scale[nseg - 1] = s;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int sg = 0; sg < nseg; ++sg) {
+        const int lo = few_bound(F.bound, sg), hi = few_bound(F.bound, sg + 1);
+        const unsigned n = (unsigned)(hi - lo);
+        const float s = F.scale[sg];
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) {
+            if (!few_touches(k, lo, hi)) continue;
+            const int j = local_base(k) - lo;
+            p[k].x = (unsigned)(j + 0) < n ? residual(p[k].x, s) : p[k].x;
+            p[k].y = (unsigned)(j + 1) < n ? residual(p[k].y, s) : p[k].y;
+            p[k].z = (unsigned)(j + 2) < n ? residual(p[k].z, s) : p[k].z;
+            p[k].w = (unsigned)(j + 3) < n ? residual(p[k].w, s) : p[k].w;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    store_tile(err_tile, p, n_valid);
+}
+
 // Writing the residual out in step.  Measured on this machine: workgroups that take consecutive
 // tiles and hold their residual tile back until all of them have posted their partial sums (as
 // the tiles of a small one-pass block do, which wait for one scale) stream faster than workgroups
@@ -999,34 +1239,28 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &s
     }
 }
 
-// Fill the first half of S.val (read as 16-bit integers) with the segment index of every element of a
-// mixed tile (0 past the end of the vector), so that element j can look up scale[fb + seg].
-__device__ __forceinline__ void build_segment_index(const Layout &L, int32_t tile, int n_valid, int32_t fb,
-                                                    int nseg, TileShared &S)
+// Start words of the mixed tiles (plan creation).  One workgroup per mixed tile.
+__global__ __launch_bounds__(THREADS) void k_start_words(Layout L, StartWord *words)
 {
+    __shared__ unsigned bits[TILE_WORDS];
+    const int32_t tile = L.mixed_tiles[blockIdx.x];
     const int64_t tile_start = (int64_t)tile * TILE;
-    uint16_t *seg = reinterpret_cast<uint16_t *>(S.val);
-    if (threadIdx.x == 0) S.n_long = 0;
+    const int32_t fb = L.tile_fb[tile], lb = L.tile_lb[tile];
+    if (threadIdx.x < TILE_WORDS) bits[threadIdx.x] = threadIdx.x == 0 ? 1u : 0u;
     __syncthreads();
-    for (int j = n_valid + (int)threadIdx.x; j < TILE; j += THREADS) seg[j] = 0;
-    for (int sg = threadIdx.x; sg < nseg; sg += THREADS) {
-        const int lo = (int)max(L.offs[fb + sg] - tile_start, (int64_t)0);
-        const int hi = (int)min(L.offs[fb + sg + 1] - tile_start, (int64_t)n_valid);
-        if (hi - lo > SMALL_SEG) {
-            S.long_list[atomicAdd(&S.n_long, 1)] = sg;
-            continue;
-        }
-        for (int j = lo; j < hi; ++j) seg[j] = (uint16_t)sg;
+    for (int32_t b = fb + 1 + (int32_t)threadIdx.x; b <= lb; b += THREADS) {
+        const int j = (int)(L.offs[b] - tile_start);
+        atomicOr(&bits[j >> 5], 1u << (j & 31));
     }
     __syncthreads();
-    const int n_long = S.n_long;
-    for (int q = wave_id(); q < n_long; q += NWAVES) {
-        const int sg = S.long_list[q];
-        const int lo = (int)max(L.offs[fb + sg] - tile_start, (int64_t)0);
-        const int hi = (int)min(L.offs[fb + sg + 1] - tile_start, (int64_t)n_valid);
-        for (int j = lo + lane_id(); j < hi; j += 64) seg[j] = (uint16_t)sg;
+    if (threadIdx.x < TILE_WORDS) {
+        unsigned before = 0;
+        for (unsigned i = 0; i < threadIdx.x; ++i) before += (unsigned)__popc(bits[i]);
+        StartWord w;
+        w.starts = bits[threadIdx.x];
+        w.rank = before;
+        words[(int64_t)blockIdx.x * TILE_WORDS + threadIdx.x] = w;
     }
-    __syncthreads();
 }
 
 }  // namespace ef

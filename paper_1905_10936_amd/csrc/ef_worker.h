@@ -38,28 +38,37 @@ __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4
     for (int k = 0; k < SUBROWS; ++k) worker_values4<MOM>(g[k], m[k], e[k], mu, r);
 }
 
-// Mixed tiles of all workers, one workgroup per (tile, worker).  Runs before
-// the uniform-tile kernel of the same call.
-template <bool MOM>
-__global__ __launch_bounds__(THREADS) void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A)
+// Mixed tiles (those of `tiles`) of all workers, one workgroup per (tile, worker).  Runs before the kernel that
+// has the whole tiles.  Bound by its chain of latencies where there are few of them, else by HBM.
+// QUAL: see k_worker_tiles.
+template <bool MOM, bool QUAL>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q, const int32_t *tiles)
 {
     const Scratch X = open_call(R);
     __shared__ TileShared S;
-    const int32_t tile = L.mixed_tiles[blockIdx.x];
+    const int32_t tile = tiles[blockIdx.x];
+    const TileRec T = L.tiles[tile];
     const int worker = blockIdx.y;
     const int n_valid = tile_valid(L, tile);
     const int64_t tile_start = (int64_t)tile * TILE;
-    const float *g = A.grad + (int64_t)worker * A.grad_stride + tile_start;
     float *m = MOM ? A.mom + (int64_t)worker * A.state_stride + tile_start : nullptr;
     float *e = A.err + (int64_t)worker * A.state_stride + tile_start;
     float4 gv[SUBROWS], mv[SUBROWS], pv[SUBROWS];
-    load_tile(g, gv, n_valid);
+    load_tile(A.grad + (int64_t)worker * A.grad_stride + tile_start, gv, n_valid);
     if (MOM) load_tile(m, mv, n_valid);
     load_tile(e, pv, n_valid);
+    const TilePlace at = tile_place(L, T);
     worker_values<MOM>(gv, mv, pv, A.mu, A.r);
     if (MOM) store_tile(m, mv, n_valid);
-    float *scales_out = A.scales + (int64_t)worker * A.scales_stride;
-    compress_mixed(pv, L, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride, scales_out, e, X, worker, S);
+    if constexpr (QUAL) {
+        float4 a[SUBROWS];
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
+        quality_of_tile(a, L, Q, tile, worker, n_valid, S);
+    }
+    compress_mixed(pv, L, T, at, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+                   A.scales + (int64_t)worker * A.scales_stride, e, X, worker, S);
 }
 
 // Uniform tiles of the worker as a persistent kernel.
@@ -82,7 +91,7 @@ __global__ __launch_bounds__(THREADS) void k_worker_mixed(Layout L, ScratchRef R
 // fuse_limit rules out, and it is bounded by spin_limit in any case.
 //
 // What is streamed comes from a producer (Algorithm 4 or Algorithm 3 worker):
-//   issue(L, idx, whole tile)  start the tile's loads (idx: which worker)
+//   issue(L, idx, tile, b)     start the tile's loads (idx: which worker)
 //   produce(L, idx, tile, p)   the corrected values p of Algorithm 4 (and the role's other stores)
 //   signs(L, idx), scales(L, idx), err_tile(idx, tile)   where that participant's outputs go
 struct HeldTile {
@@ -148,12 +157,12 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
         if (t >= total) break;
         if (threadIdx.x == 0) tk_next = atomicAdd(X.ticket, 1u);   // the answer is read at the next tile
         const int idx = (int)(t / per_part);
-        const WholeTile w = L.whole_tiles[t % per_part];
-        const int32_t tile = w.tile;
+        const int32_t tile = L.whole_tiles[t % per_part];
+        const TileRec w = L.tiles[tile];
         const int set = X.set_base + idx;
 
         // ---- this tile's loads go out first
-        prod.issue(L, idx, w);
+        prod.issue(L, idx, tile, w.fb);
 
         // ---- while they fly: follow up on the previous tile's post, write out the oldest tile held
         const int old_b = staged[0].b;
@@ -165,7 +174,7 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
             // The block of the oldest tile cannot complete while this workgroup sits on a tile of
             // the same block that is not posted yet (the new one): then do not wait, park p and
             // leave the tile to the second pass.
-            const bool may_wait = !(old_idx == idx && w.b == old_b);
+            const bool may_wait = !(old_idx == idx && w.fb == old_b);
             float4 pv_old[SUBROWS];
             stage_load(stage, staged[0].slot, pv_old);
             finish_uniform(pv_old, old_tile, TILE, block_span(L, old_b), peeked, prod.err_tile(old_idx, old_tile), L, X,
@@ -190,7 +199,7 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
         float4 pv[SUBROWS];
         prod.produce(L, idx, tile, pv);
         HeldTile &slot = held[PIPE_DEPTH - 1];
-        const int kind = compress_uniform(pv, L, tile, w.b, span_of(w.bs, w.be), TILE, prod.signs(L, idx), prod.scales(L, idx),
+        const int kind = compress_uniform(pv, L, tile, w.fb, span_of(w.bs(), w.be()), TILE, prod.signs(L, idx), prod.scales(L, idx),
                                           prod.err_tile(idx, tile), X, set, S, posted);
         posted_idx = idx;
         slot.b = -1;
@@ -199,7 +208,7 @@ __device__ __forceinline__ void persistent_uniform(const Layout &L, const Scratc
             for (int k = 0; k < SUBROWS; ++k) slot.p[k] = pv[k];
             slot.tile = tile;
             slot.idx = idx;
-            slot.b = w.b;
+            slot.b = w.fb;
         }
     }
 
@@ -235,10 +244,10 @@ struct WorkerProducer {
     {
         return A.err + (int64_t)idx * A.state_stride + (int64_t)tile * TILE;
     }
-    __device__ __forceinline__ void issue(const Layout &L, int idx, const WholeTile &w)
+    __device__ __forceinline__ void issue(const Layout &L, int idx, int32_t tile, int32_t b)
     {
-        const int64_t tile_start = (int64_t)w.tile * TILE;
-        corr = loaded_correction(L, w.b, *X, X->set_base + idx);
+        const int64_t tile_start = (int64_t)tile * TILE;
+        corr = loaded_correction(L, b, *X, X->set_base + idx);
         load_tile(A.grad + (int64_t)idx * A.grad_stride + tile_start, gv, TILE);
         if (MOM) load_tile(A.mom + (int64_t)idx * A.state_stride + tile_start, mv, TILE);
         load_tile(A.err + (int64_t)idx * A.state_stride + tile_start, ev, TILE);
@@ -267,45 +276,17 @@ void k_worker_uniform(Layout L, ScratchRef R, WorkerArgs A, int n_workers)
     snapshot_call(R);
 }
 
-// All tiles of all workers in one launch, one workgroup per (tile, worker): the mixed tiles first
-// (the first n_mixed workgroups of every worker's row of the grid), then the whole tiles in
-// ascending order.  A whole tile goes through the steps of the persistent kernel without the
-// pipeline: the workgroup waits in place for its block's scale; the momentum tile is written at
-// once, the residual tile when the scale is there, so the tiles of a block write their residuals
-// in step.  The mixed tiles run the mixed-tile code and never wait for a whole tile (MIXED =
-// false: the layout has no such tile, and the code for them is left out).  Relies on workgroups
-// being dispatched in grid order (the mixed tiles' partial sums are posted before a block's last
-// whole tile looks for them; fuse_limit keeps a block's tiles well inside what is resident at
-// once) and on spin_limit where that fails.
+// All tiles of all workers but the dense ones in one launch, one workgroup per (tile, worker), in ascending order,
+// mixed tiles among the others.  A whole tile goes through the steps of the persistent kernel without the pipeline: the
+// workgroup waits in place for its block's scale; the momentum tile is written at once, the residual tile
+// when the scale is there, so the tiles of a block write their residuals in step.  The open segments of
+// mixed tiles do the same.  (MIXED = false: the layout has no such tile, and the code for them is left out.)
+// Relies on workgroups being dispatched in grid order (fuse_limit keeps a block's tiles well inside what is
+// resident at once) and on spin_limit where that fails.
 // Eight workgroups per CU (64 VGPRs, a few spilled): the one-pass limit is half of what is
 // resident, and 2048 resident workgroups let blocks of up to 1024 tiles (4 Mi elements) finish
 // in one pass (measured: 27.1 -> 24.4 ms on the transformer-like layout, no change elsewhere).
-template <bool MOM, bool QUAL>
-__device__ __forceinline__ void worker_mixed_tile(const Layout &L, const Scratch &X, const WorkerArgs &A,
-                                                  const QualityArgs &Q, int32_t tile, int worker, int n_valid,
-                                                  TileShared &S)
-{
-    const int64_t tile_start = (int64_t)tile * TILE;
-    const float *g = A.grad + (int64_t)worker * A.grad_stride + tile_start;
-    float *m = MOM ? A.mom + (int64_t)worker * A.state_stride + tile_start : nullptr;
-    float *e = A.err + (int64_t)worker * A.state_stride + tile_start;
-    float4 gv[SUBROWS], mv[SUBROWS], pv[SUBROWS];
-    load_tile(g, gv, n_valid);
-    if (MOM) load_tile(m, mv, n_valid);
-    load_tile(e, pv, n_valid);
-    worker_values<MOM>(gv, mv, pv, A.mu, A.r);
-    if (MOM) store_tile(m, mv, n_valid);
-    if constexpr (QUAL) {
-        float4 a[SUBROWS];
-#pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
-        quality_of_tile(a, L, Q, tile, worker, n_valid, S);
-    }
-    compress_mixed(pv, L, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride,
-                   A.scales + (int64_t)worker * A.scales_stride, e, X, worker, S);
-}
-
-template <bool MIXED>
+template <bool QUAL>
 struct TilesShared {
     typedef SyncShared type;
 };
@@ -317,10 +298,10 @@ struct TilesShared<true> {
 // QUAL = true: the compressor-quality sums of p (Section 3.2: Proposition 1's phi, Eq. (1)'s delta)
 // are taken on the way, from the values the kernel holds anyway (see ef_quality.h).
 template <bool MOM, bool MIXED, bool QUAL>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED ? 7 : 8, 8)))
 void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
-    __shared__ typename TilesShared<MIXED || QUAL>::type S;
+    __shared__ typename TilesShared<QUAL>::type S;
     const int worker = blockIdx.y;
     const float *g = A.grad + (int64_t)worker * A.grad_stride;
     float *m = MOM ? A.mom + (int64_t)worker * A.state_stride : nullptr;
@@ -329,7 +310,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     uint64_t *signs = A.signs + (int64_t)worker * A.signs_stride;
     float4 gv[SUBROWS], mv[SUBROWS], pv[SUBROWS];
     if (!MIXED) {
-        // whole tile i is tile i: its loads go out before anything is looked up
+        // tile i is workgroup i's: its loads go out before anything is looked up
         const int64_t start = (int64_t)blockIdx.x * TILE;
         load_tile(g + start, gv, TILE);
         if (MOM) load_tile(m + start, mv, TILE);
@@ -337,18 +318,16 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         __builtin_amdgcn_sched_barrier(0);
     }
     const Scratch X = open_call(R);
-    const bool whole = !MIXED || (int)blockIdx.x >= L.n_mixed;
-    const WholeTile w = L.whole_tiles[!MIXED ? blockIdx.x : whole ? blockIdx.x - L.n_mixed : 0];
-    const int32_t tile = !MIXED ? (int32_t)blockIdx.x : whole ? w.tile : L.mixed_tiles[blockIdx.x];
-    const int n_valid = whole ? TILE : tile_valid(L, tile);
+    const TileRec T = MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
+    const int32_t tile = MIXED ? T.tile : (int32_t)blockIdx.x;
     const int64_t tile_start = (int64_t)tile * TILE;
+    const int n_valid = MIXED ? tile_valid(L, tile) : TILE;
     g += tile_start;
     if (MOM) m += tile_start;
     e += tile_start;
-    if (whole) {
-        Posted P;
-        const BlockSpan sp = span_of(w.bs, w.be);
-        const LoadedCorrection corr = loaded_correction(L, w.b, X, worker);
+    if (!MIXED || T.words < 0) {
+        const BlockSpan sp = span_of(T.bs(), T.be());
+        const LoadedCorrection corr = loaded_correction(L, T.fb, X, worker);
         if (MIXED) {
             load_tile(g, gv, TILE);
             if (MOM) load_tile(m, mv, TILE);
@@ -363,7 +342,8 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
             quality_of_tile(a, L, Q, tile, worker, TILE, S);
         }
-        const int kind = compress_uniform(pv, L, tile, w.b, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
+        Posted P;
+        const int kind = compress_uniform(pv, L, tile, T.fb, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
         resolve_posted(P, L, X, worker, scales_out, S);
         if (kind == UNI_PENDING) {
             finish_uniform(pv, tile, TILE, sp, 0ull, e, L, X, worker, S);
@@ -372,7 +352,22 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             store_tile(e, pv, TILE);
         }
     } else if constexpr (MIXED) {
-        worker_mixed_tile<MOM, QUAL>(L, X, A, Q, tile, worker, n_valid, S);
+        __shared__ FewShared F;
+        if (T.nseg > 0) {               // else a dense tile: finished by the kernel before
+            few_bounds(L, T, tile_start, n_valid, F.bound);
+            load_tile(g, gv, n_valid);
+            if (MOM) load_tile(m, mv, n_valid);
+            load_tile(e, pv, n_valid);
+            worker_values<MOM>(gv, mv, pv, A.mu, A.r);
+            if (MOM) store_tile(m, mv, n_valid);
+            if constexpr (QUAL) {
+                float4 a[SUBROWS];
+#pragma unroll
+                for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
+                quality_of_tile(a, L, Q, tile, worker, n_valid, S);
+            }
+            compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F);
+        }
     }
     snapshot_call(R);
 }
