@@ -104,7 +104,10 @@ namespace {
 enum { ROLE_TICKET = 0, ROLE_SERVER = 1, ROLE_TILES = 2 };
 
 constexpr int MAX_DEVICES = 64;
-constexpr int FEW_LEAD = 256;           // see build_device
+// Places a mixed tile is taken ahead of its own (see build_device).  Measured on the ResNet-50 layout (server, 7
+// workers) and on blocks of 64 tiles and 7 elements (worker, 7 workers): 0 60.4 / 590 us, 128 57.1 / 590, 256 54.9 /
+// 592, 512 53.6 / 596, 1024 56.9 / 607: far ahead, its slot is lost to the tiles it waits for.
+constexpr int FEW_LEAD = 256;
 std::mutex g_scratch_mutex;
 double *g_scratch_ptr[MAX_DEVICES];     // [device] address of `scratch` on that device, once looked up
 
@@ -505,6 +508,7 @@ int build_device(ef_plan *p)
             dense.push_back(t);
         }
     p->L.n_dense = (int32_t)dense.size();
+    p->L.n_grid = ntiles - p->L.n_dense;
     // The order in which the kernels with one workgroup per tile take the tiles: ascending, but a mixed tile FEW_LEAD
     // places ahead of where it is (or, if a block with whole tiles ends in it, of that block's first): it takes
     // longer than a whole tile, and its blocks wait for it, as the call does at its end.
@@ -514,6 +518,7 @@ int build_device(ef_plan *p)
         size_t w = 0;
         for (int32_t t : mixed) {
             const ef::TileRec &r = tiles[(size_t)t];
+            if (r.nseg < 0) continue;
             const int64_t at = (r.n > 2 || (r.n == 2 && r.from == 0) ? r.t0 : t) - (int64_t)FEW_LEAD;
             while (w < whole.size() && whole[w] < at) in_order.push_back(tiles[(size_t)whole[w++]]);
             in_order.push_back(r);
@@ -566,7 +571,7 @@ int build_device(ef_plan *p)
     p->L.mixed_tiles = p->d_mixed;
     p->L.whole_tiles = p->d_whole;
     p->L.tiles = p->d_tiles;
-    p->L.grid_tiles = in_order.empty() ? p->d_tiles : p->d_in_order;
+    p->L.grid_tiles = p->L.n_mixed ? p->d_in_order : p->d_tiles;
     p->L.words = p->d_words;
     p->L.dense_tiles = p->d_dense;
     p->L.offs = p->d_offs;
@@ -1096,7 +1101,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         EF_HIP(hipGetLastError());
     } else {
         // every tile in one launch
-        const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::THREADS);
+        const dim3 grid((unsigned)plan->L.n_grid, (unsigned)n_workers), block(ef::THREADS);
         const bool mixed = plan->L.n_mixed != 0;
         ef::QualityArgs Q;
         Q.v = nullptr;
@@ -1114,7 +1119,9 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
                 hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
             EF_HIP(hipGetLastError());
         }
-        if (quality)
+        if (!plan->L.n_grid)
+            ;                           // nothing but dense tiles
+        else if (quality)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, true, true>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom && mixed)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, true, false>), grid, block, 0, s, L, c.X, A, Q);
@@ -1195,9 +1202,11 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
                            plan->max_workers);
         EF_HIP(hipGetLastError());
     }
-    const dim3 grid((unsigned)L.ntiles), block(ef::THREADS);
+    const dim3 grid((unsigned)L.n_grid), block(ef::THREADS);
     const bool many = M > ef::SERVER_CHUNK;
-    if (L.n_mixed && many)
+    if (!L.n_grid)
+        ;                               // nothing but dense tiles
+    else if (L.n_mixed && many)
         hipLaunchKernelGGL((ef::k_server_tiles<true, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else if (L.n_mixed)
         hipLaunchKernelGGL((ef::k_server_tiles<true, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);

@@ -15,8 +15,8 @@ __device__ __forceinline__ float mean_of(float acc, float Mf, float Minv)
 }
 
 constexpr int SERVER_CHUNK = 8;     // workers whose sign words are in flight together
-constexpr int SCALE_GROUP = 4;      // mixed tiles: workers whose scales and sign bits are staged in LDS together ...
-constexpr int SCALE_STAGE = TILE;    // ... in this many floats (as many as a tile can have segments)
+constexpr int SCALE_GROUP = 4;      // dense tiles: workers whose scales are staged in LDS together ...
+constexpr int SCALE_STAGE = TILE / 2;   // ... in this many floats
 
 typedef unsigned vu4 __attribute__((ext_vector_type(4)));
 
@@ -163,64 +163,81 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
     }
 }
 
-// The same for a tile where several blocks meet (or the ragged end of the vector).  The scales of the tile's
-// segments are staged in LDS, up to SCALE_GROUP workers at a time (one coalesced read per worker instead of a
-// gather per element), and looked up there by segment.  te: the tile of the server residual.
-__device__ __forceinline__ void server_values_mixed(const Layout &L, const ServerArgs &A, int32_t tile, const TileRec &T,
-                                                    const TilePlace &at, int n_valid, const float *te, float4 (&p)[SUBROWS],
-                                                    TileShared &S)
+// The same for a tile where several blocks meet (or the ragged end of the vector): a
+// per-element segment index in LDS selects each worker's scale.  te: the tile of the server residual.
+__device__ __forceinline__ void server_values_mixed(const Layout &L, const ServerArgs &A, int32_t tile, const TileRec &T, int n_valid,
+                                                    const float *te, float4 (&p)[SUBROWS], TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
+    const int32_t fb = T.fb, nseg = abs(T.nseg);
     float acc[SUBROWS][4];
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
 
-    // A lane loads each worker's bits of 16 consecutive elements and finds those of its own four through LDS, as
-    // in server_values_whole.
-    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
-    const int64_t half0 = (tile_start >> 4) + threadIdx.x;
-    const bool in = half0 < 4 * L.W;
-    unsigned *exchange = S.half + wave_id() * 128;
-    const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
-    const int nseg = abs(T.nseg), group = min(SCALE_GROUP, SCALE_STAGE / nseg);
-    for (int i0 = 0; i0 < A.M; i0 += group) {
-        unsigned h[SCALE_GROUP];
+    // this lane's 4 sign bits of sub-row k live in the 32-bit half-word hw0 + 8k
+    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(A.signs_in);
+    const int64_t hw0 = (tile_start + local_base(0)) >> 5;
+    const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
+    const int64_t n_hw = 2 * L.W;
+    const int64_t in_hw = 2 * A.in_signs_stride;
+
+    build_segment_index(L, tile, n_valid, fb, nseg, S);
+    const ushort4 *seg4 = reinterpret_cast<const ushort4 *>(S.val);
+    // The scales of the tile's segments are staged in LDS, SCALE_GROUP workers at a time where
+    // they fit (one coalesced read per worker instead of a gather per element), and looked up
+    // there; a tile with more segments than the stage holds gathers them from global memory.
+    float *seg_scale = S.val + TILE / 2;            // the index takes the first half
+    const int group = nseg * SCALE_GROUP <= SCALE_STAGE ? SCALE_GROUP : nseg <= SCALE_STAGE ? 1 : 0;
+    if (group) {
+        for (int i0 = 0; i0 < A.M; i0 += group) {
+            uint32_t word[SCALE_GROUP][SUBROWS];
 #pragma unroll
-        for (int u = 0; u < SCALE_GROUP; ++u) {
-            const int i = min(i0 + u, A.M - 1);          // past the group or M: loaded, not used
-            h[u] = in ? s16[(int64_t)i * 4 * A.in_signs_stride + half0] : 0u;
-        }
-        if (i0 > 0) __syncthreads();                     // the stage is read no more
-        for (int u = 0; u < group && i0 + u < A.M; ++u) {
-            const float *sc_i = A.scales_in + (int64_t)(i0 + u) * A.in_scales_stride + T.fb;
-            for (int j = threadIdx.x; j < nseg; j += THREADS) S.val[u * nseg + j] = sc_i[j];
-        }
-        exchange[2 * lane_id()] = h[0] | (h[1] << 16);
-        exchange[2 * lane_id() + 1] = h[2] | (h[3] << 16);
-        __syncthreads();
+            for (int u = 0; u < SCALE_GROUP; ++u) {
+                const int i = min(i0 + u, A.M - 1);      // past the group or M: loaded, not used
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) {
-            // opaque: the sixteen segment numbers would otherwise be formed once, before the loop, and spilled
-            unsigned place = at.row[k];
-            asm volatile("" : "+v"(place));
-            int seg[4], s0 = (int)(place >> 4) - 1;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) seg[c] = s0 += (int)((place >> c) & 1u);
-            // elements 256k + 4*lane .. +3 of the wavefront: half-word 16k + lane/4, nibble lane%4
-            const int e = 2 * (16 * k + (lane_id() >> 2));
-            const unsigned two[2] = {exchange[e] >> sh, exchange[e + 1] >> sh};
+                for (int k = 0; k < SUBROWS; ++k) {
+                    const int64_t hw = hw0 + 8 * k;
+                    word[u][k] = (hw < n_hw) ? s32[(int64_t)i * in_hw + hw] : 0u;
+                }
+            }
+            if (i0 > 0) __syncthreads();                 // the stage is read no more
+            for (int u = 0; u < group && i0 + u < A.M; ++u) {
+                const float *sc_i = A.scales_in + (int64_t)(i0 + u) * A.in_scales_stride + fb;
+                for (int j = threadIdx.x; j < nseg; j += THREADS) seg_scale[u * nseg + j] = sc_i[j];
+            }
+            __syncthreads();
 #pragma unroll
             for (int u = 0; u < SCALE_GROUP; ++u) {
                 if (u < group && i0 + u < A.M) {
-                    const float *sc_u = S.val + u * nseg;
-                    const unsigned nibble = two[u >> 1] >> (16 * (u & 1));
+                    const float *sc_u = seg_scale + u * nseg;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) acc[k][c] = acc[k][c] + signed_scale(sc_u[seg[c]], (nibble >> c) & 1u);
+                    for (int k = 0; k < SUBROWS; ++k) {
+                        const unsigned nibble = (word[u][k] >> sh) & 0xFu;
+                        const ushort4 sg = seg4[local_base(k) >> 2];
+                        acc[k][0] = acc[k][0] + signed_scale(sc_u[sg.x], nibble & 1u);
+                        acc[k][1] = acc[k][1] + signed_scale(sc_u[sg.y], nibble & 2u);
+                        acc[k][2] = acc[k][2] + signed_scale(sc_u[sg.z], nibble & 4u);
+                        acc[k][3] = acc[k][3] + signed_scale(sc_u[sg.w], nibble & 8u);
+                    }
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);      // one sub-row after the other: few registers
+        }
+    } else {
+        for (int i = 0; i < A.M; ++i) {
+            const float *sc_i = A.scales_in + (int64_t)i * A.in_scales_stride + fb;
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) {
+                const int64_t hw = hw0 + 8 * k;
+                const uint32_t word = (hw < n_hw) ? s32[(int64_t)i * in_hw + hw] : 0u;
+                const unsigned nibble = (word >> sh) & 0xFu;
+                const ushort4 sg = seg4[local_base(k) >> 2];
+                acc[k][0] = acc[k][0] + signed_scale(sc_i[sg.x], nibble & 1u);
+                acc[k][1] = acc[k][1] + signed_scale(sc_i[sg.y], nibble & 2u);
+                acc[k][2] = acc[k][2] + signed_scale(sc_i[sg.z], nibble & 4u);
+                acc[k][3] = acc[k][3] + signed_scale(sc_i[sg.w], nibble & 8u);
+            }
         }
     }
     __syncthreads();            // S.val is free again
@@ -238,7 +255,7 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
 
 // The dense mixed tiles, before the kernel that has the others.  The residual tile is loaded after the payloads
 // have been added up, which keeps the registers down.
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, const int32_t *tiles, int set)
 {
     const Scratch X = open_call(R);
@@ -248,9 +265,9 @@ void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, const int32_t *tiles, 
     const int n_valid = tile_valid(L, tile);
     float *te = A.err + (int64_t)tile * TILE;
     float4 p[SUBROWS];
-    const TilePlace at = tile_place(L, T);
-    server_values_mixed(L, A, tile, T, at, n_valid, te, p, S);
-    compress_mixed(p, L, T, at, tile, n_valid, A.signs, A.scales, te, X, set, S);
+    server_values_mixed(L, A, tile, T, n_valid, te, p, S);
+    compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
+    snapshot_call(R);           // there may be no whole tiles
 }
 
 // p~ of a tile of a few segments (see compress_few): as server_values_whole, with a table of sums for one segment
@@ -397,11 +414,9 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
     } else if constexpr (MIXED) {
         __shared__ FewShared F;
-        if (T.nseg > 0) {               // else a dense tile: finished by the kernel before
-            few_bounds(L, T, tile_start, n_valid, F.bound);
-            server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
-            compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F);
-        }
+        few_bounds(L, T, tile_start, n_valid, F.bound);
+        server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
+        compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F);
     }
     snapshot_call(R);
 }

@@ -69,12 +69,13 @@ constexpr int TILE = 4096;      // elements per workgroup and step
 constexpr int THREADS = 256;    // 4 wavefronts
 constexpr int NWAVES = THREADS / 64;
 constexpr int SUBROWS = 4;      // float4 per thread
-constexpr int SMALL_SEG = 64;   // quality sums: segments up to this length are summed by one thread
+constexpr int SMALL_SEG = 64;   // segments up to this length are summed by one thread
 constexpr int MAX_LONG = TILE / SMALL_SEG;
 constexpr int TILE_WORDS = TILE / 32;
-constexpr int ROWS = TILE / 256;        // a wavefront's sub-rows of 256 elements in a tile
-constexpr int FEW_SEGS = 6;             // most segments of a tile that is taken among the whole ones (see compress_few)
-constexpr int SEG_ROUND = 384;          // segments of a mixed tile that are finished in one round (their sums lie in LDS)
+// Most segments of a tile that is taken among the whole ones (see compress_few).  Its cost grows with them: 25 M
+// elements, server call with 7 workers, few-segment tiles against dense ones: blocks of 3000 62 us / 102,
+// of 1024 (5 segments) 84 / 96, of 600 (8 segments) 105 / 98.
+constexpr int FEW_SEGS = 6;
 constexpr int DEFER_WGS = 16;   // workgroups that serve the run-time lists in the kernel that ends a call
 constexpr int FIN_WGS_MAX = 512;    // most workgroups that kernel gives to the scales of blocks larger than fuse_limit ...
 constexpr int RES_WGS_MAX = 2048;   // ... and to the segments whose p was parked
@@ -120,7 +121,8 @@ struct Layout {
     const int32_t *mixed_tiles;   // [n_mixed] ascending
     const int32_t *whole_tiles;   // [n_uniform] ascending
     const TileRec *tiles;         // [ntiles]
-    const TileRec *grid_tiles;    // the same in the order in which the kernels with one workgroup per tile take them
+    int32_t n_grid;
+    const TileRec *grid_tiles;    // [n_grid] all but the dense ones, as the kernels with one workgroup per tile take them
     const StartWord *words;       // [n_mixed][TILE_WORDS]
     int32_t n_dense;
     const int32_t *dense_tiles;   // [n_dense] the mixed tiles of many segments, ascending
@@ -294,18 +296,6 @@ __device__ __forceinline__ void guarded_store4(float *base, int local, int n_val
     if (local + 3 < n_valid) base[local + 3] = v.w;
 }
 
-// Turns a register array by one place.  Where only few tiles pass, loops over a thread's sub-rows are not
-// unrolled, to keep the registers of kernels that also stream the whole tiles down; a register array
-// cannot be indexed by a loop counter, so such a loop works on element 0 and turns.
-template <class T>
-__device__ __forceinline__ void turn(T (&v)[SUBROWS])
-{
-    const T first = v[0];
-    v[0] = v[1];
-    v[1] = v[2];
-    v[2] = v[3];
-    v[3] = first;
-}
 // A thread's four float4 of one tile.  Only the last tile of a vector can be
 // ragged; the test is uniform over the workgroup, so full tiles run straight
 // through 128-bit accesses with no per-access branch.
@@ -526,14 +516,8 @@ struct SyncShared {
 };
 // ... and what the kernels that cut a tile into segments need on top of it.
 struct TileShared : SyncShared {
-    float val[TILE];            // the tile's p, or what the kernel needs before it has p
-    union {
-        double sum[SEG_ROUND];      // segment sums ...
-        float scale[2 * SEG_ROUND]; // ... then, in the even places, scales
-        unsigned half[SEG_ROUND * 2];
-    };
-    double row_total[ROWS];
-    int row_any[ROWS];
+    float val[TILE];            // |p| per element, then the element's scale (closed segments)
+    double open_sum[2];
     int long_list[MAX_LONG];
     int n_long;
 };
@@ -830,158 +814,114 @@ __device__ __forceinline__ TilePlace tile_place(const Layout &L, const TileRec &
     }
     return q;
 }
-__device__ __forceinline__ int64_t seg_length(const Layout &L, const TileRec &T, int sg)
-{
-    return sg < abs(T.nseg) ? L.offs[T.fb + sg + 1] - L.offs[T.fb + sg] : 1;
-}
-
-// Inclusive sums of a thread's four |p| of one sub-row since the last start among them.
-__device__ __forceinline__ void row_sums(const float4 &p, unsigned starts, int valid, double (&r)[4])
-{
-    const double a[4] = {valid > 0 ? fabsf(p.x) : 0.f, valid > 1 ? fabsf(p.y) : 0.f, valid > 2 ? fabsf(p.z) : 0.f,
-                         valid > 3 ? fabsf(p.w) : 0.f};
-    r[0] = a[0];
-#pragma unroll
-    for (int c = 1; c < 4; ++c) r[c] = ((starts >> c) & 1u) ? a[c] : r[c - 1] + a[c];
-}
-
-// Mixed tile (several blocks meet, or the ragged end of the vector): sign words; segmented sums; scales and
-// residuals e' = p - Delta of the closed segments; partial sums of the (at most two) open segments posted, and
-// their residuals finished where the block's scale forms inside this kernel (bounded waits), else their
-// elements stored as p for the kernel that ends the call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of
-// Algorithm 4.)
-//
-// The sums are a segmented scan over the elements: four to a lane, the 64 lanes of a sub-row, the tile's 16
-// sub-rows; the lane that holds the next segment's start (the last lane for the last segment) leaves a
-// segment's sum in LDS.  No step depends on how long the segments are: the loops over a segment's
-// elements that this replaces ran at the length of the longest in a wavefront (25 M elements in blocks
-// of 3000, with 256, with 33: worker call, one worker, 96.8 / 92.4 / 97.5 us before).
-//
-// The kernels this runs in come before the one with the whole tiles, and only blocks that have none are
-// finished here (the last tile of such a block forms its scale); a block with whole tiles gets its
-// partial sums from here and its segments' p parked.
-__device__ __forceinline__ void compress_mixed(const float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, const TilePlace &at,
-                                               int32_t tile, int n_valid, uint64_t *signs, float *scales_out,
-                                               float *err_tile, const Scratch &X, int set, TileShared &S)
+// Mixed tile of any number of segments, in the kernels that come before the one with the whole tiles: sign
+// words; segmented fp64 sums through LDS; scales and residuals e' = p - Delta of the
+// closed segments; partial sums of the (at most two) open segments posted, and
+// their residuals finished too where the block's scale forms inside this kernel
+// (bounded waits), else their elements stored as p for the kernel that ends the
+// call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of Algorithm 4.)  The segmented scan of the kernels for
+// small launches was measured here too: 25 M elements in blocks of 33, worker call with 7 workers 600 us
+// against 618, but the server's 112 against 98, and in blocks of 5 both twice as slow.
+__device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
+                                               uint64_t *signs, float *scales_out, float *err_tile,
+                                               const Scratch &X, int set, TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
-    const int lane = lane_id(), wave = wave_id(), nseg = abs(T.nseg);
-    const int64_t db0 = seg_length(L, T, (int)threadIdx.x);         // asked for early
-    const BlockSpan hs = span_of(T.bs(), T.be());
-    const bool head_open = hs.bs < tile_start || hs.be > tile_start + TILE;
-    const bool tail_open = T.tail != 0;
+    const int32_t fb = T.fb, lb = T.fb + abs(T.nseg) - 1;
     store_signs(p, n_valid, signs, tile_start, L.W);
-    // every lane reads back only what it writes here
+
+    const int nseg = lb - fb + 1;
 #pragma unroll
-    for (int k = 0; k < SUBROWS; ++k) *reinterpret_cast<float4 *>(&S.val[local_base(k)]) = p[k];
-    TilePlace q = at;
-    double carry[SUBROWS];          // the sum since the last start before this thread's four elements
-#pragma unroll 1
     for (int k = 0; k < SUBROWS; ++k) {
-        double r[4];
-        row_sums(*reinterpret_cast<const float4 *>(&S.val[local_base(k)]), q.starts(0), n_valid - local_base(k), r);
-        const unsigned long long any = __ballot(q.starts(0) != 0u);
-        const double t = segment_scan(r[3], any);
-        carry[0] = wave_shift(t);
-        if (lane == 63) {
-            S.row_total[4 * wave + k] = t;
-            S.row_any[4 * wave + k] = any != 0ull;
+        float4 a = make_float4(fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w));
+        *reinterpret_cast<float4 *>(&S.val[local_base(k)]) = a;
+    }
+    if (threadIdx.x == 0) S.n_long = 0;
+    __syncthreads();
+    const bool head_open = L.offs[fb] < tile_start;
+    const bool tail_open = L.offs[lb + 1] > tile_start + TILE;
+    for (int sg = threadIdx.x; sg < nseg; sg += THREADS) {
+        const int64_t b = fb + sg;
+        const int64_t bs = L.offs[b], be = L.offs[b + 1];
+        const int lo = (int)max(bs - tile_start, (int64_t)0);
+        const int hi = (int)min(be - tile_start, (int64_t)n_valid);
+        if (hi - lo > SMALL_SEG) {
+            S.long_list[atomicAdd(&S.n_long, 1)] = sg;
+            continue;
         }
-        turn(q.row);
-        turn(carry);
+        double acc = 0.0;
+        for (int j = lo; j < hi; ++j) acc += (double)S.val[j];
+        const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
+        if (open) {
+            S.open_sum[sg == 0 ? 0 : 1] = acc;
+        } else {
+            const float sc = (float)(acc / (double)(be - bs));
+            scales_out[b] = sc;
+            for (int j = lo; j < hi; ++j) S.val[j] = sc;
+        }
     }
     __syncthreads();
-    const double rows = segment_scan16(S.row_total[lane & 15], (unsigned)__ballot(S.row_any[lane & 15] != 0) & 0xffffu);
-    for (int base = 0; base < nseg; base += SEG_ROUND) {
-        const int end = min(nseg, base + SEG_ROUND);
-        if (base) __syncthreads();
-#pragma unroll 1
-        for (int k = 0; k < SUBROWS; ++k) {
-            if (base == 0) {
-                // read by all lanes, outside any branch: the lane that is read from has to have formed its value
-                const int row = (int)uniform_u32((unsigned)(4 * wave + k));
-                const double below = read_lane(rows, row > 0 ? row - 1 : 0);
-                const unsigned long long any = __ballot(q.starts(0) != 0u);
-                carry[0] += (row > 0 && !(any & ((1ull << lane) - 1ull))) ? below : 0.0;
-            }
-            double r[4], before = carry[0];
-            row_sums(*reinterpret_cast<const float4 *>(&S.val[local_base(k)]), q.starts(0), n_valid - local_base(k), r);
-            int seg = q.seg(0);
-            bool started = false;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if ((q.starts(0) >> c) & 1u) {
-                    if (seg >= base && seg < end) S.sum[seg - base] = before;
-                    ++seg;
-                    started = true;
-                }
-                before = started ? r[c] : carry[0] + r[c];
-            }
-            if (k == SUBROWS - 1 && threadIdx.x == THREADS - 1 && end == nseg) S.sum[seg - base] = before;
-            turn(q.row);
-            turn(carry);
-        }
-        __syncthreads();
-        // the open segments' sums go out first
-        if (base == 0 && head_open) store_partial(S.sum[0], 0, tile, L, X, set);
-        if (end == nseg && tail_open) store_partial(S.sum[nseg - 1 - base], 1, tile, L, X, set);
-        for (int sg = base + (int)threadIdx.x; sg < end; sg += THREADS) {
-            if ((sg == 0 && head_open) || (sg == nseg - 1 && tail_open)) continue;
-            const int64_t db = sg == (int)threadIdx.x ? db0 : seg_length(L, T, sg);
-            const float sc = (float)(S.sum[sg - base] / (double)db);
-            scales_out[T.fb + sg] = sc;
-            S.scale[2 * (sg - base)] = sc;          // over the sum, which no other thread reads
-        }
-        float s_head = 0.f, s_tail = 0.f;
-        bool fin_head = false, fin_tail = false;
-        if (base == 0 && head_open) {
-            if (finishes_with_mixed(L, hs)) {
-                fin_head = (int64_t)tile == gatherer_tile(L, hs) ? finish_block(T.fb, hs, L, X, set, scales_out, S, &s_head)
-                                                                 : wait_ready(hs, 0ull, L, X, set, S, &s_head);
-                if (!fin_head) defer_segment(tile, 0, X, set);
-            }
-        }
-        if (end == nseg && tail_open) {
-            // the block starts in this tile: its whole tiles, if any, are the ones between this and its last
-            const int n = T.tail >> 1, whole = n - 1 - (T.tail & 1);
-            if (n <= L.fuse_limit && whole == 0) {
-                const int64_t gatherer = (int64_t)tile + n - 1;
-                fin_tail = wait_ready_at(X.ready + ((int64_t)set * L.ntiles + gatherer) * READY_STRIDE, 0ull, X, S, &s_tail);
-                if (!fin_tail) defer_segment(tile, 1, X, set);
-            }
-        }
-        __syncthreads();
-        // values, no longer variables whose address was taken: a choice between them and LDS would become a
-        // choice of pointers
-        const float from_head = __uint_as_float(uniform_u32(__float_as_uint(s_head)));
-        const float from_tail = __uint_as_float(uniform_u32(__float_as_uint(s_tail)));
-#pragma unroll 1
-        for (int k = 0; k < SUBROWS; ++k) {
-            float4 &row = *reinterpret_cast<float4 *>(&S.val[local_base(k)]);
-            const float4 pk = row;
-            float v[4] = {pk.x, pk.y, pk.z, pk.w};
-            int seg = q.seg(0);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                seg += (int)((q.starts(0) >> c) & 1u);
-                if (seg >= base && seg < end) {
-                    const bool head = head_open && seg == 0, tail = tail_open && seg == nseg - 1;
-                    const float own = S.scale[2 * (seg - base)], s = head ? from_head : tail ? from_tail : own;
-                    const bool keep = (head && !fin_head) || (tail && !fin_tail);
-                    v[c] = keep ? v[c] : residual(v[c], s);
-                }
-            }
-            const float4 ev = make_float4(v[0], v[1], v[2], v[3]);
-            row = ev;                               // other segments' elements may be due in a later round
-            if (end == nseg) {
-                if (n_valid == TILE)
-                    stream_store4(err_tile + local_base(k), ev);
-                else
-                    guarded_store4(err_tile, local_base(k), n_valid, ev);
-            }
-            turn(q.row);
+    const int n_long = S.n_long;
+    for (int q = wave_id(); q < n_long; q += NWAVES) {
+        const int sg = S.long_list[q];
+        const int64_t b = fb + sg;
+        const int64_t bs = L.offs[b], be = L.offs[b + 1];
+        const int lo = (int)max(bs - tile_start, (int64_t)0);
+        const int hi = (int)min(be - tile_start, (int64_t)n_valid);
+        double acc = 0.0;
+        for (int j = lo + lane_id(); j < hi; j += 64) acc += (double)S.val[j];
+        acc = wave_sum(acc);
+        const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
+        if (open) {
+            if (lane_id() == 0) S.open_sum[sg == 0 ? 0 : 1] = acc;
+        } else {
+            const float sc = (float)(acc / (double)(be - bs));
+            if (lane_id() == 0) scales_out[b] = sc;
+            for (int j = lo + lane_id(); j < hi; j += 64) S.val[j] = sc;
         }
     }
+    __syncthreads();
+    const int head_end = head_open ? (int)min(L.offs[fb + 1] - tile_start, (int64_t)n_valid) : 0;
+    const int tail_begin = tail_open ? (int)(L.offs[lb] - tile_start) : TILE;
+    if (head_open) store_partial(S.open_sum[0], 0, tile, L, X, set);
+    if (tail_open) store_partial(S.open_sum[1], 1, tile, L, X, set);
+    // An open segment whose block has no whole tile is finished in place: all tiles of such a
+    // block are mixed ones, handed out before any whole tile and in ascending order.  The first
+    // segment's block ends in this tile, which makes this workgroup the one that forms its scale;
+    // the last segment's block goes on, and its scale comes from the next mixed tile.  The segments
+    // of other blocks, and any whose wait runs out, keep p in the residual buffer for the kernel
+    // that ends the call.
+    float s_head = 0.f, s_tail = 0.f;
+    bool fin_head = false, fin_tail = false;
+    if (head_open && finishes_with_mixed(L, block_span(L, fb))) {
+        fin_head = finish_block(fb, block_span(L, fb), L, X, set, scales_out, S, &s_head);
+        if (!fin_head) defer_segment(tile, 0, X, set);
+    }
+    if (tail_open && finishes_with_mixed(L, block_span(L, lb))) {
+        fin_tail = wait_ready(block_span(L, lb), 0ull, L, X, set, S, &s_tail);
+        if (!fin_tail) defer_segment(tile, 1, X, set);
+    }
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k) {
+        const int lb0 = local_base(k);
+        const float4 sc = *reinterpret_cast<const float4 *>(&S.val[lb0]);
+        const float pv[4] = {p[k].x, p[k].y, p[k].z, p[k].w};
+        const float sv[4] = {sc.x, sc.y, sc.z, sc.w};
+        float ev[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = lb0 + c;
+            if (j < head_end)
+                ev[c] = fin_head ? residual(pv[c], s_head) : pv[c];
+            else if (j >= tail_begin)
+                ev[c] = fin_tail ? residual(pv[c], s_tail) : pv[c];
+            else
+                ev[c] = residual(pv[c], sv[c]);
+        }
+        p[k] = make_float4(ev[0], ev[1], ev[2], ev[3]);
+    }
+    store_tile(err_tile, p, n_valid);
+    __syncthreads();            // S.val is free again
 }
 
 // Deferred correction of a uniform tile's residual as loaded (see Scratch::lazy_scales): if the
@@ -1079,7 +1019,7 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
 // grid, with the segment code for any number of segments, cost the kernel registers, its first
 // workgroups 20 us, and the segments of blocks with whole tiles a pass of their own in the kernel that
 // ends the call: 25 M elements in blocks of 64 tiles and 7 elements, server call with 7 workers 65 us
-// against 48 for blocks of 64 tiles.)
+// against 48 for blocks of 64 tiles; 53 now.  Momentum-free worker in blocks of 30 011: 88 -> 67 us.)
 // bound[i]: local index of the end of segment i-1 = start of segment i, in LDS.
 struct FewShared {
     int bound[FEW_SEGS + 1];
@@ -1237,6 +1177,36 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &s
         }
         __syncthreads();
     }
+}
+
+// Fill the first half of S.val (read as 16-bit integers) with the segment index of every element of a
+// mixed tile (0 past the end of the vector), so that element j can look up scale[fb + seg].
+__device__ __forceinline__ void build_segment_index(const Layout &L, int32_t tile, int n_valid, int32_t fb,
+                                                    int nseg, TileShared &S)
+{
+    const int64_t tile_start = (int64_t)tile * TILE;
+    uint16_t *seg = reinterpret_cast<uint16_t *>(S.val);
+    if (threadIdx.x == 0) S.n_long = 0;
+    __syncthreads();
+    for (int j = n_valid + (int)threadIdx.x; j < TILE; j += THREADS) seg[j] = 0;
+    for (int sg = threadIdx.x; sg < nseg; sg += THREADS) {
+        const int lo = (int)max(L.offs[fb + sg] - tile_start, (int64_t)0);
+        const int hi = (int)min(L.offs[fb + sg + 1] - tile_start, (int64_t)n_valid);
+        if (hi - lo > SMALL_SEG) {
+            S.long_list[atomicAdd(&S.n_long, 1)] = sg;
+            continue;
+        }
+        for (int j = lo; j < hi; ++j) seg[j] = (uint16_t)sg;
+    }
+    __syncthreads();
+    const int n_long = S.n_long;
+    for (int q = wave_id(); q < n_long; q += NWAVES) {
+        const int sg = S.long_list[q];
+        const int lo = (int)max(L.offs[fb + sg] - tile_start, (int64_t)0);
+        const int hi = (int)min(L.offs[fb + sg + 1] - tile_start, (int64_t)n_valid);
+        for (int j = lo + lane_id(); j < hi; j += 64) seg[j] = (uint16_t)sg;
+    }
+    __syncthreads();
 }
 
 // Start words of the mixed tiles (plan creation).  One workgroup per mixed tile.

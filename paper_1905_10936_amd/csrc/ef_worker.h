@@ -42,7 +42,7 @@ __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4
 // has the whole tiles.  Bound by its chain of latencies where there are few of them, else by HBM.
 // QUAL: see k_worker_tiles.
 template <bool MOM, bool QUAL>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q, const int32_t *tiles)
 {
     const Scratch X = open_call(R);
@@ -58,7 +58,6 @@ void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q, const i
     load_tile(A.grad + (int64_t)worker * A.grad_stride + tile_start, gv, n_valid);
     if (MOM) load_tile(m, mv, n_valid);
     load_tile(e, pv, n_valid);
-    const TilePlace at = tile_place(L, T);
     worker_values<MOM>(gv, mv, pv, A.mu, A.r);
     if (MOM) store_tile(m, mv, n_valid);
     if constexpr (QUAL) {
@@ -67,8 +66,9 @@ void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q, const i
         for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
         quality_of_tile(a, L, Q, tile, worker, n_valid, S);
     }
-    compress_mixed(pv, L, T, at, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+    compress_mixed(pv, L, T, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride,
                    A.scales + (int64_t)worker * A.scales_stride, e, X, worker, S);
+    snapshot_call(R);           // there may be no whole tiles
 }
 
 // Uniform tiles of the worker as a persistent kernel.
@@ -353,21 +353,19 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         }
     } else if constexpr (MIXED) {
         __shared__ FewShared F;
-        if (T.nseg > 0) {               // else a dense tile: finished by the kernel before
-            few_bounds(L, T, tile_start, n_valid, F.bound);
-            load_tile(g, gv, n_valid);
-            if (MOM) load_tile(m, mv, n_valid);
-            load_tile(e, pv, n_valid);
-            worker_values<MOM>(gv, mv, pv, A.mu, A.r);
-            if (MOM) store_tile(m, mv, n_valid);
-            if constexpr (QUAL) {
-                float4 a[SUBROWS];
+        few_bounds(L, T, tile_start, n_valid, F.bound);
+        load_tile(g, gv, n_valid);
+        if (MOM) load_tile(m, mv, n_valid);
+        load_tile(e, pv, n_valid);
+        worker_values<MOM>(gv, mv, pv, A.mu, A.r);
+        if (MOM) store_tile(m, mv, n_valid);
+        if constexpr (QUAL) {
+            float4 a[SUBROWS];
 #pragma unroll
-                for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
-                quality_of_tile(a, L, Q, tile, worker, n_valid, S);
-            }
-            compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F);
+            for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
+            quality_of_tile(a, L, Q, tile, worker, n_valid, S);
         }
+        compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F);
     }
     snapshot_call(R);
 }
