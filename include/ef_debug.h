@@ -54,8 +54,13 @@ int ef_plan_fuse_limit(const ef_plan *plan);       /* the worker kernels' limit 
  * ones, and it finishes blocks of 1025 to 2304 tiles in one pass that the
  * other sends through the second pass).  ef_worker_step_sgd, and every worker
  * call in the deferred mode (ef_plan_set_lazy), use the persistent kernel only
- * after on = 1.  The server always runs one workgroup per tile.  Same results
- * either way.  Synchronises the device.
+ * after on = 1.  With on < 0, calls of up to about a thousand (tile, worker)
+ * pairs whose blocks span at most 256 tiles run kernels of their own instead,
+ * built for short launches; the server's and the update's calls on such a
+ * layout always do.  The server otherwise runs one workgroup per tile.  The
+ * families add a block's 64-bit sums in different orders; that shows in a scale
+ * only where the sums lie within 1e-15 of a rounding boundary of fp32.
+ * Synchronises the device.
  */
 int ef_plan_set_persistent(ef_plan *plan, int on);
 int ef_plan_is_persistent(const ef_plan *plan);
