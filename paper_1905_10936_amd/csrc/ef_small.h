@@ -165,8 +165,24 @@ __device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double
     return ok;
 }
 
+// One of the block's partial sums, of this call.  All of them have been stored by the time the last workgroup looks,
+// but a workgroup that was not parked stores its word and counts itself out with relaxed operations and no
+// release between them (that would write back the L2 of every streaming store), so the count says nothing
+// about the word: the word's own tag does.  The wait is for a store already made; should it never
+// show, the scale is a NaN rather than one formed from the last call's word.
+constexpr int LEFT_OVER_POLLS = 1 << 20;
+__device__ __forceinline__ double left_over_word(const unsigned long long *at, unsigned long long tag)
+{
+    for (int it = 0; it < LEFT_OVER_POLLS; ++it) {
+        const unsigned long long w = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((w >> 63) == tag) return __longlong_as_double((long long)(w & ~TAG_BIT));
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return __longlong_as_double(0x7ff8000000000000ll);
+}
+
 // A call that ran out of patience somewhere: scales not written and segments parked as p, seen to by the
-// first wavefront of the workgroup that finishes last (every partial sum has been posted by then).
+// first wavefront of the workgroup that finishes last.
 __device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &X, const SmallArgs &Z)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -180,11 +196,12 @@ __device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &
             const int64_t b = kind ? (which ? L.tile_lb[tile] : L.tile_fb[tile]) : (int64_t)(it & 0xffffffffull);
             const BlockSpan sp = block_span(L, b);
             const unsigned long long *part = set_part(X, L, set);
+            const unsigned long long tag = set_tag(X, set);
             double v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int j = lane_id() + 64 * q;
-                v[q] = j < sp.n ? __longlong_as_double((long long)(part[part_index(sp.t0 + j, sp)] & ~TAG_BIT)) : 0.0;
+                v[q] = j < sp.n ? left_over_word(part + part_index(sp.t0 + j, sp), tag) : 0.0;
             }
             const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
             const int w = set - X.set_base;

@@ -126,3 +126,25 @@ def test_small_update_with_weight_decay_and_the_momentum_free_worker(mu):
     ef.ef_apply_wd(st.plan, xd, md, st.ws[0], st.wc[0], 0.1, mu, 1e-3)
     oracle.apply_wd(x, m, s_ref, c_ref, offs, F(0.1), F(mu), F(1e-3))
     assert np.array_equal(xd.cpu().numpy(), x) and np.array_equal(md.cpu().numpy(), m)
+
+
+def test_some_workgroups_of_a_block_give_up_and_others_do_not():
+    """A budget of a few polls: workgroups that come early give up, later ones find all the block's sums there, so the
+    workgroup that finishes last adds up words that were posted by workgroups which gave nothing up."""
+    partial = 0
+    for name in ("wgs_341x3", "span_256", "span_65"):
+        offs = _offs(EDGES[name])
+        d, M = int(offs[-1]), 3
+        first, last = offs[:-1] // T, (offs[1:] - 1) // T
+        spans = last > first
+        n_open = int((last - first + 1)[spans].sum())       # segments whose block goes on in another tile
+        for spin in (1, 2, 3, 5, 8):
+            rng = np.random.default_rng(spin)
+            st = GpuState(offs, M)
+            st.plan.set_persistent(None)
+            st.plan.tune(spin_limit=spin)
+            for t, eta in enumerate([0.1, 0.05, 0.1]):
+                st.set_grads(rng.standard_normal((M, d)).astype(F))
+                synced_step(st, 0.9, 0.1 * t, eta, None, "%s, %d polls, step %d" % (name, spin, t))
+                partial += 0 < st.plan.last_fallbacks()[0] < n_open      # of the server's call
+    assert partial > 0
