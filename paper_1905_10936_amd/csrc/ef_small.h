@@ -59,6 +59,7 @@ struct SmallShared {
     double row_total[SMALL_WAVES];
     int row_any[SMALL_WAVES];
     int parked[2];              // head, tail: the wait ran out
+    int left_over;              // this workgroup is the last one, and there is something to see to
     double total;
 };
 
@@ -165,64 +166,93 @@ __device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double
     return ok;
 }
 
-// One of the block's partial sums, of this call.  All of them have been stored by the time the last workgroup looks,
+// One of the block's partial sums, of this call (w: a first look at it).  All of them have been stored by the time the last workgroup looks,
 // but a workgroup that was not parked stores its word and counts itself out with relaxed operations and no
 // release between them (that would write back the L2 of every streaming store), so the count says nothing
 // about the word: the word's own tag does.  The wait is for a store already made; should it never
 // show, the scale is a NaN rather than one formed from the last call's word.
 constexpr int LEFT_OVER_POLLS = 1 << 20;
-__device__ __forceinline__ double left_over_word(const unsigned long long *at, unsigned long long tag)
+__device__ __forceinline__ double left_over_word(const unsigned long long *at, unsigned long long w, unsigned long long tag)
 {
-    for (int it = 0; it < LEFT_OVER_POLLS; ++it) {
-        const unsigned long long w = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((w >> 63) == tag) return __longlong_as_double((long long)(w & ~TAG_BIT));
+    for (int it = 0; (w >> 63) != tag; ++it) {
+        if (it == LEFT_OVER_POLLS) return __longlong_as_double(0x7ff8000000000000ll);
         __builtin_amdgcn_s_sleep(1);
+        w = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    return __longlong_as_double(0x7ff8000000000000ll);
+    return __longlong_as_double((long long)(w & ~TAG_BIT));
 }
 
-// A call that ran out of patience somewhere: scales not written and segments parked as p, seen to by the
-// first wavefront of the workgroup that finishes last.
-__device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &X, const SmallArgs &Z)
+// e <- p - Delta over the elements [lo, hi) of a residual row whose p was parked (one wavefront).
+__device__ __forceinline__ void small_residual(float *e, int64_t lo, int64_t hi, float s)
 {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    for (int kind = 0; kind < 2; ++kind) {
-        const unsigned n = __hip_atomic_load(kind ? X.defer_cnt : X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (unsigned i = 0; i < n; ++i) {
-            const unsigned long long it = kind ? X.defer_list[i] : X.fin_list[i];
-            const int set = kind ? (int)(it >> 33) : (int)(it >> 32);
-            const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
-            const int which = (int)(it & 1ull);
-            const int64_t b = kind ? (which ? L.tile_lb[tile] : L.tile_fb[tile]) : (int64_t)(it & 0xffffffffull);
-            const BlockSpan sp = block_span(L, b);
-            const unsigned long long *part = set_part(X, L, set);
-            const unsigned long long tag = set_tag(X, set);
-            double v[4];
+    const int lane = lane_id();
+    const int64_t a = (lo + 3) & ~(int64_t)3, z = hi & ~(int64_t)3;     // whole groups of four
+    if (a >= z) {
+        if (lo + lane < hi) e[lo + lane] = residual(e[lo + lane], s);
+        return;
+    }
+    // the other elements of the first and the last group may be another wavefront's
+    if (lo + lane < a) e[lo + lane] = residual(e[lo + lane], s);
+    if (z + lane < hi) e[z + lane] = residual(e[z + lane], s);
+    for (int64_t j = a + 4 * lane; j < z; j += 4 * 256) {
+        float4 v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = lane_id() + 64 * q;
-                v[q] = j < sp.n ? left_over_word(part + part_index(sp.t0 + j, sp), tag) : 0.0;
-            }
-            const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
-            const int w = set - X.set_base;
-            if (!kind) {
-                if (lane_id() == 0) Z.scales[(int64_t)w * Z.scales_stride + b] = s;
-                continue;
-            }
-            const int64_t lo = max(sp.bs, (int64_t)tile * TILE), hi = min(sp.be, ((int64_t)tile + 1) * TILE);
-            float *e = Z.err + (int64_t)w * Z.err_stride;
-            for (int64_t j = lo + lane_id(); j < hi; j += 64) e[j] = residual(e[j], s);
+        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const float4 *>(e + min(j + 256 * q, z - 4));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            residual4(v[q], s);
+            if (j + 256 * q < z) *reinterpret_cast<float4 *>(e + j + 256 * q) = v[q];
         }
     }
 }
 
-// The workgroup is done (its wavefront 0 calls this): the last one to get here ends the call.
-__device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, const SmallArgs &Z)
+// A call that ran out of patience somewhere: scales not written and segments parked as p, seen to by the
+// workgroup that finishes last, a wavefront to an entry of the two lists.  (A call whose every
+// wait gives up, 1000 tiles in blocks of 200: 630 us; one wavefront for all took 26 ms, the kernel that ends the calls of
+// k_worker_tiles takes 150 us of such a call.)
+__device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &X, const SmallArgs &Z)
 {
-    int last = 0;
-    if (lane_id() == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const unsigned n_fin = __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned n_def = __hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (unsigned i = uniform_u32(threadIdx.x >> 6); i < n_fin + n_def; i += SMALL_WAVES) {
+        const bool parked = i >= n_fin;
+        const unsigned long long it = parked ? X.defer_list[i - n_fin] : X.fin_list[i];
+        const int set = parked ? (int)(it >> 33) : (int)(it >> 32);
+        const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
+        const int which = (int)(it & 1ull);
+        const int64_t b = parked ? (which ? L.tile_lb[tile] : L.tile_fb[tile]) : (int64_t)(it & 0xffffffffull);
+        const BlockSpan sp = block_span(L, b);
+        const unsigned long long *part = set_part(X, L, set);
+        const unsigned long long tag = set_tag(X, set);
+        unsigned long long word[4];
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)     // past the block: its last word, not used
+            word[q] = __hip_atomic_load(part + part_index(sp.t0 + min(lane_id() + 64 * q, sp.n - 1), sp), __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = lane_id() + 64 * q;
+            v[q] = j < sp.n ? left_over_word(part + part_index(sp.t0 + j, sp), word[q], tag) : 0.0;
+        }
+        const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
+        const int w = set - X.set_base;
+        if (parked)
+            small_residual(Z.err + (int64_t)w * Z.err_stride, max(sp.bs, (int64_t)tile * TILE),
+                           min(sp.be, ((int64_t)tile + 1) * TILE), s);
+        else if (lane_id() == 0)
+            Z.scales[(int64_t)w * Z.scales_stride + b] = s;
+    }
+}
+
+// The workgroup is done (called by all of it): the last one to get here ends the call.
+__device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, const SmallArgs &Z, SmallShared &S)
+{
+    if (threadIdx.x == 0) {
         const unsigned n = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x, g = me % DONE_GROUPS;
         const unsigned in_group = (n + DONE_GROUPS - 1 - g) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
+        int last = 0;
         if (atomicAdd(Z.done + g * DONE_STRIDE, 1u) + 1u == in_group) {
             Z.done[g * DONE_STRIDE] = 0u;
             if (atomicAdd(Z.done + DONE_GROUPS * DONE_STRIDE, 1u) + 1u == groups) {
@@ -230,12 +260,16 @@ __device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, 
                 last = 1;
             }
         }
+        int left = 0;
+        if (last) {
+            left = (__hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+                    __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
+            advance_call(Z.state, X, Z.nsets, Z.lazy);       // clears the next call's counters, not this one's
+        }
+        S.left_over = left;
     }
-    if (!__any(last)) return;
-    if (__hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
-        __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        small_left_over(L, X, Z);
-    if (lane_id() == 0) advance_call(Z.state, X, Z.nsets, Z.lazy);
+    __syncthreads();
+    if (S.left_over) small_left_over(L, X, Z);
 }
 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
@@ -348,12 +382,14 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     }
     small_store4(err_tile, n_valid, make_float4(v[0], v[1], v[2], v[3]));
     if (park_head | park_tail) {
-        // whoever ends the call reads what was parked, and the list entry
-        __threadfence();
+        // whoever ends the call reads what was parked, and the list entry.  One wavefront releases for all, whose
+        // stores have reached the L2 by then: with a write-back for
+        // each, that call took 1170 us.
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        __threadfence();
+        if (wave == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     }
-    if (wave == 0) small_finish(L, X, Z);
+    small_finish(L, X, Z, S);
 }
 
 template <bool MOM>
