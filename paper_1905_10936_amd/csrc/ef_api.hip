@@ -77,6 +77,7 @@ struct ef_plan {
     // launches that (nearly) fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
     // counters, null: this layout has none)
     int small_wgs;                  // most workgroups such a launch may have
+    int small_span;                 // most tiles of a block in it
     bool has_small;                 // this layout has such launches
     ef::SmallArgs small;
     bool worker_kernel_auto;        // ef_plan_set_persistent has not been used to pick one
@@ -370,7 +371,7 @@ int refresh_limits_unguarded(ef_plan *p)
         ticket.fuse_limit = tiles.fuse_limit = p->persistent_forced ? 0 : LAZY_WAIT_LIMIT;
         // A layout of few tiles whose server residual the caller never sees is finished in one launch,
         // where waiting is cheap.
-        server.fuse_limit = p->has_small && p->held ? ef::SMALL_SPAN : 0;
+        server.fuse_limit = p->has_small && p->held ? p->small_span : 0;
     } else {
         ticket.fuse_limit = clamp(p->lim_persistent);
         server.fuse_limit = clamp(p->lim_server);
@@ -398,7 +399,8 @@ int refresh_limits(ef_plan *p)
 }
 
 // Records of the kernels for launches that (nearly) fit on the GPU all at once, if the
-// layout has calls for them: few enough tiles, and no block of more tiles than a wavefront adds up.
+// layout has calls for them: few enough tiles, and no block of more tiles than a wavefront adds up, or than are
+// sure to be resident together.
 void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
 {
     const int32_t ntiles = p->L.ntiles;
@@ -406,7 +408,7 @@ void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
     const int64_t *o = p->offs_host.data();
     const int64_t d = p->L.d;
     for (int64_t b = 0; b < p->L.B; ++b)
-        if (tiles_of_block(p, b) > ef::SMALL_SPAN) return;
+        if (tiles_of_block(p, b) > p->small_span) return;
     out.resize((size_t)ntiles);
     p->has_small = true;
     int32_t words = 0;
@@ -469,11 +471,12 @@ int build_device(ef_plan *p)
     p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
     p->lim_direct = (int32_t)((int64_t)facts.cus * facts.tiles / 2);
     // Launches that (nearly) fit on the GPU all at once: up to twice what is resident.  A block's tiles are at
-    // most half of that and are dispatched in order, as the other one-pass kernels assume.  Measured, worker
+    // most half of what is resident and are dispatched in order, as the other one-pass kernels assume.  Measured, worker
     // calls in blocks of 30 000 elements, these kernels against k_worker_tiles + k_tail: 64 workgroups 7.7 /
     // 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3; server calls with 4 workers, against
     // k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
     p->small_wgs = 2 * facts.cus * facts.small;
+    p->small_span = ef::small_span(facts.cus * facts.small);
     std::vector<ef::SmallTile> small;
     small_tables(p, small);
 

@@ -12,6 +12,7 @@
 //   * no kernel follows: the last workgroup to finish steps the call state (and sees to the segments
 //     whose bounded wait ran out, normally none).
 #pragma once
+#include "ef_layout.h"
 #include "ef_tile.h"
 #include "ef_worker.h"
 #include "ef_server.h"
@@ -21,7 +22,6 @@ namespace ef {
 
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_WAVES = SMALL_THREADS / 64;
-constexpr int SMALL_SPAN = 256;         // most tiles of a block that spans tiles
 constexpr int DONE_GROUPS = 8;          // workgroups count themselves out on this many words ...
 constexpr int DONE_STRIDE = 32;         // ... a cache line apart, and these on one more
 

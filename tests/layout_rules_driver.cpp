@@ -1,0 +1,26 @@
+// Rules of csrc/ef_layout.h, checked on the host; built and run by tests/test_layout_rules.py.  Test infrastructure only.
+#include "ef_layout.h"
+
+#include <cstdio>
+#include <initializer_list>
+
+#define REQUIRE(cond)                                                  \
+    do {                                                               \
+        if (!(cond)) {                                                 \
+            std::fprintf(stderr, "line %d: %s failed\n", __LINE__, #cond); \
+            return 1;                                                  \
+        }                                                              \
+    } while (0)
+
+int main()
+{
+    // a block's tiles fit twice over into what is resident, from a whole MI355X (256 units, two workgroups each) to
+    // an eighth of one
+    for (int units : {256, 128, 64, 32, 1}) {
+        const int resident = 2 * units, span = ef::small_span(resident);
+        REQUIRE(span >= 1 && 2 * span <= resident && span <= ef::SMALL_SPAN);
+    }
+    REQUIRE(ef::small_span(512) == ef::SMALL_SPAN);
+    std::puts("layout rules ok");
+    return 0;
+}
