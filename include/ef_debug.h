@@ -56,14 +56,22 @@ int ef_plan_fuse_limit(const ef_plan *plan);       /* the worker kernels' limit 
  * call in the deferred mode (ef_plan_set_lazy), use the persistent kernel only
  * after on = 1.  With on < 0, calls of up to about a thousand (tile, worker)
  * pairs whose blocks span at most 256 tiles run kernels of their own instead,
- * built for short launches; the server's and the update's calls on such a
- * layout always do.  The server otherwise runs one workgroup per tile.  The
+ * built for short launches, and so do the server's and the update's calls on
+ * such a layout; on = 0 or 1 sends all three to the kernels of the larger
+ * layouts (see ef_plan_small_calls).  The server otherwise runs one workgroup per tile.  The
  * families add a block's 64-bit sums in different orders; that shows in a scale
  * only where the sums lie within 1e-15 of a rounding boundary of fp32.
  * Synchronises the device.
  */
 int ef_plan_set_persistent(ef_plan *plan, int on);
 int ef_plan_is_persistent(const ef_plan *plan);
+
+/*
+ * Which calls on this plan run the kernels for short launches: bit 0 worker
+ * calls over n_workers workers (but those that report the quality), bit 1
+ * server calls, bit 2 the parameter updates.  0 for a NULL plan.
+ */
+int ef_plan_small_calls(const ef_plan *plan, int n_workers);
 
 /*
  * Writing the residual out in step.  In the worker kernel that runs one

@@ -80,7 +80,7 @@ struct ef_plan {
     int small_span;                 // most tiles of a block in it
     bool has_small;                 // this layout has such launches
     ef::SmallArgs small;
-    bool worker_kernel_auto;        // ef_plan_set_persistent has not been used to pick one
+    bool kernels_auto;              // ef_plan_set_persistent has not been used to pick the kernels
 };
 
 // Scratch of ef_compressor_quality_static: device memory that exists from the moment the library
@@ -371,7 +371,7 @@ int refresh_limits_unguarded(ef_plan *p)
         ticket.fuse_limit = tiles.fuse_limit = p->persistent_forced ? 0 : LAZY_WAIT_LIMIT;
         // A layout of few tiles whose server residual the caller never sees is finished in one launch,
         // where waiting is cheap.
-        server.fuse_limit = p->has_small && p->held ? p->small_span : 0;
+        server.fuse_limit = p->has_small && p->kernels_auto && p->held ? p->small_span : 0;
     } else {
         ticket.fuse_limit = clamp(p->lim_persistent);
         server.fuse_limit = clamp(p->lim_server);
@@ -651,8 +651,11 @@ int worker_role(const ef_plan *plan, bool has_mom)
 // block may be left for a second pass (a limit set by the caller, or that of the deferred mode).
 bool small_call(const ef_plan *plan, int role, int nsets)
 {
-    return plan->has_small && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs && plan->role[role].n_late == 0;
+    return plan->has_small && plan->kernels_auto && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs &&
+           plan->role[role].n_late == 0;
 }
+
+bool small_update(const ef_plan *plan) { return plan->has_small && plan->kernels_auto; }
 
 ef::SmallArgs small_args(const ef_plan *plan, int nsets, float *err, int64_t err_stride, float *scales, int64_t scales_stride)
 {
@@ -776,7 +779,7 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
         r.fuse_limit = 0;
     }
     p->has_small = false;
-    p->worker_kernel_auto = true;
+    p->kernels_auto = true;
 
     try {
         p->offs_host.assign(block_offsets_host, block_offsets_host + B + 1);
@@ -934,8 +937,15 @@ int ef_plan_set_persistent(ef_plan *plan, int on)
     if (pending) return EF_ERR_ARG;
     plan->persistent = on < 0 ? plan->persistent_auto : (on ? 1 : 0);
     plan->persistent_forced = on > 0 ? 1 : 0;
-    plan->worker_kernel_auto = on < 0;
+    plan->kernels_auto = on < 0;
     return refresh_limits(plan);
+}
+
+int ef_plan_small_calls(const ef_plan *plan, int n_workers)
+{
+    if (!plan || n_workers < 1) return 0;
+    return (small_call(plan, ROLE_TILES, n_workers) ? 1 : 0) | (small_call(plan, ROLE_SERVER, 1) ? 2 : 0) |
+           (small_update(plan) ? 4 : 0);
 }
 
 int64_t ef_plan_d(const ef_plan *plan) { return plan ? plan->L.d : 0; }
@@ -1065,7 +1075,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         if (n_workers > plan->lazy_sets_seen) plan->lazy_sets_seen = n_workers;
     }
     const CallScratch c = next_call(plan, 0, n_workers);
-    if (!quality && plan->worker_kernel_auto && small_call(plan, ROLE_TILES, n_workers)) {
+    if (!quality && small_call(plan, ROLE_TILES, n_workers)) {
         const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::SMALL_THREADS);
         const ef::SmallArgs Z = small_args(plan, n_workers, err, state_stride, scales, scales_stride);
         if (has_mom)
@@ -1243,7 +1253,7 @@ int ef_apply(const ef_plan *plan, float *params, const uint64_t *packed_signs, c
     if (!aligned(params, 16) || !aligned(packed_signs, 8) || !aligned(scales, 4)) return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    if (plan->has_small)
+    if (small_update(plan))
         hipLaunchKernelGGL(ef::k_apply_small<false>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
                            (float *)nullptr, packed_signs, scales, eta, 0.0f, 0.0f);
     else
@@ -1264,7 +1274,7 @@ int ef_apply_wd(const ef_plan *plan, float *params, float *decay_mom, const uint
         return EF_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
-    if (plan->has_small)
+    if (small_update(plan))
         hipLaunchKernelGGL(ef::k_apply_small<true>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
                            decay_mom, packed_signs, scales, eta, mu, lambda);
     else
