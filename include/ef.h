@@ -330,8 +330,7 @@ int ef_state_import(const ef_plan *plan, ef_state *state, const float *mom, cons
 /*
  * ef_worker_step that also reports how well the compressor approximated what
  * it was given: exactly ef_worker_step (same arguments, same results, bit for
- * bit, but that on layouts of about a thousand tiles and less the two may add
- * a block's 64-bit sum in different orders), plus quality[2i] = phi(p_i) and quality[2i+1] = delta(p_i) of worker
+ * bit), plus quality[2i] = phi(p_i) and quality[2i+1] = delta(p_i) of worker
  * i's corrected gradient p_i (Proposition 1 bounds the step's compression
  * error by (1 - phi(p)) ||p||^2).  The sums of |p| and p^2 are taken inside
  * the worker kernel on the values it holds anyway, so no tensor is read a

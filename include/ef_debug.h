@@ -58,10 +58,9 @@ int ef_plan_fuse_limit(const ef_plan *plan);       /* the worker kernels' limit 
  * pairs whose blocks span at most 256 tiles run kernels of their own instead,
  * built for short launches, and so do the server's and the update's calls on
  * such a layout; on = 0 or 1 sends all three to the kernels of the larger
- * layouts (see ef_plan_small_calls).  The server otherwise runs one workgroup per tile.  The
- * families add a block's 64-bit sums in different orders; that shows in a scale
- * only where the sums lie within 1e-15 of a rounding boundary of fp32.
- * Synchronises the device.
+ * layouts (see ef_plan_small_calls).  The server otherwise runs one workgroup per
+ * tile.  Same results either way (every kernel adds a block's 64-bit sum in the
+ * same order).  Synchronises the device.
  */
 int ef_plan_set_persistent(ef_plan *plan, int on);
 int ef_plan_is_persistent(const ef_plan *plan);

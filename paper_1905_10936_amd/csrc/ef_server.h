@@ -389,7 +389,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED |
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
     __shared__ SyncShared S;
-    __shared__ float lds[SERVER_LDS];
+    __shared__ __align__(16) float lds[MIXED ? TILE : SERVER_LDS];
+    static_assert(SERVER_LDS <= TILE, "one array for the sum tables and for compress_few");
     float4 tv[SUBROWS], p[SUBROWS];
     if (!MIXED) {
         // tile i is workgroup i's: its residual is asked for before anything is looked up
@@ -416,7 +417,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         __shared__ FewShared F;
         few_bounds(L, T, tile_start, n_valid, F.bound);
         server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
-        compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F);
+        compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F, lds);
     }
     snapshot_call(R);
 }

@@ -53,11 +53,15 @@ struct SmallArgs {
     int64_t scales_stride;
 };
 
+constexpr int SMALL_BY_WAVE = 64;   // up to this many segments of a tile get a wavefront each, one after the other
+
 struct SmallShared {
     double sum[TILE];           // segment sums; a whole tile: one row sum per thread
+    float val[TILE];            // |p| per element
     float scale[TILE];          // segment scales
-    double row_total[SMALL_WAVES];
-    int row_any[SMALL_WAVES];
+    int bound[SMALL_BY_WAVE + 1];       // where the segments start, and the last one ends
+    int long_list[MAX_LONG];    // of more segments: the ones too long for one thread
+    int n_long;
     int parked[2];              // head, tail: the wait ran out
     int left_over;              // this workgroup is the last one, and there is something to see to
     double total;
@@ -273,9 +277,9 @@ __device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, 
 }
 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
-// of the blocks that end here, e' = p - Delta.  db: elements of the block of segment threadIdx.x.
+// of the blocks that end here, e' = p - Delta.  [bs, be): the block of segment threadIdx.x.
 __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallArgs &Z, const SmallTile &T,
-                                               const SmallPlace &at, int64_t db, int n_valid, uint64_t *signs, float *scales_out,
+                                               const SmallPlace &at, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
                                                float *err_tile, const Scratch &X, int set, SmallShared &S)
 {
     const int32_t tile = blockIdx.x;
@@ -300,39 +304,43 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
             S.total = small_total(q);
         }
     } else {
-        // Segmented sums.  r[c]: the sum from element 0, or the last start, to element c; T: the same from
-        // the last start of the row of 256 elements that this wavefront has.
-        const unsigned st = at.starts;
-        double r[4];
-        r[0] = a[0];
-#pragma unroll
-        for (int c = 1; c < 4; ++c) r[c] = ((st >> c) & 1u) ? a[c] : r[c - 1] + a[c];
-        const unsigned long long any = __ballot(st != 0u);
-        const double t = segment_scan(r[3], any);
-        double carry = wave_shift(t);
-        if (lane == 63) {
-            S.row_total[wave] = t;
-            S.row_any[wave] = any != 0ull;
-        }
-        __syncthreads();
-        const int l16 = lane & 15;
-        const double rows = segment_scan16(S.row_total[l16], (unsigned)__ballot(S.row_any[l16]) & 0xffffu);
-        // read by all lanes, outside any branch: the lane that is read from has to have formed its value
-        const double below = read_lane(rows, (int)uniform_u32(wave ? wave - 1 : 0));
-        carry += (wave && !(any & ((1ull << lane) - 1ull))) ? below : 0.0;
-        int seg = at.seg;
-        double before = carry;
-        bool started = false;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if ((st >> c) & 1u) {
-                if (seg >= 0) S.sum[seg] = before;
-                ++seg;
-                started = true;
+        // the order of segment_sum
+        *reinterpret_cast<float4 *>(&S.val[j0]) = make_float4(fabsf(p.x), fabsf(p.y), fabsf(p.z), fabsf(p.w));
+        const int64_t start = (int64_t)tile * TILE;
+        if (T.nseg <= SMALL_BY_WAVE) {
+            if ((int)threadIdx.x < T.nseg) {
+                S.bound[threadIdx.x] = (int)max(bs - start, (int64_t)0);
+                if ((int)threadIdx.x == T.nseg - 1) S.bound[T.nseg] = (int)min(be - start, (int64_t)n_valid);
             }
-            before = started ? r[c] : carry + r[c];
+            __syncthreads();
+#pragma unroll 1
+            for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < T.nseg; sg += SMALL_WAVES) {
+                const double total = segment_sum(S.val, (int)uniform_u32((unsigned)S.bound[sg]), (int)uniform_u32((unsigned)S.bound[sg + 1]));
+                if (lane == 0) S.sum[sg] = total;
+            }
+        } else {
+            if (threadIdx.x == 0) S.n_long = 0;
+            __syncthreads();
+            for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
+                const int64_t b = T.fb + sg;
+                const int lo = (int)max((sg < SMALL_THREADS ? bs : L.offs[b]) - start, (int64_t)0);
+                const int hi = (int)min((sg < SMALL_THREADS ? be : L.offs[b + 1]) - start, (int64_t)n_valid);
+                if (hi - lo > SMALL_SEG) {
+                    S.long_list[atomicAdd(&S.n_long, 1)] = sg;
+                    continue;
+                }
+                S.sum[sg] = ordered_sum<1>(S.val, lo, hi, 0.0);
+            }
+            __syncthreads();
+            const int n_long = S.n_long;
+#pragma unroll 1
+            for (int q = (int)uniform_u32(threadIdx.x >> 6); q < n_long; q += SMALL_WAVES) {
+                const int sg = S.long_list[q];
+                const int64_t b = T.fb + sg;
+                const double total = segment_sum(S.val, (int)max(L.offs[b] - start, (int64_t)0), (int)min(L.offs[b + 1] - start, (int64_t)n_valid));
+                if (lane == 0) S.sum[sg] = total;
+            }
         }
-        if (threadIdx.x == SMALL_THREADS - 1) S.sum[seg] = before;
     }
     __syncthreads();
     // the open segments' sums go out first, then the closed segments' scales are formed while others post
@@ -344,7 +352,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     if (tail) store_partial(tail_sum, 1, tile, L, X, set);
     for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
         if ((sg == 0 && head) || (sg == T.nseg - 1 && tail)) continue;
-        if (sg >= SMALL_THREADS) db = L.offs[T.fb + sg + 1] - L.offs[T.fb + sg];
+        const int64_t db = sg < SMALL_THREADS ? be - bs : L.offs[T.fb + sg + 1] - L.offs[T.fb + sg];
         const float sc = (float)((whole ? S.total : S.sum[sg]) / (double)db);
         S.scale[sg] = sc;
         scales_out[T.fb + sg] = sc;
@@ -409,12 +417,15 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
     SmallPlace at = {0u, -1};
-    int64_t db = 1;
+    int64_t bs = 0, be = 1;
     if (T.words >= 0) at = small_place(L, T);
-    if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
+    if ((int)threadIdx.x < T.nseg) {
+        bs = L.offs[T.fb + threadIdx.x];
+        be = L.offs[T.fb + threadIdx.x + 1];
+    }
     worker_values4<MOM>(g, m, e, A.mu, A.r);
     if (MOM) small_store4(mt, n_valid, m);
-    small_compress(e, L, Z, T, at, db, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+    small_compress(e, L, Z, T, at, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
                    A.scales + (int64_t)worker * A.scales_stride, et, X, worker, S);
 }
 
@@ -432,9 +443,12 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
     SmallPlace at = {0u, -1};
-    int64_t db = 1;
+    int64_t bs = 0, be = 1;
     if (T.words >= 0) at = small_place(L, T);
-    if ((int)threadIdx.x < T.nseg) db = L.offs[T.fb + threadIdx.x + 1] - L.offs[T.fb + threadIdx.x];
+    if ((int)threadIdx.x < T.nseg) {
+        bs = L.offs[T.fb + threadIdx.x];
+        be = L.offs[T.fb + threadIdx.x + 1];
+    }
     int seg[4];
     {
         int sg = T.words >= 0 ? at.seg : 0;
@@ -470,7 +484,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
     p.y = mean_of(acc[1], A.Mf, A.Minv) + A.r * te.y;
     p.z = mean_of(acc[2], A.Mf, A.Minv) + A.r * te.z;
     p.w = mean_of(acc[3], A.Mf, A.Minv) + A.r * te.w;
-    small_compress(p, L, Z, T, at, db, n_valid, A.signs, A.scales, et, X, set, S);
+    small_compress(p, L, Z, T, at, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
 }
 
 // Parameter update (see apply_tile), one workgroup of 1024 threads per tile.

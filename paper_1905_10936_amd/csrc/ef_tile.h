@@ -17,7 +17,7 @@
 // tile that lies inside one block is "uniform"; a tile where several blocks
 // meet, and the ragged last tile of the vector, is "mixed".  A segment whose block lies entirely inside the tile is "closed":
 // its L1 norm, scale and residual are finished by the tile alone (in fp64, in
-// ascending order for short segments).  The other segments are "open": their
+// the one order of segment_sum).  The other segments are "open": their
 // fp64 partial sums go to a per-(tile, slot) scratch word, and whoever needs
 // the block's scale adds the block's partials in one fixed order (thread t
 // takes tiles t, t+256, ... ascending, then a fixed tree), so the scale has the
@@ -365,66 +365,35 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Segmented sums along lanes.  t: a lane's sum since the last start among its own elements (all of
-// them if none of its elements starts a segment); `any`: the lanes with a start.  Returns the sum since the
-// last start at or before the lane's last element, from lane 0 on if there is none, as a fixed tree
-// over the lanes: Hillis-Steele steps, in which a lane takes in the value `off` lanes below only if no start
-// lies in between.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double row_fetch(double v)      // 0 where there is no such lane, or in rows not in ROWS
+// Sum of val[j], val[j + STEP], ... below hi, one after the other, on top of acc.  The reads go out eight at a time;
+// adding the +0 that stands for one past the end changes nothing, since no element is negative.
+template <int STEP>
+__device__ __forceinline__ double ordered_sum(const float *val, int j, int hi, double acc)
 {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+#pragma unroll 1
+    for (; j + 7 * STEP < hi; j += 8 * STEP) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = val[j + q * STEP];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += (double)v[q];
+    }
+    float v[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] = val[min(j + q * STEP, hi - 1)];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) acc += (double)(j + q * STEP < hi ? v[q] : 0.f);
+    return acc;
 }
-#define EF_DPP_ROW_SHR(n) (0x110 + (n))     // lane i <- lane i-n of its row of 16
-#define EF_DPP_WAVE_SHR1 0x138              // lane i <- lane i-1
-#define EF_DPP_BCAST15 0x142                // a row <- the last lane of the row below
-#define EF_DPP_BCAST31 0x143                // lanes 32-63 <- lane 31
-__device__ __forceinline__ double segment_scan16(double t, unsigned any)    // over each row of 16 lanes by itself
+
+// Sum of |p| over the segment [lo, hi) of a tile, val: |p| of the tile's elements, in LDS.  THE order, whichever kernel
+// forms it, so that a block's scale has the same bits on every route: up to SMALL_SEG elements ascending; else lane l
+// adds lo + l, lo + l + 64, ... and the lanes are added up by wave_sum.  One wavefront, lo and hi the same in all
+// lanes; every lane gets the sum.
+__device__ __forceinline__ double segment_sum(const float *val, int lo, int hi)
 {
-    const int l = lane_id() & 15;
-    const unsigned le = any & ((2u << l) - 1u);
-    const int dist = le ? l - (31 - __clz((int)le)) : 16;      // lanes back to the last start
-    double n;
-    n = row_fetch<EF_DPP_ROW_SHR(1), 0xf>(t);
-    t += dist >= 1 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(2), 0xf>(t);
-    t += dist >= 2 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(4), 0xf>(t);
-    t += dist >= 4 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(8), 0xf>(t);
-    t += dist >= 8 ? n : 0.0;
-    return t;
-}
-__device__ __forceinline__ double segment_scan(double t, unsigned long long any)
-{
-    const int l = lane_id();
-    const unsigned long long le = any & (~0ull >> (63 - l));
-    const int dist = le ? l - (63 - __clzll((long long)le)) : 64;
-    double n;
-    n = row_fetch<EF_DPP_ROW_SHR(1), 0xf>(t);
-    t += dist >= 1 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(2), 0xf>(t);
-    t += dist >= 2 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(4), 0xf>(t);
-    t += dist >= 4 ? n : 0.0;
-    n = row_fetch<EF_DPP_ROW_SHR(8), 0xf>(t);
-    t += dist >= 8 ? n : 0.0;
-    n = row_fetch<EF_DPP_BCAST15, 0xa>(t);          // rows 1 and 3 take in the row below whole
-    t += dist > (l & 15) ? n : 0.0;
-    n = row_fetch<EF_DPP_BCAST31, 0xc>(t);          // the upper half takes in the lower
-    t += dist > (l & 31) ? n : 0.0;
-    return t;
-}
-__device__ __forceinline__ double wave_shift(double t) { return row_fetch<EF_DPP_WAVE_SHR1, 0xf>(t); }
-__device__ __forceinline__ double read_lane(double v, int lane)             // lane: the same in all lanes
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    if (hi - lo > SMALL_SEG) return wave_sum(ordered_sum<64>(val, lo + lane_id(), hi, 0.0));
+    return ordered_sum<1>(val, lo, hi, 0.0);        // one address for all lanes: one access
 }
 
 // Workgroup sum in a fixed order; every thread gets the same bits.
@@ -819,9 +788,8 @@ __device__ __forceinline__ TilePlace tile_place(const Layout &L, const TileRec &
 // closed segments; partial sums of the (at most two) open segments posted, and
 // their residuals finished too where the block's scale forms inside this kernel
 // (bounded waits), else their elements stored as p for the kernel that ends the
-// call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of Algorithm 4.)  The segmented scan of the kernels for
-// small launches was measured here too: 25 M elements in blocks of 33, worker call with 7 workers 600 us
-// against 618, but the server's 112 against 98, and in blocks of 5 both twice as slow.
+// call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of Algorithm 4.)  The sums are those of
+// segment_sum, short segments a thread each.
 __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
                                                uint64_t *signs, float *scales_out, float *err_tile,
                                                const Scratch &X, int set, TileShared &S)
@@ -1013,9 +981,9 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
 
 // A tile where at most FEW_SEGS blocks meet, or the ragged end of the vector, taken among the whole tiles: the
 // ends of large blocks with the small ones between them (weights, then biases and norms), which is what
-// the mixed tiles of a network's layout are.  The segments are summed one after the other, every thread's
-// elements masked by the segment's range, in the registers the whole tiles need anyway and without LDS
-// arrays; an open segment waits for its block's scale like a whole tile does.  (Mixed tiles at the head of the
+// the mixed tiles of a network's layout are.  The segments are summed from LDS, a wavefront each, and
+// corrected in the registers the whole tiles need anyway, every thread's elements masked by the segment's range;
+// an open segment waits for its block's scale like a whole tile does.  (Mixed tiles at the head of the
 // grid, with the segment code for any number of segments, cost the kernel registers, its first
 // workgroups 20 us, and the segments of blocks with whole tiles a pass of their own in the kernel that
 // ends the call: 25 M elements in blocks of 64 tiles and 7 elements, server call with 7 workers 65 us
@@ -1024,6 +992,7 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
 struct FewShared {
     int bound[FEW_SEGS + 1];
     float scale[FEW_SEGS];      // of the segments; 0 leaves p as it is
+    double sum[FEW_SEGS];
 };
 // Called by the whole workgroup early; a barrier comes before the first use.
 __device__ __forceinline__ void few_bounds(const Layout &L, const TileRec &T, int64_t tile_start, int n_valid, int *bound)
@@ -1040,45 +1009,33 @@ __device__ __forceinline__ bool few_touches(int k, int lo, int hi)
     const int first = (int)uniform_u32(threadIdx.x >> 6) * 1024 + k * 256;
     return first < hi && first + 256 > lo;
 }
-__device__ __forceinline__ double abs_sum_range(const float4 (&p)[SUBROWS], int lo, int hi)
-{
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < SUBROWS; ++k) {
-        if (!few_touches(k, lo, hi)) continue;
-        const int j = local_base(k) - lo;
-        const unsigned n = (unsigned)(hi - lo);
-        const float a[4] = {fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w)};
-        double row = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) row += (unsigned)(j + c) < n ? (double)a[c] : 0.0;
-        acc += row;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return acc;
-}
+// val: TILE floats of LDS.
 __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
                                              uint64_t *signs, float *scales_out, float *err_tile, const Scratch &X, int set,
-                                             SyncShared &S, FewShared &F)
+                                             SyncShared &S, FewShared &F, float *val)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
     const int nseg = T.nseg;
     const BlockSpan hs = span_of(T.bs(), T.be());
     const bool head_open = hs.bs < tile_start || hs.be > tile_start + TILE, tail_open = T.tail != 0;
     store_signs(p, n_valid, signs, tile_start, L.W);
-    __syncthreads();                // the bounds are there
+#pragma unroll
+    for (int k = 0; k < SUBROWS; ++k)
+        *reinterpret_cast<float4 *>(val + local_base(k)) = make_float4(fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w));
+    __syncthreads();                // that, and the bounds
 #pragma unroll 1
-    for (int i = 0; i < nseg; ++i) {
-        // the first segment, the last, then those between: what others may wait for goes out first
-        const int sg = i == 0 ? 0 : i == 1 ? nseg - 1 : i - 1;
-        const int lo = few_bound(F.bound, sg), hi = few_bound(F.bound, sg + 1);
-        const double total = block_sum(abs_sum_range(p, lo, hi), S.red);
-        if (sg == 0 && head_open) {
-            store_partial(total, 0, tile, L, X, set);
-        } else if (sg == nseg - 1 && tail_open) {
-            store_partial(total, 1, tile, L, X, set);
-        } else if (threadIdx.x == 0) {
-            const float s = (float)(total / (double)(hi - lo));
+    for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < nseg; sg += NWAVES) {
+        const double total = segment_sum(val, few_bound(F.bound, sg), few_bound(F.bound, sg + 1));
+        if (lane_id() == 0) F.sum[sg] = total;
+    }
+    __syncthreads();
+    // what others may wait for goes out first
+    if (head_open) store_partial(F.sum[0], 0, tile, L, X, set);
+    if (tail_open) store_partial(F.sum[nseg - 1], 1, tile, L, X, set);
+    if ((int)threadIdx.x < nseg) {
+        const int sg = (int)threadIdx.x;
+        if (!(sg == 0 && head_open) && !(sg == nseg - 1 && tail_open)) {
+            const float s = (float)(F.sum[sg] / (double)(F.bound[sg + 1] - F.bound[sg]));
             scales_out[T.fb + sg] = s;
             F.scale[sg] = s;
         }

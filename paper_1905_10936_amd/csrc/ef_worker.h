@@ -353,6 +353,13 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         }
     } else if constexpr (MIXED) {
         __shared__ FewShared F;
+        float *val;
+        if constexpr (QUAL) {
+            val = S.val;            // quality_of_tile is done with it before
+        } else {
+            __shared__ __align__(16) float few_val[TILE];
+            val = few_val;
+        }
         few_bounds(L, T, tile_start, n_valid, F.bound);
         load_tile(g, gv, n_valid);
         if (MOM) load_tile(m, mv, n_valid);
@@ -365,7 +372,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
             quality_of_tile(a, L, Q, tile, worker, n_valid, S);
         }
-        compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F);
+        compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, val);
     }
     snapshot_call(R);
 }
