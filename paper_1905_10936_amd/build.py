@@ -16,7 +16,7 @@ TARGETS = {
                                            "ef_quality.h", "ef_small.h", "ef_layout.h")] +
           [os.path.join(ROOT, "include", h) for h in ("ef.h", "ef_debug.h")]),
     BENCH_LIB: (os.path.join(CSRC, "ef_bench.hip"),
-                [os.path.join(CSRC, h) for h in ("ef_tile.h", "ef_probe.h")] +
+                [os.path.join(CSRC, h) for h in ("ef_tile.h", "ef_layout.h", "ef_probe.h")] +
                 [os.path.join(ROOT, "include", h) for h in ("ef.h", "ef_bench.h")]),
 }
 

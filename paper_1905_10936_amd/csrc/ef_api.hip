@@ -66,9 +66,8 @@ struct ef_plan {
     unsigned long long *d_fin_list;
     int32_t *d_mixed;               // tile lists
     int32_t *d_whole;
-    ef::TileRec *d_tiles, *d_in_order;
+    ef::TileRec *d_tiles, *d_in_order, *d_mixed_recs;
     ef::StartWord *d_words;         // [n_mixed][TILE_WORDS]
-    int32_t *d_dense;
     std::vector<char> dense_host;   // [ntiles] is the tile a dense one?
     // compressor-quality diagnostics
     int32_t *d_cross;               // blocks that span several tiles
@@ -262,9 +261,9 @@ int device_facts(int device, DeviceFacts *out)
         int small_s = 0;
         EF_HIP(hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, device));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, false, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<false, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<true, true>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, ef::ALL_WHOLE, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<ef::ALL_WHOLE, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::DENSE_TILES, true>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
         if (small_s < f.small) f.small = small_s;
@@ -496,7 +495,13 @@ int build_device(ef_plan *p)
     // that a block without whole tiles shares with it, so that such a block is finished in one kernel.
     std::vector<int32_t> dense;
     p->dense_host.assign((size_t)ntiles, 0);
-    for (int32_t t : mixed) p->dense_host[(size_t)t] = tiles[(size_t)t].nseg > ef::FEW_SEGS;
+    int64_t between = 0;
+    for (int32_t t : mixed) {
+        const int n = tiles[(size_t)t].nseg;
+        between += n > ef::few_segments(p->max_workers) && n <= ef::FEW_SEGS;
+    }
+    const int few = ef::few_segments(p->max_workers, ntiles, between);
+    for (int32_t t : mixed) p->dense_host[(size_t)t] = tiles[(size_t)t].nseg > few;
     auto joined = [&](int32_t t) {              // does a block without whole tiles go from tile t into t + 1?
         const int64_t b = lb[t];
         return t + 1 < ntiles && fb[t + 1] == b && tiles_of_block(p, b) == 2 && !has_uniform_tile(p, b);
@@ -505,19 +510,27 @@ int build_device(ef_plan *p)
         if (p->dense_host[(size_t)t] && joined(t)) p->dense_host[(size_t)t + 1] = 1;
     for (int32_t t = ntiles - 1; t > 0; --t)
         if (p->dense_host[(size_t)t] && joined(t - 1)) p->dense_host[(size_t)t - 1] = 1;
+    // Without whole tiles the layout runs one kernel, by the majority.
+    if (whole.empty()) {
+        int32_t n = 0;
+        for (int32_t t : mixed) n += p->dense_host[(size_t)t];
+        if (2 * n >= ntiles) p->dense_host.assign((size_t)ntiles, 1);
+    }
     for (int32_t t : mixed)
         if (p->dense_host[(size_t)t]) {
             tiles[(size_t)t].nseg = -tiles[(size_t)t].nseg;
             dense.push_back(t);
         }
     p->L.n_dense = (int32_t)dense.size();
-    p->L.n_grid = ntiles - p->L.n_dense;
+    p->L.n_grid = ntiles;
     // The order in which the kernels with one workgroup per tile take the tiles: ascending, but a mixed tile FEW_LEAD
     // places ahead of where it is (or, if a block with whole tiles ends in it, of that block's first): it takes
     // longer than a whole tile, and its blocks wait for it, as the call does at its end.
-    std::vector<ef::TileRec> in_order;
+    std::vector<ef::TileRec> in_order, mixed_recs;
+    for (int32_t t : mixed) mixed_recs.push_back(tiles[(size_t)t]);
     if (!mixed.empty()) {
         in_order.reserve((size_t)ntiles);
+        for (int32_t t : dense) in_order.push_back(tiles[(size_t)t]);
         size_t w = 0;
         for (int32_t t : mixed) {
             const ef::TileRec &r = tiles[(size_t)t];
@@ -551,7 +564,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_tiles, nt, Arena::COPY, tiles.data());
     mem.add(&p->d_in_order, in_order.size(), Arena::COPY, in_order.data());
     mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
-    mem.add(&p->d_dense, dense.size(), Arena::COPY, dense.data());
+    mem.add(&p->d_mixed_recs, mixed_recs.size(), Arena::COPY, mixed_recs.data());
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
@@ -576,7 +589,7 @@ int build_device(ef_plan *p)
     p->L.tiles = p->d_tiles;
     p->L.grid_tiles = p->L.n_mixed ? p->d_in_order : p->d_tiles;
     p->L.words = p->d_words;
-    p->L.dense_tiles = p->d_dense;
+    p->L.mixed_recs = p->d_mixed_recs;
     p->L.offs = p->d_offs;
     p->L.tile_fb = p->d_tile_fb;
     p->L.tile_lb = p->d_tile_lb;
@@ -1097,11 +1110,9 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         if (plan->L.n_mixed) {
             const dim3 grid((unsigned)plan->L.n_mixed, (unsigned)n_workers);
             if (has_mom)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs(),
-                                   (const int32_t *)plan->d_mixed);
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
             else
-                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs(),
-                                   (const int32_t *)plan->d_mixed);
+                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
             EF_HIP(hipGetLastError());
         }
         int64_t wgs = (int64_t)plan->L.n_uniform * n_workers;
@@ -1115,35 +1126,34 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     } else {
         // every tile in one launch
         const dim3 grid((unsigned)plan->L.n_grid, (unsigned)n_workers), block(ef::THREADS);
-        const bool mixed = plan->L.n_mixed != 0;
         ef::QualityArgs Q;
         Q.v = nullptr;
         Q.stride = 0;
         Q.tile_sums = plan->d_qtile;
         Q.part_sums = plan->d_qpart;
         Q.out = quality;
-        if (plan->L.n_dense) {
-            const dim3 dense((unsigned)plan->L.n_dense, (unsigned)n_workers);
+        const int kind = plan->L.n_dense ? 2 : plan->L.n_mixed ? 1 : 0;
+        if (plan->L.n_dense == plan->L.ntiles) {
             if (quality)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, true>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, true>), grid, block, 0, s, L, c.X, A, Q);
             else if (has_mom)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, block, 0, s, L, c.X, A, Q);
             else
-                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), dense, block, 0, s, L, c.X, A, Q, L.dense_tiles);
-            EF_HIP(hipGetLastError());
-        }
-        if (!plan->L.n_grid)
-            ;                           // nothing but dense tiles
-        else if (quality)
-            hipLaunchKernelGGL((ef::k_worker_tiles<true, true, true>), grid, block, 0, s, L, c.X, A, Q);
-        else if (has_mom && mixed)
-            hipLaunchKernelGGL((ef::k_worker_tiles<true, true, false>), grid, block, 0, s, L, c.X, A, Q);
+                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, block, 0, s, L, c.X, A, Q);
+        } else if (quality)
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::DENSE_TILES, true>), grid, block, 0, s, L, c.X, A, Q);
+        else if (has_mom && kind == 2)
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::DENSE_TILES, false>), grid, block, 0, s, L, c.X, A, Q);
+        else if (has_mom && kind == 1)
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::FEW_TILES, false>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom)
-            hipLaunchKernelGGL((ef::k_worker_tiles<true, false, false>), grid, block, 0, s, L, c.X, A, Q);
-        else if (mixed)
-            hipLaunchKernelGGL((ef::k_worker_tiles<false, true, false>), grid, block, 0, s, L, c.X, A, Q);
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::ALL_WHOLE, false>), grid, block, 0, s, L, c.X, A, Q);
+        else if (kind == 2)
+            hipLaunchKernelGGL((ef::k_worker_tiles<false, ef::DENSE_TILES, false>), grid, block, 0, s, L, c.X, A, Q);
+        else if (kind == 1)
+            hipLaunchKernelGGL((ef::k_worker_tiles<false, ef::FEW_TILES, false>), grid, block, 0, s, L, c.X, A, Q);
         else
-            hipLaunchKernelGGL((ef::k_worker_tiles<false, false, false>), grid, block, 0, s, L, c.X, A, Q);
+            hipLaunchKernelGGL((ef::k_worker_tiles<false, ef::ALL_WHOLE, false>), grid, block, 0, s, L, c.X, A, Q);
         EF_HIP(hipGetLastError());
     }
     int rc = launch_tail(plan, role, c, n_workers, err, state_stride, scales, scales_stride, s);
@@ -1210,23 +1220,22 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
         return EF_OK;
     }
     const ef::Layout L = role_layout(plan, ROLE_SERVER);
-    if (L.n_dense) {
-        hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_dense), dim3(ef::THREADS), 0, s, L, c.X, A, L.dense_tiles,
-                           plan->max_workers);
-        EF_HIP(hipGetLastError());
-    }
     const dim3 grid((unsigned)L.n_grid), block(ef::THREADS);
     const bool many = M > ef::SERVER_CHUNK;
-    if (!L.n_grid)
-        ;                               // nothing but dense tiles
+    if (L.n_dense == L.ntiles)
+        hipLaunchKernelGGL(ef::k_server_mixed, grid, block, 0, s, L, c.X, A, plan->max_workers);
+    else if (L.n_dense && many)
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::DENSE_TILES, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+    else if (L.n_dense)
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::DENSE_TILES, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else if (L.n_mixed && many)
-        hipLaunchKernelGGL((ef::k_server_tiles<true, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::FEW_TILES, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else if (L.n_mixed)
-        hipLaunchKernelGGL((ef::k_server_tiles<true, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::FEW_TILES, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else if (many)
-        hipLaunchKernelGGL((ef::k_server_tiles<false, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::ALL_WHOLE, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     else
-        hipLaunchKernelGGL((ef::k_server_tiles<false, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+        hipLaunchKernelGGL((ef::k_server_tiles<ef::ALL_WHOLE, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
     EF_HIP(hipGetLastError());
     return launch_tail(plan, ROLE_SERVER, c, 1, server_err, (int64_t)0, out_scales, (int64_t)0, s);
 }

@@ -1,6 +1,7 @@
 // Server kernels of libef (Algorithm 4 of arxiv 1905.10936): see ef_tile.h for the tile scheme.
 #pragma once
 #include "ef_tile.h"
+#include "ef_worker.h"
 
 namespace ef {
 
@@ -256,12 +257,12 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
 // The dense mixed tiles, before the kernel that has the others.  The residual tile is loaded after the payloads
 // have been added up, which keeps the registers down.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
-void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, const int32_t *tiles, int set)
+void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, int set)
 {
     const Scratch X = open_call(R);
     __shared__ TileShared S;
-    const int32_t tile = tiles[blockIdx.x];
-    const TileRec T = L.tiles[tile];
+    const TileRec T = L.mixed_recs[blockIdx.x];
+    const int32_t tile = T.tile;
     const int n_valid = tile_valid(L, tile);
     float *te = A.err + (int64_t)tile * TILE;
     float4 p[SUBROWS];
@@ -384,13 +385,21 @@ __device__ __forceinline__ void server_values_few(const Layout &L, const ServerA
 // worker-payload set of the ResNet-50 layout, 7 workers: 80 us against 66 at seven and 67 at six; 354 M
 // elements in transformer blocks, 16 workers: 1180 us against 1017 and 1047).
 // MANY: more than SERVER_CHUNK workers.
-template <bool MIXED, bool MANY>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED || MANY ? 7 : 8, 8)))
+template <bool SEGMENTS>
+struct ServerShared : SyncShared {
+    float val[SERVER_LDS];
+};
+template <>
+struct ServerShared<true> : TileShared {};
+static_assert(SERVER_LDS <= TILE, "one array for the sum tables and for the segments");
+
+template <int TILES, bool MANY>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TILES == DENSE_TILES ? 6 : TILES == FEW_TILES || MANY ? 7 : 8, 8)))
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
-    __shared__ SyncShared S;
-    __shared__ __align__(16) float lds[MIXED ? TILE : SERVER_LDS];
-    static_assert(SERVER_LDS <= TILE, "one array for the sum tables and for compress_few");
+    constexpr bool MIXED = TILES != ALL_WHOLE;
+    __shared__ __align__(16) ServerShared<MIXED> S;
+    float *lds = S.val;
     float4 tv[SUBROWS], p[SUBROWS];
     if (!MIXED) {
         // tile i is workgroup i's: its residual is asked for before anything is looked up
@@ -414,6 +423,12 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         resolve_posted(P, L, X, set, A.scales, S);
         if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
     } else if constexpr (MIXED) {
+        if (TILES == DENSE_TILES && T.nseg < 0) {
+            server_values_mixed(L, A, tile, T, n_valid, te, p, S);
+            compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
+            snapshot_call(R);
+            return;
+        }
         __shared__ FewShared F;
         few_bounds(L, T, tile_start, n_valid, F.bound);
         server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);

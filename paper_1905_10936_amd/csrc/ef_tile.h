@@ -63,6 +63,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ef_layout.h"
+
 namespace ef {
 
 constexpr int TILE = 4096;      // elements per workgroup and step
@@ -72,10 +74,6 @@ constexpr int SUBROWS = 4;      // float4 per thread
 constexpr int SMALL_SEG = 64;   // segments up to this length are summed by one thread
 constexpr int MAX_LONG = TILE / SMALL_SEG;
 constexpr int TILE_WORDS = TILE / 32;
-// Most segments of a tile that is taken among the whole ones (see compress_few).  Its cost grows with them: 25 M
-// elements, server call with 7 workers, few-segment tiles against dense ones: blocks of 3000 62 us / 102,
-// of 1024 (5 segments) 84 / 96, of 600 (8 segments) 105 / 98.
-constexpr int FEW_SEGS = 6;
 constexpr int DEFER_WGS = 16;   // workgroups that serve the run-time lists in the kernel that ends a call
 constexpr int FIN_WGS_MAX = 512;    // most workgroups that kernel gives to the scales of blocks larger than fuse_limit ...
 constexpr int RES_WGS_MAX = 2048;   // ... and to the segments whose p was parked
@@ -119,13 +117,13 @@ struct Layout {
     const int32_t *tile_fb;     // [ntiles] block holding the tile's first element
     const int32_t *tile_lb;     // [ntiles] block holding the tile's last valid element
     const int32_t *mixed_tiles;   // [n_mixed] ascending
+    const TileRec *mixed_recs;    // [n_mixed] the same
     const int32_t *whole_tiles;   // [n_uniform] ascending
     const TileRec *tiles;         // [ntiles]
     int32_t n_grid;
-    const TileRec *grid_tiles;    // [n_grid] all but the dense ones, as the kernels with one workgroup per tile take them
+    const TileRec *grid_tiles;    // [n_grid] as the kernels with one workgroup per tile take them: the dense ones first
     const StartWord *words;       // [n_mixed][TILE_WORDS]
-    int32_t n_dense;
-    const int32_t *dense_tiles;   // [n_dense] the mixed tiles of many segments, ascending
+    int32_t n_dense;              // mixed tiles of many segments
     // Deferred correction (see Scratch::lazy_scales): on or off, and for every block its position
     // among the blocks larger than fuse_limit (-1 for the others).
     int32_t lazy;
@@ -378,11 +376,21 @@ __device__ __forceinline__ double ordered_sum(const float *val, int j, int hi, d
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc += (double)v[q];
     }
-    float v[7];
+    if (j + 3 * STEP < hi) {
+        float v[4];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = val[min(j + q * STEP, hi - 1)];
+        for (int q = 0; q < 4; ++q) v[q] = val[j + q * STEP];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) acc += (double)(j + q * STEP < hi ? v[q] : 0.f);
+        for (int q = 0; q < 4; ++q) acc += (double)v[q];
+        j += 4 * STEP;
+    }
+    if (j < hi) {
+        float v[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] = val[min(j + q * STEP, hi - 1)];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) acc += (double)(j + q * STEP < hi ? v[q] : 0.f);
+    }
     return acc;
 }
 
@@ -817,7 +825,7 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
             S.long_list[atomicAdd(&S.n_long, 1)] = sg;
             continue;
         }
-        double acc = 0.0;
+        double acc = 0.0;               // most are a few elements: ordered_sum's groups of eight cost more than they hide
         for (int j = lo; j < hi; ++j) acc += (double)S.val[j];
         const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
         if (open) {
@@ -836,9 +844,7 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
         const int64_t bs = L.offs[b], be = L.offs[b + 1];
         const int lo = (int)max(bs - tile_start, (int64_t)0);
         const int hi = (int)min(be - tile_start, (int64_t)n_valid);
-        double acc = 0.0;
-        for (int j = lo + lane_id(); j < hi; j += 64) acc += (double)S.val[j];
-        acc = wave_sum(acc);
+        const double acc = wave_sum(ordered_sum<64>(S.val, lo + lane_id(), hi, 0.0));
         const bool open = (sg == 0 && head_open) || (sg == nseg - 1 && tail_open);
         if (open) {
             if (lane_id() == 0) S.open_sum[sg == 0 ? 0 : 1] = acc;

@@ -43,12 +43,12 @@ __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4
 // QUAL: see k_worker_tiles.
 template <bool MOM, bool QUAL>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
-void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q, const int32_t *tiles)
+void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
     const Scratch X = open_call(R);
     __shared__ TileShared S;
-    const int32_t tile = tiles[blockIdx.x];
-    const TileRec T = L.tiles[tile];
+    const TileRec T = L.mixed_recs[blockIdx.x];
+    const int32_t tile = T.tile;
     const int worker = blockIdx.y;
     const int n_valid = tile_valid(L, tile);
     const int64_t tile_start = (int64_t)tile * TILE;
@@ -286,7 +286,8 @@ void k_worker_uniform(Layout L, ScratchRef R, WorkerArgs A, int n_workers)
 // Eight workgroups per CU (64 VGPRs, a few spilled): the one-pass limit is half of what is
 // resident, and 2048 resident workgroups let blocks of up to 1024 tiles (4 Mi elements) finish
 // in one pass (measured: 27.1 -> 24.4 ms on the transformer-like layout, no change elsewhere).
-template <bool QUAL>
+enum { ALL_WHOLE = 0, FEW_TILES = 1, DENSE_TILES = 2 };
+template <bool SEGMENTS>
 struct TilesShared {
     typedef SyncShared type;
 };
@@ -297,11 +298,12 @@ struct TilesShared<true> {
 
 // QUAL = true: the compressor-quality sums of p (Section 3.2: Proposition 1's phi, Eq. (1)'s delta)
 // are taken on the way, from the values the kernel holds anyway (see ef_quality.h).
-template <bool MOM, bool MIXED, bool QUAL>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MIXED ? 7 : 8, 8)))
+template <bool MOM, int TILES, bool QUAL>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8, 8)))
 void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
-    __shared__ typename TilesShared<QUAL>::type S;
+    constexpr bool MIXED = TILES != ALL_WHOLE;
+    __shared__ typename TilesShared<MIXED || QUAL>::type S;
     const int worker = blockIdx.y;
     const float *g = A.grad + (int64_t)worker * A.grad_stride;
     float *m = MOM ? A.mom + (int64_t)worker * A.state_stride : nullptr;
@@ -353,14 +355,8 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         }
     } else if constexpr (MIXED) {
         __shared__ FewShared F;
-        float *val;
-        if constexpr (QUAL) {
-            val = S.val;            // quality_of_tile is done with it before
-        } else {
-            __shared__ __align__(16) float few_val[TILE];
-            val = few_val;
-        }
-        few_bounds(L, T, tile_start, n_valid, F.bound);
+        const bool dense = TILES == DENSE_TILES && T.nseg < 0;
+        if (!dense) few_bounds(L, T, tile_start, n_valid, F.bound);
         load_tile(g, gv, n_valid);
         if (MOM) load_tile(m, mv, n_valid);
         load_tile(e, pv, n_valid);
@@ -372,7 +368,10 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
             quality_of_tile(a, L, Q, tile, worker, n_valid, S);
         }
-        compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, val);
+        if (dense)
+            compress_mixed(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S);
+        else
+            compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, S.val);
     }
     snapshot_call(R);
 }

@@ -21,6 +21,16 @@ int main()
         REQUIRE(span >= 1 && 2 * span <= resident && span <= ef::SMALL_SPAN);
     }
     REQUIRE(ef::small_span(512) == ef::SMALL_SPAN);
+
+    // no tile of more segments than compress_few has room for is taken as one of few; rare ones up to that are
+    for (int workers : {1, 8, 9, 64})
+        for (int64_t tiles : {1, 16, 1000})
+            for (int64_t between : {0, 1, 60, 63, 1000}) {
+                const int few = ef::few_segments(workers, tiles, between);
+                REQUIRE(few <= ef::FEW_SEGS && few >= ef::few_segments(workers));
+                REQUIRE((few == ef::FEW_SEGS) == (16 * between <= tiles));
+            }
+    REQUIRE(ef::few_segments(8) == 6 && ef::few_segments(9) == 5);
     std::puts("layout rules ok");
     return 0;
 }
