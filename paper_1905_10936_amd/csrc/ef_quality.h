@@ -162,7 +162,8 @@ __global__ __launch_bounds__(THREADS) void k_quality_tiles(Layout L, QualityArgs
     const int vec = blockIdx.y;
     const int n_valid = tile_valid(L, tile);
     float4 a[SUBROWS];
-    load_tile(Q.v + (int64_t)vec * Q.stride + (int64_t)tile * TILE, a, n_valid);     // elements past d read as 0
+    load_tile(Q.v + (int64_t)vec * Q.stride + (int64_t)tile * TILE, a, n_valid);
+    clear_past_end(a, n_valid);
     quality_of_tile(a, L, Q, tile, vec, n_valid, S);
 }
 

@@ -381,11 +381,11 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     }
     __syncthreads();
     const int park_head = S.parked[0], park_tail = S.parked[1];
-    int seg = whole ? 0 : at.seg;
+    int seg = at.seg;
     float v[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        seg += (int)((at.starts >> c) & 1u);     // a whole tile has no start bits
+        seg += (int)((at.starts >> c) & 1u);
         const float e = residual(v[c], S.scale[seg]);
         const bool keep = (park_head && seg == 0) || (park_tail && seg == T.nseg - 1);
         v[c] = keep ? v[c] : e;
@@ -418,9 +418,9 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
     const float4 g = small_load4(A.grad + (int64_t)worker * A.grad_stride + start, n_valid);
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
-    SmallPlace at = {0u, -1};
+    SmallPlace at = {0u, 0};         // one segment
     int64_t bs = 0, be = 1;
-    if (T.words >= 0) at = small_place(L, T);
+    if (T.nseg > 1) at = small_place(L, T);
     if ((int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
         be = L.offs[T.fb + threadIdx.x + 1];
@@ -444,16 +444,16 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
     const int64_t start = (int64_t)tile * TILE;
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
-    SmallPlace at = {0u, -1};
+    SmallPlace at = {0u, 0};         // one segment
     int64_t bs = 0, be = 1;
-    if (T.words >= 0) at = small_place(L, T);
+    if (T.nseg > 1) at = small_place(L, T);
     if ((int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
         be = L.offs[T.fb + threadIdx.x + 1];
     }
     int seg[4];
     {
-        int sg = T.words >= 0 ? at.seg : 0;
+        int sg = at.seg;
 #pragma unroll
         for (int c = 0; c < 4; ++c) seg[c] = sg += (int)((at.starts >> c) & 1u);
     }
@@ -504,8 +504,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallAr
     const uint32_t word = hw < 2 * L.W ? s32[hw] : 0u;
     float4 m4 = x4;
     if (WD) m4 = small_load4(mt + start, n_valid);
-    SmallPlace at = {0u, 0};
-    if (T.words >= 0) at = small_place(L, T);
+    SmallPlace at = {0u, 0};         // one segment
+    if (T.nseg > 1) at = small_place(L, T);
     float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
     int seg = at.seg;
 #pragma unroll

@@ -61,6 +61,7 @@ void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     worker_values<MOM>(gv, mv, pv, A.mu, A.r);
     if (MOM) store_tile(m, mv, n_valid);
     if constexpr (QUAL) {
+        clear_past_end(pv, n_valid);
         float4 a[SUBROWS];
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];
@@ -363,6 +364,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         worker_values<MOM>(gv, mv, pv, A.mu, A.r);
         if (MOM) store_tile(m, mv, n_valid);
         if constexpr (QUAL) {
+            clear_past_end(pv, n_valid);
             float4 a[SUBROWS];
 #pragma unroll
             for (int k = 0; k < SUBROWS; ++k) a[k] = pv[k];

@@ -37,8 +37,10 @@ def test_which_calls_are_small_ones():
     assert plan.small_calls(4) == EVERY
     state.close()
     # more workgroups than twice what is resident; a block that is too long
-    assert ef.ef_plan_create(_offs([30000] * 100), 16).small_calls(16) == {"server", "update"}
+    assert ef.ef_plan_create(_offs([30000] * 60), 16).small_calls(16) == {"server", "update"}
     assert ef.ef_plan_create(_offs([257 * T]), 1).small_calls(1) == set()
+    assert ef.ef_plan_create(_offs([200 * T, 200 * T, 112 * T]), 1).small_calls(1) == EVERY
+    assert ef.ef_plan_create(_offs([200 * T, 200 * T, 112 * T, 1]), 1).small_calls(1) == {"worker", "server"}
 
 
 @pytest.mark.parametrize("route", ROUTES)
