@@ -104,10 +104,6 @@ namespace {
 enum { ROLE_TICKET = 0, ROLE_SERVER = 1, ROLE_TILES = 2 };
 
 constexpr int MAX_DEVICES = 64;
-// Places a mixed tile is taken ahead of its own (see build_device).  Measured on the ResNet-50 layout (server, 7
-// workers) and on blocks of 64 tiles and 7 elements (worker, 7 workers): 0 60.4 / 590 us, 128 57.1 / 590, 256 54.9 /
-// 592, 512 53.6 / 596, 1024 56.9 / 607: far ahead, its slot is lost to the tiles it waits for.
-constexpr int FEW_LEAD = 256;
 std::mutex g_scratch_mutex;
 double *g_scratch_ptr[MAX_DEVICES];     // [device] address of `scratch` on that device, once looked up
 
@@ -470,10 +466,16 @@ int build_device(ef_plan *p)
     p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
     p->lim_direct = (int32_t)((int64_t)facts.cus * facts.tiles / 2);
     // Launches that (nearly) fit on the GPU all at once: up to twice what is resident.  A block's tiles are at
-    // most half of what is resident and are dispatched in order, as the other one-pass kernels assume.  Measured, worker
-    // calls in blocks of 30 000 elements, these kernels against k_worker_tiles + k_tail: 64 workgroups 7.7 /
-    // 15.7 us, 512 11.1 / 18.5, 1024 19.9 / 24.7, 2048 37.8 / 38.3; server calls with 4 workers, against
-    // k_server_tiles + k_tail: 1024 tiles 21.0 / 24.9 us, 2048 35.2 / 33.7.
+    // most half of what is resident and are dispatched in order, as the other one-pass kernels assume.  Measured, these
+    // kernels / k_worker_tiles or k_server_tiles + k_tail, us, by tiles of one worker:
+    //                                   64          512          1000
+    //   worker, blocks of 30 000       9.2 / 13.0  11.2 / 15.1  21.5 / 20.8
+    //   worker, blocks of 700          9.2 / 13.7  11.7 / 16.6  20.9 / 22.3
+    //   server, 8 workers, of 30 000   8.9 / 12.0  12.3 / 13.3  20.8 / 16.1
+    //   server, 8 workers, of 700      9.0 / 19.8  12.6 / 22.1  20.9 / 26.2
+    //   server, 8 workers, 1 to 64 elements         13.6 / -    23.2 / 33.9
+    // In the second round of workgroups the general kernels are ahead where all but a few tiles are whole, these
+    // where they are not.
     p->small_wgs = 2 * facts.cus * facts.small;
     p->small_span = ef::small_span(facts.cus * facts.small);
     std::vector<ef::SmallTile> small;
@@ -491,8 +493,8 @@ int build_device(ef_plan *p)
                             (int32_t)tiles_of_block(p, fb[t]), (int16_t)(bs % ef::TILE), (int16_t)(be % ef::TILE)};
         (one ? whole : mixed).push_back(t);
     }
-    // Which mixed tiles run in a kernel of their own: those of many segments, and with one of them every tile
-    // that a block without whole tiles shares with it, so that such a block is finished in one kernel.
+    // Which mixed tiles are dense ones: those of many segments, and with one of them every tile that a block
+    // without whole tiles shares with it, so that such a block is finished among tiles of one kind.
     std::vector<int32_t> dense;
     p->dense_host.assign((size_t)ntiles, 0);
     int64_t between = 0;
@@ -523,9 +525,12 @@ int build_device(ef_plan *p)
         }
     p->L.n_dense = (int32_t)dense.size();
     p->L.n_grid = ntiles;
-    // The order in which the kernels with one workgroup per tile take the tiles: ascending, but a mixed tile FEW_LEAD
-    // places ahead of where it is (or, if a block with whole tiles ends in it, of that block's first): it takes
-    // longer than a whole tile, and its blocks wait for it, as the call does at its end.
+    // the server's limit is that of the kernel this layout runs (2^28 elements in blocks of 1024 tiles, 8 workers:
+    // 560 us in one pass, 755 in two)
+    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[mixed.empty() ? 0 : 1] / 2);
+    // The order in which the kernels with one workgroup per tile take the tiles: the dense ones, then the others
+    // ascending, but for those of few segments (see few_place).
+    const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
     std::vector<ef::TileRec> in_order, mixed_recs;
     for (int32_t t : mixed) mixed_recs.push_back(tiles[(size_t)t]);
     if (!mixed.empty()) {
@@ -535,7 +540,7 @@ int build_device(ef_plan *p)
         for (int32_t t : mixed) {
             const ef::TileRec &r = tiles[(size_t)t];
             if (r.nseg < 0) continue;
-            const int64_t at = (r.n > 2 || (r.n == 2 && r.from == 0) ? r.t0 : t) - (int64_t)FEW_LEAD;
+            const int64_t at = ef::few_place(t, r.t0, r.n, r.from != 0, awaited);
             while (w < whole.size() && whole[w] < at) in_order.push_back(tiles[(size_t)whole[w++]]);
             in_order.push_back(r);
         }
@@ -543,9 +548,6 @@ int build_device(ef_plan *p)
     }
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
-    // the server's limit is that of the kernel this layout runs (2^28 elements in blocks of 1024 tiles, 8 workers:
-    // 560 us in one pass, 755 in two)
-    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[p->L.n_mixed ? 1 : 0] / 2);
     // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
     for (int64_t b = 0; b < B; ++b)
         if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);

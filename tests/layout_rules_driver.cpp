@@ -31,6 +31,15 @@ int main()
                 REQUIRE((few == ef::FEW_SEGS) == (16 * between <= tiles));
             }
     REQUIRE(ef::few_segments(8) == 6 && ef::few_segments(9) == 5);
+    // a tile where a block ends goes ahead of that block's whole tiles, but no further than what waits for it
+    const int limit = 1024;
+    for (int n : {1, 2, 3, 64, 1024, 1025, 12565, 300000})
+        for (bool first_shared : {false, true}) {
+            const int64_t tile = 1000000, t0 = tile - (n - 1), at = ef::few_place(tile, t0, n, first_shared, limit);
+            const bool whole = n - 1 - (first_shared ? 1 : 0) >= 1;
+            REQUIRE(at >= tile - ef::FEW_LEAD - limit);
+            REQUIRE(at == (whole && n <= limit ? t0 : tile) - ef::FEW_LEAD);
+        }
     std::puts("layout rules ok");
     return 0;
 }
