@@ -195,14 +195,20 @@ class Run:
         return ms, calls, payload
 
     def worker_kernel(self):
+        """The kernel that moves most of a worker call's bytes, as the profiler spells it."""
         w = self.w
-        mixed = bool(np.any(w.offsets[1:] % TILE != 0))
         mom = "false" if self.variant == "sgd" else "true"
+        if self.variant != "quality":
+            if "worker" in self.plan.small_calls(w.M):
+                return "ef::k_worker_small<%s>" % mom
+            if self.plan.persistent and self.variant != "sgd":
+                return "ef::k_worker_uniform<%s>" % mom
+        tiles, whole, dense = wl.tile_kinds(w.offsets, w.M)
+        if dense == tiles:
+            return "ef::k_worker_mixed<%s, %s>" % (mom, "true" if self.variant == "quality" else "false")
         if self.variant == "quality":
-            return "ef::k_worker_tiles<true, true, true>"
-        if self.plan.persistent and self.variant != "sgd":
-            return "ef::k_worker_uniform<%s>" % mom
-        return "ef::k_worker_tiles<%s, %s, false>" % (mom, "true" if mixed else "false")
+            return "ef::k_worker_tiles<true, 2, true>"
+        return "ef::k_worker_tiles<%s, %d, false>" % (mom, 2 if dense else 1 if whole < tiles else 0)
 
     def close(self):
         self.plan.close()

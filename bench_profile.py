@@ -100,17 +100,10 @@ def short(name):
 
 
 def layout_counts(w):
-    offs = w.offsets
-    ntiles = (w.d + TILE - 1) // TILE
-    import numpy as np
-    first = np.searchsorted(offs, np.arange(ntiles, dtype=np.int64) * TILE, side="right") - 1
-    last_el = np.minimum((np.arange(ntiles, dtype=np.int64) + 1) * TILE, w.d) - 1
-    last = np.searchsorted(offs, last_el, side="right") - 1
-    full = (np.arange(ntiles, dtype=np.int64) + 1) * TILE <= w.d
-    whole = (first == last) & full
-    n_whole = int(whole.sum())
+    import ef_workloads as wl
+    ntiles, n_whole, n_dense = wl.tile_kinds(w.offsets, w.M)
     el_whole = n_whole * TILE
-    return dict(ntiles=int(ntiles), n_whole=n_whole, n_mixed=int(ntiles - n_whole), el_whole=el_whole,
+    return dict(ntiles=ntiles, n_whole=n_whole, n_mixed=ntiles - n_whole, n_dense=n_dense, el_whole=el_whole,
                 el_mixed=int(w.d - el_whole))
 
 
@@ -118,19 +111,19 @@ def algorithmic(kernel, w, c):
     """Bytes one launch of `kernel` must move on workload w (what the method itself needs: state read
     once and written once, sign bits, scales); None where no simple count applies."""
     d, B, M = w.d, w.B, w.M
-    if kernel.startswith("ef::k_worker_tiles<false"):       # Algorithm 3: no momentum buffer
+    if kernel.startswith(("ef::k_worker_tiles<false", "ef::k_worker_small<false")):     # Algorithm 3: no momentum buffer
         return M * (12.125 * d + 4.0 * B)
-    if kernel.startswith("ef::k_worker_tiles"):
+    if kernel.startswith(("ef::k_worker_tiles", "ef::k_worker_small")):
         return M * (20.125 * d + 4.0 * B)
     if kernel.startswith("ef::k_worker_uniform"):
         return M * 20.125 * c["el_whole"]
-    if kernel.startswith("ef::k_worker_mixed"):
-        return M * (20.125 * c["el_mixed"] + 4.0 * B)
-    if kernel.startswith("ef::k_server_tiles"):
+    if kernel.startswith("ef::k_worker_mixed"):             # ahead of the persistent kernel, or a layout of dense tiles
+        return M * ((12.125 if kernel.startswith("ef::k_worker_mixed<false") else 20.125) * c["el_mixed"] + 4.0 * B)
+    if kernel.startswith("ef::k_server_"):                  # each of them has the whole call's tiles
         return 8.0 * d + (M + 1) * d / 8.0 + 4.0 * B * (M + 1)
-    if kernel == "ef::k_apply":
+    if kernel in ("ef::k_apply", "ef::k_apply_small<false>"):
         return 8.125 * d + 4.0 * B
-    if kernel == "ef::k_apply_wd":
+    if kernel in ("ef::k_apply_wd", "ef::k_apply_small<true>"):
         return 16.125 * d + 4.0 * B
     if kernel == "ef::k_quality_tiles":                     # one read of every vector
         return 4.0 * d * M
@@ -173,8 +166,8 @@ def summarize(workload, lazy):
     lines = ["# rocprofv3 summary: %s%s%s (d = %d, B = %d, M = %d), MI355X" %
              (workload, ", deferred-correction mode" if lazy else "",
               "" if VARIANT == "sgdm" else ", bench.py --variant " + VARIANT, w.d, w.B, w.M), "",
-             "Layout: %d tiles of 4096 elements, %d whole (inside one block), %d mixed.  Measured at commit %s."
-             % (c["ntiles"], c["n_whole"], c["n_mixed"], meta.get("commit")),
+             "Layout: %d tiles of 4096 elements, %d whole (inside one block), %d mixed, %d of them dense.  Measured at commit %s."
+             % (c["ntiles"], c["n_whole"], c["n_mixed"], c["n_dense"], meta.get("commit")),
              "Commands (from /tmp with TMPDIR=/tmp; `python bench_profile.py collect %s%s%s` runs them):" %
              (workload, " --lazy" if lazy else "", "" if VARIANT == "sgdm" else " --variant " + VARIANT), ""]
     lines += ["    " + " ".join(cmd).replace(ROOT, "$R") for cmd in cmds]

@@ -235,3 +235,25 @@ WORKLOADS = {
 
 def get(name):
     return WORKLOADS[name]()
+
+
+TILE = 4096                     # elements per workgroup and step (csrc/ef_tile.h)
+
+
+def tile_kinds(offsets, max_workers):
+    """(tiles, whole ones, dense ones) of a layout, by the rules of csrc/ef_layout.h and plan creation: a mixed tile of
+    many segments is dense, and a layout without whole tiles goes by the majority.  (Tiles that a dense one takes
+    with it through a block of two tiles are not counted.)"""
+    offsets = np.asarray(offsets, dtype=np.int64)
+    d = int(offsets[-1])
+    n = (d + TILE - 1) // TILE
+    first = np.arange(n, dtype=np.int64) * TILE
+    last = np.minimum(first + TILE, d) - 1
+    nseg = np.searchsorted(offsets, last, side="right") - np.searchsorted(offsets, first, side="right") + 1
+    whole = (nseg == 1) & (first + TILE <= d)
+    base = 5 if max_workers > 8 else 6
+    few = 16 if 16 * int(((nseg > base) & (nseg <= 16) & ~whole).sum()) <= n else base
+    dense = nseg > few
+    if not whole.any() and 2 * int(dense.sum()) >= n:
+        dense[:] = True
+    return n, int(whole.sum()), int(dense.sum())
