@@ -254,8 +254,8 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
     }
 }
 
-// The dense mixed tiles, before the kernel that has the others.  The residual tile is loaded after the payloads
-// have been added up, which keeps the registers down.
+// Layouts of dense tiles alone (33-element blocks, 25 M elements, 7 workers: 95 us, 118 with the whole tiles' code in
+// the kernel).  The residual tile is loaded after the payloads have been added up, which keeps the registers down.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, int set)
 {
@@ -375,15 +375,13 @@ __device__ __forceinline__ void server_values_few(const Layout &L, const ServerA
     }
 }
 
-// Server part of Algorithm 4, all tiles in one launch, one workgroup per tile in ascending order (see k_worker_tiles).  p~ as above, then
-// compressed like a worker's p; the workgroup of a whole tile waits in the kernel for its
-// block's scale.
-// MIXED = false: the layout has only whole tiles, and the code for the others is left out.
-// Bound by HBM and, where blocks wait for their scale, by the workgroups resident meanwhile.  Layouts of
-// whole tiles run eight workgroups per CU (64 VGPRs, 2^28 elements, 8 workers, blocks of 2^20: 457 us against
-// 465 at seven and 491 at six), the others seven: at eight the mixed tiles spill 39 registers (one
-// worker-payload set of the ResNet-50 layout, 7 workers: 80 us against 66 at seven and 67 at six; 354 M
-// elements in transformer blocks, 16 workers: 1180 us against 1017 and 1047).
+// Server part of Algorithm 4, all tiles in one launch, one workgroup per tile, in the order of k_worker_tiles.  p~ as
+// above, then compressed like a worker's p; the workgroup of a whole tile waits in the kernel for its block's scale.
+// Bound by HBM and, where blocks wait for their scale, by the workgroups resident meanwhile.  Workgroups per CU:
+//   whole tiles only    eight (64 VGPRs; 2^28 elements, 8 workers, blocks of 2^20: 457 us against 465 at seven, 491 at six)
+//   tiles of few segments, or MANY    seven (68 VGPRs, none spilled; with the dense tiles' code at eight 39 are)
+//   dense tiles         six (80 VGPRs; 643 965 tiny blocks, 2 workers: 46.3 us against 49.4 at seven, where 6 spill;
+//                       16 workers, 300 000: 51.0 against 52.8)
 // MANY: more than SERVER_CHUNK workers.
 template <bool SEGMENTS>
 struct ServerShared : SyncShared {

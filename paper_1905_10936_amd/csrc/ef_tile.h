@@ -42,13 +42,13 @@
 //   * the others look at the ready word when they come to write the tile.
 // The kernels that run one workgroup per tile take the mixed tiles of a few
 // segments in their place among the whole ones, and their open segments wait like
-// whole tiles do.  The "dense" ones, of many segments, and before the persistent
-// worker kernel all mixed tiles, run in a kernel of their own ahead of the whole
-// tiles, so their partial sums are there when a block's last whole tile comes to form the
-// scale; there they never wait for a whole tile: a block without whole tiles is
-// finished among the mixed tiles themselves (its last tile forms its scale, the
+// whole tiles do.  The "dense" ones, of many segments, come first in their grid, and before the
+// persistent worker kernel all mixed tiles run in a kernel of their own,
+// so their partial sums are there when a block's last whole tile comes to form the
+// scale; they never wait for a whole tile: a block without whole tiles is
+// finished among them (its last tile forms its scale, the
 // others wait for it), while the segments that a block with whole tiles has in
-// mixed tiles get p parked in the residual buffer.  Parked p (those segments, all
+// them get p parked in the residual buffer.  Parked p (those segments, all
 // tiles of blocks larger than fuse_limit, any tile whose bounded wait ran out) is finished by one kernel
 // after the main one, which also computes the scales still missing and steps
 // the plan to its next call.
@@ -91,7 +91,7 @@ constexpr int FUSE_LIMIT_MAX = 4096;                     // most tiles a one-pas
 struct alignas(32) TileRec {
     int32_t tile;
     int32_t fb;                 // first block
-    int32_t nseg;               // segments; < 0: that many, and they run in the dense tiles' own kernel
+    int32_t nseg;               // segments; < 0: that many, and the tile is a dense one
     int32_t words;              // < 0: a whole tile; else which set of start words (its place among the mixed tiles)
     int32_t tail;               // 0, or, if the last of several segments goes on past the tile: its block's tiles * 2,
                                 // + 1 if the block ends inside its last tile
@@ -839,7 +839,7 @@ __device__ __forceinline__ TilePlace tile_place(const Layout &L, const TileRec &
     }
     return q;
 }
-// Mixed tile of any number of segments, in the kernels that come before the one with the whole tiles: sign
+// Mixed tile of any number of segments, among the dense ones or ahead of the persistent kernel: sign
 // words; segmented fp64 sums through LDS; scales and residuals e' = p - Delta of the
 // closed segments; partial sums of the (at most two) open segments posted, and
 // their residuals finished too where the block's scale forms inside this kernel
@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void finish_uniform(float4 (&p)[SUBROWS], int32_t til
 // grid, with the segment code for any number of segments, cost the kernel registers, its first
 // workgroups 20 us, and the segments of blocks with whole tiles a pass of their own in the kernel that
 // ends the call: 25 M elements in blocks of 64 tiles and 7 elements, server call with 7 workers 65 us
-// against 48 for blocks of 64 tiles; 53 now.  Momentum-free worker in blocks of 30 011: 88 -> 67 us.)
+// against 48 for blocks of 64 tiles; 53 now.  Momentum-free worker in blocks of 30 011: 88 -> 66 us.)
 // bound[i]: local index of the end of segment i-1 = start of segment i, in LDS.
 struct FewShared {
     int bound[FEW_SEGS + 1];

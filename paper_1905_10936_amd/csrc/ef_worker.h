@@ -38,8 +38,8 @@ __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4
     for (int k = 0; k < SUBROWS; ++k) worker_values4<MOM>(g[k], m[k], e[k], mu, r);
 }
 
-// Mixed tiles (those of `tiles`) of all workers, one workgroup per (tile, worker).  Runs before the kernel that
-// has the whole tiles.  Bound by its chain of latencies where there are few of them, else by HBM.
+// Mixed tiles of all workers, one workgroup per (tile, worker): ahead of the persistent kernel, and layouts that have
+// no others than dense ones.  Bound by its chain of latencies where there are few of them, else by HBM.
 // QUAL: see k_worker_tiles.
 template <bool MOM, bool QUAL>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
@@ -277,17 +277,20 @@ void k_worker_uniform(Layout L, ScratchRef R, WorkerArgs A, int n_workers)
     snapshot_call(R);
 }
 
-// All tiles of all workers but the dense ones in one launch, one workgroup per (tile, worker), in ascending order,
-// mixed tiles among the others.  A whole tile goes through the steps of the persistent kernel without the pipeline: the
-// workgroup waits in place for its block's scale; the momentum tile is written at once, the residual tile
-// when the scale is there, so the tiles of a block write their residuals in step.  The open segments of
-// mixed tiles do the same.  (MIXED = false: the layout has no such tile, and the code for them is left out.)
-// Relies on workgroups being dispatched in grid order (fuse_limit keeps a block's tiles well inside what is
+// All tiles of all workers in one launch, one workgroup per (tile, worker): the dense tiles, then the others in
+// ascending order, mixed ones among them (see few_place).  A whole tile goes through the steps of the persistent
+// kernel without the pipeline: the workgroup waits in place for its block's scale; the momentum tile is written at
+// once, the residual tile when the scale is there, so the tiles of a block write their residuals in step.  The
+// open segments of tiles of few segments do the same; dense tiles never wait for a whole tile.
+// Relies on workgroups being dispatched in grid order (the one-pass limit keeps a block's tiles well inside what is
 // resident at once) and on spin_limit where that fails.
-// Eight workgroups per CU (64 VGPRs, a few spilled): the one-pass limit is half of what is
-// resident, and 2048 resident workgroups let blocks of up to 1024 tiles (4 Mi elements) finish
-// in one pass (measured: 27.1 -> 24.4 ms on the transformer-like layout, no change elsewhere).
-enum { ALL_WHOLE = 0, FEW_TILES = 1, DENSE_TILES = 2 };
+// TILES says which kinds of tiles the layout has; the code for the others is left out.  Workgroups per CU: eight (64
+// VGPRs, 6 to 8 spilled; blocks of up to 1024 tiles, half of the 2048 resident, then finish in one pass: 27.1 ->
+// 24.4 ms on the transformer-like layout), but seven where they are measured faster, the momentum worker
+// with dense tiles (109 832 tiny blocks and four of 2 M, 8 workers: 291 us against 297) and the
+// momentum-free one without (blocks of 30 011: 65.9 against 67.7); the other two the other way round (25 M elements
+// in 64-tile blocks and less, 7 workers: 603 against 609; 259 400 tiny blocks, 16 workers: 213 against 223).
+enum { ALL_WHOLE = 0, FEW_TILES = 1, DENSE_TILES = 2 };        // each with those before it
 template <bool SEGMENTS>
 struct TilesShared {
     typedef SyncShared type;
