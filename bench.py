@@ -204,11 +204,10 @@ class Run:
             if self.plan.persistent and self.variant != "sgd":
                 return "ef::k_worker_uniform<%s>" % mom
         tiles, whole, dense = wl.tile_kinds(w.offsets, w.M)
+        quality = "true" if self.variant == "quality" else "false"
         if dense == tiles:
-            return "ef::k_worker_mixed<%s, %s>" % (mom, "true" if self.variant == "quality" else "false")
-        if self.variant == "quality":
-            return "ef::k_worker_tiles<true, 2, true>"
-        return "ef::k_worker_tiles<%s, %d, false>" % (mom, 2 if dense else 1 if whole < tiles else 0)
+            return "ef::k_worker_mixed<%s, %s>" % (mom, quality)
+        return "ef::k_worker_tiles<%s, %d, %s>" % (mom, 2 if dense else 1 if whole < tiles else 0, quality)
 
     def close(self):
         self.plan.close()

@@ -1147,8 +1147,12 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
                 hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, block, 0, s, L, c.X, A, Q);
             else
                 hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, block, 0, s, L, c.X, A, Q);
-        } else if (quality)
+        } else if (quality && kind == 2)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::DENSE_TILES, true>), grid, block, 0, s, L, c.X, A, Q);
+        else if (quality && kind == 1)
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::FEW_TILES, true>), grid, block, 0, s, L, c.X, A, Q);
+        else if (quality)
+            hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::ALL_WHOLE, true>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom && kind == 2)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::DENSE_TILES, false>), grid, block, 0, s, L, c.X, A, Q);
         else if (has_mom && kind == 1)

@@ -301,9 +301,10 @@ struct TilesShared<true> {
 };
 
 // QUAL = true: the compressor-quality sums of p (Section 3.2: Proposition 1's phi, Eq. (1)'s delta)
-// are taken on the way, from the values the kernel holds anyway (see ef_quality.h).
+// are taken on the way, from the values the kernel holds anyway (see ef_quality.h).  Seven workgroups per CU (2^27
+// elements in blocks of 2^20, 8 workers: 3585 us, 3763 at eight, where 15 registers spill).
 template <bool MOM, int TILES, bool QUAL>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(QUAL || TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8, 8)))
 void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
     constexpr bool MIXED = TILES != ALL_WHOLE;
