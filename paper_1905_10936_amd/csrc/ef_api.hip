@@ -244,7 +244,7 @@ private:
 struct DeviceFacts {
     bool known;
     int cus;                                    // compute units
-    int uniform, tiles, server[2], small;       // workgroups per unit of the kernels of these names (server: without, with mixed tiles)
+    int uniform, tiles, server[3], small;       // workgroups per unit of the kernels of these names (server: whole tiles, few, dense ones)
 };
 DeviceFacts g_facts[MAX_DEVICES];
 
@@ -259,7 +259,8 @@ int device_facts(int device, DeviceFacts *out)
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, ef::ALL_WHOLE, false>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<ef::ALL_WHOLE, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::DENSE_TILES, true>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::FEW_TILES, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[2], (ef::k_server_tiles<ef::DENSE_TILES, false>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
         if (small_s < f.small) f.small = small_s;
@@ -461,7 +462,8 @@ int build_device(ef_plan *p)
     // A block finishes in one pass if its tiles fit twice over into the tiles a kernel's workgroups hold at
     // once: grid x (PIPE_DEPTH + STAGE_DEPTH) for the persistent kernel, the resident workgroups for the
     // kernels that run one workgroup per tile (dispatched in grid order).  Larger limits were measured slower:
-    // a block that fills most of the machine makes its first tiles wait for its last.
+    // a block that fills most of the machine makes its first tiles wait for its last.  (The worker's is that of layouts of
+    // whole tiles, 1024, for all: 57 % of what its kernel with dense tiles keeps resident.)
     p->worker_grid = facts.cus * facts.uniform;
     p->lim_persistent = (int32_t)((int64_t)p->worker_grid * (ef::PIPE_DEPTH + ef::STAGE_DEPTH) / 2);
     p->lim_direct = (int32_t)((int64_t)facts.cus * facts.tiles / 2);
@@ -525,9 +527,10 @@ int build_device(ef_plan *p)
         }
     p->L.n_dense = (int32_t)dense.size();
     p->L.n_grid = ntiles;
-    // the server's limit is that of the kernel this layout runs (2^28 elements in blocks of 1024 tiles, 8 workers:
-    // 560 us in one pass, 755 in two)
-    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[mixed.empty() ? 0 : 1] / 2);
+    // the server's limit is that of the kernel this layout runs, 1024, 896 or 768 tiles on 256 units (8 workers; 2^28
+    // elements in blocks of 1024 tiles: 560 us in one pass, 755 in two; twelve blocks of 850 tiles off the tile
+    // boundaries: 87 and 119; with 100 000 tiny blocks among them 121 and 123, 16 workers 164 and 148)
+    p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[mixed.empty() ? 0 : dense.empty() ? 1 : 2] / 2);
     // The order in which the kernels with one workgroup per tile take the tiles: the dense ones, then the others
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
