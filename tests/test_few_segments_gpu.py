@@ -3,6 +3,7 @@
 keeps these layouts from the kernels for small launches.  Same bar as the other parity tests."""
 import numpy as np
 import pytest
+import torch
 
 import paper_1905_10936_amd as ef  # noqa: F401
 from tests.parity_util import F, GpuState, synced_step
@@ -59,3 +60,37 @@ def test_one_pass_limits_and_worker_counts(limit, M):
     for t, eta in enumerate([0.1, 0.2]):
         st.set_grads(rng.standard_normal((M, d)).astype(F))
         synced_step(st, 0.5, 0.1 * t, eta, None, "M=%d limit=%d step %d" % (M, limit, t))
+
+
+@pytest.mark.parametrize("spin", [None, 0])
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_momentum_free_and_diagnosing_workers(name, spin):
+    """The other variants of the worker's kernels give the bits of the plain call (checked against the oracle above),
+    also where every wait gives up."""
+    offs = _offs(LAYOUTS[name])
+    d, M = int(offs[-1]), 3
+    rng = np.random.default_rng(len(name))
+    g, m, e = (rng.standard_normal((M, d)).astype(F) for _ in range(3))
+
+    def run(kind, mu, spin):
+        st = GpuState(offs, M)
+        st.plan.set_persistent(False)
+        if spin is not None:
+            st.plan.tune(spin_limit=spin)
+        st.set_grads(g)
+        st.m[:, :d].copy_(torch.as_tensor(m))
+        st.e[:, :d].copy_(torch.as_tensor(e))
+        if kind == "sgd":
+            ef.ef_worker_step_sgd(st.plan, st.g, st.e, 0.1, 0.2, st.ws, st.wc)
+        elif kind == "quality":
+            q = torch.zeros((M, 2), dtype=torch.float64, device="cuda")
+            ef.ef_worker_step_quality(st.plan, st.g, st.m, st.e, mu, 0.1, 0.2, st.ws, st.wc, q)
+        else:
+            ef.ef_worker_step(st.plan, st.g, st.m, st.e, mu, 0.1, 0.2, st.ws, st.wc)
+        torch.cuda.synchronize()
+        return st
+
+    for kind, mu in (("sgd", 0.0), ("quality", 0.9)):
+        want, got = run("plain", mu, None), run(kind, mu, spin)
+        for field in ("ws", "wc", "e"):
+            assert torch.equal(getattr(want, field), getattr(got, field)), "%s: %s" % (kind, field)
