@@ -254,8 +254,9 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
     }
 }
 
-// Layouts of dense tiles alone (25 M elements in blocks of 33, 7 workers: 86 us; blocks of 256, 4 workers, 16 M: 48.9,
-// 52 in a kernel with the whole tiles' code at six workgroups per CU).  The residual tile is loaded after the payloads have been added up, which keeps the registers down.
+// Layouts of dense tiles alone (25 M elements in blocks of 33, 7 workers: 86 us; blocks of 256, 4 workers, 16 M
+// elements: 49.5, against 52.2 in a kernel with the whole tiles' code).  The residual tile is loaded after the
+// payloads have been added up, which keeps the registers down.
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, int set)
 {
