@@ -139,7 +139,7 @@ struct Layout {
 // scratch set's partial words carry since the last call that used the set.
 // The kernel that ends a call (k_tail) moves it on; its own workgroups go by the copy that the call's
 // main kernel leaves in ScratchRef::snapshot, so nothing has to wait for them.
-struct CallState {
+struct alignas(32) CallState {
     unsigned int calls;
     unsigned int server_tag;            // bit 0
     unsigned long long worker_tags;     // bit i: worker i
@@ -188,10 +188,21 @@ struct Scratch {
 
 __device__ __forceinline__ unsigned uniform_u32(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
 
+__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v)
+{
+    return ((unsigned long long)uniform_u32((unsigned)(v >> 32)) << 32) | uniform_u32((unsigned)v);
+}
+
+// Every workgroup's first dependent load, ahead of anything it can ask for by tile: the whole record in one scalar
+// load and no branch between it and what follows.
 __device__ __forceinline__ Scratch open_call(const ScratchRef &R)
 {
     Scratch X;
-    const unsigned calls = uniform_u32(R.state->calls);
+    const CallState now = *R.state;
+    const unsigned calls = uniform_u32(now.calls);
+    const unsigned long long worker_tags = uniform_u64(now.worker_tags), worker_pending = uniform_u64(now.worker_pending);
+    const unsigned server_tag = uniform_u32(now.server_tag), server_pending = uniform_u32(now.server_pending);
+    const bool workers = R.set_base == 0;
     const unsigned cur = calls & 1u;
     X.part = R.part;
     X.ready = R.ready;
@@ -202,20 +213,10 @@ __device__ __forceinline__ Scratch open_call(const ScratchRef &R)
     X.ticket = R.list_cnt + 4 + cur;
     X.next_cnt = R.list_cnt + (cur ^ 1u);
     // this call's tags are the stored ones flipped
-    if (R.set_base == 0) {
-        const unsigned long long t = R.state->worker_tags;
-        X.tags = ~(((unsigned long long)uniform_u32((unsigned)(t >> 32)) << 32) | uniform_u32((unsigned)t));
-    } else {
-        X.tags = (unsigned long long)(uniform_u32(R.state->server_tag) ^ 1u);
-    }
+    X.tags = workers ? ~worker_tags : (unsigned long long)(server_tag ^ 1u);
     X.lazy_scales = R.lazy_scales;
     X.lazy_stride = R.lazy_stride;
-    if (R.set_base == 0) {
-        const unsigned long long t = R.state->worker_pending;
-        X.pending = ((unsigned long long)uniform_u32((unsigned)(t >> 32)) << 32) | uniform_u32((unsigned)t);
-    } else {
-        X.pending = (unsigned long long)(uniform_u32(R.state->server_pending) & 1u);
-    }
+    X.pending = workers ? worker_pending : (unsigned long long)(server_pending & 1u);
     X.epoch = calls % 0xffffffffu + 1u;     // never 0: 0 marks "no scale posted"
     X.set_base = R.set_base;
     X.spin_limit = R.spin_limit;
@@ -351,7 +352,7 @@ __device__ __forceinline__ int tile_valid(const Layout &L, int32_t tile)
 template <int CTRL>
 __device__ __forceinline__ unsigned row_move(unsigned v)
 {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
 }
 template <int CTRL>
 __device__ __forceinline__ double row_move(double v)
@@ -361,6 +362,26 @@ __device__ __forceinline__ double row_move(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// v of this lane plus v of the lane whose index differs in bit 4 (WIDTH = 16) or bit 5 (32).  The swap leaves both
+// rows' values in every lane of the pair of rows, in one instruction per half of the number and without LDS.
+template <int WIDTH>
+__device__ __forceinline__ double add_other_row(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+    typedef unsigned vu2 __attribute__((ext_vector_type(2)));
+    vu2 l, h;
+    if constexpr (WIDTH == 16) {
+        l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    } else {
+        l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    }
+    return __longlong_as_double((long long)(((unsigned long long)h.x << 32) | l.x)) +
+           __longlong_as_double((long long)(((unsigned long long)h.y << 32) | l.y));
+}
+
 // Sum over the 64 lanes in a fixed order: every lane ends with the same bits.
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -368,9 +389,8 @@ __device__ __forceinline__ double wave_sum(double v)
     v += row_move<EF_DPP_XOR2>(v);
     v += row_move<EF_DPP_HALF_MIRROR>(v);
     v += row_move<EF_DPP_MIRROR>(v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    v = add_other_row<16>(v);
+    return add_other_row<32>(v);
 }
 
 // Sum of val[j], val[j + STEP], ... below hi, one after the other, on top of acc.  The reads go out eight at a time;
@@ -477,44 +497,33 @@ __device__ __forceinline__ void residual4(float4 &v, float s)
 }
 
 // Sign words of the tile whose values are in p (bit = p >= 0, Appendix A with
-// sign(0) read as +1; elements past n_valid give 0 bits).  Within a sub-row, 16
-// consecutive lanes make one 64-bit word; each wavefront stores its 16 words.
+// sign(0) read as +1; elements past n_valid give 0 bits).  A lane's 16 bits are four from each of its
+// sub-rows; four neighbouring lanes transpose their 4 x 4 nibbles (two exchanges) so that each is left
+// with 16 consecutive elements of one sub-row, and stores those: the wavefront's 64 half-words fill 128 contiguous
+// bytes.  (Gathering the nibbles of each sub-row's words over 16 lanes took 110 vector instructions, this 50.)
 __device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_valid, uint64_t *signs,
                                             int64_t tile_start, int64_t W)
 {
     const int lane = lane_id();
-    const int l16 = lane & 15;
-    const unsigned sh = (unsigned)(l16 & 7) * 4u;
-    unsigned mylo = 0, myhi = 0;
+    unsigned v = 0;                     // bits 4k .. 4k + 3: this lane's elements of sub-row k
 #pragma unroll
-    for (int k = 0; k < SUBROWS; ++k) {
-        const int lb0 = local_base(k);
+    for (int k = SUBROWS - 1; k >= 0; --k) {
         unsigned nib = (p[k].x >= 0.f ? 1u : 0u) | (p[k].y >= 0.f ? 2u : 0u) | (p[k].z >= 0.f ? 4u : 0u) |
                        (p[k].w >= 0.f ? 8u : 0u);
         if (n_valid != TILE) {
-            unsigned vm = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) vm |= (lb0 + c < n_valid) ? (1u << c) : 0u;
-            nib &= vm;
+            const int left = n_valid - local_base(k);
+            nib = left >= 4 ? nib : left > 0 ? nib & ((1u << left) - 1u) : 0u;
         }
-        unsigned lo = (l16 < 8) ? (nib << sh) : 0u;
-        unsigned hi = (l16 >= 8) ? (nib << sh) : 0u;
-        // OR over the 16 lanes of the word
-        lo |= row_move<EF_DPP_XOR1>(lo);
-        hi |= row_move<EF_DPP_XOR1>(hi);
-        lo |= row_move<EF_DPP_XOR2>(lo);
-        hi |= row_move<EF_DPP_XOR2>(hi);
-        lo |= row_move<EF_DPP_HALF_MIRROR>(lo);
-        hi |= row_move<EF_DPP_HALF_MIRROR>(hi);
-        lo |= row_move<EF_DPP_MIRROR>(lo);
-        hi |= row_move<EF_DPP_MIRROR>(hi);
-        if (l16 == k) { mylo = lo; myhi = hi; }
+        v |= nib << (4 * k);
     }
-    if (l16 < SUBROWS) {
-        // lane 16q + k holds word 4k + q of the wavefront's 16 words
-        const int64_t w = (tile_start + wave_id() * 1024) / 64 + 4 * l16 + (lane >> 4);
-        if (w < W) signs[w] = ((uint64_t)myhi << 32) | (uint64_t)mylo;
-    }
+    // lanes 0 and 1 of a quad keep sub-rows 0 and 1, lanes 2 and 3 the others; then even lanes the first, odd the second
+    const unsigned w = row_move<EF_DPP_XOR2>(v);
+    const unsigned t = __builtin_amdgcn_perm(w, v, (lane & 2) ? 0x0c0c0105u : 0x0c0c0400u);
+    const unsigned u = row_move<EF_DPP_XOR1>(t);
+    const unsigned own = (lane & 1) ? 0xf0f0u : 0x0f0fu;
+    const unsigned half = (t & own) | (((lane & 1) ? u >> 4 : u << 4) & ~own);
+    const int64_t at = (tile_start >> 4) + wave_id() * 64 + 16 * (lane & 3) + (lane >> 2);
+    if (n_valid == TILE || at < 4 * W) reinterpret_cast<uint16_t *>(signs)[at] = (uint16_t)half;
 }
 
 // fp64 sum of |p| over the thread's valid elements, sub-row by sub-row
