@@ -66,7 +66,7 @@ struct ef_plan {
     unsigned long long *d_fin_list;
     int32_t *d_mixed;               // tile lists
     int32_t *d_whole;
-    ef::TileRec *d_tiles, *d_in_order, *d_mixed_recs;
+    ef::TileRec *d_tiles, *d_in_order, *d_paired, *d_mixed_recs;
     ef::StartWord *d_words;         // [n_mixed][TILE_WORDS]
     std::vector<char> dense_host;   // [ntiles] is the tile a dense one?
     // compressor-quality diagnostics
@@ -245,6 +245,7 @@ struct DeviceFacts {
     bool known;
     int cus;                                    // compute units
     int uniform, tiles, server[3], small;       // workgroups per unit of the kernels of these names (server: whole tiles, few, dense ones)
+    int pairs[2];                               // of the server's with two tiles to a workgroup (up to eight workers, more)
 };
 DeviceFacts g_facts[MAX_DEVICES];
 
@@ -258,9 +259,11 @@ int device_facts(int device, DeviceFacts *out)
         EF_HIP(hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, device));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.uniform, ef::k_worker_uniform<true>, ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.tiles, (ef::k_worker_tiles<true, ef::ALL_WHOLE, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<ef::ALL_WHOLE, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::FEW_TILES, false>), ef::THREADS, 0));
-        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[2], (ef::k_server_tiles<ef::DENSE_TILES, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<ef::ALL_WHOLE, false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::FEW_TILES, false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[2], (ef::k_server_tiles<ef::DENSE_TILES, false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.pairs[0], (ef::k_server_tiles<ef::DENSE_TILES, false, true>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.pairs[1], (ef::k_server_tiles<ef::DENSE_TILES, true, true>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&small_s, ef::k_server_small, ef::SMALL_THREADS, 0));
         if (small_s < f.small) f.small = small_s;
@@ -491,7 +494,7 @@ int build_device(ef_plan *p)
         const bool goes_on = lb[t] != fb[t] && last_end > ((int64_t)t + 1) * ef::TILE;
         const int32_t tail = goes_on ? (int32_t)(2 * tiles_of_block(p, lb[t]) + (last_end % ef::TILE != 0 ? 1 : 0)) : 0;
         const int64_t bs = p->offs_host[(size_t)fb[t]], be = p->offs_host[(size_t)fb[t] + 1];
-        tiles[(size_t)t] = {t, fb[t], lb[t] - fb[t] + 1, one ? -1 : (int32_t)mixed.size(), tail, (int32_t)(bs / ef::TILE),
+        tiles[(size_t)t] = {t, fb[t], lb[t] - fb[t] + 1, one ? ef::TILE_ALONE : (int32_t)mixed.size(), tail, (int32_t)(bs / ef::TILE),
                             (int32_t)tiles_of_block(p, fb[t]), (int16_t)(bs % ef::TILE), (int16_t)(be % ef::TILE)};
         (one ? whole : mixed).push_back(t);
     }
@@ -549,6 +552,29 @@ int build_device(ef_plan *p)
         }
         while (w < whole.size()) in_order.push_back(tiles[(size_t)whole[w++]]);
     }
+    // The same with the whole tiles of a block two by two, where at least three in four tiles are in pairs that wait for
+    // their block.  The limit is then half of the tiles that this kernel keeps resident, 1792 or 1536.
+    std::vector<ef::TileRec> paired;
+    {
+        const int32_t limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
+        std::vector<char> second((size_t)ntiles, 0);
+        int64_t waiting = 0;
+        paired.reserve((size_t)ntiles);
+        for (const ef::TileRec &r : mixed.empty() ? tiles : in_order) {
+            if (second[(size_t)r.tile]) continue;
+            paired.push_back(r);
+            const int32_t next = r.tile + 1;
+            if (r.words >= 0 || next >= ntiles || tiles[(size_t)next].words >= 0 || tiles[(size_t)next].fb != r.fb) continue;
+            paired.back().words = ef::TILE_PAIR;
+            second[(size_t)next] = 1;
+            waiting += r.n <= limit ? 2 : 0;
+        }
+        if (p->max_workers > ef::PAIR_WORKERS || waiting * 4 < (int64_t)ntiles * 3)
+            paired.clear();
+        else
+            p->lim_server = limit;
+    }
+    p->L.n_paired = (int32_t)paired.size();
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
     // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
@@ -568,6 +594,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_whole, whole.size(), Arena::COPY, whole.data());
     mem.add(&p->d_tiles, nt, Arena::COPY, tiles.data());
     mem.add(&p->d_in_order, in_order.size(), Arena::COPY, in_order.data());
+    mem.add(&p->d_paired, paired.size(), Arena::COPY, paired.data());
     mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
     mem.add(&p->d_mixed_recs, mixed_recs.size(), Arena::COPY, mixed_recs.data());
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
@@ -593,6 +620,7 @@ int build_device(ef_plan *p)
     p->L.whole_tiles = p->d_whole;
     p->L.tiles = p->d_tiles;
     p->L.grid_tiles = p->L.n_mixed ? p->d_in_order : p->d_tiles;
+    p->L.paired_tiles = p->d_paired;
     p->L.words = p->d_words;
     p->L.mixed_recs = p->d_mixed_recs;
     p->L.offs = p->d_offs;
@@ -1234,22 +1262,21 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
         return EF_OK;
     }
     const ef::Layout L = role_layout(plan, ROLE_SERVER);
-    const dim3 grid((unsigned)L.n_grid), block(ef::THREADS);
-    const bool many = M > ef::SERVER_CHUNK;
-    if (L.n_dense == L.ntiles)
-        hipLaunchKernelGGL(ef::k_server_mixed, grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else if (L.n_dense && many)
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::DENSE_TILES, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else if (L.n_dense)
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::DENSE_TILES, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else if (L.n_mixed && many)
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::FEW_TILES, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else if (L.n_mixed)
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::FEW_TILES, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else if (many)
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::ALL_WHOLE, true>), grid, block, 0, s, L, c.X, A, plan->max_workers);
-    else
-        hipLaunchKernelGGL((ef::k_server_tiles<ef::ALL_WHOLE, false>), grid, block, 0, s, L, c.X, A, plan->max_workers);
+    const dim3 block(ef::THREADS);
+    const int kind = L.n_dense ? 2 : L.n_mixed ? 1 : 0;
+    const bool many = M > ef::SERVER_CHUNK, pairs = L.n_paired != 0 && L.fuse_limit > 0;
+    if (L.n_dense == L.ntiles) {
+        hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_grid), block, 0, s, L, c.X, A, plan->max_workers);
+    } else {
+        typedef void (*Kernel)(ef::Layout, ef::ScratchRef, ef::ServerArgs, int);
+        static const Kernel kernels[2][2][3] = {
+            {{ef::k_server_tiles<0, false, false>, ef::k_server_tiles<1, false, false>, ef::k_server_tiles<2, false, false>},
+             {ef::k_server_tiles<0, true, false>, ef::k_server_tiles<1, true, false>, ef::k_server_tiles<2, true, false>}},
+            {{ef::k_server_tiles<0, false, true>, ef::k_server_tiles<1, false, true>, ef::k_server_tiles<2, false, true>},
+             {ef::k_server_tiles<0, true, true>, ef::k_server_tiles<1, true, true>, ef::k_server_tiles<2, true, true>}}};
+        hipLaunchKernelGGL(kernels[pairs][many][kind], dim3((unsigned)(pairs ? L.n_paired : L.n_grid)), block, 0, s, L, c.X, A,
+                           plan->max_workers);
+    }
     EF_HIP(hipGetLastError());
     return launch_tail(plan, ROLE_SERVER, c, 1, server_err, (int64_t)0, out_scales, (int64_t)0, s);
 }

@@ -15,6 +15,22 @@ __device__ __forceinline__ float mean_of(float acc, float Mf, float Minv)
     return Minv != 0.0f ? acc * Minv : acc / Mf;
 }
 
+// The same for a thread's elements, with one branch.
+__device__ __forceinline__ void mean_of_all(float (&acc)[SUBROWS][4], float Mf, float Minv)
+{
+    if (Minv != 0.0f) {
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] *= Minv;
+    } else {
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] /= Mf;
+    }
+}
+
 constexpr int SERVER_CHUNK = 8;     // workers whose sign words are in flight together
 constexpr int SCALE_GROUP = 4;      // dense tiles: workers whose scales are staged in LDS together ...
 constexpr int SCALE_STAGE = TILE / 2;   // ... in this many floats
@@ -23,36 +39,62 @@ typedef unsigned vu4 __attribute__((ext_vector_type(4)));
 
 // Bit matrix transpose: h[u] holds worker u's sign bits of 16 consecutive elements (bit e: element
 // e); byte e of the result (element 0 in the lowest byte of .x) holds element e's bits of the eight
-// workers (bit u: worker u).  The bytes are gathered into two 8x8 bit matrices, each transposed by
-// swapping 1x1, 2x2 and 4x4 blocks across the diagonal.
+// workers (bit u: worker u).  Each step exchanges one bit of u, first a register number, with one bit of e, first
+// a bit position; the last puts an element's byte where it belongs (40 instructions).
 __device__ __forceinline__ vu4 transpose_signs(const unsigned (&h)[SERVER_CHUNK])
 {
-    unsigned lo[2], hi[2];          // [half]: rows 0-3 and rows 4-7 of the matrix of elements 8*half .. 8*half+7
-    {
-        // v_perm_b32: selector values 0-3 take bytes of the second operand, 4-7 of the first
-        const unsigned a = __builtin_amdgcn_perm(h[1], h[0], 0x05010400u), b = __builtin_amdgcn_perm(h[3], h[2], 0x05010400u);
-        const unsigned c = __builtin_amdgcn_perm(h[5], h[4], 0x05010400u), d = __builtin_amdgcn_perm(h[7], h[6], 0x05010400u);
-        lo[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-        lo[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-        hi[0] = __builtin_amdgcn_perm(d, c, 0x05040100u);
-        hi[1] = __builtin_amdgcn_perm(d, c, 0x07060302u);
-    }
-    unsigned out[4];
+    unsigned q[4];                  // bit 0 of u <-> bit 0 of e; elements of odd e in the upper half
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        unsigned x = lo[q], y = hi[q], t;
-        t = (x ^ (x >> 7)) & 0x00AA00AAu;
-        x ^= t ^ (t << 7);
-        t = (y ^ (y >> 7)) & 0x00AA00AAu;
-        y ^= t ^ (t << 7);
-        t = (x ^ (x >> 14)) & 0x0000CCCCu;
-        x ^= t ^ (t << 14);
-        t = (y ^ (y >> 14)) & 0x0000CCCCu;
-        y ^= t ^ (t << 14);
-        out[2 * q] = (x & 0x0F0F0F0Fu) | ((y & 0x0F0F0F0Fu) << 4);
-        out[2 * q + 1] = ((x >> 4) & 0x0F0F0F0Fu) | (y & 0xF0F0F0F0u);
+    for (int r = 0; r < 4; ++r) {
+        const unsigned a = h[2 * r], b = h[2 * r + 1];
+        const unsigned even = (a & 0x5555u) | ((b << 1) & ~0x5555u), odd = ((a >> 1) & 0x5555u) | (b & ~0x5555u);
+        // v_perm_b32: selector values 0-3 take bytes of the second operand, 4-7 of the first
+        q[r] = __builtin_amdgcn_perm(odd, even, 0x05040100u);
     }
-    return vu4{out[0], out[1], out[2], out[3]};
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {        // bit 1 <-> bit 1
+        const unsigned a = q[r], b = q[r + 1];
+        q[r] = (a & 0x33333333u) | ((b << 2) & ~0x33333333u);
+        q[r + 1] = ((a >> 2) & 0x33333333u) | (b & ~0x33333333u);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {           // bit 2 <-> bit 2
+        const unsigned a = q[r], b = q[r + 2];
+        q[r] = (a & 0x0F0F0F0Fu) | ((b << 4) & ~0x0F0F0F0Fu);
+        q[r + 2] = ((a >> 4) & 0x0F0F0F0Fu) | (b & ~0x0F0F0F0Fu);
+    }
+    // element e is byte 2 * (bit 0 of e) + (bit 3 of e) of q[bits 1 and 2 of e]
+    return vu4{__builtin_amdgcn_perm(q[1], q[0], 0x06040200u), __builtin_amdgcn_perm(q[3], q[2], 0x06040200u),
+               __builtin_amdgcn_perm(q[1], q[0], 0x07050301u), __builtin_amdgcn_perm(q[3], q[2], 0x07050301u)};
+}
+
+// s if bit u of minus is 0, else -s
+__device__ __forceinline__ float negated_by(float s, unsigned minus, int u)
+{
+    return __uint_as_float(__float_as_uint(s) ^ ((minus << (31 - u)) & 0x80000000u));
+}
+
+// This lane's sign bits of workers i0 .. i0 + 7 (past M: the last worker's again, not used): 16 consecutive elements,
+// 16 * threadIdx.x of the tile.  Asked for ahead of everything that is looked up by block.
+__device__ __forceinline__ void load_sign_halves(const ServerArgs &A, int64_t tile_start, int i0, unsigned (&h)[SERVER_CHUNK])
+{
+    const uint16_t *row = reinterpret_cast<const uint16_t *>(A.signs_in + (int64_t)i0 * A.in_signs_stride) + (tile_start >> 4);
+#pragma unroll
+    for (int u = 0; u < SERVER_CHUNK; ++u) {
+        h[u] = row[threadIdx.x];
+        row += i0 + u + 1 < A.M ? 4 * A.in_signs_stride : 0;
+    }
+}
+// Block b's scales from workers i0 .. i0 + 7; past M 0, which changes no sum.
+__device__ __forceinline__ void load_scales(const ServerArgs &A, int32_t b, int i0, float (&sc)[SERVER_CHUNK])
+{
+    const float *at = A.scales_in + (int64_t)i0 * A.in_scales_stride + b;
+#pragma unroll
+    for (int u = 0; u < SERVER_CHUNK; ++u) {
+        const float s = *at;
+        sc[u] = i0 + u < A.M ? s : 0.0f;
+        at += i0 + u + 1 < A.M ? A.in_scales_stride : 0;
+    }
 }
 
 // LDS of server_values_whole.
@@ -76,30 +118,21 @@ constexpr int SERVER_LDS = NIBBLE_AT + SERVER_CHUNK * 64;      // floats
 // one bit-field extract and one 128-bit LDS read.
 // Called by every thread of the workgroup; lds (SERVER_LDS floats) is free again on return.
 template <bool MANY>
-__device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t tile_start, int32_t b,
+__device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t tile_start, int32_t b, const unsigned (&h0)[SERVER_CHUNK],
                                                     const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], float *lds)
 {
     float acc[SUBROWS][4];
-    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(A.signs_in);
-    const int64_t in_half = 4 * A.in_signs_stride;
-    const int64_t half0 = (tile_start >> 4) + threadIdx.x;      // this lane's 16 elements: 16 * threadIdx.x of the tile
     const float r = A.r, Mf = A.Mf, Minv = A.Minv;
     unsigned *exchange = reinterpret_cast<unsigned *>(lds) + EXCHANGE_AT + wave_id() * 256;
     {
-        unsigned h[SERVER_CHUNK];
         float sc[SERVER_CHUNK];
-#pragma unroll
-        for (int u = 0; u < SERVER_CHUNK; ++u) {
-            const int i = min(u, A.M - 1);               // past M: a valid address whose value is not used
-            h[u] = s16[(int64_t)i * in_half + half0];
-            sc[u] = A.scales_in[(int64_t)i * A.in_scales_stride + b];
-        }
+        load_scales(A, b, 0, sc);
         float sum = 0.0f;
+        const unsigned minus = ~threadIdx.x;
 #pragma unroll
-        for (int u = 0; u < SERVER_CHUNK; ++u)
-            if (u < A.M) sum = sum + signed_scale(sc[u], (threadIdx.x >> u) & 1u);
+        for (int u = 0; u < SERVER_CHUNK; ++u) sum = sum + negated_by(sc[u], minus, u);
         lds[threadIdx.x] = MANY ? sum : mean_of(sum, Mf, Minv);
-        *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) = transpose_signs(h);
+        *reinterpret_cast<vu4 *>(exchange + 4 * lane_id()) = transpose_signs(h0);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) {
@@ -114,12 +147,8 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
         for (int i0 = SERVER_CHUNK; i0 < A.M; i0 += SERVER_CHUNK) {
             unsigned h[SERVER_CHUNK];
             float sc[SERVER_CHUNK];
-#pragma unroll
-            for (int u = 0; u < SERVER_CHUNK; ++u) {
-                const int i = min(i0 + u, A.M - 1);
-                h[u] = s16[(int64_t)i * in_half + half0];
-                sc[u] = A.scales_in[(int64_t)i * A.in_scales_stride + b];
-            }
+            load_sign_halves(A, tile_start, i0, h);
+            load_scales(A, b, i0, sc);
             if (i0 > SERVER_CHUNK) __syncthreads();      // the table is read no more
             if (threadIdx.x < SERVER_CHUNK * 16) {
                 const int u = threadIdx.x >> 4, nib = threadIdx.x & 15;
@@ -149,10 +178,7 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
                 }
             }
         }
-#pragma unroll
-        for (int k = 0; k < SUBROWS; ++k)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[k][c] = mean_of(acc[k][c], Mf, Minv);
+        mean_of_all(acc, Mf, Minv);
     }
     __syncthreads();            // lds is free again
 #pragma unroll
@@ -244,13 +270,14 @@ __device__ __forceinline__ void server_values_mixed(const Layout &L, const Serve
     __syncthreads();            // S.val is free again
     float4 tv[SUBROWS];
     load_tile(te, tv, n_valid);
-    const float r = A.r, Mf = A.Mf, Minv = A.Minv;
+    const float r = A.r;
+    mean_of_all(acc, A.Mf, A.Minv);
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
-        p[k].x = mean_of(acc[k][0], Mf, Minv) + r * tv[k].x;
-        p[k].y = mean_of(acc[k][1], Mf, Minv) + r * tv[k].y;
-        p[k].z = mean_of(acc[k][2], Mf, Minv) + r * tv[k].z;
-        p[k].w = mean_of(acc[k][3], Mf, Minv) + r * tv[k].w;
+        p[k].x = acc[k][0] + r * tv[k].x;
+        p[k].y = acc[k][1] + r * tv[k].y;
+        p[k].z = acc[k][2] + r * tv[k].z;
+        p[k].w = acc[k][3] + r * tv[k].w;
     }
 }
 
@@ -359,12 +386,7 @@ __device__ __forceinline__ void server_values_few(const Layout &L, const ServerA
             __syncthreads();                             // the table, and after the last segment the exchange, are free
         }
     }
-    if (MANY) {
-#pragma unroll
-        for (int k = 0; k < SUBROWS; ++k)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[k][c] = mean_of(acc[k][c], Mf, Minv);
-    }
+    if (MANY) mean_of_all(acc, Mf, Minv);
     float4 tv[SUBROWS];             // loaded only now: few registers
     load_tile(te, tv, n_valid);
 #pragma unroll
@@ -376,48 +398,280 @@ __device__ __forceinline__ void server_values_few(const Layout &L, const ServerA
     }
 }
 
-// Server part of Algorithm 4, all tiles in one launch, one workgroup per tile, in the order of k_worker_tiles.  p~ as
+// Two whole tiles of one block, next to each other, as one workgroup's work: wavefront w has the elements
+// 2048w .. 2048w + 2047 of the pair as two quarters of a tile each laid out like a quarter elsewhere, so that a
+// tile's sum is formed in the same order.
+__device__ __forceinline__ int pair_base(int half, int k) { return (2 * wave_id() + half) * 1024 + k * 256 + lane_id() * 4; }
+
+// As transpose_signs, for 32 consecutive elements: dword j of the result holds the bytes of elements 4j .. 4j + 3.
+__device__ __forceinline__ void transpose_signs32(const unsigned (&h)[SERVER_CHUNK], vu4 (&out)[2])
+{
+    unsigned q[SERVER_CHUNK];
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {            // bit 0 of u <-> bit 0 of e
+        const unsigned a = h[u], b = h[u + 1];
+        q[u] = (a & 0x55555555u) | ((b << 1) & ~0x55555555u);
+        q[u + 1] = ((a >> 1) & 0x55555555u) | (b & ~0x55555555u);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {               // bit 1 <-> bit 1
+        const int u = (i & 1) | ((i & 2) << 1);
+        const unsigned a = q[u], b = q[u + 2];
+        q[u] = (a & 0x33333333u) | ((b << 2) & ~0x33333333u);
+        q[u + 2] = ((a >> 2) & 0x33333333u) | (b & ~0x33333333u);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {               // bit 2 <-> bit 2
+        const unsigned a = q[u], b = q[u + 4];
+        q[u] = (a & 0x0F0F0F0Fu) | ((b << 4) & ~0x0F0F0F0Fu);
+        q[u + 4] = ((a >> 4) & 0x0F0F0F0Fu) | (b & ~0x0F0F0F0Fu);
+    }
+    // element e is byte (bits 3 and 4 of e) of q[bits 0 to 2 of e]: 4 x 4 bytes transposed, twice
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const unsigned a = q[4 * g], b = q[4 * g + 1], c = q[4 * g + 2], d = q[4 * g + 3];
+        const unsigned ab0 = __builtin_amdgcn_perm(b, a, 0x05010400u), ab1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+        const unsigned cd0 = __builtin_amdgcn_perm(d, c, 0x05010400u), cd1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+        out[0][g] = __builtin_amdgcn_perm(cd0, ab0, 0x05040100u);
+        out[0][g + 2] = __builtin_amdgcn_perm(cd0, ab0, 0x07060302u);
+        out[1][g] = __builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
+        out[1][g + 2] = __builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
+    }
+}
+
+// LDS of server_pair (floats): the wavefronts' exchanges (2 KiB each, for more than SERVER_CHUNK workers twice) and the
+// tables of sums and of more workers' values.
+constexpr int PAIR_WORKERS = 2 * SERVER_CHUNK;
+constexpr int PAIR_EXCHANGE = NWAVES * 512;
+constexpr int PAIR_TABLES = SUM_TABLE + SERVER_CHUNK * 64;
+
+__device__ __forceinline__ void load_sign_dwords(const ServerArgs &A, int64_t start, int i0, unsigned (&h)[SERVER_CHUNK])
+{
+    const unsigned *row = reinterpret_cast<const unsigned *>(A.signs_in + (int64_t)i0 * A.in_signs_stride) + (start >> 5);
+#pragma unroll
+    for (int u = 0; u < SERVER_CHUNK; ++u) {
+        h[u] = row[threadIdx.x];
+        row += i0 + u + 1 < A.M ? 2 * A.in_signs_stride : 0;
+    }
+}
+
+// p~ of a pair, as server_values_whole; M at most PAIR_WORKERS.  v: the server residual's tiles, then p~.
+template <bool MANY>
+__device__ __forceinline__ void server_values_pair(const ServerArgs &A, int64_t start, int32_t b, const unsigned (&h0)[SERVER_CHUNK],
+                                                   const unsigned (&h1)[SERVER_CHUNK], float4 (&v)[2][SUBROWS], float *exchanges, float *lds)
+{
+    const float r = A.r, Mf = A.Mf, Minv = A.Minv;
+    unsigned *exchange = reinterpret_cast<unsigned *>(exchanges) + wave_id() * 512;
+    {
+        float sc[SERVER_CHUNK];
+        load_scales(A, b, 0, sc);
+        float sum = 0.0f;
+        const unsigned minus = ~threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < SERVER_CHUNK; ++u) sum = sum + negated_by(sc[u], minus, u);
+        lds[threadIdx.x] = MANY ? sum : mean_of(sum, Mf, Minv);
+        vu4 bytes[2];
+        transpose_signs32(h0, bytes);
+        *reinterpret_cast<vu4 *>(exchange + 8 * lane_id()) = bytes[0];
+        *reinterpret_cast<vu4 *>(exchange + 8 * lane_id() + 4) = bytes[1];
+    }
+    if constexpr (!MANY) {
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) {
+                const unsigned pat = exchange[256 * h + 64 * k + lane_id()];
+                v[h][k].x = lds[pat & 255u] + r * v[h][k].x;
+                v[h][k].y = lds[(pat >> 8) & 255u] + r * v[h][k].y;
+                v[h][k].z = lds[(pat >> 16) & 255u] + r * v[h][k].z;
+                v[h][k].w = lds[pat >> 24] + r * v[h][k].w;
+            }
+    } else {
+        // the ninth worker to the sixteenth: their sign words as they are, and the values a nibble of them stands for
+        float4 *table = reinterpret_cast<float4 *>(lds + SUM_TABLE);
+        if (threadIdx.x < SERVER_CHUNK * 16) {
+            const unsigned nib = threadIdx.x & 15u;
+            const int i = SERVER_CHUNK + (int)(threadIdx.x >> 4);
+            float s = A.scales_in[(int64_t)min(i, A.M - 1) * A.in_scales_stride + b];
+            s = i < A.M ? s : 0.0f;     // past M: +-0, which changes no sum (one that began with +0 is never -0)
+            table[threadIdx.x] = make_float4(signed_scale(s, nib & 1u), signed_scale(s, nib & 2u), signed_scale(s, nib & 4u),
+                                             signed_scale(s, nib & 8u));
+        }
+        const unsigned *signs = exchange + PAIR_EXCHANGE + 8 * (lane_id() >> 3);
+        unsigned *mine = exchange + PAIR_EXCHANGE + 8 * lane_id();
+        *reinterpret_cast<vu4 *>(mine) = vu4{h1[0], h1[1], h1[2], h1[3]};
+        *reinterpret_cast<vu4 *>(mine + 4) = vu4{h1[4], h1[5], h1[6], h1[7]};
+        const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
+        __syncthreads();
+        // one half after the other, so that the sums of one are in registers at a time
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            float acc[SUBROWS][4];
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) {
+                const unsigned pat = exchange[256 * q + 64 * k + lane_id()];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[k][c] = lds[(pat >> (8 * c)) & 255u];
+            }
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                if (g == 1 && A.M <= SERVER_CHUNK + 4) continue;
+#pragma unroll
+                for (int k = 0; k < SUBROWS; ++k) {
+                    const vu4 w = *reinterpret_cast<const vu4 *>(signs + 8 * (32 * q + 8 * k) + 4 * g);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float4 dv = table[(4 * g + u) * 16 + ((w[u] >> sh) & 15u)];
+                        acc[k][0] = acc[k][0] + dv.x;
+                        acc[k][1] = acc[k][1] + dv.y;
+                        acc[k][2] = acc[k][2] + dv.z;
+                        acc[k][3] = acc[k][3] + dv.w;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);      // reads four ahead, not thirty: registers
+                }
+            }
+            mean_of_all(acc, Mf, Minv);
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) {
+                v[q][k].x = acc[k][0] + r * v[q][k].x;
+                v[q][k].y = acc[k][1] + r * v[q][k].y;
+                v[q][k].z = acc[k][2] + r * v[q][k].z;
+                v[q][k].w = acc[k][3] + r * v[q][k].w;
+            }
+        }
+    }
+}
+
+// A pair from loads to stores (compress_uniform, resolve_posted and finish_uniform for both tiles at once).
+template <bool MANY>
+__device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A, const TileRec &T, const Scratch &X, int set,
+                                            SyncShared &S, float *exchanges, float *tables)
+{
+    const int64_t start = (int64_t)T.tile * TILE;
+    float *te = A.err + start;
+    unsigned h[SERVER_CHUNK], h1[SERVER_CHUNK];
+    float4 v[2][SUBROWS];
+    load_sign_dwords(A, start, 0, h);
+    if (MANY) load_sign_dwords(A, start, SERVER_CHUNK, h1);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) v[q][k] = stream_load4(te + pair_base(q, k));
+    __builtin_amdgcn_sched_barrier(0);
+    const BlockSpan sp = span_of(T.bs(), T.be());
+    const LoadedCorrection corr = loaded_correction(L, T.fb, X, set);
+    correct_loaded_residual(v[0], corr);
+    correct_loaded_residual(v[1], corr);
+    server_values_pair<MANY>(A, start, T.fb, h, h1, v, exchanges, tables);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        reinterpret_cast<uint16_t *>(A.signs)[(start >> 4) + (2 * wave_id() + q) * 64 + sign_half_place()] =
+            (uint16_t)sign_half(v[q], TILE);
+        const double quarter = wave_sum(abs_sum(v[q], TILE));
+        if (lane_id() == 0) S.red[2 * wave_id() + q] = quarter;
+    }
+    __syncthreads();
+    const double first = ((S.red[0] + S.red[1]) + S.red[2]) + S.red[3], second = ((S.red[4] + S.red[5]) + S.red[6]) + S.red[7];
+    __syncthreads();
+    bool finished = false;
+    float s = 0.f;
+    if (threadIdx.x < 2) {
+        const unsigned long long w = (unsigned long long)__double_as_longlong(threadIdx.x ? second : first);
+        __hip_atomic_store(set_part(X, L, set) + 2 * ((int64_t)T.tile + threadIdx.x), w | (set_tag(X, set) ? TAG_BIT : 0ull),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (is_counted(L, sp)) {
+        if ((int64_t)T.tile + 1 == last_whole_tile(sp))
+            finished = finish_block(T.fb, sp, L, X, set, A.scales, S, &s);
+        else
+            finished = wait_ready(sp, 0ull, L, X, set, S, &s);
+        if (!finished) {
+            defer_segment(T.tile, 0, X, set);
+            defer_segment(T.tile + 1, 0, X, set);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (finished)
+#pragma unroll
+            for (int k = 0; k < SUBROWS; ++k) residual4(v[q][k], s);
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) stream_store4(te + pair_base(q, k), v[q][k]);
+    }
+}
+
+// Server part of Algorithm 4, all tiles in one launch, in the order of k_worker_tiles.  p~ as
 // above, then compressed like a worker's p; the workgroup of a whole tile waits in the kernel for its block's scale.
-// Bound by HBM and, where blocks wait for their scale, by the workgroups resident meanwhile.  Workgroups per CU:
+// Bound by HBM and, where blocks wait for their scale, by the tiles resident meanwhile: a workgroup's life is
+// half decoding, half the wait for the slowest tile of its block.  PAIRS: two whole tiles of a block to a workgroup, both
+// loaded ahead of all else, so that a CU has 14 tiles instead of 8 (12 instead of 7 beyond eight workers), one wait and
+// one table for two.  7 workers, 25 M elements of a bottleneck network: 54.9 -> 44.3 us; 16 workers, 354 M of a
+// transformer, whose blocks of 1025 tiles then finish in one pass: 1092 -> 907; 8 workers, 2^28 in blocks of 2^20:
+// 450 -> 400.  Where nothing waits (every block beyond the limit) one tile to a workgroup is the faster (4
+// workers, 2^26: 4 us less).  Workgroups per CU:
+//   pairs               seven (72 VGPRs), MANY six (80, 10 spilled); one less each: 46.3 us, 942 us
 //   whole tiles only    eight (64 VGPRs; 2^28 elements, 8 workers, blocks of 2^20: 457 us against 465 at seven, 491 at six)
 //   tiles of few segments, or MANY    seven (68 VGPRs, none spilled; with the dense tiles' code at eight 39 are)
 //   dense tiles         six (80 VGPRs; 643 965 tiny blocks, 2 workers: 46.3 us against 49.4 at seven, where 6 spill;
 //                       16 workers, 300 000: 51.0 against 52.8)
 // MANY: more than SERVER_CHUNK workers.
-template <bool SEGMENTS>
+template <bool SEGMENTS, int FLOATS>
 struct ServerShared : SyncShared {
-    float val[SERVER_LDS];
+    float val[FLOATS];
 };
-template <>
-struct ServerShared<true> : TileShared {};
-static_assert(SERVER_LDS <= TILE, "one array for the sum tables and for the segments");
+template <int FLOATS>
+struct ServerShared<true, FLOATS> : TileShared {
+    static_assert(FLOATS <= TILE, "one array for the sum tables, the exchanges and the segments");
+};
 
-template <int TILES, bool MANY>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(TILES == DENSE_TILES ? 6 : TILES == FEW_TILES || MANY ? 7 : 8, 8)))
+// Workgroups per CU.
+constexpr int server_occupancy(int tiles, bool many, bool pairs)
+{
+    return pairs ? (many ? 6 : 7) : tiles == DENSE_TILES ? 6 : tiles == FEW_TILES || many ? 7 : 8;
+}
+
+template <int TILES, bool MANY, bool PAIRS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(server_occupancy(TILES, MANY, PAIRS), 8)))
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
     constexpr bool MIXED = TILES != ALL_WHOLE;
-    __shared__ __align__(16) ServerShared<MIXED> S;
+    constexpr int EXCHANGE = PAIRS ? (MANY ? 2 : 1) * PAIR_EXCHANGE : 0;
+    __shared__ __align__(16) ServerShared<MIXED, (EXCHANGE > SERVER_LDS ? EXCHANGE : SERVER_LDS)> S;
     float *lds = S.val;
     float4 tv[SUBROWS], p[SUBROWS];
-    if (!MIXED) {
-        // tile i is workgroup i's: its residual is asked for before anything is looked up
+    unsigned h[SERVER_CHUNK];
+    if (!MIXED && !PAIRS) {
+        // tile i is workgroup i's: its sign words and its residual are asked for before anything is looked up
+        load_sign_halves(A, (int64_t)blockIdx.x * TILE, 0, h);
         load_tile(A.err + (int64_t)blockIdx.x * TILE, tv, TILE);
         __builtin_amdgcn_sched_barrier(0);
     }
     const Scratch X = open_call(R);
-    const TileRec T = MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
-    const int32_t tile = MIXED ? T.tile : (int32_t)blockIdx.x;
+    const TileRec T = PAIRS ? L.paired_tiles[blockIdx.x] : MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
+    if constexpr (PAIRS) {
+        if (T.words == TILE_PAIR) {
+            __shared__ __align__(16) float tables[MANY ? PAIR_TABLES : SUM_TABLE];
+            server_pair<MANY>(L, A, T, X, set, S, lds, tables);
+            snapshot_call(R);
+            return;
+        }
+    }
+    const int32_t tile = MIXED || PAIRS ? T.tile : (int32_t)blockIdx.x;
     const int64_t tile_start = (int64_t)tile * TILE;
     const int n_valid = MIXED ? tile_valid(L, tile) : TILE;
     float *te = A.err + tile_start;
     if (!MIXED || T.words < 0) {
-        if (MIXED) load_tile(te, tv, TILE);
+        if (MIXED || PAIRS) {
+            load_sign_halves(A, tile_start, 0, h);
+            load_tile(te, tv, TILE);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         Posted P;
         const BlockSpan sp = span_of(T.bs(), T.be());
         const LoadedCorrection corr = loaded_correction(L, T.fb, X, set);
         correct_loaded_residual(tv, corr);
-        server_values_whole<MANY>(A, tile_start, T.fb, tv, p, lds);
+        server_values_whole<MANY>(A, tile_start, T.fb, h, tv, p, lds);
         const int kind = compress_uniform(p, L, tile, T.fb, sp, TILE, A.signs, A.scales, te, X, set, S, P);
         resolve_posted(P, L, X, set, A.scales, S);
         if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);

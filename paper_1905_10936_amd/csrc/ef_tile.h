@@ -88,11 +88,12 @@ constexpr int FUSE_LIMIT_MAX = 4096;                     // most tiles a one-pas
 // What the kernels need to know about a tile, in one record: looked up piece by piece (tile, its block, the
 // block's ends) it is three dependent loads before the first scale can be asked for, and two more between
 // a tile's sum and its posting.
+constexpr int32_t TILE_ALONE = -1, TILE_PAIR = -2;
 struct alignas(32) TileRec {
     int32_t tile;
     int32_t fb;                 // first block
     int32_t nseg;               // segments; < 0: that many, and the tile is a dense one
-    int32_t words;              // < 0: a whole tile; else which set of start words (its place among the mixed tiles)
+    int32_t words;              // < 0: a whole tile (TILE_PAIR: it and the next one); else which set of start words (its place among the mixed tiles)
     int32_t tail;               // 0, or, if the last of several segments goes on past the tile: its block's tiles * 2,
                                 // + 1 if the block ends inside its last tile
     int32_t t0, n;              // tiles of the first block
@@ -122,6 +123,8 @@ struct Layout {
     const TileRec *tiles;         // [ntiles]
     int32_t n_grid;
     const TileRec *grid_tiles;    // [n_grid] as the kernels with one workgroup per tile take them: the dense ones first
+    int32_t n_paired;
+    const TileRec *paired_tiles;  // [n_paired] the same for k_server_tiles with two whole tiles to a workgroup
     const StartWord *words;       // [n_mixed][TILE_WORDS]
     int32_t n_dense;              // mixed tiles of many segments
     // Deferred correction (see Scratch::lazy_scales): on or off, and for every block its position
@@ -496,13 +499,12 @@ __device__ __forceinline__ void residual4(float4 &v, float s)
     v.w = residual(v.w, s);
 }
 
-// Sign words of the tile whose values are in p (bit = p >= 0, Appendix A with
-// sign(0) read as +1; elements past n_valid give 0 bits).  A lane's 16 bits are four from each of its
+// Sign bits (bit = p >= 0, Appendix A with sign(0) read as +1; elements past n_valid give 0 bits) of a quarter of a tile,
+// 1024 elements a wavefront: which 16 bits of it a lane has the answer tells.  A lane's 16 bits are four from each of its
 // sub-rows; four neighbouring lanes transpose their 4 x 4 nibbles (two exchanges) so that each is left
-// with 16 consecutive elements of one sub-row, and stores those: the wavefront's 64 half-words fill 128 contiguous
-// bytes.  (Gathering the nibbles of each sub-row's words over 16 lanes took 110 vector instructions, this 50.)
-__device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_valid, uint64_t *signs,
-                                            int64_t tile_start, int64_t W)
+// with 16 consecutive elements of one sub-row.  (Gathering the nibbles of each sub-row's words over 16 lanes took 110
+// vector instructions, this 50.)
+__device__ __forceinline__ unsigned sign_half(const float4 (&p)[SUBROWS], int n_valid)
 {
     const int lane = lane_id();
     unsigned v = 0;                     // bits 4k .. 4k + 3: this lane's elements of sub-row k
@@ -521,8 +523,17 @@ __device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_va
     const unsigned t = __builtin_amdgcn_perm(w, v, (lane & 2) ? 0x0c0c0105u : 0x0c0c0400u);
     const unsigned u = row_move<EF_DPP_XOR1>(t);
     const unsigned own = (lane & 1) ? 0xf0f0u : 0x0f0fu;
-    const unsigned half = (t & own) | (((lane & 1) ? u >> 4 : u << 4) & ~own);
-    const int64_t at = (tile_start >> 4) + wave_id() * 64 + 16 * (lane & 3) + (lane >> 2);
+    return (t & own) | (((lane & 1) ? u >> 4 : u << 4) & ~own);
+}
+// Where they go, in half-words from the quarter's first: the 64 of a wavefront fill 128 contiguous bytes.
+__device__ __forceinline__ int sign_half_place() { return 16 * (lane_id() & 3) + (lane_id() >> 2); }
+
+// Sign words of the tile whose values are in p.
+__device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_valid, uint64_t *signs,
+                                            int64_t tile_start, int64_t W)
+{
+    const unsigned half = sign_half(p, n_valid);
+    const int64_t at = (tile_start >> 4) + wave_id() * 64 + sign_half_place();
     if (n_valid == TILE || at < 4 * W) reinterpret_cast<uint16_t *>(signs)[at] = (uint16_t)half;
 }
 
@@ -544,7 +555,7 @@ __device__ __forceinline__ double abs_sum(const float4 (&p)[SUBROWS], int n_vali
 
 // LDS of a workgroup: what every kernel needs for reductions and broadcasts ...
 struct SyncShared {
-    double red[NWAVES];
+    double red[2 * NWAVES];     // one a wavefront, two where it has two tiles (k_server_pairs)
     int flag[2];
     unsigned ticket;
 };
