@@ -537,43 +537,54 @@ int build_device(ef_plan *p)
     // The order in which the kernels with one workgroup per tile take the tiles: the dense ones, then the others
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
-    std::vector<ef::TileRec> in_order, mixed_recs;
-    for (int32_t t : mixed) mixed_recs.push_back(tiles[(size_t)t]);
-    if (!mixed.empty()) {
-        in_order.reserve((size_t)ntiles);
-        for (int32_t t : dense) in_order.push_back(tiles[(size_t)t]);
-        size_t w = 0;
-        for (int32_t t : mixed) {
-            const ef::TileRec &r = tiles[(size_t)t];
-            if (r.nseg < 0) continue;
-            const int64_t at = ef::few_place(t, r.t0, r.n, r.from != 0, awaited);
-            while (w < whole.size() && whole[w] < at) in_order.push_back(tiles[(size_t)whole[w++]]);
-            in_order.push_back(r);
+    // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least three in
+    // four tiles are in pairs that wait for their block.  Its limit is then half of the tiles that this kernel keeps
+    // resident, 1792 or 1536.
+    const int32_t pair_limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
+    const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 4 >= (size_t)ntiles * 3;
+    std::vector<uint32_t> in_order, paired;
+    int64_t waiting = 0;
+    if (!mixed.empty()) in_order.reserve((size_t)ntiles);
+    if (may_pair) paired.reserve((size_t)ntiles);
+    size_t w = 0;
+    bool is_second = false;
+    int32_t block = -1;
+    int64_t counts = 0;                         // what a pair of the block adds to `waiting`
+    auto whole_up_to = [&](int64_t end) {       // the whole tiles below `end` that have not come yet
+        for (; w < whole.size() && whole[w] < end; ++w) {
+            const int32_t t = whole[w];
+            if (!mixed.empty()) in_order.push_back((uint32_t)t);
+            if (!may_pair) continue;
+            if (fb[t] != block) {
+                block = fb[t];
+                is_second = false;
+                counts = tiles_of_block(p, block) <= pair_limit ? 2 : 0;
+            }
+            if (is_second) {
+                is_second = false;
+                continue;
+            }
+            is_second = w + 1 < whole.size() && whole[w + 1] == t + 1 && fb[t + 1] == block;
+            paired.push_back((uint32_t)t | (is_second ? ef::PAIR_BIT : 0u));
+            waiting += is_second ? counts : 0;
         }
-        while (w < whole.size()) in_order.push_back(tiles[(size_t)whole[w++]]);
+    };
+    auto take = [&](int32_t t) {
+        in_order.push_back((uint32_t)t);
+        if (may_pair) paired.push_back((uint32_t)t);
+    };
+    for (int32_t t : dense) take(t);
+    for (int32_t t : mixed) {
+        const ef::TileRec &r = tiles[(size_t)t];
+        if (r.nseg < 0) continue;
+        whole_up_to(ef::few_place(t, r.t0, r.n, r.from != 0, awaited));
+        take(t);
     }
-    // The same with the whole tiles of a block two by two, where at least three in four tiles are in pairs that wait for
-    // their block.  The limit is then half of the tiles that this kernel keeps resident, 1792 or 1536.
-    std::vector<ef::TileRec> paired;
-    {
-        const int32_t limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
-        std::vector<char> second((size_t)ntiles, 0);
-        int64_t waiting = 0;
-        paired.reserve((size_t)ntiles);
-        for (const ef::TileRec &r : mixed.empty() ? tiles : in_order) {
-            if (second[(size_t)r.tile]) continue;
-            paired.push_back(r);
-            const int32_t next = r.tile + 1;
-            if (r.words >= 0 || next >= ntiles || tiles[(size_t)next].words >= 0 || tiles[(size_t)next].fb != r.fb) continue;
-            paired.back().words = ef::TILE_PAIR;
-            second[(size_t)next] = 1;
-            waiting += r.n <= limit ? 2 : 0;
-        }
-        if (p->max_workers > ef::PAIR_WORKERS || waiting * 4 < (int64_t)ntiles * 3)
-            paired.clear();
-        else
-            p->lim_server = limit;
-    }
+    whole_up_to(ntiles);
+    if (waiting * 4 < (int64_t)ntiles * 3)
+        paired.clear();
+    else
+        p->lim_server = pair_limit;
     p->L.n_paired = (int32_t)paired.size();
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
@@ -593,10 +604,13 @@ int build_device(ef_plan *p)
     mem.add(&p->d_mixed, mixed.size(), Arena::COPY, mixed.data());
     mem.add(&p->d_whole, whole.size(), Arena::COPY, whole.data());
     mem.add(&p->d_tiles, nt, Arena::COPY, tiles.data());
-    mem.add(&p->d_in_order, in_order.size(), Arena::COPY, in_order.data());
-    mem.add(&p->d_paired, paired.size(), Arena::COPY, paired.data());
+    uint32_t *d_order[3];           // of d_in_order, d_paired and d_mixed_recs
+    mem.add(&d_order[0], in_order.size(), Arena::COPY, in_order.data());
+    mem.add(&d_order[1], paired.size(), Arena::COPY, paired.data());
+    mem.add(&p->d_in_order, in_order.size(), Arena::LEAVE);
+    mem.add(&p->d_paired, paired.size(), Arena::LEAVE);
     mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
-    mem.add(&p->d_mixed_recs, mixed_recs.size(), Arena::COPY, mixed_recs.data());
+    mem.add(&p->d_mixed_recs, mixed.size(), Arena::LEAVE);
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
@@ -621,6 +635,15 @@ int build_device(ef_plan *p)
     p->L.tiles = p->d_tiles;
     p->L.grid_tiles = p->L.n_mixed ? p->d_in_order : p->d_tiles;
     p->L.paired_tiles = p->d_paired;
+    d_order[2] = reinterpret_cast<uint32_t *>(p->d_mixed);
+    const size_t n_order[3] = {in_order.size(), paired.size(), mixed.size()};
+    ef::TileRec *const taken[3] = {p->d_in_order, p->d_paired, p->d_mixed_recs};
+    for (int k = 0; k < 3; ++k) {
+        if (!n_order[k]) continue;
+        hipLaunchKernelGGL(ef::k_take_records, dim3((unsigned)((n_order[k] + ef::THREADS - 1) / ef::THREADS)), dim3(ef::THREADS), 0, nullptr,
+                           (const ef::TileRec *)p->d_tiles, (const uint32_t *)d_order[k], (int)n_order[k], taken[k]);
+        EF_HIP(hipGetLastError());
+    }
     p->L.words = p->d_words;
     p->L.mixed_recs = p->d_mixed_recs;
     p->L.offs = p->d_offs;

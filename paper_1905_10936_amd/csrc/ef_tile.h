@@ -1240,6 +1240,18 @@ __device__ __forceinline__ void build_segment_index(const Layout &L, int32_t til
     __syncthreads();
 }
 
+// Tile records in another order (plan creation: a list of 4-byte numbers is copied to the device, not 32-byte records).  The
+// top bit of a number: the tile and the next one as a pair.
+constexpr uint32_t PAIR_BIT = 1u << 31;
+__global__ __launch_bounds__(THREADS) void k_take_records(const TileRec *tiles, const uint32_t *order, int n, TileRec *out)
+{
+    const int i = blockIdx.x * THREADS + threadIdx.x;
+    if (i >= n) return;
+    TileRec r = tiles[order[i] & ~PAIR_BIT];
+    if (order[i] & PAIR_BIT) r.words = TILE_PAIR;
+    out[i] = r;
+}
+
 // Start words of the mixed tiles (plan creation).  One workgroup per mixed tile.
 __global__ __launch_bounds__(THREADS) void k_start_words(Layout L, StartWord *words)
 {
