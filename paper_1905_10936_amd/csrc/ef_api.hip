@@ -24,7 +24,8 @@ struct ef_plan {
     // the kernel's own grid keeps resident): role 0 = the persistent worker kernel, 1 = the server,
     // 2 = the worker kernel that runs one workgroup per tile.
     struct Role {
-        int32_t fuse_limit;
+        int32_t fuse_limit, keep;   // see Layout
+        bool beyond;                // there are blocks larger than fuse_limit
         uint32_t n_static;          // segments whose p the first kernels always park
         uint32_t n_late;            // blocks whose scale the first kernels never write
         uint32_t *d_static;         // [n_static]
@@ -294,8 +295,17 @@ bool finishes_with_mixed(const ef_plan *p, const ef_plan::Role &r, int64_t b)
     return n >= 2 && n <= r.fuse_limit && !has_uniform_tile(p, b);
 }
 
+// Host mirror of first_kept in ef_tile.h.
+int64_t first_kept(const ef_plan *p, const ef_plan::Role &r, int64_t b)
+{
+    const int64_t *o = p->offs_host.data();
+    const int64_t first = o[b] % ef::TILE != 0 ? 1 : 0, whole = tiles_of_block(p, b) - first - (o[b + 1] % ef::TILE != 0 ? 1 : 0);
+    const int64_t parked = whole > r.keep ? whole - r.keep : 0;
+    return o[b] / ef::TILE + first + parked + (parked & 1);
+}
+
 // What the main kernels of a call always leave to the kernel that ends it: the scales of the
-// blocks larger than fuse_limit, and the residual of every open segment that is not finished
+// blocks larger than fuse_limit (in the deferred mode, or if they have no whole tile), and the residual of every open segment that is not finished
 // where it is computed (the segments of those large blocks and, before the persistent worker kernel, the segments
 // that blocks with whole tiles have in mixed tiles).
 int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
@@ -304,9 +314,13 @@ int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
     std::vector<int32_t> late, late_index, lazy_tiles;
     if (p->lazy) late_index.assign((size_t)p->L.B, -1);
     const int64_t *o = p->offs_host.data();
+    r.keep = p->lazy ? 0 : r.fuse_limit;
+    r.beyond = false;
     for (int64_t b = 0; b < p->L.B; ++b) {
         const int64_t n = tiles_of_block(p, b);
         if (n < 2 || n <= r.fuse_limit) continue;
+        r.beyond = true;
+        if (r.keep > 0 && has_uniform_tile(p, b)) continue;     // its last whole tile forms the scale
         if (p->lazy && has_uniform_tile(p, b)) late_index[(size_t)b] = (int32_t)late.size();
         late.push_back((int32_t)b);
     }
@@ -320,9 +334,9 @@ int static_list(ef_plan *p, ef_plan::Role &r, std::vector<uint32_t> &all)
         const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
         const bool full = end <= p->L.d;
         if (fb == lb && full) {
-            // a whole tile parks p only for blocks beyond fuse_limit
+            // a whole tile parks p only for blocks beyond fuse_limit, and their last whole tiles do not
             const bool open = (o[fb] < start) || (o[fb + 1] > end);
-            if (open && tiles_of_block(p, fb) > r.fuse_limit) {
+            if (open && tiles_of_block(p, fb) > r.fuse_limit && !(r.keep > 0 && t >= first_kept(p, r, fb))) {
                 if (p->lazy)
                     lazy_tiles.push_back(t);        // deferred: corrected when the buffer is next loaded
                 else
@@ -537,19 +551,18 @@ int build_device(ef_plan *p)
     // The order in which the kernels with one workgroup per tile take the tiles: the dense ones, then the others
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
-    // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least three in
-    // four tiles are in pairs that wait for their block.  Its limit is then half of the tiles that this kernel keeps
-    // resident, 1792 or 1536.
+    // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least half of the
+    // tiles are in pairs.  Its limit is then half of the tiles that this kernel keeps
+    // resident, 1792 or 1536.  (Four blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
     const int32_t pair_limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
-    const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 4 >= (size_t)ntiles * 3;
+    const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 2 >= (size_t)ntiles;
     std::vector<uint32_t> in_order, paired;
-    int64_t waiting = 0;
+    int64_t in_pairs = 0;
     if (!mixed.empty()) in_order.reserve((size_t)ntiles);
     if (may_pair) paired.reserve((size_t)ntiles);
     size_t w = 0;
     bool is_second = false;
     int32_t block = -1;
-    int64_t counts = 0;                         // what a pair of the block adds to `waiting`
     auto whole_up_to = [&](int64_t end) {       // the whole tiles below `end` that have not come yet
         for (; w < whole.size() && whole[w] < end; ++w) {
             const int32_t t = whole[w];
@@ -558,7 +571,6 @@ int build_device(ef_plan *p)
             if (fb[t] != block) {
                 block = fb[t];
                 is_second = false;
-                counts = tiles_of_block(p, block) <= pair_limit ? 2 : 0;
             }
             if (is_second) {
                 is_second = false;
@@ -566,7 +578,7 @@ int build_device(ef_plan *p)
             }
             is_second = w + 1 < whole.size() && whole[w + 1] == t + 1 && fb[t + 1] == block;
             paired.push_back((uint32_t)t | (is_second ? ef::PAIR_BIT : 0u));
-            waiting += is_second ? counts : 0;
+            in_pairs += is_second ? 2 : 0;
         }
     };
     auto take = [&](int32_t t) {
@@ -581,7 +593,7 @@ int build_device(ef_plan *p)
         take(t);
     }
     whole_up_to(ntiles);
-    if (waiting * 4 < (int64_t)ntiles * 3)
+    if (in_pairs * 2 < (int64_t)ntiles)
         paired.clear();
     else
         p->lim_server = pair_limit;
@@ -721,7 +733,7 @@ int worker_role(const ef_plan *plan, bool has_mom)
 bool small_call(const ef_plan *plan, int role, int nsets)
 {
     return plan->has_small && plan->kernels_auto && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs &&
-           plan->role[role].n_late == 0;
+           !plan->role[role].beyond;
 }
 
 // The updates, where nothing waits: as long as all of it is resident (with / without, weight decay, blocks of
@@ -764,6 +776,7 @@ ef::Layout role_layout(const ef_plan *plan, int role)
 {
     ef::Layout L = plan->L;
     L.fuse_limit = plan->role[role].fuse_limit;
+    L.keep = plan->role[role].keep;
     L.lazy = plan->lazy;
     L.late_index = plan->role[role].d_late_index;
     L.sync_group = plan->sync_group;
@@ -850,7 +863,8 @@ int ef_plan_create(ef_plan **out, const int64_t *block_offsets_host, int64_t B, 
     p->lazy_sets_seen = 0;
     for (auto &r : p->role) {
         r.n_static = r.n_late = r.n_lazy_tiles = 0;
-        r.fuse_limit = 0;
+        r.fuse_limit = r.keep = 0;
+        r.beyond = false;
     }
     p->has_small = false;
     p->kernels_auto = true;

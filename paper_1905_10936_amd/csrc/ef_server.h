@@ -581,12 +581,15 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
         __hip_atomic_store(set_part(X, L, set) + 2 * ((int64_t)T.tile + threadIdx.x), w | (set_tag(X, set) ? TAG_BIT : 0ull),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (is_counted(L, sp)) {
+    const bool counted = is_counted(L, sp), kept = counted || (L.keep > 0 && (int64_t)T.tile >= first_kept(L, sp));
+    if (counted || L.keep > 0) {
         if ((int64_t)T.tile + 1 == last_whole_tile(sp))
             finished = finish_block(T.fb, sp, L, X, set, A.scales, S, &s);
-        else
+        else if (kept)
             finished = wait_ready(sp, 0ull, L, X, set, S, &s);
-        if (!finished) {
+        if (!kept)
+            finished = false;           // parked like the others of its block, whatever it has formed
+        else if (!finished) {
             defer_segment(T.tile, 0, X, set);
             defer_segment(T.tile + 1, 0, X, set);
         }

@@ -48,8 +48,8 @@
 // scale; they never wait for a whole tile: a block without whole tiles is
 // finished among them (its last tile forms its scale, the
 // others wait for it), while the segments that a block with whole tiles has in
-// them get p parked in the residual buffer.  Parked p (those segments, all
-// tiles of blocks larger than fuse_limit, any tile whose bounded wait ran out) is finished by one kernel
+// them get p parked in the residual buffer.  Parked p (those segments, the
+// tiles of blocks larger than fuse_limit but for the last ones (first_kept), any tile whose bounded wait ran out) is finished by one kernel
 // after the main one, which also computes the scales still missing and steps
 // the plan to its next call.
 //
@@ -113,6 +113,7 @@ struct Layout {
     int64_t W;                  // sign words
     int32_t ntiles;
     int32_t fuse_limit;         // blocks of up to this many tiles finish in one pass
+    int32_t keep;               // of larger ones about this many of the last whole tiles do too (see first_kept); 0: none
     int32_t n_mixed, n_uniform;
     const int64_t *offs;        // [B+1] device copy of block_offsets
     const int32_t *tile_fb;     // [ntiles] block holding the tile's first element
@@ -618,6 +619,19 @@ __device__ __forceinline__ bool finishes_with_mixed(const Layout &L, const Block
     return is_counted(L, s) && !has_uniform_tile(s);
 }
 
+// A block larger than fuse_limit: its whole tiles from this one on keep p and wait for the scale like those of a one-pass
+// block do, so that the pass over what was parked leaves them out; its last whole tile forms the scale.  (An even number of
+// whole tiles is parked: pairs are of one kind.)  As many as are sure to be resident are kept, the limit again.  us without
+// and with: server, 16 workers, a block of 12 565 tiles in 86 000, 901 / 876 (the pass over what is parked 68 -> 59, and
+// k_tail no longer adds up 12 565 partial sums, 24 -> 5); worker, the same layout, 1301 / 1289; step of 4 workers with
+// four blocks of 2049 tiles on the server, 917 / 905, and 891 with pairs, whose limit is 1792.
+__device__ __forceinline__ int64_t first_kept(const Layout &L, const BlockSpan &s)
+{
+    const int first = (s.bs % TILE) != 0 ? 1 : 0, whole = s.n - first - ((s.be % TILE) != 0 ? 1 : 0);
+    const int parked = whole > L.keep ? whole - L.keep : 0;
+    return s.t0 + first + parked + (parked & 1);
+}
+
 // Scratch word of block b's segment in tile t: slot 1 of the block's first tile
 // if b starts inside that tile (it is then the tile's last segment), slot 0
 // everywhere else (first or only segment).
@@ -698,58 +712,44 @@ __device__ __forceinline__ double sum_block_partials(const Layout &L, int64_t b,
 // Wait (bounded) until every tile of block b has posted this call's partial,
 // then form the block's scale.  Called by every thread of the workgroup with
 // the same arguments; returns the same answer to all of them.
-constexpr int GATHER_KEEP = 4;      // partial words per thread whose values are kept while polling
+constexpr int GATHER_DEEP = 4;      // partial words a thread has in flight
 
 __device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &L, const Scratch &X, int set, SyncShared &S,
                                              float *s)
 {
     const unsigned long long *part = set_part(X, L, set);
     const unsigned long long tag = set_tag(X, set);
-    // Thread t is in charge of tiles t, t + 256, ...  All of them are polled in every round, so
-    // that the loads of a round overlap.  The values of the first GATHER_KEEP (blocks of up to
-    // 1024 tiles: all) are kept as they arrive; words beyond that are only checked for this
-    // call's tag and read once more when everything has arrived.
-    double v[GATHER_KEEP];
-    unsigned have = 0;
-#pragma unroll
-    for (int q = 0; q < GATHER_KEEP; ++q) v[q] = 0.0;
-    bool complete = false;
-    for (int it = 0; it < X.spin_limit; ++it) {
-        int all = 1;
-#pragma unroll
-        for (int q = 0; q < GATHER_KEEP; ++q) {
-            const int i = (int)threadIdx.x + q * THREADS;
-            if (i < sp.n && !((have >> q) & 1u)) {
-                const unsigned long long w =
-                    __hip_atomic_load(part + part_index(sp.t0 + i, sp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((w >> 63) == tag) {
-                    v[q] = __longlong_as_double((long long)(w & ~TAG_BIT));
-                    have |= 1u << q;
-                } else {
-                    all = 0;
-                }
+    // Thread t is in charge of tiles t, t + 256, ..., and adds them in this order (that of sum_block_partials), a few at a
+    // time: all of them are asked for in every round, so that the loads of a round overlap, until all have this
+    // call's tag.
+    double acc = 0.0;
+    int polls = 0, ok = 1;
+#pragma unroll 1
+    for (int from = 0; from < sp.n && ok; from += GATHER_DEEP * THREADS) {
+        unsigned long long w[GATHER_DEEP];
+        const int mine = from + (int)threadIdx.x;
+        for (;;) {
+            if (polls++ >= X.spin_limit) {
+                ok = 0;
+                break;
             }
-        }
-        for (int i = (int)threadIdx.x + GATHER_KEEP * THREADS; i < sp.n; i += THREADS) {
-            const unsigned long long w =
-                __hip_atomic_load(part + part_index(sp.t0 + i, sp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((w >> 63) != tag) all = 0;
-        }
-        if (__syncthreads_and(all)) {
-            complete = true;
-            break;
-        }
-        __builtin_amdgcn_s_sleep(8);
-    }
-    if (!complete) return false;
-    double acc = 0.0;               // same order as sum_block_partials: thread t adds tiles t, t + 256, ... ascending
 #pragma unroll
-    for (int q = 0; q < GATHER_KEEP; ++q) acc += v[q];   // absent words were left at +0
-    for (int i = (int)threadIdx.x + GATHER_KEEP * THREADS; i < sp.n; i += THREADS) {
-        const unsigned long long w =
-            __hip_atomic_load(part + part_index(sp.t0 + i, sp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        acc += __longlong_as_double((long long)(w & ~TAG_BIT));
+            for (int q = 0; q < GATHER_DEEP; ++q)           // past the block: its last word, not used
+                if (from + q * THREADS < sp.n)
+                    w[q] = __hip_atomic_load(part + part_index(sp.t0 + min(mine + q * THREADS, sp.n - 1), sp), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+            bool all = true;
+#pragma unroll
+            for (int q = 0; q < GATHER_DEEP; ++q)
+                if (from + q * THREADS < sp.n) all = all && (w[q] >> 63) == tag;
+            if (all) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+#pragma unroll
+        for (int q = 0; q < GATHER_DEEP; ++q)
+            if (from + q * THREADS < sp.n) acc += mine + q * THREADS < sp.n ? __longlong_as_double((long long)(w[q] & ~TAG_BIT)) : 0.0;
     }
+    if (!__syncthreads_and(ok)) return false;
     const double total = block_sum(acc, S.red);
     *s = (float)(total / (double)(sp.be - sp.bs));
     return true;
@@ -998,7 +998,7 @@ __device__ __forceinline__ void correct_loaded_residual(float4 (&e)[SUBROWS], co
 // Returns what is left to do with it:
 //   UNI_DONE    the block is this tile alone: scale and residual written;
 //   UNI_PARKED  block larger than fuse_limit: partial posted, p parked for the
-//               kernel that ends the call;
+//               kernel that ends the call (P may say that this tile must form the scale all the same);
 //   UNI_PENDING partial posted: p stays with the caller until the block's
 //               scale is posted; P says whether this tile must form it.
 //   UNI_HELD    (only with hold = true) as UNI_PARKED, but p is still to be written by the caller,
@@ -1023,16 +1023,15 @@ __device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layo
         return UNI_DONE;
     }
     store_partial(total, 0, tile, L, X, set);
-    if (!is_counted(L, sp)) {
-        if (hold && L.sync_group > 1) return UNI_HELD;
-        store_tile(err_tile, p, n_valid);
-        return UNI_PARKED;
-    }
-    if ((int64_t)tile == gatherer_tile(L, sp)) {
+    const bool counted = is_counted(L, sp);
+    if ((counted || L.keep > 0) && (int64_t)tile == gatherer_tile(L, sp)) {
         P.gather = b;
         P.sp = sp;
     }
-    return UNI_PENDING;
+    if (counted || (L.keep > 0 && (int64_t)tile >= first_kept(L, sp))) return UNI_PENDING;
+    if (hold && L.sync_group > 1) return UNI_HELD;
+    store_tile(err_tile, p, n_valid);
+    return UNI_PARKED;
 }
 
 // Write the residual of a uniform tile of counted block b whose p was kept
