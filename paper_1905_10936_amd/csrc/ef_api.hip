@@ -616,13 +616,14 @@ int build_device(ef_plan *p)
     mem.add(&p->d_mixed, mixed.size(), Arena::COPY, mixed.data());
     mem.add(&p->d_whole, whole.size(), Arena::COPY, whole.data());
     mem.add(&p->d_tiles, nt, Arena::COPY, tiles.data());
-    uint32_t *d_order[3];           // of d_in_order, d_paired and d_mixed_recs
-    mem.add(&d_order[0], in_order.size(), Arena::COPY, in_order.data());
-    mem.add(&d_order[1], paired.size(), Arena::COPY, paired.data());
-    mem.add(&p->d_in_order, in_order.size(), Arena::LEAVE);
-    mem.add(&p->d_paired, paired.size(), Arena::LEAVE);
+    // the records in grid order, in pairs and the mixed ones alone, one after the other
+    const size_t n_in_order = in_order.size(), n_taken = n_in_order + paired.size() + mixed.size();
+    in_order.insert(in_order.end(), paired.begin(), paired.end());
+    in_order.insert(in_order.end(), mixed.begin(), mixed.end());
+    uint32_t *d_order;
+    mem.add(&d_order, n_taken, Arena::COPY, in_order.data());
+    mem.add(&p->d_in_order, n_taken, Arena::LEAVE);
     mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
-    mem.add(&p->d_mixed_recs, mixed.size(), Arena::LEAVE);
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
@@ -646,14 +647,12 @@ int build_device(ef_plan *p)
     p->L.whole_tiles = p->d_whole;
     p->L.tiles = p->d_tiles;
     p->L.grid_tiles = p->L.n_mixed ? p->d_in_order : p->d_tiles;
+    p->d_paired = p->d_in_order + n_in_order;
+    p->d_mixed_recs = p->d_paired + paired.size();
     p->L.paired_tiles = p->d_paired;
-    d_order[2] = reinterpret_cast<uint32_t *>(p->d_mixed);
-    const size_t n_order[3] = {in_order.size(), paired.size(), mixed.size()};
-    ef::TileRec *const taken[3] = {p->d_in_order, p->d_paired, p->d_mixed_recs};
-    for (int k = 0; k < 3; ++k) {
-        if (!n_order[k]) continue;
-        hipLaunchKernelGGL(ef::k_take_records, dim3((unsigned)((n_order[k] + ef::THREADS - 1) / ef::THREADS)), dim3(ef::THREADS), 0, nullptr,
-                           (const ef::TileRec *)p->d_tiles, (const uint32_t *)d_order[k], (int)n_order[k], taken[k]);
+    if (n_taken) {
+        hipLaunchKernelGGL(ef::k_take_records, dim3((unsigned)((n_taken + ef::THREADS - 1) / ef::THREADS)), dim3(ef::THREADS), 0, nullptr,
+                           (const ef::TileRec *)p->d_tiles, (const uint32_t *)d_order, (int)n_taken, p->d_in_order);
         EF_HIP(hipGetLastError());
     }
     p->L.words = p->d_words;

@@ -566,8 +566,7 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
     server_values_pair<MANY>(A, start, T.fb, h, h1, v, exchanges, tables);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        reinterpret_cast<uint16_t *>(A.signs)[(start >> 4) + (2 * wave_id() + q) * 64 + sign_half_place()] =
-            (uint16_t)sign_half(v[q], TILE);
+        store_quarter_signs<false>(sign_half(v[q], TILE), A.signs, (start >> 6) + (2 * wave_id() + q) * 16, L.W);
         const double quarter = wave_sum(abs_sum(v[q], TILE));
         if (lane_id() == 0) S.red[2 * wave_id() + q] = quarter;
     }

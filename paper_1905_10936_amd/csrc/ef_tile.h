@@ -353,6 +353,8 @@ __device__ __forceinline__ int tile_valid(const Layout &L, int32_t tile)
 #define EF_DPP_XOR2 0x4E            // quad_perm [2,3,0,1]
 #define EF_DPP_HALF_MIRROR 0x141    // lane i <- lane 7-i of its group of 8
 #define EF_DPP_MIRROR 0x140         // lane i <- lane 15-i of its row
+#define EF_DPP_FROM_4_ON 0x104      // lane i <- lane i+4 of its row (0 past the row)
+#define EF_DPP_FROM_8_ON 0x108      // lane i <- lane i+8
 template <int CTRL>
 __device__ __forceinline__ unsigned row_move(unsigned v)
 {
@@ -501,7 +503,7 @@ __device__ __forceinline__ void residual4(float4 &v, float s)
 }
 
 // Sign bits (bit = p >= 0, Appendix A with sign(0) read as +1; elements past n_valid give 0 bits) of a quarter of a tile,
-// 1024 elements a wavefront: which 16 bits of it a lane has the answer tells.  A lane's 16 bits are four from each of its
+// 1024 elements a wavefront: this lane's 16 of them, elements 256 (lane % 4) + 16 (lane / 4) on.  A lane's 16 bits are four from each of its
 // sub-rows; four neighbouring lanes transpose their 4 x 4 nibbles (two exchanges) so that each is left
 // with 16 consecutive elements of one sub-row.  (Gathering the nibbles of each sub-row's words over 16 lanes took 110
 // vector instructions, this 50.)
@@ -524,18 +526,31 @@ __device__ __forceinline__ unsigned sign_half(const float4 (&p)[SUBROWS], int n_
     const unsigned t = __builtin_amdgcn_perm(w, v, (lane & 2) ? 0x0c0c0105u : 0x0c0c0400u);
     const unsigned u = row_move<EF_DPP_XOR1>(t);
     const unsigned own = (lane & 1) ? 0xf0f0u : 0x0f0fu;
-    return (t & own) | (((lane & 1) ? u >> 4 : u << 4) & ~own);
+    return (t & own) | (((lane & 1) ? u >> 4 : u << 4) & (own ^ 0xffffu));
 }
-// Where they go, in half-words from the quarter's first: the 64 of a wavefront fill 128 contiguous bytes.
-__device__ __forceinline__ int sign_half_place() { return 16 * (lane_id() & 3) + (lane_id() >> 2); }
+// Sign bits of a quarter of a tile, stored from word `at` on: the 64 halves of a wavefront fill 128 contiguous bytes.
+// WORDS: four lanes' halves are put together first, and lanes 0 to 3 of each row of 16 store 8 bytes, which the momentum
+// worker with one workgroup per tile prefers (16 workers, 2734 tiles: 598.1 us against 600.6) and the others do not (server, 16
+// workers, 86 000 tiles: 892 against 868; momentum-free worker in blocks of 30 011: 66.6 against 66.0).
+template <bool WORDS>
+__device__ __forceinline__ void store_quarter_signs(unsigned half, uint64_t *signs, int64_t at, int64_t W)
+{
+    if constexpr (WORDS) {
+        const unsigned lo = half | (row_move<EF_DPP_FROM_4_ON>(half) << 16), hi = row_move<EF_DPP_FROM_8_ON>(lo);
+        const int64_t w = at + 4 * (lane_id() & 3) + (lane_id() >> 4);
+        if ((lane_id() & 15) < SUBROWS && w < W) signs[w] = ((uint64_t)hi << 32) | (uint64_t)lo;
+    } else {
+        const int64_t h = 4 * at + 16 * (lane_id() & 3) + (lane_id() >> 2);
+        if (h < 4 * W) reinterpret_cast<uint16_t *>(signs)[h] = (uint16_t)half;
+    }
+}
 
 // Sign words of the tile whose values are in p.
+template <bool WORDS>
 __device__ __forceinline__ void store_signs(const float4 (&p)[SUBROWS], int n_valid, uint64_t *signs,
                                             int64_t tile_start, int64_t W)
 {
-    const unsigned half = sign_half(p, n_valid);
-    const int64_t at = (tile_start >> 4) + wave_id() * 64 + sign_half_place();
-    if (n_valid == TILE || at < 4 * W) reinterpret_cast<uint16_t *>(signs)[at] = (uint16_t)half;
+    store_quarter_signs<WORDS>(sign_half(p, n_valid), signs, (tile_start >> 6) + wave_id() * 16, W);
 }
 
 // fp64 sum of |p| over the thread's valid elements, sub-row by sub-row
@@ -728,26 +743,26 @@ __device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &
     for (int from = 0; from < sp.n && ok; from += GATHER_DEEP * THREADS) {
         unsigned long long w[GATHER_DEEP];
         const int mine = from + (int)threadIdx.x;
+#pragma unroll
+        for (int q = 0; q < GATHER_DEEP; ++q) w[q] = tag << 63;         // past the block: +0 with this call's tag
         for (;;) {
             if (polls++ >= X.spin_limit) {
                 ok = 0;
                 break;
             }
 #pragma unroll
-            for (int q = 0; q < GATHER_DEEP; ++q)           // past the block: its last word, not used
-                if (from + q * THREADS < sp.n)
-                    w[q] = __hip_atomic_load(part + part_index(sp.t0 + min(mine + q * THREADS, sp.n - 1), sp), __ATOMIC_RELAXED,
+            for (int q = 0; q < GATHER_DEEP; ++q)
+                if (mine + q * THREADS < sp.n)
+                    w[q] = __hip_atomic_load(part + part_index(sp.t0 + mine + q * THREADS, sp), __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
             bool all = true;
 #pragma unroll
-            for (int q = 0; q < GATHER_DEEP; ++q)
-                if (from + q * THREADS < sp.n) all = all && (w[q] >> 63) == tag;
+            for (int q = 0; q < GATHER_DEEP; ++q) all = all && (w[q] >> 63) == tag;
             if (all) break;
             __builtin_amdgcn_s_sleep(8);
         }
 #pragma unroll
-        for (int q = 0; q < GATHER_DEEP; ++q)
-            if (from + q * THREADS < sp.n) acc += mine + q * THREADS < sp.n ? __longlong_as_double((long long)(w[q] & ~TAG_BIT)) : 0.0;
+        for (int q = 0; q < GATHER_DEEP; ++q) acc += __longlong_as_double((long long)(w[q] & ~TAG_BIT));
     }
     if (!__syncthreads_and(ok)) return false;
     const double total = block_sum(acc, S.red);
@@ -872,7 +887,7 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
 {
     const int64_t tile_start = (int64_t)tile * TILE;
     const int32_t fb = T.fb, lb = T.fb + abs(T.nseg) - 1;
-    store_signs(p, n_valid, signs, tile_start, L.W);
+    store_signs<false>(p, n_valid, signs, tile_start, L.W);
 
     const int nseg = lb - fb + 1;
 #pragma unroll
@@ -1005,6 +1020,7 @@ __device__ __forceinline__ void correct_loaded_residual(float4 (&e)[SUBROWS], co
 //               after sync_group_wait.
 enum { UNI_DONE = 0, UNI_PARKED = 1, UNI_PENDING = 2, UNI_HELD = 3 };
 
+template <bool WORDS = false>
 __device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layout &L, int32_t tile, int32_t b,
                                                 const BlockSpan &sp, int n_valid, uint64_t *signs, float *scales_out,
                                                 float *err_tile, const Scratch &X, int set, SyncShared &S, Posted &P,
@@ -1012,7 +1028,7 @@ __device__ __forceinline__ int compress_uniform(float4 (&p)[SUBROWS], const Layo
 {
     const int64_t tile_start = (int64_t)tile * TILE;
     clear_posted(P);
-    store_signs(p, n_valid, signs, tile_start, L.W);
+    store_signs<WORDS>(p, n_valid, signs, tile_start, L.W);
     const double total = block_sum(abs_sum(p, n_valid), S.red);
     if (sp.bs >= tile_start && sp.be <= tile_start + TILE) {
         const float s = (float)(total / (double)(sp.be - sp.bs));
@@ -1083,6 +1099,7 @@ __device__ __forceinline__ bool few_touches(int k, int lo, int hi)
     return first < hi && first + 256 > lo;
 }
 // val: TILE floats of LDS.
+template <bool WORDS = false>
 __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
                                              uint64_t *signs, float *scales_out, float *err_tile, const Scratch &X, int set,
                                              SyncShared &S, FewShared &F, float *val)
@@ -1091,7 +1108,7 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
     const int nseg = T.nseg;
     const BlockSpan hs = span_of(T.bs(), T.be());
     const bool head_open = hs.bs < tile_start || hs.be > tile_start + TILE, tail_open = T.tail != 0;
-    store_signs(p, n_valid, signs, tile_start, L.W);
+    store_signs<WORDS>(p, n_valid, signs, tile_start, L.W);
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k)
         *reinterpret_cast<float4 *>(val + local_base(k)) = make_float4(fabsf(p[k].x), fabsf(p[k].y), fabsf(p[k].z), fabsf(p[k].w));

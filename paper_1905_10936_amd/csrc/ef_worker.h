@@ -350,7 +350,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             quality_of_tile(a, L, Q, tile, worker, TILE, S);
         }
         Posted P;
-        const int kind = compress_uniform(pv, L, tile, T.fb, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
+        const int kind = compress_uniform<MOM>(pv, L, tile, T.fb, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
         resolve_posted(P, L, X, worker, scales_out, S);
         if (kind == UNI_PENDING) {
             finish_uniform(pv, tile, TILE, sp, 0ull, e, L, X, worker, S);
@@ -377,7 +377,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         if (dense)
             compress_mixed(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S);
         else
-            compress_few(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, S.val);
+            compress_few<MOM>(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, S.val);
     }
     snapshot_call(R);
 }
