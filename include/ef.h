@@ -98,8 +98,8 @@ int ef_plan_destroy(ef_plan *plan);
  * (and the server's) step with e <- p - Delta.  For a block of more than
  * fuse_limit tiles the scale of Delta is known only after the first kernel
  * has passed over the whole block, so that kernel leaves p in the residual
- * buffer and a second one reads it back and writes e (8 more bytes of HBM
- * traffic per element).  With on = 1 that second pass is not run: the buffer
+ * buffer (all but the block's last tiles, which wait for the scale) and a second
+ * one reads it back and writes e (8 more bytes of HBM traffic per element).  With on = 1 that second pass is not run: the buffer
  * keeps p over the whole tiles of such blocks, the plan remembers the block's
  * scale, and the next ef_worker_step* / ef_server_step on that buffer forms
  * e = p - Delta as it loads the data: the same fp32 subtraction on the same

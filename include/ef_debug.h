@@ -19,22 +19,24 @@ extern "C" {
  * needs the whole block's scale): workgroups of a block spanning at most
  * fuse_limit tiles of 4096 elements keep p in registers and wait for the scale,
  * polling at most spin_limit times before they fall back to the two-pass route
- * that larger blocks always take.  Results are identical on either route.
+ * that larger blocks take but for their last fuse_limit whole tiles.  Results are
+ * identical on either route.
  * Negative values leave a setting unchanged; fuse_limit = 0 sends every block
  * through two passes, spin_limit = 0 makes every wait give up at once (used by
  * tests to exercise the fallback).  The default spin_limit is 2048 polls of
  * about 1.2 us: waits on an idle GPU were measured to end within 64, so a wait
  * that cannot succeed costs about 2.5 ms.  Synchronises the device.  By default each
  * kernel gets its own limit: half the tiles its workgroups can hold at once
- * (resident workgroups; times six for the persistent worker kernel, which
+ * (resident workgroups; times two where the server takes two tiles to a
+ * workgroup; times six for the persistent worker kernel, which
  * keeps three tiles in registers and three in LDS), at most 4096 tiles.  A
  * limit set here applies to worker and server alike.
  *
  * For the caller's choice of blocks this means: a block of up to about 9.4 M
  * elements (2304 tiles, the persistent worker kernel's default limit on a GPU
  * with 256 compute units) costs 20.125 bytes of HBM traffic per element and
- * worker; a larger block has its corrected gradient written out and read back
- * once more (28.125 bytes) unless the deferred mode is on (ef_plan_set_lazy).
+ * worker; a larger block has its corrected gradient, but for the last 2304 tiles, written
+ * out and read back once more (28.125 bytes) unless the deferred mode is on (ef_plan_set_lazy).
  * Within one pass, blocks of 8 to 64 tiles (32 K to 256 K elements) stream
  * fastest (about 6 % faster than blocks of 256 tiles, 12 % faster than blocks
  * of 1024).  Proposition 1 favours finer blocks as well.

@@ -544,7 +544,7 @@ int build_device(ef_plan *p)
         }
     p->L.n_dense = (int32_t)dense.size();
     p->L.n_grid = ntiles;
-    // the server's limit is that of the kernel this layout runs, 1024, 896 or 768 tiles on 256 units (8 workers; 2^28
+    // the server's limit is that of the kernel this layout runs, 1024 or, with dense tiles, 768 tiles on 256 units (8 workers; 2^28
     // elements in blocks of 1024 tiles: 560 us in one pass, 755 in two; twelve blocks of 850 tiles off the tile
     // boundaries: 87 and 119; with 100 000 tiny blocks among them 121 and 123, 16 workers 164 and 148)
     p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[mixed.empty() ? 0 : dense.empty() ? 1 : 2] / 2);

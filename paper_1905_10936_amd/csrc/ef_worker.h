@@ -284,9 +284,9 @@ void k_worker_uniform(Layout L, ScratchRef R, WorkerArgs A, int n_workers)
 // open segments of tiles of few segments do the same; dense tiles never wait for a whole tile.
 // Relies on workgroups being dispatched in grid order (the one-pass limit keeps a block's tiles well inside what is
 // resident at once) and on spin_limit where that fails.
-// TILES says which kinds of tiles the layout has; the code for the others is left out.  Workgroups per CU: eight (64
-// VGPRs, 6 to 8 spilled; blocks of up to 1024 tiles, half of the 2048 resident, then finish in one pass: 27.1 ->
-// 24.4 ms on the transformer-like layout), but seven where they are measured faster, the momentum worker
+// TILES says which kinds of tiles the layout has; the code for the others is left out.  Workgroups per CU: eight (60
+// VGPRs, none spilled; blocks of up to 1024 tiles, half of the 2048 resident, then finish in one pass: 27.1 ->
+// 24.4 ms on the transformer-like layout), but no more than seven where they are measured faster, the momentum worker
 // with dense tiles (109 832 tiny blocks and four of 2 M, 8 workers: 291 us against 297) and the
 // momentum-free one without (blocks of 30 011: 65.9 against 67.7); the other two the other way round (25 M elements
 // in 64-tile blocks and less, 7 workers: 603 against 609; 259 400 tiny blocks, 16 workers: 213 against 223).
@@ -304,7 +304,7 @@ struct TilesShared<true> {
 // are taken on the way, from the values the kernel holds anyway (see ef_quality.h).  Seven workgroups per CU (2^27
 // elements in blocks of 2^20, 8 workers: 3585 us, 3763 at eight, where 15 registers spill).
 template <bool MOM, int TILES, bool QUAL>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(QUAL || TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8, 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(QUAL || TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8, QUAL || TILES == (MOM ? DENSE_TILES : FEW_TILES) ? 7 : 8)))
 void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
 {
     constexpr bool MIXED = TILES != ALL_WHOLE;
