@@ -552,12 +552,12 @@ int build_device(ef_plan *p)
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
     // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least half of the
-    // tiles are in pairs.  Its limit is then half of the tiles that this kernel keeps
+    // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 400 not).  Its limit is then half of the tiles that this kernel keeps
     // resident, 1792 or 1536.  (Four blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
     const int32_t pair_limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
     const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 2 >= (size_t)ntiles;
     std::vector<uint32_t> in_order, paired;
-    int64_t in_pairs = 0;
+    double in_pairs = 0.0, part = 1.0;          // tiles in pairs that wait; the part of the block's that do
     if (!mixed.empty()) in_order.reserve((size_t)ntiles);
     if (may_pair) paired.reserve((size_t)ntiles);
     size_t w = 0;
@@ -571,6 +571,8 @@ int build_device(ef_plan *p)
             if (fb[t] != block) {
                 block = fb[t];
                 is_second = false;
+                const int64_t n = tiles_of_block(p, block);
+                part = n <= pair_limit ? 1.0 : (double)pair_limit / (double)n;
             }
             if (is_second) {
                 is_second = false;
@@ -578,7 +580,7 @@ int build_device(ef_plan *p)
             }
             is_second = w + 1 < whole.size() && whole[w + 1] == t + 1 && fb[t + 1] == block;
             paired.push_back((uint32_t)t | (is_second ? ef::PAIR_BIT : 0u));
-            in_pairs += is_second ? 2 : 0;
+            in_pairs += is_second ? 2.0 * part : 0.0;
         }
     };
     auto take = [&](int32_t t) {
@@ -593,7 +595,7 @@ int build_device(ef_plan *p)
         take(t);
     }
     whole_up_to(ntiles);
-    if (in_pairs * 2 < (int64_t)ntiles)
+    if (in_pairs * 2.0 < (double)ntiles)
         paired.clear();
     else
         p->lim_server = pair_limit;
@@ -620,9 +622,20 @@ int build_device(ef_plan *p)
     const size_t n_in_order = in_order.size(), n_taken = n_in_order + paired.size() + mixed.size();
     in_order.insert(in_order.end(), paired.begin(), paired.end());
     in_order.insert(in_order.end(), mixed.begin(), mixed.end());
-    uint32_t *d_order;
-    mem.add(&d_order, n_taken, Arena::COPY, in_order.data());
-    mem.add(&p->d_in_order, n_taken, Arena::LEAVE);
+    // few of them travel with the small tables; many are taken on the device, where a launch costs less than the copy
+    uint32_t *d_order = nullptr;
+    std::vector<ef::TileRec> taken;
+    if (n_taken <= 4096) {
+        taken.reserve(n_taken);
+        for (uint32_t i : in_order) {
+            taken.push_back(tiles[i & ~ef::PAIR_BIT]);
+            if (i & ef::PAIR_BIT) taken.back().words = ef::TILE_PAIR;
+        }
+        mem.add(&p->d_in_order, n_taken, Arena::COPY, taken.data());
+    } else {
+        mem.add(&d_order, n_taken, Arena::COPY, in_order.data());
+        mem.add(&p->d_in_order, n_taken, Arena::LEAVE);
+    }
     mem.add(&p->d_words, mixed.size() * ef::TILE_WORDS, Arena::LEAVE);
     mem.add(&p->d_cross, cross.size(), Arena::COPY, cross.data());
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
@@ -650,7 +663,7 @@ int build_device(ef_plan *p)
     p->d_paired = p->d_in_order + n_in_order;
     p->d_mixed_recs = p->d_paired + paired.size();
     p->L.paired_tiles = p->d_paired;
-    if (n_taken) {
+    if (d_order) {
         hipLaunchKernelGGL(ef::k_take_records, dim3((unsigned)((n_taken + ef::THREADS - 1) / ef::THREADS)), dim3(ef::THREADS), 0, nullptr,
                            (const ef::TileRec *)p->d_tiles, (const uint32_t *)d_order, (int)n_taken, p->d_in_order);
         EF_HIP(hipGetLastError());
