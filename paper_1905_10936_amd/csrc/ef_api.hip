@@ -552,8 +552,8 @@ int build_device(ef_plan *p)
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
     // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least half of the
-    // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 400 not).  Its limit is then half of the tiles that this kernel keeps
-    // resident, 1792 or 1536.  (Four blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
+    // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 429 not).
+    // Its limit is then half of the tiles that this kernel keeps resident, 1792 or 1536.  (Four blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
     const int32_t pair_limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
     const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 2 >= (size_t)ntiles;
     std::vector<uint32_t> in_order, paired;
