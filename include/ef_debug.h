@@ -76,8 +76,8 @@ int ef_plan_small_calls(const ef_plan *plan, int n_workers);
 
 /*
  * Writing the residual out in step.  In the worker kernel that runs one
- * workgroup per tile, the whole tiles of a block larger than fuse_limit have
- * nothing to wait for; they are made to wait (bounded by spin_limit, and with
+ * workgroup per tile, the whole tiles of a block larger than fuse_limit, but for the last
+ * ones, which wait for the scale, have nothing to wait for; they are made to wait (bounded by spin_limit, and with
  * nothing depending on the outcome) for their neighbours, in groups of `tiles`
  * consecutive tiles, before they write their residual tile: measured faster
  * than workgroups that each write when done (worker call on 2^28 elements,
@@ -90,7 +90,8 @@ int ef_plan_set_sync_group(ef_plan *plan, int tiles);
 /*
  * How often the most recent ef_worker_step / ef_server_step on this plan left
  * the one-pass route at run time: tiles whose wait for the block scale was not
- * taken or ran out (p parked, finished by the second pass) and blocks whose
+ * taken or ran out (p parked, finished by the second pass), together with the tiles
+ * whose wait for their group ran out (ef_plan_set_sync_group), and blocks whose
  * scale had to be formed by the second pass.  Results do not depend on these
  * counts; they are a performance diagnostic.  Synchronises the device.  Either
  * pointer may be NULL (HOST pointers).

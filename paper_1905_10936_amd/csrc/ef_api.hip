@@ -58,7 +58,7 @@ struct ef_plan {
     int32_t *d_tile_lb;
     unsigned long long *d_part;
     unsigned long long *d_ready;
-    unsigned int *d_list_cnt;       // [6]: defer_cnt[2], fin_cnt[2], ticket[2] (alternating between calls)
+    unsigned int *d_list_cnt;       // [8]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2] (alternating between calls)
     int worker_grid;                // workgroups of the persistent worker kernel
     int persistent;                 // worker: 1 pipelined persistent kernel, 0 one workgroup per tile
     int persistent_auto;            // what plan creation chose for this layout
@@ -295,13 +295,11 @@ bool finishes_with_mixed(const ef_plan *p, const ef_plan::Role &r, int64_t b)
     return n >= 2 && n <= r.fuse_limit && !has_uniform_tile(p, b);
 }
 
-// Host mirror of first_kept in ef_tile.h.
 int64_t first_kept(const ef_plan *p, const ef_plan::Role &r, int64_t b)
 {
     const int64_t *o = p->offs_host.data();
     const int64_t first = o[b] % ef::TILE != 0 ? 1 : 0, whole = tiles_of_block(p, b) - first - (o[b + 1] % ef::TILE != 0 ? 1 : 0);
-    const int64_t parked = whole > r.keep ? whole - r.keep : 0;
-    return o[b] / ef::TILE + first + parked + (parked & 1);
+    return ef::first_kept(o[b] / ef::TILE + first, (int)whole, r.keep);
 }
 
 // What the main kernels of a call always leave to the kernel that ends it: the scales of the
@@ -641,7 +639,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
     mem.add(&p->d_ready, (size_t)ef::READY_STRIDE * nt * ns, Arena::ZERO);
-    mem.add(&p->d_list_cnt, 6, Arena::ZERO);
+    mem.add(&p->d_list_cnt, 8, Arena::ZERO);
     mem.add(&p->d_state, 2, Arena::ZERO);
     mem.add(&p->d_lazy_scales, max_cross * ns, Arena::ZERO);
     mem.add(&p->d_defer_list, 2 * nt * ns, Arena::LEAVE);
@@ -1015,16 +1013,16 @@ int ef_plan_last_fallbacks(ef_plan *plan, unsigned int *parked_tiles, unsigned i
 {
     if (!plan) return EF_ERR_NULL;
     EF_HIP(hipDeviceSynchronize());
-    unsigned int a = 0, b = 0;
+    unsigned int cnt[8] = {};
+    unsigned last = 0;
     ef::CallState st;
     EF_HIP(hipMemcpy(&st, plan->d_state, sizeof st, hipMemcpyDeviceToHost));
     if (st.calls > 0) {         // the most recent call used the counters of parity (calls - 1) & 1
-        const unsigned last = (st.calls - 1u) & 1u;
-        EF_HIP(hipMemcpy(&a, plan->d_list_cnt + last, sizeof a, hipMemcpyDeviceToHost));
-        EF_HIP(hipMemcpy(&b, plan->d_list_cnt + 2 + last, sizeof b, hipMemcpyDeviceToHost));
+        last = (st.calls - 1u) & 1u;
+        EF_HIP(hipMemcpy(cnt, plan->d_list_cnt, sizeof cnt, hipMemcpyDeviceToHost));
     }
-    if (parked_tiles) *parked_tiles = a;
-    if (late_blocks) *late_blocks = b;
+    if (parked_tiles) *parked_tiles = cnt[last] + cnt[6 + last];
+    if (late_blocks) *late_blocks = cnt[2 + last];
     return EF_OK;
 }
 

@@ -93,6 +93,7 @@ __device__ __forceinline__ void advance_call(CallState *state, const Scratch &X,
     X.next_cnt[0] = 0u;
     X.next_cnt[2] = 0u;
     X.next_cnt[4] = 0u;
+    X.next_cnt[6] = 0u;
     state->calls = state->calls + 1u;
     if (X.set_base == 0) {
         state->worker_tags ^= used;

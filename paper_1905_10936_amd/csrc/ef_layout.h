@@ -50,4 +50,27 @@ inline int64_t few_place(int64_t tile, int64_t t0, int n, bool first_shared, int
     return (awaited ? t0 : tile) - FEW_LEAD;
 }
 
+// A block larger than the one-pass limit has its first whole tiles parked (their p waits in memory for the scale) and keeps
+// the last ones, about `keep` of them (0: none), in registers, as a one-pass block does.  How many of its `whole` tiles are
+// parked: an even number, where any are kept (pairs are of one kind).
+constexpr int parked_tiles(int whole, int keep)
+{
+    const int parked = whole > keep ? whole - keep : 0;
+    return parked + (parked & 1) < whole ? parked + (parked & 1) : whole;
+}
+// The first tile that is kept; the whole ones start at `first_whole`.
+constexpr int64_t first_kept(int64_t first_whole, int whole, int keep) { return first_whole + parked_tiles(whole, keep); }
+
+// Parked tiles that are written out in step (sync_group_wait): `group` consecutive ones from the block's first whole tile
+// on, fewer in the last group.  The last tile of a group is the one the others wait for, so it has to be a parked one, too:
+// a kept tile never comes to that wait.
+constexpr int64_t group_first(int64_t tile, int64_t first_whole, int group)
+{
+    return first_whole + (tile - first_whole) / group * group;
+}
+constexpr int64_t group_last(int64_t first, int group, int64_t first_kept)
+{
+    return first + group < first_kept ? first + group - 1 : first_kept - 1;
+}
+
 }  // namespace ef

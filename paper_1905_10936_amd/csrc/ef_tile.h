@@ -157,7 +157,7 @@ struct ScratchRef {
     unsigned long long *ready;
     unsigned long long *defer_list;
     unsigned long long *fin_list;
-    unsigned int *list_cnt;             // [6]: defer_cnt[2], fin_cnt[2], ticket[2] (a call uses those of its parity)
+    unsigned int *list_cnt;             // [8]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2] (a call uses those of its parity)
     float *lazy_scales;                 // [nsets][lazy_stride] last scale of every block larger than fuse_limit
     int lazy_stride;
     const CallState *state;
@@ -179,7 +179,8 @@ struct Scratch {
     unsigned int epoch;         // this call's number on the plan (never 0), carried by the ready words
     int set_base;               // first set this call uses (0 for workers, max_workers for the server)
     int spin_limit;             // polls before a waiting workgroup gives up and parks p
-    unsigned int *next_cnt;     // the three list counters of the next call (zeroed by this call's last kernel)
+    unsigned int *lost_cnt;     // waits of a group (sync_group_wait) that ran out in this call: a diagnostic
+    unsigned int *next_cnt;     // the counters of the next call (zeroed by this call's last kernel)
     // Deferred correction.  A block larger than fuse_limit cannot have its residual finished in
     // the first kernel; instead of a second pass over it (p written, read back, e written: 8 more
     // bytes per element), the residual buffer keeps p, the block's scale is remembered here, and
@@ -215,6 +216,7 @@ __device__ __forceinline__ Scratch open_call(const ScratchRef &R)
     X.defer_cnt = R.list_cnt + cur;
     X.fin_cnt = R.list_cnt + 2 + cur;
     X.ticket = R.list_cnt + 4 + cur;
+    X.lost_cnt = R.list_cnt + 6 + cur;
     X.next_cnt = R.list_cnt + (cur ^ 1u);
     // this call's tags are the stored ones flipped
     X.tags = workers ? ~worker_tags : (unsigned long long)(server_tag ^ 1u);
@@ -635,16 +637,14 @@ __device__ __forceinline__ bool finishes_with_mixed(const Layout &L, const Block
 }
 
 // A block larger than fuse_limit: its whole tiles from this one on keep p and wait for the scale like those of a one-pass
-// block do, so that the pass over what was parked leaves them out; its last whole tile forms the scale.  (An even number of
-// whole tiles is parked: pairs are of one kind.)  As many as are sure to be resident are kept, the limit again.  us without
+// block do, so that the pass over what was parked leaves them out; its last whole tile forms the scale.  As many as are sure to be resident are kept, the limit again.  us without
 // and with: server, 16 workers, a block of 12 565 tiles in 86 000, 901 / 876 (the pass over what is parked 68 -> 59, and
 // k_tail no longer adds up 12 565 partial sums, 24 -> 5); worker, the same layout, 1301 / 1289; step of 4 workers with
 // four blocks of 2049 tiles on the server, 917 / 905, and 891 with pairs, whose limit is 1792.
 __device__ __forceinline__ int64_t first_kept(const Layout &L, const BlockSpan &s)
 {
     const int first = (s.bs % TILE) != 0 ? 1 : 0, whole = s.n - first - ((s.be % TILE) != 0 ? 1 : 0);
-    const int parked = whole > L.keep ? whole - L.keep : 0;
-    return s.t0 + first + parked + (parked & 1);
+    return first_kept(s.t0 + first, whole, L.keep);
 }
 
 // Scratch word of block b's segment in tile t: slot 1 of the block's first tile
@@ -1181,21 +1181,22 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
 // that each write as soon as they are done (2^28 elements, 8 workers: 6.6 ms in blocks of 8 to
 // 16 tiles against 7.7 ms without any wait; the momentum tile is written at once in both cases,
 // holding it back as well was measured slower).  For a uniform tile of a block larger than
-// fuse_limit nothing has to be waited for, so the kernel that runs one workgroup per tile makes
-// it wait for its neighbours instead: the whole tiles of the block form groups of L.sync_group
-// consecutive tiles; the last tile of a group looks for this call's tag on the partial words of
+// fuse_limit that is parked nothing has to be waited for, so the kernel that runs one workgroup per tile makes
+// it wait for its neighbours instead: the parked tiles of the block form groups of L.sync_group
+// consecutive tiles (group_first, group_last); the last tile of a group looks for this call's tag on the partial words of
 // the others (posted just before) and then posts the call number in its own ready line, where
 // the others look for it.  Both waits are bounded, and nothing depends on their outcome:
-// whoever runs out of patience just writes.
+// whoever runs out of patience just writes, and is counted.  (Groups cut from all whole tiles could end in a kept one, which
+// never comes here: the others then polled until spin_limit, 0.65 ms a call.  Eight blocks of 5 M elements, one
+// worker: 851 -> 151 us; 124 M in 12 transformer layers and an embedding: 993 -> 388.)
 // Called by every thread of the workgroup, after compress_uniform returned UNI_HELD.
 __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
                                                 SyncShared &S)
 {
-    const int64_t first_whole = sp.t0 + ((sp.bs % TILE) != 0 ? 1 : 0);
-    const int64_t last_whole = last_whole_tile(sp);
-    const int64_t g0 = first_whole + ((int64_t)tile - first_whole) / L.sync_group * L.sync_group;
-    const int64_t g1 = min(g0 + L.sync_group - 1, last_whole);
+    const int64_t g0 = group_first(tile, sp.t0 + ((sp.bs % TILE) != 0 ? 1 : 0), L.sync_group);
+    const int64_t g1 = group_last(g0, L.sync_group, first_kept(L, sp));
     if (g1 == g0) return;
+    bool lost = X.spin_limit > 0;       // until the wait is over
     // the second word of the tile's line: the first may be the block's ready word
     unsigned long long *line = X.ready + ((int64_t)set * L.ntiles + g1) * READY_STRIDE + 1;
     if ((int64_t)tile == g1) {
@@ -1209,7 +1210,10 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &s
                                                                __HIP_MEMORY_SCOPE_AGENT);
                 all = (w >> 63) == tag ? 1 : 0;
             }
-            if (__syncthreads_and(all)) break;
+            if (__syncthreads_and(all)) {
+                lost = false;
+                break;
+            }
             __builtin_amdgcn_s_sleep(8);
         }
         if (threadIdx.x == 0)
@@ -1218,12 +1222,16 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &s
         if (threadIdx.x == 0) {
             for (int it = 0; it < X.spin_limit; ++it) {
                 const unsigned long long w = __hip_atomic_load(line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((unsigned)(w >> 32) == X.epoch) break;
+                if ((unsigned)(w >> 32) == X.epoch) {
+                    lost = false;
+                    break;
+                }
                 __builtin_amdgcn_s_sleep(8);
             }
         }
         __syncthreads();
     }
+    if (threadIdx.x == 0 && lost) atomicAdd(X.lost_cnt, 1u);
 }
 
 // Fill the first half of S.val (read as 16-bit integers) with the segment index of every element of a

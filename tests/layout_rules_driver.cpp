@@ -40,6 +40,26 @@ int main()
             REQUIRE(at >= tile - ef::FEW_LEAD - limit);
             REQUIRE(at == (whole && n <= limit ? t0 : tile) - ef::FEW_LEAD);
         }
+    // what a block beyond the one-pass limit parks: as many whole tiles as the limit are kept, one less where that makes an
+    // even number of parked ones; without a limit none.  A parked tile's group ends in a parked tile (it is what the
+    // others wait for), and all tiles of a group name the same one.
+    for (int whole = 1; whole <= 130; ++whole)
+        for (int keep : {0, 1, 2, 3, 7, 16, 64, 100, 129, 130, 1000}) {
+            const int64_t first = 1000003;
+            const int parked = ef::parked_tiles(whole, keep), kept = whole - parked;
+            REQUIRE(parked >= 0 && kept >= 0 && kept <= keep);
+            REQUIRE(kept == 0 || (parked % 2 == 0 && kept >= (keep < whole ? keep : whole) - 1));
+            REQUIRE(kept > 0 || keep <= 1);
+            REQUIRE(ef::first_kept(first, whole, keep) == first + parked);
+            for (int group : {2, 3, 5, 16, 256})
+                for (int64_t t = first; t < first + parked; ++t) {
+                    const int64_t g0 = ef::group_first(t, first, group), g1 = ef::group_last(g0, group, first + parked);
+                    REQUIRE(g0 >= first && g0 <= t && t <= g1 && g1 < g0 + group);
+                    REQUIRE(g1 < first + parked);
+                    REQUIRE(g1 == g0 + group - 1 || g1 + 1 == first + parked);
+                    REQUIRE((g0 - first) % group == 0 && ef::group_first(g1, first, group) == g0);
+                }
+        }
     std::puts("layout rules ok");
     return 0;
 }
