@@ -42,3 +42,23 @@ def test_every_group_ends(name, variant, group):
         ef.ef_worker_step_quality(st.plan, st.g, st.m, st.e, 0.9, 0.0, 0.1, st.ws, st.wc, q)
     assert st.plan.last_fallbacks() == (0, 0)
     st.plan.close()
+
+
+def test_the_gather_of_a_block_of_more_rounds_than_polls():
+    """A block's partial sums are read 1024 at a time, and a round that finds all of them costs no poll: with 96 polls the
+    scale of 100 * 1024 + 8 tiles is still formed in the main kernel.  (Its kept tiles may give up on so small a budget.)
+    The scale is the mean of |g|, rounded once from a sum in 64 bits."""
+    d = (100 * 1024 + 8) * T
+    plan = ef.ef_plan_create(np.array([0, d]), 1)
+    plan.set_persistent(False)
+    plan.tune(spin_limit=96)
+    g = torch.randn(d, dtype=torch.float32, device="cuda", generator=torch.Generator("cuda").manual_seed(7))
+    e = torch.zeros_like(g)
+    ws = torch.zeros(plan.W, dtype=torch.int64, device="cuda")
+    wc = torch.zeros(1, dtype=torch.float32, device="cuda")
+    ef.ef_worker_step_sgd(plan, g, e, 0.0, 0.1, ws, wc)
+    assert plan.last_fallbacks()[1] == 0
+    scale = sum(float(part.abs().sum(dtype=torch.float64)) for part in g.split(1 << 24)) / d
+    assert abs(float(wc) - scale) <= 2.0 ** -23 * scale         # one rounding to 32 bits, and the order of the 64-bit sum
+    assert torch.equal(e, torch.where(g >= 0, g - wc, g + wc))
+    plan.close()
