@@ -75,6 +75,14 @@ int ef_plan_is_persistent(const ef_plan *plan);
 int ef_plan_small_calls(const ef_plan *plan, int n_workers);
 
 /*
+ * Whether server calls over n_workers workers run the kernel that takes two whole
+ * tiles of a block to a workgroup: 1 or 0.  By default plan creation's choice for
+ * the layout; after ef_plan_set_persistent with on = 0 or 1 wherever the layout's
+ * tiles have been paired.  0 for a NULL plan.
+ */
+int ef_plan_server_pairs(const ef_plan *plan, int n_workers);
+
+/*
  * Writing the residual out in step.  In the worker kernel that runs one
  * workgroup per tile, the whole tiles of a block larger than fuse_limit, but for the last
  * ones, which wait for the scale, have nothing to wait for; they are made to wait (bounded by spin_limit, and with

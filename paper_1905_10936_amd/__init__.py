@@ -36,7 +36,7 @@ ABI_SYMBOLS = (
 # ... and what include/ef_debug.h declares (tuning and diagnostics the tests use)
 DEBUG_SYMBOLS = (
     "ef_plan_tune", "ef_plan_fuse_limit", "ef_plan_set_persistent", "ef_plan_is_persistent", "ef_plan_set_sync_group",
-    "ef_plan_last_fallbacks", "ef_plan_small_calls",
+    "ef_plan_last_fallbacks", "ef_plan_small_calls", "ef_plan_server_pairs",
 )
 
 
@@ -81,6 +81,8 @@ def lib():
     L.ef_plan_is_persistent.argtypes = [vp]
     L.ef_plan_small_calls.restype = c_int
     L.ef_plan_small_calls.argtypes = [vp, c_int]
+    L.ef_plan_server_pairs.restype = c_int
+    L.ef_plan_server_pairs.argtypes = [vp, c_int]
     L.ef_plan_set_lazy.restype = c_int
     L.ef_plan_set_lazy.argtypes = [vp, c_int]
     L.ef_plan_set_sync_group.restype = c_int
@@ -214,6 +216,10 @@ class Plan:
         """Which calls run the kernels for short launches: any of "worker", "server", "update"."""
         bits = lib().ef_plan_small_calls(self._h, int(n_workers))
         return {name for k, name in enumerate(("worker", "server", "update")) if bits >> k & 1}
+
+    def server_pairs(self, n_workers):
+        """Do server calls over n_workers workers take two whole tiles of a block to a workgroup?"""
+        return bool(lib().ef_plan_server_pairs(self._h, int(n_workers)))
 
     def set_lazy(self, on):
         """Deferred residual correction for blocks larger than fuse_limit (see ef_plan_set_lazy)."""

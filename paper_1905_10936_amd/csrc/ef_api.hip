@@ -81,6 +81,7 @@ struct ef_plan {
     bool has_small;                 // this layout has such launches
     ef::SmallArgs small;
     bool kernels_auto;              // ef_plan_set_persistent has not been used to pick the kernels
+    bool server_pairs[2];           // the server's calls (of up to eight workers, of more) take the whole tiles in pairs, if there are any
 };
 
 // Scratch of ef_compressor_quality_static: device memory that exists from the moment the library
@@ -247,6 +248,7 @@ struct DeviceFacts {
     int cus;                                    // compute units
     int uniform, tiles, server[3], small;       // workgroups per unit of the kernels of these names (server: whole tiles, few, dense ones)
     int pairs[2];                               // of the server's with two tiles to a workgroup (up to eight workers, more)
+    int server_many;                            // of the server's with one, for more than eight workers and tiles of few segments
 };
 DeviceFacts g_facts[MAX_DEVICES];
 
@@ -263,6 +265,7 @@ int device_facts(int device, DeviceFacts *out)
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[0], (ef::k_server_tiles<ef::ALL_WHOLE, false, false>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[1], (ef::k_server_tiles<ef::FEW_TILES, false, false>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server[2], (ef::k_server_tiles<ef::DENSE_TILES, false, false>), ef::THREADS, 0));
+        EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.server_many, (ef::k_server_tiles<ef::FEW_TILES, true, false>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.pairs[0], (ef::k_server_tiles<ef::DENSE_TILES, false, true>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.pairs[1], (ef::k_server_tiles<ef::DENSE_TILES, true, true>), ef::THREADS, 0));
         EF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f.small, ef::k_worker_small<true>, ef::SMALL_THREADS, 0));
@@ -550,9 +553,22 @@ int build_device(ef_plan *p)
     // ascending, but for those of few segments (see few_place).
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
     // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least half of the
-    // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 429 not).
-    // Its limit is then half of the tiles that this kernel keeps resident, 1792 or 1536.  (Four blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
-    const int32_t pair_limit = facts.cus * facts.pairs[p->max_workers > ef::SERVER_CHUNK ? 1 : 0];
+    // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 429 not), and
+    // server_pairs says so.  Its limit is then half of the tiles that this kernel keeps resident, 1792 or 1536.  (Four
+    // blocks of 2049 tiles among as many dense tiles, 4 workers: step 905 -> 893 us.)
+    const bool many = p->max_workers > ef::SERVER_CHUNK;
+    int32_t pair_limit = facts.cus * facts.pairs[many ? 1 : 0];
+    int64_t pairs_only = 0;                     // tiles of blocks that one pass takes in pairs alone
+    // the blocks that span several tiles
+    for (int64_t b = 0; b < B; ++b) {
+        const int64_t n = tiles_of_block(p, b);
+        if (n < 2) continue;
+        cross.push_back((int32_t)b);
+        pairs_only += n > p->lim_server && n <= pair_limit ? n : 0;
+    }
+    p->server_pairs[0] = ef::server_pairs(false, ntiles, (int64_t)mixed.size(), !dense.empty(), pairs_only, (int64_t)facts.cus * facts.server[2]);
+    p->server_pairs[1] = ef::server_pairs(true, ntiles, (int64_t)mixed.size(), !dense.empty(), pairs_only, (int64_t)facts.cus * facts.server_many);
+    if (!p->server_pairs[many ? 1 : 0]) pair_limit = p->lim_server;     // fewer workers than the plan is for may still take pairs
     const bool may_pair = p->max_workers <= ef::PAIR_WORKERS && whole.size() * 2 >= (size_t)ntiles;
     std::vector<uint32_t> in_order, paired;
     double in_pairs = 0.0, part = 1.0;          // tiles in pairs that wait; the part of the block's that do
@@ -600,9 +616,7 @@ int build_device(ef_plan *p)
     p->L.n_paired = (int32_t)paired.size();
     p->L.n_mixed = (int32_t)mixed.size();
     p->L.n_uniform = (int32_t)whole.size();
-    // compressor-quality diagnostics: the blocks that span several tiles, and the per-tile sums
-    for (int64_t b = 0; b < B; ++b)
-        if (tiles_of_block(p, b) >= 2) cross.push_back((int32_t)b);
+    // compressor-quality diagnostics: those blocks, and the per-tile sums
     p->n_cross = (int32_t)cross.size();
 
     const size_t nt = (size_t)ntiles, ns = (size_t)nsets, nv = (size_t)p->max_workers;
@@ -744,6 +758,13 @@ bool small_call(const ef_plan *plan, int role, int nsets)
 {
     return plan->has_small && plan->kernels_auto && (int64_t)plan->L.ntiles * nsets <= plan->small_wgs &&
            !plan->role[role].beyond;
+}
+
+// Does the server's call over M workers take two whole tiles to a workgroup?
+bool takes_pairs(const ef_plan *plan, int M)
+{
+    return plan->L.n_paired != 0 && plan->role[ROLE_SERVER].fuse_limit > 0 &&
+           (!plan->kernels_auto || plan->server_pairs[M > ef::SERVER_CHUNK ? 1 : 0]);
 }
 
 // The updates, where nothing waits: as long as all of it is resident (with / without, weight decay, blocks of
@@ -1046,6 +1067,11 @@ int ef_plan_small_calls(const ef_plan *plan, int n_workers)
            (small_update(plan) ? 4 : 0);
 }
 
+int ef_plan_server_pairs(const ef_plan *plan, int n_workers)
+{
+    return plan && n_workers >= 1 && n_workers <= plan->max_workers && !small_call(plan, ROLE_SERVER, 1) && takes_pairs(plan, n_workers);
+}
+
 int64_t ef_plan_d(const ef_plan *plan) { return plan ? plan->L.d : 0; }
 int64_t ef_plan_blocks(const ef_plan *plan) { return plan ? plan->L.B : 0; }
 
@@ -1311,7 +1337,7 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
     const ef::Layout L = role_layout(plan, ROLE_SERVER);
     const dim3 block(ef::THREADS);
     const int kind = L.n_dense ? 2 : L.n_mixed ? 1 : 0;
-    const bool many = M > ef::SERVER_CHUNK, pairs = L.n_paired != 0 && L.fuse_limit > 0;
+    const bool many = M > ef::SERVER_CHUNK, pairs = takes_pairs(plan, M);
     if (L.n_dense == L.ntiles) {
         hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_grid), block, 0, s, L, c.X, A, plan->max_workers);
     } else {

@@ -50,6 +50,23 @@ inline int64_t few_place(int64_t tile, int64_t t0, int n, bool first_shared, int
     return (awaited ? t0 : tile) - FEW_LEAD;
 }
 
+// Does the server take two whole tiles of a block to a workgroup (k_server_tiles with PAIRS)?  many: more than eight workers.
+// `mixed` of the layout's `tiles` are mixed ones, `between` lie in blocks that only pairs finish in one pass, and `resident`
+// workgroups of the kernel with one tile to each run at once.  Server call, pairs / one tile, us:
+//   up to eight workers, whole tiles and those of few segments: pairs, for any number of tiles (blocks of 64 tiles, 8 workers,
+//   1200 tiles 12.4 / 12.2, 2400 16.3 / 19.4, 12 000 74.8 / 80.1); with dense ones where not all of it is resident
+//   with one tile to a workgroup anyway (20 000 tiny blocks and four large ones, 1374 tiles 30.3 / 27.7, 2274 32.1 / 33.3)
+//   more, whole tiles alone: one tile to a workgroup (16 workers, blocks of 64, 1200 tiles 17.8 / 14.8, 2400 25.9 / 25.8,
+//   12 000 104 / 92), but where most tiles are in blocks of 1025 to 1536 of them (six of 1100, 72.6 / 78.6)
+//   more, with mixed tiles (9 workers; 16): 1788 29.4 / 26.8; 34.9 / 33.1, 2212 31.0 / 31.6; 37.2 / 37.4, 2680 34.3 / 37.4;
+//   38.5 / 48.5 (bottleneck networks), 19 469 189 / 192; 193 / 214 (a transformer, one tile of 400 mixed), but
+//   blocks of 64 and one ragged end, 5986 56.5 / 52.1; 55.8 / 56.2
+inline bool server_pairs(bool many, int64_t tiles, int64_t mixed, bool dense, int64_t between, int64_t resident)
+{
+    if (!many) return !dense || between > 0 || tiles > resident;
+    return 3 * tiles > 4 * resident && (1024 * mixed >= tiles || 2 * between > tiles);
+}
+
 // A block larger than the one-pass limit has its first whole tiles parked (their p waits in memory for the scale) and keeps
 // the last ones, about `keep` of them (0: none), in registers, as a one-pass block does.  How many of its `whole` tiles are
 // parked: an even number, where any are kept (pairs are of one kind).

@@ -40,6 +40,21 @@ int main()
             REQUIRE(at >= tile - ef::FEW_LEAD - limit);
             REQUIRE(at == (whole && n <= limit ? t0 : tile) - ef::FEW_LEAD);
         }
+    // server, two tiles to a workgroup or one: the layouts on both sides of each line of the rule
+    const int64_t dense_resident = 1536, many_resident = 1792;
+    for (int64_t tiles : {300, 1536, 1537, 90000}) {
+        REQUIRE(ef::server_pairs(false, tiles, 0, false, 0, dense_resident));
+        REQUIRE(ef::server_pairs(false, tiles, 60, true, 0, dense_resident) == (tiles > dense_resident));
+        REQUIRE(ef::server_pairs(false, tiles, 60, true, 1100, dense_resident));
+    }
+    for (int64_t tiles : {300, 2389, 2390, 30000}) {
+        const bool large = tiles > many_resident * 4 / 3;
+        REQUIRE(!ef::server_pairs(true, tiles, 0, false, 0, many_resident));
+        REQUIRE(!ef::server_pairs(true, tiles, (tiles - 1) / 1024, false, tiles / 2, many_resident));
+        REQUIRE(ef::server_pairs(true, tiles, tiles / 1024 + 1, false, 0, many_resident) == large);
+        REQUIRE(ef::server_pairs(true, tiles, tiles, true, 0, many_resident) == large);
+        REQUIRE(ef::server_pairs(true, tiles, 0, false, tiles / 2 + 1, many_resident) == large);
+    }
     // what a block beyond the one-pass limit parks: as many whole tiles as the limit are kept, one less where that makes an
     // even number of parked ones; without a limit none.  A parked tile's group ends in a parked tile (it is what the
     // others wait for), and all tiles of a group name the same one.

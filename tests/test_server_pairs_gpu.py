@@ -3,7 +3,9 @@ exactly two, ends inside tiles, worker counts on both sides of the two tables, e
 finished.  Same bar as the other parity tests; the layouts are short, so the kernels for large launches are asked for."""
 import numpy as np
 import pytest
+import torch
 
+import paper_1905_10936_amd as ef
 from tests.parity_util import F, GpuState, synced_step
 from tests.test_parity_gpu import _offs
 
@@ -27,6 +29,7 @@ def _steps(name, M, limit=-1, spin=None, fused=False):
     st.plan.set_persistent(False)
     st.plan.tune(fuse_limit=limit) if limit >= 0 else None
     st.plan.tune(spin_limit=spin) if spin is not None else None
+    assert st.plan.server_pairs(M) == (M <= 16 and limit != 0)
     eta_prev, stats = 0.0, {}
     for t, eta in enumerate([0.1, 0.05]):
         g = rng.standard_normal((M, d)).astype(F)
@@ -55,3 +58,41 @@ def test_one_pass_limits(name, limit):
 @pytest.mark.parametrize("name", list(LAYOUTS))
 def test_no_wait_succeeds(name, M):
     _steps(name, M, spin=0)
+
+
+WHICH = {           # layout, and whether calls of up to eight workers, of more, take pairs by plan creation's choice
+    "whole_tiles": ([64 * T] * 20, True, False),
+    "many_whole_tiles": ([64 * T] * 50, True, False),
+    "off_the_tiles": ([100 * T + 77] * 30, True, True),
+    "one_ragged_end": ([64 * T] * 40 + [33 * T + 55], True, False),
+    "longer_than_one_tile_alone_takes": ([1100 * T] * 3, True, True),
+    "dense_and_all_resident": ([33] * 20000 + [330 * T] * 4, False, False),
+    "dense": ([33] * 20000 + [700 * T] * 4, True, True),
+    "no_two_of_a_block": ([7 * T // 4] * 1400, False, False),
+}
+
+
+@pytest.mark.parametrize("name", list(WHICH))
+def test_which_calls_take_pairs(name):
+    """The choice, and the same results from every kernel it picks: a plan for sixteen workers and one for as many as there are
+    agree on sign words, scales and the residual."""
+    sizes, few, many = WHICH[name]
+    offs = _offs(sizes)
+    d = int(offs[-1])
+    plan = ef.ef_plan_create(offs, 16)
+    assert (plan.server_pairs(8), plan.server_pairs(9), plan.server_pairs(16)) == (few, many, many)
+    assert not plan.server_pairs(17) and not ef.ef_plan_create(offs, 17).server_pairs(16)
+    gen = torch.Generator("cuda").manual_seed(3)
+    ws = torch.randint(-2 ** 63, 2 ** 63 - 1, (16, plan.W), dtype=torch.int64, device="cuda", generator=gen)
+    wc = torch.rand(16, plan.B, device="cuda", generator=gen)
+    te = torch.randn(d, device="cuda", generator=gen)
+    for M in (3, 8, 9, 16):
+        outs = []
+        for p in (plan, ef.ef_plan_create(offs, M), ef.ef_plan_create(offs, 17)):
+            e = te.clone()
+            s, c = torch.zeros(plan.W, dtype=torch.int64, device="cuda"), torch.zeros(plan.B, device="cuda")
+            ef.ef_server_step(p, M, ws[:M].contiguous(), wc[:M].contiguous(), e, 0.1, 0.05, s, c)
+            assert p.last_fallbacks() == (0, 0)
+            outs.append((s, c.view(torch.int32), e.view(torch.int32)))
+        for other in outs[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(outs[0], other)), "%s M=%d" % (name, M)
