@@ -24,8 +24,8 @@ extern "C" {
  * Negative values leave a setting unchanged; fuse_limit = 0 sends every block
  * through two passes, spin_limit = 0 makes every wait give up at once (used by
  * tests to exercise the fallback).  The default spin_limit is 2048 polls of
- * about 1.2 us: waits on an idle GPU were measured to end within 64, so a wait
- * that cannot succeed costs about 2.5 ms.  Synchronises the device.  By default each
+ * about 0.3 us: waits on an idle GPU were measured to end within 64, so a wait
+ * that cannot succeed costs about 0.65 ms.  Synchronises the device.  By default each
  * kernel gets its own limit: half the tiles its workgroups can hold at once
  * (resident workgroups; times two where the server takes two tiles to a
  * workgroup; times six for the persistent worker kernel, which
@@ -53,15 +53,15 @@ int ef_plan_fuse_limit(const ef_plan *plan);       /* the worker kernels' limit 
  * workgroup gets at least 16 tiles and the layout's blocks are cheaper on it
  * by the measured cost per tile of either kernel (one workgroup per tile is
  * the faster on blocks of up to 256 tiles, the persistent kernel on larger
- * ones, and it finishes blocks of 1025 to 2304 tiles in one pass that the
- * other sends through the second pass).  ef_worker_step_sgd, and every worker
+ * ones, and it finishes blocks of 1025 to 2304 tiles in one pass, whose first
+ * tiles the other sends through the second pass).  ef_worker_step_sgd, and every worker
  * call in the deferred mode (ef_plan_set_lazy), use the persistent kernel only
  * after on = 1.  With on < 0, calls of up to about a thousand (tile, worker)
  * pairs whose blocks span at most 256 tiles run kernels of their own instead,
  * built for short launches, and so do the server's and the update's calls on
  * such a layout; on = 0 or 1 sends all three to the kernels of the larger
  * layouts (see ef_plan_small_calls).  The server otherwise runs one workgroup per
- * tile.  Same results either way (every kernel adds a block's 64-bit sum in the
+ * tile or two (see ef_plan_server_pairs).  Same results either way (every kernel adds a block's 64-bit sum in the
  * same order).  Synchronises the device.
  */
 int ef_plan_set_persistent(ef_plan *plan, int on);

@@ -548,7 +548,8 @@ int build_device(ef_plan *p)
     // boundaries: 87 and 119; with 100 000 tiny blocks among them 121 and 123, 16 workers 164 and 148)
     p->lim_server = (int32_t)((int64_t)facts.cus * facts.server[mixed.empty() ? 0 : dense.empty() ? 1 : 2] / 2);
     // The order in which the kernels with one workgroup per tile take the tiles: the dense ones, then the others
-    // ascending, but for those of few segments (see few_place).
+    // ascending, but for those of few segments (see few_place).  The limit for that is the one without pairs: the end of a
+    // longer block keeps its place, also where pairs then take the block in one pass.
     const int awaited = p->lim_server > p->lim_direct ? p->lim_server : p->lim_direct;
     // And the same with the whole tiles of a block two by two, from its first on, for the server: where at least half of the
     // tiles are in pairs that wait for their block (one block of 2^28 elements, where few do: 462 us in pairs, 429 not), and
@@ -697,7 +698,8 @@ int build_device(ef_plan *p)
     // kernel by block size (2^28 elements, 8 workers, relative to the persistent kernel's 7.0 ms,
     // which does not depend on the block size up to its one-pass limit): the kernel with one
     // workgroup per tile is faster on blocks of up to 256 tiles, level up to 512, slower beyond,
-    // and sends blocks above its own limit through the second pass.
+    // and sends the first tiles of blocks above its own limit through the second pass.  (Such blocks are charged with two
+    // passes over all of their tiles, as before their last ones were kept.)
     {
         const int64_t tiles_per_wg = (int64_t)p->L.n_uniform * p->max_workers / (p->worker_grid > 0 ? p->worker_grid : 1);
         const int64_t lim_hi = p->lim_persistent < ef::FUSE_LIMIT_MAX ? p->lim_persistent : ef::FUSE_LIMIT_MAX;
@@ -721,8 +723,8 @@ int build_device(ef_plan *p)
         if (rc_scratch) return rc_scratch;
     }
     // Measured on an otherwise idle GPU: every wait of every benchmark layout ends within 64 polls
-    // (about 1.2 us each); 2048 polls leave a factor of 32 for a GPU that is shared, and a wait that
-    // is lost (its gatherer not resident) costs about 2.5 ms before the tile takes the second pass.
+    // (about 0.3 us each); 2048 polls leave a factor of 32 for a GPU that is shared, and a wait that
+    // is lost (its gatherer not resident) costs about 0.65 ms before the tile takes the second pass.
     p->spin_limit = 1 << 11;
     p->persistent = p->persistent_auto;
     p->persistent_forced = 0;

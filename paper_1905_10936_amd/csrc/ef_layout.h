@@ -41,8 +41,8 @@ inline int few_segments(int max_workers, int64_t tiles, int64_t between)
 // tiles it waits for.
 constexpr int FEW_LEAD = 256;
 // If a block that it ends has whole tiles before it (n tiles from t0 on, the first shared with another block or not),
-// these wait for its part of the sum, and it goes ahead of them; but not of a block larger than `limit`, whose
-// tiles wait for nothing: a large block's end would stand thousands of places early, in a slot that
+// these wait for its part of the sum, and it goes ahead of them; but not of a block larger than `limit`, of which
+// only the last tiles wait, if any (first_kept): a large block's end would stand thousands of places early, in a slot that
 // waits for the block after it all the while.
 inline int64_t few_place(int64_t tile, int64_t t0, int n, bool first_shared, int limit)
 {

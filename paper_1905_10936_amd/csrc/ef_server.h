@@ -611,10 +611,10 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 // one table for two.  7 workers, 25 M elements of a bottleneck network: 54.9 -> 44.3 us; 16 workers, 354 M of a
 // transformer, whose blocks of 1025 tiles then finish in one pass: 1092 -> 907 (870 with first_kept and gather_scale as they are); 8 workers, 2^28 in blocks of 2^20:
 // 450 -> 400.  Where nothing waits (every block beyond the limit) one tile to a workgroup is the faster (4
-// workers, 2^26: 4 us less).  Workgroups per CU:
+// workers, 2^26: 4 us less), and elsewhere by server_pairs (ef_layout.h).  Workgroups per CU:
 //   pairs               seven (72 VGPRs), MANY six (80, 15 spilled); one less each: 46.3 us, 942 us; one more: 47.0, 985
 //   whole tiles only    eight (64 VGPRs; 2^28 elements, 8 workers, blocks of 2^20: 457 us against 465 at seven, 491 at six)
-//   tiles of few segments    eight (60 VGPRs), MANY seven (67)
+//   tiles of few segments    eight (59 VGPRs), MANY seven (68); MANY on whole tiles only eight (62)
 //   dense tiles         six (80 VGPRs; 643 965 tiny blocks, 2 workers: 46.3 us against 49.4 at seven, where 6 spill;
 //                       16 workers, 300 000: 51.0 against 52.8)
 // MANY: more than SERVER_CHUNK workers.

@@ -573,7 +573,7 @@ __device__ __forceinline__ double abs_sum(const float4 (&p)[SUBROWS], int n_vali
 
 // LDS of a workgroup: what every kernel needs for reductions and broadcasts ...
 struct SyncShared {
-    double red[2 * NWAVES];     // one a wavefront, two where it has two tiles (k_server_pairs)
+    double red[2 * NWAVES];     // one a wavefront, two where it has two tiles (server_pair)
     int flag[2];
     unsigned ticket;
 };

@@ -47,6 +47,7 @@ int main()
     REQUIRE(ef_plan_set_lazy(nullptr, 1) == EF_ERR_NULL);
     REQUIRE(ef_plan_set_sync_group(nullptr, 16) == EF_ERR_NULL);
     REQUIRE(ef_plan_last_fallbacks(nullptr, &a, &b) == EF_ERR_NULL);
+    REQUIRE(ef_plan_server_pairs(nullptr, 1) == 0);
     REQUIRE(ef_plan_small_calls(nullptr, 1) == 0);
     REQUIRE(ef_plan_fuse_limit(nullptr) == 0 && ef_plan_is_persistent(nullptr) == 0 && ef_plan_is_lazy(nullptr) == 0);
     REQUIRE(ef_plan_d(nullptr) == 0 && ef_plan_blocks(nullptr) == 0 && ef_sign_words(nullptr) == 0);
