@@ -116,11 +116,20 @@ constexpr int SERVER_LDS = NIBBLE_AT + SERVER_CHUNK * 64;      // floats
 // Workers beyond the eighth are added one by one, eight at a time: entry (u, nibble) of a second table
 // holds the four values +-s_u that a nibble of worker u's bits stands for, so four addends cost
 // one bit-field extract and one 128-bit LDS read.
+// h: the sign bits of the ninth to the sixteenth, asked for with those of the first eight, as are the scales of the table's
+// makers.  (12 000 tiles in blocks of 64: 16 workers 98.5 -> 93.1 us, 11 workers 98.0 -> 93.2.)
 // Called by every thread of the workgroup; lds (SERVER_LDS floats) is free again on return.
+__device__ __forceinline__ float nibble_scale(const ServerArgs &A, int32_t b, int i0)
+{
+    return A.scales_in[(int64_t)min(i0 + (int)(threadIdx.x >> 4), A.M - 1) * A.in_scales_stride + b];
+}
 template <bool MANY>
 __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t tile_start, int32_t b, const unsigned (&h0)[SERVER_CHUNK],
-                                                    const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], float *lds)
+                                                    unsigned (&h)[SERVER_CHUNK], const float4 (&tv)[SUBROWS], float4 (&p)[SUBROWS], float *lds)
 {
+    // the scale of the worker whose nibbles this thread tabulates, asked for ahead of the tile's values
+    float next = 0.0f;
+    if (MANY && threadIdx.x < SERVER_CHUNK * 16) next = nibble_scale(A, b, SERVER_CHUNK);
     float acc[SUBROWS][4];
     const float r = A.r, Mf = A.Mf, Minv = A.Minv;
     unsigned *exchange = reinterpret_cast<unsigned *>(lds) + EXCHANGE_AT + wave_id() * 256;
@@ -145,16 +154,14 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
         float4 *table = reinterpret_cast<float4 *>(lds + NIBBLE_AT);
         const unsigned sh = (unsigned)(lane_id() & 3) * 4u;
         for (int i0 = SERVER_CHUNK; i0 < A.M; i0 += SERVER_CHUNK) {
-            unsigned h[SERVER_CHUNK];
-            float sc[SERVER_CHUNK];
-            load_sign_halves(A, tile_start, i0, h);
-            load_scales(A, b, i0, sc);
-            if (i0 > SERVER_CHUNK) __syncthreads();      // the table is read no more
+            if (i0 > SERVER_CHUNK) {
+                load_sign_halves(A, tile_start, i0, h);
+                __syncthreads();                         // the table is read no more
+            }
             if (threadIdx.x < SERVER_CHUNK * 16) {
-                const int u = threadIdx.x >> 4, nib = threadIdx.x & 15;
-                float su = sc[0];
-#pragma unroll
-                for (int q = 1; q < SERVER_CHUNK; ++q) su = (u == q) ? sc[q] : su;
+                const int nib = threadIdx.x & 15;
+                const float su = i0 + (int)(threadIdx.x >> 4) < A.M ? next : 0.0f;
+                if (i0 + SERVER_CHUNK < A.M) next = nibble_scale(A, b, i0 + SERVER_CHUNK);
                 table[threadIdx.x] = make_float4(signed_scale(su, nib & 1), signed_scale(su, nib & 2),
                                                  signed_scale(su, nib & 4), signed_scale(su, nib & 8));
             }
@@ -167,14 +174,13 @@ __device__ __forceinline__ void server_values_whole(const ServerArgs &A, int64_t
                 const vu4 w = *reinterpret_cast<const vu4 *>(exchange + 4 * (16 * k + (lane_id() >> 2)));
 #pragma unroll
                 for (int u = 0; u < SERVER_CHUNK; ++u) {
-                    if (i0 + u < A.M) {
-                        const unsigned two = w[u >> 1];
-                        const float4 dv = table[u * 16 + ((two >> (sh + 16 * (u & 1))) & 15u)];
-                        acc[k][0] = acc[k][0] + dv.x;
-                        acc[k][1] = acc[k][1] + dv.y;
-                        acc[k][2] = acc[k][2] + dv.z;
-                        acc[k][3] = acc[k][3] + dv.w;
-                    }
+                    // past M +-0, which changes no sum (one that began with +0 is never -0): no branch between the reads
+                    const unsigned two = w[u >> 1];
+                    const float4 dv = table[u * 16 + ((two >> (sh + 16 * (u & 1))) & 15u)];
+                    acc[k][0] = acc[k][0] + dv.x;
+                    acc[k][1] = acc[k][1] + dv.y;
+                    acc[k][2] = acc[k][2] + dv.z;
+                    acc[k][3] = acc[k][3] + dv.w;
                 }
             }
         }
@@ -400,8 +406,14 @@ __device__ __forceinline__ void server_values_few(const Layout &L, const ServerA
 
 // Two whole tiles of one block, next to each other, as one workgroup's work: wavefront w has the elements
 // 2048w .. 2048w + 2047 of the pair as two quarters of a tile each laid out like a quarter elsewhere, so that a
-// tile's sum is formed in the same order.
-__device__ __forceinline__ int pair_base(int half, int k) { return (2 * wave_id() + half) * 1024 + k * 256 + lane_id() * 4; }
+// tile's sum is formed in the same order.  One offset, in the middle of a wavefront's 8 KiB, serves all of a thread's eight
+// accesses, which lie within what an instruction can add to it (from its start on, the upper half needed four addresses).
+__device__ __forceinline__ float *pair_part(float *te, int half, int k)
+{
+    unsigned middle = (2u * (threadIdx.x >> 6) + 1u) * 4096u + (threadIdx.x & 63u) * 16u;
+    asm("" : "+v"(middle));             // one register, not an address and its upper half's
+    return reinterpret_cast<float *>(reinterpret_cast<char *>(te) + middle) + (half - 1) * 1024 + k * 256;
+}
 
 // As transpose_signs, for 32 consecutive elements: dword j of the result holds the bytes of elements 4j .. 4j + 3.
 __device__ __forceinline__ void transpose_signs32(const unsigned (&h)[SERVER_CHUNK], vu4 (&out)[2])
@@ -439,11 +451,13 @@ __device__ __forceinline__ void transpose_signs32(const unsigned (&h)[SERVER_CHU
     }
 }
 
-// LDS of server_pair (floats): the wavefronts' exchanges (2 KiB each, for more than SERVER_CHUNK workers twice) and the
-// tables of sums and of more workers' values.
+// LDS of server_pair (32-bit words): the wavefronts' exchanges (2 KiB each), and the table of sums, over the first eight workers or
+// the first twelve; beyond those, the values four more workers' signs stand for.
 constexpr int PAIR_WORKERS = 2 * SERVER_CHUNK;
 constexpr int PAIR_EXCHANGE = NWAVES * 512;
-constexpr int PAIR_TABLES = SUM_TABLE + SERVER_CHUNK * 64;
+constexpr int TWELVE = SERVER_CHUNK + 4;
+constexpr int PAIR_SUMS = 1 << TWELVE;
+constexpr int PAIR_VALUES = 16 * 4;
 
 __device__ __forceinline__ void load_sign_dwords(const ServerArgs &A, int64_t start, int i0, unsigned (&h)[SERVER_CHUNK])
 {
@@ -455,98 +469,134 @@ __device__ __forceinline__ void load_sign_dwords(const ServerArgs &A, int64_t st
     }
 }
 
-// p~ of a pair, as server_values_whole; M at most PAIR_WORKERS.  v: the server residual's tiles, then p~.
-template <bool MANY>
-__device__ __forceinline__ void server_values_pair(const ServerArgs &A, int64_t start, int32_t b, const unsigned (&h0)[SERVER_CHUNK],
-                                                   const unsigned (&h1)[SERVER_CHUNK], float4 (&v)[2][SUBROWS], float *exchanges, float *lds)
+// A thread's bytes of a pair, by half and sub-row: dword (h, k) holds the bytes of elements 0 to 3 of pair_part(h, k).
+__device__ __forceinline__ unsigned pair_bytes(const unsigned *exchange, int half, int k) { return exchange[256 * half + 64 * k + lane_id()]; }
+__device__ __forceinline__ void put_pair_bytes(unsigned *exchange, const unsigned (&h)[SERVER_CHUNK])
+{
+    vu4 bytes[2];
+    transpose_signs32(h, bytes);
+    *reinterpret_cast<vu4 *>(exchange + 8 * lane_id()) = bytes[0];
+    *reinterpret_cast<vu4 *>(exchange + 8 * lane_id() + 4) = bytes[1];
+}
+// Sum over the first eight workers of sign pattern threadIdx.x.
+__device__ __forceinline__ float eight_sum(const ServerArgs &A, int32_t b)
+{
+    float sc[SERVER_CHUNK];
+    load_scales(A, b, 0, sc);
+    float sum = 0.0f;
+    const unsigned minus = ~threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < SERVER_CHUNK; ++u) sum = sum + negated_by(sc[u], minus, u);
+    return sum;
+}
+
+// p~ of a pair of up to eight workers, as server_values_whole.  v: the server residual's tiles, then p~.  sums: SUM_TABLE floats.
+__device__ __forceinline__ void server_values_pair(const ServerArgs &A, int32_t b, const unsigned (&h)[SERVER_CHUNK],
+                                                   float4 (&v)[2][SUBROWS], unsigned *exchanges, float *sums)
+{
+    const float r = A.r;
+    unsigned *exchange = exchanges + wave_id() * 512;
+    sums[threadIdx.x] = mean_of(eight_sum(A, b), A.Mf, A.Minv);
+    put_pair_bytes(exchange, h);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) {
+            const unsigned pat = pair_bytes(exchange, q, k);
+            v[q][k].x = sums[pat & 255u] + r * v[q][k].x;
+            v[q][k].y = sums[(pat >> 8) & 255u] + r * v[q][k].y;
+            v[q][k].z = sums[(pat >> 16) & 255u] + r * v[q][k].z;
+            v[q][k].w = sums[pat >> 24] + r * v[q][k].w;
+        }
+}
+
+// The same for nine to sixteen workers (PAIR_WORKERS).  The table has the sums over the first twelve, in worker order from +0, 4096
+// of them: thread t makes the sixteen that begin with pattern t, 30 additions on top of the eight, where adding the four workers
+// one by one takes each of its 32 elements four additions, four reads and as many bit fields.  The next four are added one by
+// one; their values +-s come in one read for an element.  An element's sixteen bits are two bytes, transposed
+// and exchanged one after the other.  Server call, 354 M of a transformer, us: 11 workers 845 -> 732, 14 900 -> 791, 16 870 -> 808;
+// 25 M of a bottleneck network, 16 workers: 76 -> 70.
+// sums: PAIR_SUMS floats; values: PAIR_VALUES.
+__device__ __forceinline__ void server_values_pair_many(const ServerArgs &A, int32_t b, const unsigned (&h0)[SERVER_CHUNK],
+                                                        const unsigned (&h1)[SERVER_CHUNK], float4 (&v)[2][SUBROWS],
+                                                        unsigned *exchanges, float *sums, float *values)
 {
     const float r = A.r, Mf = A.Mf, Minv = A.Minv;
-    unsigned *exchange = reinterpret_cast<unsigned *>(exchanges) + wave_id() * 512;
+    const bool more = A.M > TWELVE;
+    unsigned *exchange = exchanges + wave_id() * 512;
     {
-        float sc[SERVER_CHUNK];
-        load_scales(A, b, 0, sc);
-        float sum = 0.0f;
-        const unsigned minus = ~threadIdx.x;
+        // past M: +-0, which changes no sum (one that began with +0 is never -0)
+        float sum[16], sc[4];
+        sum[0] = eight_sum(A, b);
 #pragma unroll
-        for (int u = 0; u < SERVER_CHUNK; ++u) sum = sum + negated_by(sc[u], minus, u);
-        lds[threadIdx.x] = MANY ? sum : mean_of(sum, Mf, Minv);
-        vu4 bytes[2];
-        transpose_signs32(h0, bytes);
-        *reinterpret_cast<vu4 *>(exchange + 8 * lane_id()) = bytes[0];
-        *reinterpret_cast<vu4 *>(exchange + 8 * lane_id() + 4) = bytes[1];
-    }
-    if constexpr (!MANY) {
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int k = 0; k < SUBROWS; ++k) {
-                const unsigned pat = exchange[256 * h + 64 * k + lane_id()];
-                v[h][k].x = lds[pat & 255u] + r * v[h][k].x;
-                v[h][k].y = lds[(pat >> 8) & 255u] + r * v[h][k].y;
-                v[h][k].z = lds[(pat >> 16) & 255u] + r * v[h][k].z;
-                v[h][k].w = lds[pat >> 24] + r * v[h][k].w;
-            }
-    } else {
-        // the ninth worker to the sixteenth: their sign words as they are, and the values a nibble of them stands for
-        float4 *table = reinterpret_cast<float4 *>(lds + SUM_TABLE);
-        if (threadIdx.x < SERVER_CHUNK * 16) {
-            const unsigned nib = threadIdx.x & 15u;
-            const int i = SERVER_CHUNK + (int)(threadIdx.x >> 4);
-            float s = A.scales_in[(int64_t)min(i, A.M - 1) * A.in_scales_stride + b];
-            s = i < A.M ? s : 0.0f;     // past M: +-0, which changes no sum (one that began with +0 is never -0)
-            table[threadIdx.x] = make_float4(signed_scale(s, nib & 1u), signed_scale(s, nib & 2u), signed_scale(s, nib & 4u),
-                                             signed_scale(s, nib & 8u));
+        for (int u = 0; u < 4; ++u) {
+            const float s = A.scales_in[(int64_t)min(SERVER_CHUNK + u, A.M - 1) * A.in_scales_stride + b];
+            sc[u] = SERVER_CHUNK + u < A.M ? s : 0.0f;
         }
-        const unsigned *signs = exchange + PAIR_EXCHANGE + 8 * (lane_id() >> 3);
-        unsigned *mine = exchange + PAIR_EXCHANGE + 8 * lane_id();
-        *reinterpret_cast<vu4 *>(mine) = vu4{h1[0], h1[1], h1[2], h1[3]};
-        *reinterpret_cast<vu4 *>(mine + 4) = vu4{h1[4], h1[5], h1[6], h1[7]};
-        const unsigned sh = (unsigned)(lane_id() & 7) * 4u;
-        __syncthreads();
-        // one half after the other, so that the sums of one are in registers at a time
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            float acc[SUBROWS][4];
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int k = 0; k < SUBROWS; ++k) {
-                const unsigned pat = exchange[256 * q + 64 * k + lane_id()];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[k][c] = lds[(pat >> (8 * c)) & 255u];
+            for (int i = 0; i < (1 << u); ++i) {
+                sum[i + (1 << u)] = sum[i] + sc[u];
+                sum[i] = sum[i] + -sc[u];
             }
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                if (g == 1 && A.M <= SERVER_CHUNK + 4) continue;
+        for (int i = 0; i < 16; ++i) sums[256 * i + threadIdx.x] = more ? sum[i] : mean_of(sum[i], Mf, Minv);
+    }
+    if (more && threadIdx.x < PAIR_VALUES) {
+        const int i = TWELVE + (int)(threadIdx.x & 3u);
+        float s = A.scales_in[(int64_t)min(i, A.M - 1) * A.in_scales_stride + b];
+        s = i < A.M ? s : 0.0f;
+        values[threadIdx.x] = signed_scale(s, (threadIdx.x >> (2 + (threadIdx.x & 3u))) & 1u);
+    }
+    unsigned first[2][SUBROWS];
+    put_pair_bytes(exchange, h0);
 #pragma unroll
-                for (int k = 0; k < SUBROWS; ++k) {
-                    const vu4 w = *reinterpret_cast<const vu4 *>(signs + 8 * (32 * q + 8 * k) + 4 * g);
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const float4 dv = table[(4 * g + u) * 16 + ((w[u] >> sh) & 15u)];
-                        acc[k][0] = acc[k][0] + dv.x;
-                        acc[k][1] = acc[k][1] + dv.y;
-                        acc[k][2] = acc[k][2] + dv.z;
-                        acc[k][3] = acc[k][3] + dv.w;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);      // reads four ahead, not thirty: registers
+        for (int k = 0; k < SUBROWS; ++k) first[q][k] = pair_bytes(exchange, q, k);
+    put_pair_bytes(exchange, h1);
+    __syncthreads();
+    // four elements at a time: more in flight are more registers than there are
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) {
+            const unsigned second = pair_bytes(exchange, q, k);
+            // two elements' sixteen bits to a word
+            const unsigned w[2] = {__builtin_amdgcn_perm(second, first[q][k], 0x05010400u), __builtin_amdgcn_perm(second, first[q][k], 0x07030602u)};
+            float acc[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = sums[(w[c >> 1] >> (16 * (c & 1))) & (unsigned)(PAIR_SUMS - 1)];
+            if (more) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float4 dv = *reinterpret_cast<const float4 *>(values + 4 * ((w[c >> 1] >> (16 * (c & 1) + TWELVE)) & 15u));
+                    acc[c] = (((acc[c] + dv.x) + dv.y) + dv.z) + dv.w;
+                }
+                if (Minv != 0.0f) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] *= Minv;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] /= Mf;
                 }
             }
-            mean_of_all(acc, Mf, Minv);
-#pragma unroll
-            for (int k = 0; k < SUBROWS; ++k) {
-                v[q][k].x = acc[k][0] + r * v[q][k].x;
-                v[q][k].y = acc[k][1] + r * v[q][k].y;
-                v[q][k].z = acc[k][2] + r * v[q][k].z;
-                v[q][k].w = acc[k][3] + r * v[q][k].w;
-            }
+            v[q][k].x = acc[0] + r * v[q][k].x;
+            v[q][k].y = acc[1] + r * v[q][k].y;
+            v[q][k].z = acc[2] + r * v[q][k].z;
+            v[q][k].w = acc[3] + r * v[q][k].w;
+            // formed here: put off to where they are used, the 32 sums and the residuals need a register each
+            asm volatile("" : "+v"(v[q][k].x), "+v"(v[q][k].y), "+v"(v[q][k].z), "+v"(v[q][k].w));
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
 }
 
 // A pair from loads to stores (compress_uniform, resolve_posted and finish_uniform for both tiles at once).
 template <bool MANY>
 __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A, const TileRec &T, const Scratch &X, int set,
-                                            SyncShared &S, float *exchanges, float *tables)
+                                            SyncShared &S, float *lds, float *more)
 {
     const int64_t start = (int64_t)T.tile * TILE;
     float *te = A.err + start;
@@ -557,13 +607,16 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) v[q][k] = stream_load4(te + pair_base(q, k));
+        for (int k = 0; k < SUBROWS; ++k) v[q][k] = stream_load4(pair_part(te, q, k));
     __builtin_amdgcn_sched_barrier(0);
     const BlockSpan sp = span_of(T.bs(), T.be());
     const LoadedCorrection corr = loaded_correction(L, T.fb, X, set);
     correct_loaded_residual(v[0], corr);
     correct_loaded_residual(v[1], corr);
-    server_values_pair<MANY>(A, start, T.fb, h, h1, v, exchanges, tables);
+    if constexpr (MANY)
+        server_values_pair_many(A, T.fb, h, h1, v, reinterpret_cast<unsigned *>(more), lds, more + PAIR_EXCHANGE);
+    else
+        server_values_pair(A, T.fb, h, v, reinterpret_cast<unsigned *>(lds), more);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         store_quarter_signs<false>(sign_half(v[q], TILE), A.signs, (start >> 6) + (2 * wave_id() + q) * 16, L.W);
@@ -599,7 +652,7 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 #pragma unroll
             for (int k = 0; k < SUBROWS; ++k) residual4(v[q][k], s);
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) stream_store4(te + pair_base(q, k), v[q][k]);
+        for (int k = 0; k < SUBROWS; ++k) stream_store4(pair_part(te, q, k), v[q][k]);
     }
 }
 
@@ -612,7 +665,7 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 // transformer, whose blocks of 1025 tiles then finish in one pass: 1092 -> 907 (870 with first_kept and gather_scale as they are); 8 workers, 2^28 in blocks of 2^20:
 // 450 -> 400.  Where nothing waits (every block beyond the limit) one tile to a workgroup is the faster (4
 // workers, 2^26: 4 us less), and elsewhere by server_pairs (ef_layout.h).  Workgroups per CU:
-//   pairs               seven (72 VGPRs), MANY six (80, 15 spilled); one less each: 46.3 us, 942 us; one more: 47.0, 985
+//   pairs               seven (72 VGPRs), MANY six (77; 25 KB of LDS); one less: 46.3 us, MANY 916 against 826
 //   whole tiles only    eight (64 VGPRs; 2^28 elements, 8 workers, blocks of 2^20: 457 us against 465 at seven, 491 at six)
 //   tiles of few segments    eight (59 VGPRs), MANY seven (68); MANY on whole tiles only eight (62)
 //   dense tiles         six (80 VGPRs; 643 965 tiny blocks, 2 workers: 46.3 us against 49.4 at seven, where 6 spill;
@@ -638,14 +691,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(server_
 void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
 {
     constexpr bool MIXED = TILES != ALL_WHOLE;
-    constexpr int EXCHANGE = PAIRS ? (MANY ? 2 : 1) * PAIR_EXCHANGE : 0;
-    __shared__ __align__(16) ServerShared<MIXED, (EXCHANGE > SERVER_LDS ? EXCHANGE : SERVER_LDS)> S;
+    constexpr int FOR_PAIRS = PAIRS ? (MANY ? PAIR_SUMS : PAIR_EXCHANGE) : 0;
+    __shared__ __align__(16) ServerShared<MIXED, (FOR_PAIRS > SERVER_LDS ? FOR_PAIRS : SERVER_LDS)> S;
     float *lds = S.val;
     float4 tv[SUBROWS], p[SUBROWS];
-    unsigned h[SERVER_CHUNK];
+    unsigned h[SERVER_CHUNK], h1[SERVER_CHUNK];
     if (!MIXED && !PAIRS) {
         // tile i is workgroup i's: its sign words and its residual are asked for before anything is looked up
         load_sign_halves(A, (int64_t)blockIdx.x * TILE, 0, h);
+        if (MANY) load_sign_halves(A, (int64_t)blockIdx.x * TILE, SERVER_CHUNK, h1);
         load_tile(A.err + (int64_t)blockIdx.x * TILE, tv, TILE);
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -653,8 +707,8 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
     const TileRec T = PAIRS ? L.paired_tiles[blockIdx.x] : MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
     if constexpr (PAIRS) {
         if (T.words == TILE_PAIR) {
-            __shared__ __align__(16) float tables[MANY ? PAIR_TABLES : SUM_TABLE];
-            server_pair<MANY>(L, A, T, X, set, S, lds, tables);
+            __shared__ __align__(16) float more[MANY ? PAIR_EXCHANGE + PAIR_VALUES : SUM_TABLE];
+            server_pair<MANY>(L, A, T, X, set, S, lds, more);
             snapshot_call(R);
             return;
         }
@@ -666,6 +720,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
     if (!MIXED || T.words < 0) {
         if (MIXED || PAIRS) {
             load_sign_halves(A, tile_start, 0, h);
+            if (MANY) load_sign_halves(A, tile_start, SERVER_CHUNK, h1);
             load_tile(te, tv, TILE);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -673,7 +728,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         const BlockSpan sp = span_of(T.bs(), T.be());
         const LoadedCorrection corr = loaded_correction(L, T.fb, X, set);
         correct_loaded_residual(tv, corr);
-        server_values_whole<MANY>(A, tile_start, T.fb, h, tv, p, lds);
+        server_values_whole<MANY>(A, tile_start, T.fb, h, h1, tv, p, lds);
         const int kind = compress_uniform(p, L, tile, T.fb, sp, TILE, A.signs, A.scales, te, X, set, S, P);
         resolve_posted(P, L, X, set, A.scales, S);
         if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
