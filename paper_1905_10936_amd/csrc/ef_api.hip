@@ -58,7 +58,8 @@ struct ef_plan {
     int32_t *d_tile_lb;
     unsigned long long *d_part;
     unsigned long long *d_ready;
-    unsigned int *d_list_cnt;       // [8]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2] (alternating between calls)
+    unsigned int *d_list_cnt;       // [CALL_WORDS]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2] and the count of workgroups (alternating between calls)
+    unsigned long long *d_parked;   // entries of segments parked in a call that ends without k_tail
     int worker_grid;                // workgroups of the persistent worker kernel
     int persistent;                 // worker: 1 pipelined persistent kernel, 0 one workgroup per tile
     int persistent_auto;            // what plan creation chose for this layout
@@ -647,7 +648,9 @@ int build_device(ef_plan *p)
     mem.add(&p->d_part, 2 * nt * ns, Arena::ZERO);          // zeroed partial words carry tag 0
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
     mem.add(&p->d_ready, (size_t)ef::READY_STRIDE * nt * ns, Arena::ZERO);
-    mem.add(&p->d_list_cnt, 8, Arena::ZERO);
+    mem.add(&p->d_list_cnt, ef::CALL_WORDS, Arena::ZERO);
+    // at most two entries a workgroup
+    mem.add(&p->d_parked, 2 * (nt * nv < (size_t)ef::ENDS_WGS_MAX ? nt * nv : (size_t)ef::ENDS_WGS_MAX), Arena::ZERO);
     mem.add(&p->d_state, 2, Arena::ZERO);
     mem.add(&p->d_lazy_scales, max_cross * ns, Arena::ZERO);
     mem.add(&p->d_defer_list, 2 * nt * ns, Arena::LEAVE);
@@ -686,6 +689,8 @@ int build_device(ef_plan *p)
     p->X.list_cnt = p->d_list_cnt;
     p->X.state = p->d_state;
     p->X.snapshot = p->d_state + 1;
+    p->X.step = p->d_state;
+    p->X.parked = p->d_parked;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
     if (p->L.n_mixed) {
@@ -789,12 +794,30 @@ struct CallScratch {
 
 CallScratch next_call(const ef_plan *plan, int set_base, int nsets)
 {
-    (void)nsets;
     CallScratch c;
     c.X = plan->X;
     c.X.set_base = set_base;
     c.X.spin_limit = plan->spin_limit;
+    c.X.ends = 0;
+    c.X.nsets = nsets;
+    c.X.lazy = plan->lazy;
     return c;
+}
+
+// Does the main kernel end the call, with `columns` workgroups to a set (ScratchRef::ends)?  Then nothing may be left for certain to
+// a kernel after it, and what it has to hand on is set here.
+bool main_kernel_ends(const ef_plan *plan, int role, CallScratch &c, int columns, float *err, int64_t err_stride, float *scales,
+                      int64_t scales_stride)
+{
+    const ef_plan::Role &r = plan->role[role];
+    if (role == ROLE_TICKET || r.n_static || r.n_late || (int64_t)columns * c.X.nsets > ef::ENDS_WGS_MAX) return false;
+    c.X.ends = 1;
+    c.X.columns = columns;
+    c.X.err = err;
+    c.X.err_stride = err_stride;
+    c.X.scales = scales;
+    c.X.scales_stride = scales_stride;
+    return true;
 }
 
 // The kernel after the main one(s): missing scales, parked residuals, and the step to the next call.
@@ -1193,7 +1216,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         plan->lazy_stride_seen = state_stride;
         if (n_workers > plan->lazy_sets_seen) plan->lazy_sets_seen = n_workers;
     }
-    const CallScratch c = next_call(plan, 0, n_workers);
+    CallScratch c = next_call(plan, 0, n_workers);
     if (!quality && small_call(plan, ROLE_TILES, n_workers)) {
         const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::SMALL_THREADS);
         const ef::SmallArgs Z = small_args(plan, n_workers, err, state_stride, scales, scales_stride);
@@ -1206,6 +1229,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     }
     const int role = quality ? (int)ROLE_TILES : worker_role(plan, has_mom);
     const ef::Layout L = role_layout(plan, role);
+    const bool ends = main_kernel_ends(plan, role, c, plan->L.n_grid, err, state_stride, scales, scales_stride);
     if (quality) {
         if (!aligned(quality, 8)) return EF_ERR_ALIGN;
         hipLaunchKernelGGL(ef::k_quality_init, dim3(1), dim3(ef::THREADS), 0, s, quality, n_workers);
@@ -1266,7 +1290,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
             hipLaunchKernelGGL((ef::k_worker_tiles<false, ef::ALL_WHOLE, false>), grid, block, 0, s, L, c.X, A, Q);
         EF_HIP(hipGetLastError());
     }
-    int rc = launch_tail(plan, role, c, n_workers, err, state_stride, scales, scales_stride, s);
+    int rc = ends ? (int)EF_OK : launch_tail(plan, role, c, n_workers, err, state_stride, scales, scales_stride, s);
     if (rc || !quality) return rc;
     // the quality sums of the tiles are there: combine them per block and per vector
     ef::QualityArgs Q;
@@ -1321,7 +1345,7 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
         if (plan->lazy_buf[1] && plan->lazy_buf[1] != server_err) return EF_ERR_ARG;
         plan->lazy_buf[1] = server_err;
     }
-    const CallScratch c = next_call(plan, plan->max_workers, 1);
+    CallScratch c = next_call(plan, plan->max_workers, 1);
     if (small_call(plan, ROLE_SERVER, 1)) {
         const ef::SmallArgs Z = small_args(plan, 1, server_err, 0, out_scales, 0);
         hipLaunchKernelGGL(ef::k_server_small, dim3((unsigned)plan->L.ntiles), dim3(ef::SMALL_THREADS), 0, s, plan->L, c.X, A, Z,
@@ -1333,6 +1357,7 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
     const dim3 block(ef::THREADS);
     const int kind = L.n_dense ? 2 : L.n_mixed ? 1 : 0;
     const bool many = M > ef::SERVER_CHUNK, pairs = takes_pairs(plan, M);
+    const bool ends = ef::server_ends(many, pairs) && main_kernel_ends(plan, ROLE_SERVER, c, pairs ? L.n_paired : L.n_grid, server_err, 0, out_scales, 0);
     if (L.n_dense == L.ntiles) {
         hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_grid), block, 0, s, L, c.X, A, plan->max_workers);
     } else {
@@ -1346,6 +1371,7 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
                            plan->max_workers);
     }
     EF_HIP(hipGetLastError());
+    if (ends) return EF_OK;
     return launch_tail(plan, ROLE_SERVER, c, 1, server_err, (int64_t)0, out_scales, (int64_t)0, s);
 }
 

@@ -1,6 +1,7 @@
 // Kernels that run after the main kernel of a call, and the parameter update: see ef_tile.h for the tile scheme.
 #pragma once
 #include "ef_tile.h"
+#include "ef_end.h"
 
 namespace ef {
 
@@ -85,27 +86,7 @@ __device__ __forceinline__ float tail_scale(const Layout &L, const Scratch &X, i
     return (float)(total / (double)(sp.be - sp.bs));
 }
 
-// The call is over: count it, flip the tags of the sets it used, clear the counters the next
-// call will use (one thread).
-__device__ __forceinline__ void advance_call(CallState *state, const Scratch &X, int nsets, int lazy)
-{
-    const unsigned long long used = nsets >= 64 ? ~0ull : ((1ull << nsets) - 1ull);
-    X.next_cnt[0] = 0u;
-    X.next_cnt[2] = 0u;
-    X.next_cnt[4] = 0u;
-    X.next_cnt[6] = 0u;
-    state->calls = state->calls + 1u;
-    if (X.set_base == 0) {
-        state->worker_tags ^= used;
-        // with the deferred correction on, the large blocks of these sets now hold p
-        state->worker_pending = lazy ? (state->worker_pending | used) : (state->worker_pending & ~used);
-    } else {
-        state->server_tag ^= 1u;
-        state->server_pending = lazy ? 1u : 0u;
-    }
-}
-
-// Ends a worker or server call.  In this order of workgroups:
+// Ends a worker or server call whose main kernels do not (ScratchRef::ends).  In this order of workgroups:
 //   fin_wgs workgroups   form the scales of the blocks larger than fuse_limit (per-layout list),
 //                        write them out and post them in the blocks' ready words;
 //   res_wgs workgroups   e <- p - Delta on the segments whose p is always parked (per-layout
@@ -120,10 +101,11 @@ __device__ __forceinline__ void advance_call(CallState *state, const Scratch &X,
 __global__ __launch_bounds__(THREADS) void k_tail(Layout L, ScratchRef R, TailArgs T)
 {
     R.state = R.snapshot;
+    R.ends = 0;
     const Scratch X = open_call(R);
     __shared__ SyncShared S;
     const int wg = blockIdx.x;
-    if (wg == 0 && threadIdx.x == 0) advance_call(T.state, X, T.nsets, T.lazy);
+    if (wg == 0 && threadIdx.x < 64) advance_call(T.state, *T.state, X, T.nsets, T.lazy);
     if (wg < T.fin_wgs) {
         const int n = T.n_late * T.nsets;
         for (int i = wg; i < n; i += T.fin_wgs) {

@@ -301,8 +301,9 @@ void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, int set)
     float *te = A.err + (int64_t)tile * TILE;
     float4 p[SUBROWS];
     server_values_mixed(L, A, tile, T, n_valid, te, p, S);
+    const unsigned before = arrive(X, S);
     compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
-    snapshot_call(R);           // there may be no whole tiles
+    end_call(arrived(before, X), R, X, S);      // there may be no whole tiles
 }
 
 // p~ of a tile of a few segments (see compress_few): as server_values_whole, with a table of sums for one segment
@@ -593,10 +594,10 @@ __device__ __forceinline__ void server_values_pair_many(const ServerArgs &A, int
         }
 }
 
-// A pair from loads to stores (compress_uniform, resolve_posted and finish_uniform for both tiles at once).
+// A pair from loads to stores (compress_uniform and settle_uniform for both tiles at once).  Returns arrived()'s answer.
 template <bool MANY>
-__device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A, const TileRec &T, const Scratch &X, int set,
-                                            SyncShared &S, float *lds, float *more)
+__device__ __forceinline__ unsigned server_pair(const Layout &L, const ServerArgs &A, const TileRec &T, const Scratch &X, int set,
+                                                SyncShared &S, float *lds, float *more)
 {
     const int64_t start = (int64_t)T.tile * TILE;
     float *te = A.err + start;
@@ -633,19 +634,11 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
         __hip_atomic_store(set_part(X, L, set) + 2 * ((int64_t)T.tile + threadIdx.x), w | (set_tag(X, set) ? TAG_BIT : 0ull),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    const unsigned before = arrive(X, S);
     const bool counted = is_counted(L, sp), kept = counted || (L.keep > 0 && (int64_t)T.tile >= first_kept(L, sp));
-    if (counted || L.keep > 0) {
-        if ((int64_t)T.tile + 1 == last_whole_tile(sp))
-            finished = finish_block(T.fb, sp, L, X, set, A.scales, S, &s);
-        else if (kept)
-            finished = wait_ready(sp, 0ull, L, X, set, S, &s);
-        if (!kept)
-            finished = false;           // parked like the others of its block, whatever it has formed
-        else if (!finished) {
-            defer_segment(T.tile, 0, X, set);
-            defer_segment(T.tile + 1, 0, X, set);
-        }
-    }
+    const bool forms = (counted || L.keep > 0) && (int64_t)T.tile + 1 == last_whole_tile(sp);
+    if (kept || forms) finished = block_scale(forms, T.fb, sp, L, X, set, A.scales, S, 0, &s) && kept;    // else parked like the others of its block
+    const unsigned left = arrived(before, X);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         if (finished)
@@ -654,6 +647,8 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) stream_store4(pair_part(te, q, k), v[q][k]);
     }
+    if (kept && !finished) park_segment(T.tile, 0, true, X, set, S);
+    return left;
 }
 
 // Server part of Algorithm 4, all tiles in one launch, in the order of k_worker_tiles.  p~ as
@@ -673,7 +668,7 @@ __device__ __forceinline__ void server_pair(const Layout &L, const ServerArgs &A
 // MANY: more than SERVER_CHUNK workers.
 template <bool SEGMENTS, int FLOATS>
 struct ServerShared : SyncShared {
-    float val[FLOATS];
+    alignas(16) float val[FLOATS];      // read 128 bits at a time
 };
 template <int FLOATS>
 struct ServerShared<true, FLOATS> : TileShared {
@@ -685,6 +680,10 @@ constexpr int server_occupancy(int tiles, bool many, bool pairs)
 {
     return pairs ? (many ? 6 : 7) : tiles == DENSE_TILES ? 6 : tiles == FEW_TILES || many ? 7 : 8;
 }
+
+// Pairs of more than eight workers leave the end of their calls to k_tail: the code for it costs the pairs more than that
+// (354 M of a transformer, 14 workers: 730 us without, 783 with it).
+constexpr bool server_ends(bool many, bool pairs) { return !(many && pairs); }
 
 template <int TILES, bool MANY, bool PAIRS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(server_occupancy(TILES, MANY, PAIRS), 8)))
@@ -703,13 +702,14 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         load_tile(A.err + (int64_t)blockIdx.x * TILE, tv, TILE);
         __builtin_amdgcn_sched_barrier(0);
     }
-    const Scratch X = open_call(R);
+    Scratch X = open_call(R);
+    if (!server_ends(MANY, PAIRS)) X.ends = 0;
     const TileRec T = PAIRS ? L.paired_tiles[blockIdx.x] : MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
     if constexpr (PAIRS) {
         if (T.words == TILE_PAIR) {
             __shared__ __align__(16) float more[MANY ? PAIR_EXCHANGE + PAIR_VALUES : SUM_TABLE];
-            server_pair<MANY>(L, A, T, X, set, S, lds, more);
-            snapshot_call(R);
+            const unsigned left = server_pair<MANY>(L, A, T, X, set, S, lds, more);
+            end_call(left, R, X, S);
             return;
         }
     }
@@ -717,6 +717,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
     const int64_t tile_start = (int64_t)tile * TILE;
     const int n_valid = MIXED ? tile_valid(L, tile) : TILE;
     float *te = A.err + tile_start;
+    unsigned left;
     if (!MIXED || T.words < 0) {
         if (MIXED || PAIRS) {
             load_sign_halves(A, tile_start, 0, h);
@@ -730,21 +731,23 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         correct_loaded_residual(tv, corr);
         server_values_whole<MANY>(A, tile_start, T.fb, h, h1, tv, p, lds);
         const int kind = compress_uniform(p, L, tile, T.fb, sp, TILE, A.signs, A.scales, te, X, set, S, P);
-        resolve_posted(P, L, X, set, A.scales, S);
-        if (kind == UNI_PENDING) finish_uniform(p, tile, TILE, sp, 0ull, te, L, X, set, S);
+        left = settle_uniform(p, kind, P, tile, T.fb, sp, A.scales, te, L, X, set, S);
     } else if constexpr (MIXED) {
         if (TILES == DENSE_TILES && T.nseg < 0) {
             server_values_mixed(L, A, tile, T, n_valid, te, p, S);
+            const unsigned before = arrive(X, S);
             compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
-            snapshot_call(R);
+            end_call(arrived(before, X), R, X, S);
             return;
         }
         __shared__ FewShared F;
         few_bounds(L, T, tile_start, n_valid, F.bound);
         server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
+        const unsigned before = arrive(X, S);
         compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F, lds);
+        left = arrived(before, X);
     }
-    snapshot_call(R);
+    end_call(left, R, X, S);
 }
 
 }  // namespace ef

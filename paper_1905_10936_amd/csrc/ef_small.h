@@ -59,7 +59,7 @@ constexpr int SMALL_BY_WAVE = 16;
 
 struct SmallShared {
     double sum[TILE];           // segment sums; a whole tile: one row sum per thread
-    float val[TILE];            // |p| per element
+    alignas(16) float val[TILE];        // |p| per element
     float scale[TILE];          // segment scales
     int bound[SMALL_BY_WAVE + 1];       // where the segments start, and the last one ends
     int long_list[MAX_LONG];    // of more segments: the ones too long for one thread
@@ -255,10 +255,10 @@ __device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &
 // The workgroup is done (called by all of it): the last one to get here ends the call.
 __device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, const SmallArgs &Z, SmallShared &S)
 {
+    int last = 0;
     if (threadIdx.x == 0) {
         const unsigned n = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x, g = me % DONE_GROUPS;
         const unsigned in_group = (n + DONE_GROUPS - 1 - g) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
-        int last = 0;
         if (atomicAdd(Z.done + g * DONE_STRIDE, 1u) + 1u == in_group) {
             Z.done[g * DONE_STRIDE] = 0u;
             if (atomicAdd(Z.done + DONE_GROUPS * DONE_STRIDE, 1u) + 1u == groups) {
@@ -270,10 +270,11 @@ __device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, 
         if (last) {
             left = (__hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
                     __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
-            advance_call(Z.state, X, Z.nsets, Z.lazy);       // clears the next call's counters, not this one's
         }
         S.left_over = left;
     }
+    // clears the next call's counters, not this one's
+    if (wave_id() == 0 && uniform_u32((unsigned)last)) advance_call(Z.state, *Z.state, X, Z.nsets, Z.lazy);
     __syncthreads();
     if (S.left_over) small_left_over(L, X, Z);
 }

@@ -62,6 +62,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "ef_layout.h"
 
@@ -141,8 +142,8 @@ struct Layout {
 // arguments of a call are the same every time (a captured HIP graph of the
 // calls can be replayed): the number of calls made on the plan and the tag each
 // scratch set's partial words carry since the last call that used the set.
-// The kernel that ends a call (k_tail) moves it on; its own workgroups go by the copy that the call's
-// main kernel leaves in ScratchRef::snapshot, so nothing has to wait for them.
+// Whoever ends a call moves it on: the last workgroup of the main kernel to begin (arrived), or k_tail, whose own
+// workgroups go by the copy that the call's main kernel leaves in ScratchRef::snapshot, so nothing has to wait for them.
 struct alignas(32) CallState {
     unsigned int calls;
     unsigned int server_tag;            // bit 0
@@ -151,20 +152,64 @@ struct alignas(32) CallState {
     unsigned int server_pending;        // bit 0: the same for the server residual
 };
 
+// A call whose main kernel leaves nothing for certain to another one ends without k_tail (ScratchRef::ends).  Every workgroup
+// counts itself in once it has read the call state, on one of ARRIVE_GROUPS words a cache line apart; the last of a group
+// counts the group on one word more, and the last of all steps the call state: nobody reads it any more.  The count's answer
+// comes back while the workgroup waits for its block's scale, so that it costs no time.  (Counting out at the end does: an atomic's answer takes several us while HBM is saturated.)
+// A wait that runs out goes by the same word.  The workgroup leaves p in the residual buffer.  If all workgroups have begun, all
+// partial sums are sure to come (each posts its own ahead of its waits), and it waits for them at its end and finishes the
+// segment.  Else it is counted there as parked and leaves an entry in ScratchRef::parked, and the last workgroup to begin, which
+// finds the number of entries in its own count's answer, does that for them.
+constexpr int ARRIVE_GROUPS = 32, ARRIVE_STRIDE = 32;       // words
+constexpr int ARRIVE_AT = 32;                               // the first of them, after a parity's counters (ScratchRef::list_cnt)
+constexpr int CALL_WORDS = ARRIVE_AT + (ARRIVE_GROUPS + 1) * ARRIVE_STRIDE;
+constexpr unsigned ARRIVED_MASK = 255u, PARKED_ONE = 256u;  // on the last word: groups that are complete; parked entries
+constexpr int64_t ENDS_WGS_MAX = 1 << 16;                   // workgroups of such a call: of more, k_tail's 5 us are nothing
+constexpr unsigned long long PARKED_VALID = 1ull << 63;     // entry: | PARKED_BOTH | PARKED_FORMS | (set << 33) | (tile << 1) | slot
+constexpr unsigned long long PARKED_BOTH = 1ull << 62;      // the tile and the next one
+constexpr unsigned long long PARKED_FORMS = 1ull << 61;     // the block's scale is still to be written, too
+constexpr unsigned PARK_FORMS = 1u << 31;                   // the same beside an entry's number (SyncShared::park)
+constexpr unsigned PARK_OWN = PARK_FORMS - 1u;              // in place of the number: the workgroup's own to see to
+
 // Kernel argument: the plan's scratch.  A "set" is one worker, or the server.
 struct ScratchRef {
     unsigned long long *part;
     unsigned long long *ready;
     unsigned long long *defer_list;
     unsigned long long *fin_list;
-    unsigned int *list_cnt;             // [8]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2] (a call uses those of its parity)
+    unsigned int *list_cnt;             // [CALL_WORDS]: defer_cnt[2], fin_cnt[2], ticket[2], lost_cnt[2], then the words of the
+                                        // count of workgroups, two each (a call uses those of its parity)
     float *lazy_scales;                 // [nsets][lazy_stride] last scale of every block larger than fuse_limit
     int lazy_stride;
     const CallState *state;
     CallState *snapshot;                // what the call's main kernel found in *state, for the kernel that ends the call
     int set_base;                       // first set this call uses (0 for workers, max_workers for the server)
     int spin_limit;
+    // of a call that ends without k_tail
+    int ends;
+    int columns, nsets;                 // workgroups: of a set, and sets
+    int lazy;
+    CallState *step;
+    unsigned long long *parked;         // entries, all 0 between calls
+    float *err;                         // residual buffers of the call's sets, err_stride apart
+    int64_t err_stride;
+    float *scales;                      // scale arrays of the call's sets, scales_stride apart
+    int64_t scales_stride;
 };
+
+// The arguments every kernel that may end its call begins with, read again where they are seldom needed: kept from the
+// kernel's start they cost it scalar registers throughout.
+struct CallArgs {
+    Layout L;
+    ScratchRef R;
+};
+__device__ __forceinline__ const CallArgs &call_args()
+{
+    typedef __attribute__((address_space(4))) const void *Segment;
+    Segment at = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const CallArgs *)at;
+}
 
 // Scratch of one call, formed by every kernel from ScratchRef and CallState (open_call).
 struct Scratch {
@@ -180,7 +225,8 @@ struct Scratch {
     int set_base;               // first set this call uses (0 for workers, max_workers for the server)
     int spin_limit;             // polls before a waiting workgroup gives up and parks p
     unsigned int *lost_cnt;     // waits of a group (sync_group_wait) that ran out in this call: a diagnostic
-    unsigned int *next_cnt;     // the counters of the next call (zeroed by this call's last kernel)
+    unsigned int *next_cnt;     // the counters of the next call (zeroed by whoever ends this one)
+    int ends;                   // the call ends without k_tail
     // Deferred correction.  A block larger than fuse_limit cannot have its residual finished in
     // the first kernel; instead of a second pass over it (p written, read back, e written: 8 more
     // bytes per element), the residual buffer keeps p, the block's scale is remembered here, and
@@ -226,6 +272,7 @@ __device__ __forceinline__ Scratch open_call(const ScratchRef &R)
     X.epoch = calls % 0xffffffffu + 1u;     // never 0: 0 marks "no scale posted"
     X.set_base = R.set_base;
     X.spin_limit = R.spin_limit;
+    X.ends = R.ends;
     return X;
 }
 
@@ -234,7 +281,7 @@ __device__ __forceinline__ Scratch open_call(const ScratchRef &R)
 // them scalar loads (measured: server call with 16 workers 1.12 -> 1.26 ms).
 __device__ __forceinline__ void snapshot_call(const ScratchRef &R)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *R.snapshot = *R.state;
+    if (!R.ends && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *R.snapshot = *R.state;
 }
 
 struct WorkerArgs {
@@ -298,6 +345,15 @@ __device__ __forceinline__ void guarded_store4(float *base, int local, int n_val
     if (local + 3 < n_valid) base[local + 3] = v.w;
 }
 
+template <class T>
+__device__ __forceinline__ T *tile_part(T *base, int k)
+{
+    unsigned at = (threadIdx.x >> 6) * 4096u + (threadIdx.x & 63u) * 16u;
+    asm("" : "+v"(at));
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type C;
+    return reinterpret_cast<T *>(reinterpret_cast<C *>(base) + at) + k * 256;
+}
+
 // A thread's four float4 of one tile.  Only the last tile of a vector can be
 // ragged; the test is uniform over the workgroup, so full tiles run straight
 // through 128-bit accesses with no per-access branch.
@@ -305,7 +361,7 @@ __device__ __forceinline__ void load_tile(const float *base, float4 (&v)[SUBROWS
 {
     if (n_valid == TILE) {
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) v[k] = stream_load4(base + local_base(k));
+        for (int k = 0; k < SUBROWS; ++k) v[k] = stream_load4(tile_part(base, k));
     } else {
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) {
@@ -332,7 +388,7 @@ __device__ __forceinline__ void store_tile(float *base, const float4 (&v)[SUBROW
 {
     if (n_valid == TILE) {
 #pragma unroll
-        for (int k = 0; k < SUBROWS; ++k) stream_store4(base + local_base(k), v[k]);
+        for (int k = 0; k < SUBROWS; ++k) stream_store4(tile_part(base, k), v[k]);
     } else {
 #pragma unroll
         for (int k = 0; k < SUBROWS; ++k) guarded_store4(base, local_base(k), n_valid, v[k]);
@@ -576,10 +632,12 @@ struct SyncShared {
     double red[2 * NWAVES];     // one a wavefront, two where it has two tiles (server_pair)
     int flag[2];
     unsigned ticket;
+    unsigned park[2];           // waits that ran out (head, tail): number of the entry, and PARK_FORMS
+    unsigned long long own[2];  // this workgroup's own segments to see to (0: none)
 };
 // ... and what the kernels that cut a tile into segments need on top of it.
 struct TileShared : SyncShared {
-    float val[TILE];            // |p| per element, then the element's scale (closed segments)
+    alignas(16) float val[TILE];    // |p| per element, then the element's scale (closed segments)
     double open_sum[2];
     int long_list[MAX_LONG];
     int n_long;
@@ -594,6 +652,75 @@ __device__ __forceinline__ unsigned long long *set_part(const Scratch &X, const 
 __device__ __forceinline__ unsigned long long set_tag(const Scratch &X, int set)
 {
     return (X.tags >> (set - X.set_base)) & 1ull;
+}
+
+// -------------------------------------------------- the end of the call ---
+
+// The call is over: count it, flip the tags of the sets it used, clear the words the next
+// call will use (one wavefront).  now: what *state holds.
+__device__ __forceinline__ void advance_call(CallState *state, const CallState &now, const Scratch &X, int nsets, int lazy)
+{
+    const int lane = lane_id();
+    if (lane < 4) X.next_cnt[2 * lane] = 0u;
+    if (lane <= ARRIVE_GROUPS) X.next_cnt[ARRIVE_AT + lane * ARRIVE_STRIDE] = 0u;
+    if (lane != 0) return;
+    const unsigned long long used = nsets >= 64 ? ~0ull : ((1ull << nsets) - 1ull);
+    state->calls = now.calls + 1u;
+    if (X.set_base == 0) {
+        state->worker_tags = now.worker_tags ^ used;
+        // with the deferred correction on, the large blocks of these sets now hold p
+        state->worker_pending = lazy ? (now.worker_pending | used) : (now.worker_pending & ~used);
+    } else {
+        state->server_tag = now.server_tag ^ 1u;
+        state->server_pending = lazy ? 1u : 0u;
+    }
+}
+
+// This call's words of the count (its defer_cnt is the first word of its parity).
+__device__ __forceinline__ unsigned *arrive_word(const Scratch &X, unsigned g) { return X.defer_cnt + ARRIVE_AT + g * ARRIVE_STRIDE; }
+
+// Thread 0 counts its workgroup in; the answer goes to arrived().  Called when the tile's values are there: an atomic ahead of
+// the loads of scales and block offsets would keep the compiler from making them scalar loads, and where many values
+// are still to come it costs the server's pairs 7 spilled registers.  (The lane number, 0 here, keeps the compiler from
+// making one addition of the wavefront's, whose answer it would wait for at once.)
+__device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
+{
+    unsigned before = 0u;
+    if (X.ends && threadIdx.x == 0) {
+        S.own[0] = S.own[1] = 0ull;
+        unsigned *at = arrive_word(X, blockIdx.x % ARRIVE_GROUPS) + __builtin_amdgcn_mbcnt_lo(~0u, 0u);
+        before = __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return before;
+}
+__device__ __forceinline__ unsigned arrive_groups(const ScratchRef &R) { return min((unsigned)R.columns, (unsigned)ARRIVE_GROUPS); }
+
+// The last workgroup to have counted itself in steps the call state, its first wavefront alone.  Returns to that one the number
+// of entries that are left to it, 0 to all others.  Called when the answer is likely to be there: after the wait for a scale.
+__device__ __forceinline__ unsigned arrived(unsigned before, const Scratch &X)
+{
+    if (!X.ends || uniform_u32(threadIdx.x >> 6) != 0u) return 0u;
+    const ScratchRef &R = call_args().R;
+    const unsigned g = blockIdx.x % ARRIVE_GROUPS;
+    if (uniform_u32(before) + 1u != (unsigned)R.nsets * (((unsigned)R.columns + ARRIVE_GROUPS - 1u - g) / ARRIVE_GROUPS)) return 0u;
+    typedef __attribute__((address_space(4))) const void *Segment;
+    Segment state = (Segment)R.step;        // nobody has changed it yet: a scalar load, like the first one
+    asm("" : "+s"(state));
+    const CallState now = *(const CallState *)state;
+    unsigned top = 0u;
+    if (lane_id() == 0) top = atomicAdd(arrive_word(X, ARRIVE_GROUPS), 1u);
+    top = uniform_u32(top);
+    if ((top & ARRIVED_MASK) + 1u != arrive_groups(R)) return 0u;
+    advance_call(R.step, now, X, R.nsets, R.lazy);
+    return top / PARKED_ONE;
+}
+
+// Thread 0: a wait has run out.  If all workgroups have begun, this one sees to the segment itself at its end, where the sums
+// are sure to come; else the segment gets the number of an entry.
+__device__ __forceinline__ void give_up(const Scratch &X, SyncShared &S, int slot, unsigned forms)
+{
+    const unsigned top = atomicAdd(arrive_word(X, ARRIVE_GROUPS), PARKED_ONE);
+    S.park[slot] = ((top & ARRIVED_MASK) == arrive_groups(call_args().R) ? PARK_OWN : top / PARKED_ONE) | forms;
 }
 
 // ------------------------------------------ cross-tile block reductions ---
@@ -729,8 +856,8 @@ __device__ __forceinline__ double sum_block_partials(const Layout &L, int64_t b,
 // the same arguments; returns the same answer to all of them.
 constexpr int GATHER_DEEP = 4;      // partial words a thread has in flight
 
-__device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &L, const Scratch &X, int set, SyncShared &S,
-                                             float *s)
+__device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &L, const Scratch &X, int set, int spin_limit,
+                                             SyncShared &S, float *s)
 {
     const unsigned long long *part = set_part(X, L, set);
     const unsigned long long tag = set_tag(X, set);
@@ -748,7 +875,7 @@ __device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &
 #pragma unroll
         for (int q = 0; q < GATHER_DEEP; ++q) w[q] = tag << 63;         // past the block: +0 with this call's tag
         for (;;) {
-            if (polls++ >= X.spin_limit) {
+            if (polls++ >= spin_limit) {
                 ok = 0;
                 break;
             }
@@ -772,25 +899,36 @@ __device__ __forceinline__ bool gather_scale(const BlockSpan &sp, const Layout &
     return true;
 }
 
+// A scale is there: written out and posted for the block's other tiles.  One thread.
+__device__ __forceinline__ void post_scale(int64_t b, const BlockSpan &sp, float s, const Layout &L, const Scratch &X, int set,
+                                           float *scales_out)
+{
+    scales_out[b] = s;
+    __hip_atomic_store(ready_word(X, L, set, sp), ((unsigned long long)X.epoch << 32) | (unsigned long long)__float_as_uint(s),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The workgroup that holds the gatherer tile of one-pass block b forms the
 // scale from the partials (waiting, bounded, for those still in flight: every
 // other tile of the block was handed out earlier), writes it out and posts it
 // for the block's other tiles.  Called by every thread of that workgroup;
 // returns to all of them whether the scale could be formed, and the scale.
 __device__ __forceinline__ bool finish_block(int64_t b, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
-                                             float *scales_out, SyncShared &S, float *scale)
+                                             float *scales_out, SyncShared &S, int slot, float *scale)
 {
     float s = 0.f;
-    const bool ok = gather_scale(sp, L, X, set, S, &s);
+    const bool ok = gather_scale(sp, L, X, set, X.spin_limit, S, &s);
     if (threadIdx.x == 0) {
         if (ok) {
-            scales_out[b] = s;
-            __hip_atomic_store(ready_word(X, L, set, sp),
-                               ((unsigned long long)X.epoch << 32) | (unsigned long long)__float_as_uint(s),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            post_scale(b, sp, s, L, X, set, scales_out);
         } else {
             const unsigned k = atomicAdd(X.fin_cnt, 1u);
-            X.fin_list[k] = ((unsigned long long)set << 32) | (unsigned long long)b;
+            if (X.ends) {
+                atomicAdd(X.defer_cnt, 1u);
+                give_up(X, S, slot, PARK_FORMS);
+            } else {
+                X.fin_list[k] = ((unsigned long long)set << 32) | (unsigned long long)b;
+            }
         }
     }
     *scale = s;
@@ -803,7 +941,7 @@ __device__ __forceinline__ void resolve_posted(const Posted &P, const Layout &L,
                                                float *scales_out, SyncShared &S)
 {
     float s;
-    if (P.gather >= 0) (void)finish_block(P.gather, P.sp, L, X, set, scales_out, S, &s);
+    if (P.gather >= 0) (void)finish_block(P.gather, P.sp, L, X, set, scales_out, S, 0, &s);
 }
 
 // Thread 0's early look at the ready word of block b (b < 0: none).
@@ -854,6 +992,50 @@ __device__ __forceinline__ void defer_segment(int32_t tile, int which, const Scr
         const unsigned i = atomicAdd(X.defer_cnt, 1u);
         X.defer_list[i] = ((unsigned long long)set << 33) | ((unsigned long long)tile << 1) | (unsigned)which;
     }
+}
+
+// The scale of a one-pass block (or one with kept tiles), which the gatherer (`forms`) makes of the partial sums, writes out
+// and posts, and the others wait for; both bounded.  False: the wait ran out, and p is to be parked (park_segment).  Called by
+// every thread of the workgroup; same answer to all of them.  word: the block's ready word.
+__device__ __forceinline__ bool wait_scale(const unsigned long long *word, const Scratch &X, SyncShared &S, int slot, float *scale)
+{
+    if (wait_ready_at(word, 0ull, X, S, scale)) return true;
+    if (X.ends && threadIdx.x == 0) {
+        atomicAdd(X.defer_cnt, 1u);
+        give_up(X, S, slot, 0u);
+    }
+    return false;
+}
+__device__ __forceinline__ bool block_scale(bool forms, int64_t b, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
+                                            float *scales_out, SyncShared &S, int slot, float *scale)
+{
+    if (!forms) return wait_scale(ready_word(X, L, set, sp), X, S, slot, scale);
+    return finish_block(b, sp, L, X, set, scales_out, S, slot, scale);
+}
+
+// The segment (both: the whole tile and the next one) whose wait ran out has been stored as p: an entry for whoever ends
+// the call.  One wavefront releases for all of them, whose stores have reached the L2 by then.
+__device__ __forceinline__ void park_segment(int32_t tile, int which, bool both, const Scratch &X, int set, SyncShared &S)
+{
+    if (!X.ends) {
+        defer_segment(tile, which, X, set);
+        if (both) defer_segment(tile + 1, which, X, set);
+        return;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned at = S.park[which];
+        const unsigned long long entry = PARKED_VALID | (both ? PARKED_BOTH : 0ull) | ((at & PARK_FORMS) ? PARKED_FORMS : 0ull) |
+                                         ((unsigned long long)set << 33) | ((unsigned long long)tile << 1) | (unsigned)which;
+        if ((at & ~PARK_FORMS) == PARK_OWN) {
+            S.own[which] = entry;
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __hip_atomic_store(call_args().R.parked + (at & ~PARK_FORMS), entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
 }
 
 // ------------------------------------------------------- tile compression ---
@@ -952,13 +1134,14 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
     // that ends the call.
     float s_head = 0.f, s_tail = 0.f;
     bool fin_head = false, fin_tail = false;
+    bool park_head = false, park_tail = false;
     if (head_open && finishes_with_mixed(L, block_span(L, fb))) {
-        fin_head = finish_block(fb, block_span(L, fb), L, X, set, scales_out, S, &s_head);
-        if (!fin_head) defer_segment(tile, 0, X, set);
+        fin_head = finish_block(fb, block_span(L, fb), L, X, set, scales_out, S, 0, &s_head);
+        park_head = !fin_head;
     }
     if (tail_open && finishes_with_mixed(L, block_span(L, lb))) {
-        fin_tail = wait_ready(block_span(L, lb), 0ull, L, X, set, S, &s_tail);
-        if (!fin_tail) defer_segment(tile, 1, X, set);
+        fin_tail = wait_scale(ready_word(X, L, set, block_span(L, lb)), X, S, 1, &s_tail);
+        park_tail = !fin_tail;
     }
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
@@ -980,6 +1163,8 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
         p[k] = make_float4(ev[0], ev[1], ev[2], ev[3]);
     }
     store_tile(err_tile, p, n_valid);
+    if (park_head) park_segment(tile, 0, false, X, set, S);
+    if (park_tail) park_segment(tile, 1, false, X, set, S);
     __syncthreads();            // S.val is free again
 }
 
@@ -1132,15 +1317,12 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
             F.scale[sg] = s;
         }
     }
+    bool park_head = false, park_tail = false;
     if (head_open) {
         float s = 0.f;
         if (is_counted(L, hs)) {
-            const bool ok = (int64_t)tile == gatherer_tile(L, hs) ? finish_block(T.fb, hs, L, X, set, scales_out, S, &s)
-                                                                  : wait_ready(hs, 0ull, L, X, set, S, &s);
-            if (!ok) {
-                s = 0.f;
-                defer_segment(tile, 0, X, set);
-            }
+            park_head = !block_scale((int64_t)tile == gatherer_tile(L, hs), T.fb, hs, L, X, set, scales_out, S, 0, &s);
+            if (park_head) s = 0.f;
         }
         if (threadIdx.x == 0) F.scale[0] = s;
     }
@@ -1150,10 +1332,8 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
         if (n <= L.fuse_limit) {
             // the block starts in this tile: its whole tiles, if any, are the ones between this and its last
             const int64_t gatherer = (int64_t)tile + (whole > 0 ? whole : n - 1);
-            if (!wait_ready_at(X.ready + ((int64_t)set * L.ntiles + gatherer) * READY_STRIDE, 0ull, X, S, &s)) {
-                s = 0.f;
-                defer_segment(tile, 1, X, set);
-            }
+            park_tail = !wait_scale(X.ready + ((int64_t)set * L.ntiles + gatherer) * READY_STRIDE, X, S, 1, &s);
+            if (park_tail) s = 0.f;
         }
         if (threadIdx.x == 0) F.scale[nseg - 1] = s;
     }
@@ -1175,6 +1355,8 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
         }
     }
     store_tile(err_tile, p, n_valid);
+    if (park_head) park_segment(tile, 0, false, X, set, S);
+    if (park_tail) park_segment(tile, 1, false, X, set, S);
 }
 
 // Writing the residual out in step.  Measured on this machine: workgroups that take consecutive
@@ -1234,6 +1416,32 @@ __device__ __forceinline__ void sync_group_wait(int32_t tile, const BlockSpan &s
         __syncthreads();
     }
     if (threadIdx.x == 0 && lost) atomicAdd(X.lost_cnt, 1u);
+}
+
+// What the kernels with one workgroup per tile do with a uniform tile once its sum is posted (compress_uniform's answers):
+// its block's scale, formed here or waited for in place, then its residual.
+// Returns what arrived() answers.
+__device__ __forceinline__ unsigned settle_uniform(float4 (&p)[SUBROWS], int kind, const Posted &P, int32_t tile, int32_t b,
+                                                   const BlockSpan &sp, float *scales_out, float *err_tile, const Layout &L,
+                                                   const Scratch &X, int set, SyncShared &S)
+{
+    const unsigned before = arrive(X, S);
+    float s = 0.f;
+    bool ok = false;
+    if (kind == UNI_PENDING || P.gather >= 0) ok = block_scale(P.gather >= 0, b, sp, L, X, set, scales_out, S, 0, &s);
+    const unsigned left = arrived(before, X);
+    if (kind == UNI_HELD) {
+        sync_group_wait(tile, sp, L, X, set, S);
+        store_tile(err_tile, p, TILE);
+    }
+    if (kind != UNI_PENDING) return left;
+    if (ok) {
+#pragma unroll
+        for (int k = 0; k < SUBROWS; ++k) residual4(p[k], s);
+    }
+    store_tile(err_tile, p, TILE);
+    if (!ok) park_segment(tile, 0, false, X, set, S);
+    return left;
 }
 
 // Fill the first half of S.val (read as 16-bit integers) with the segment index of every element of a

@@ -1,6 +1,7 @@
 // Worker kernels of libef (Algorithm 4 and Algorithm 3 of arxiv 1905.10936): see ef_tile.h for the tile scheme.
 #pragma once
 #include "ef_tile.h"
+#include "ef_end.h"
 #include "ef_quality.h"
 
 namespace ef {
@@ -60,6 +61,7 @@ void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     load_tile(e, pv, n_valid);
     worker_values<MOM>(gv, mv, pv, A.mu, A.r);
     if (MOM) store_tile(m, mv, n_valid);
+    const unsigned before = arrive(X, S);
     if constexpr (QUAL) {
         clear_past_end(pv, n_valid);
         float4 a[SUBROWS];
@@ -69,7 +71,7 @@ void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     }
     compress_mixed(pv, L, T, tile, n_valid, A.signs + (int64_t)worker * A.signs_stride,
                    A.scales + (int64_t)worker * A.scales_stride, e, X, worker, S);
-    snapshot_call(R);           // there may be no whole tiles
+    end_call(arrived(before, X), R, X, S);      // there may be no whole tiles
 }
 
 // Uniform tiles of the worker as a persistent kernel.
@@ -332,6 +334,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
     g += tile_start;
     if (MOM) m += tile_start;
     e += tile_start;
+    unsigned left;
     if (!MIXED || T.words < 0) {
         const BlockSpan sp = span_of(T.bs(), T.be());
         const LoadedCorrection corr = loaded_correction(L, T.fb, X, worker);
@@ -351,13 +354,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         }
         Posted P;
         const int kind = compress_uniform<MOM>(pv, L, tile, T.fb, sp, TILE, signs, scales_out, e, X, worker, S, P, true);
-        resolve_posted(P, L, X, worker, scales_out, S);
-        if (kind == UNI_PENDING) {
-            finish_uniform(pv, tile, TILE, sp, 0ull, e, L, X, worker, S);
-        } else if (kind == UNI_HELD) {
-            sync_group_wait(tile, sp, L, X, worker, S);
-            store_tile(e, pv, TILE);
-        }
+        left = settle_uniform(pv, kind, P, tile, T.fb, sp, scales_out, e, L, X, worker, S);
     } else if constexpr (MIXED) {
         __shared__ FewShared F;
         const bool dense = TILES == DENSE_TILES && T.nseg < 0;
@@ -367,6 +364,7 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         load_tile(e, pv, n_valid);
         worker_values<MOM>(gv, mv, pv, A.mu, A.r);
         if (MOM) store_tile(m, mv, n_valid);
+        const unsigned before = arrive(X, S);
         if constexpr (QUAL) {
             clear_past_end(pv, n_valid);
             float4 a[SUBROWS];
@@ -378,8 +376,9 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
             compress_mixed(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S);
         else
             compress_few<MOM>(pv, L, T, tile, n_valid, signs, scales_out, e, X, worker, S, F, S.val);
+        left = arrived(before, X);
     }
-    snapshot_call(R);
+    end_call(left, R, X, S);
 }
 
 }  // namespace ef

@@ -1,0 +1,67 @@
+"""Calls that their main kernel ends (no kernel after it): the last workgroup to begin steps the call state, and a workgroup whose
+wait runs out either finishes its segment itself, if all have begun, or leaves it to the last one to begin.  Launches of
+more workgroups than are resident at once, so that both happen, for whole tiles, pairs, tiles of few segments and dense ones;
+every result has the bits of a plan whose waits succeed, call after call, and calls that k_tail ends stand between."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_10936_amd as ef
+
+pytestmark = pytest.mark.gpu
+
+T = 4096
+LAYOUTS = {
+    "whole_tiles": [16 * T] * 300,
+    "one_tile_blocks": [T] * 4500,
+    "few_segments": [15 * T + 300, 7, 9 * T - 100] * 170,
+    "dense": [33] * 120_000,
+    "dense_between": ([40] * 300 + [6 * T + 5]) * 400,
+}
+
+
+def _tensors(offs, M, seed):
+    d, B, W = int(offs[-1]), len(offs) - 1, (int(offs[-1]) + 63) // 64
+    ds = (d + 3) // 4 * 4
+    gen = torch.Generator("cuda").manual_seed(seed)
+    t = {k: torch.randn(M, ds, device="cuda", generator=gen) for k in ("g", "m", "e")}
+    t["te"] = torch.randn(d, device="cuda", generator=gen)
+    t["ws"], t["wc"] = torch.zeros(M, W, dtype=torch.int64, device="cuda"), torch.zeros(M, B, device="cuda")
+    t["ss"], t["sc"] = torch.zeros(W, dtype=torch.int64, device="cuda"), torch.zeros(B, device="cuda")
+    return t
+
+
+def _step(plan, t, M, sgd):
+    if sgd:
+        ef.ef_worker_step_sgd(plan, t["g"], t["e"], 0.1, 0.05, t["ws"], t["wc"])
+    else:
+        ef.ef_worker_step(plan, t["g"], t["m"], t["e"], 0.9, 0.1, 0.05, t["ws"], t["wc"])
+    given_up = [plan.last_fallbacks()[0]]
+    ef.ef_server_step(plan, M, t["ws"], t["wc"], t["te"], 0.1, 0.05, t["ss"], t["sc"])
+    given_up.append(plan.last_fallbacks()[0])
+    return given_up
+
+
+@pytest.mark.parametrize("M", [1, 2, 9])
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_waits_that_run_out_end_with_the_same_bits(name, M):
+    offs = np.concatenate([[0], np.cumsum(LAYOUTS[name])])
+    good, bad = ef.ef_plan_create(offs, M), ef.ef_plan_create(offs, M)
+    a, b = _tensors(offs, M, 5), _tensors(offs, M, 5)
+    for p in (good, bad):
+        p.set_persistent(False)
+    for k, spin in enumerate((0, 1, 0, 4, 2048)):
+        bad.tune(spin_limit=spin)
+        if k == 3:                      # a call that k_tail ends, in between: every block in two passes
+            for p, t in ((good, a), (bad, b)):
+                limit = p.fuse_limit
+                p.tune(fuse_limit=0)
+                _step(p, t, M, False)
+                p.tune(fuse_limit=limit)
+        assert _step(good, a, M, sgd=k == 2) == [0, 0]
+        given_up = _step(bad, b, M, sgd=k == 2)
+        if spin == 0 and any(n > T for n in LAYOUTS[name]):
+            assert min(given_up) > 0
+        torch.cuda.synchronize()
+        for key in a:
+            assert torch.equal(a[key].view(torch.int32), b[key].view(torch.int32)), "%s M=%d call %d: %s" % (name, M, k, key)
