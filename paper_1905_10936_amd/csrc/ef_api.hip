@@ -76,12 +76,13 @@ struct ef_plan {
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
     double *d_qtile, *d_qpart;      // [max_workers][ntiles][2], [max_workers][2*ntiles][2]
-    // launches that (nearly) fit on the GPU all at once (ef_small.h): records and start words of the tiles and the
-    // counters, null: this layout has none)
+    // launches that (nearly) fit on the GPU all at once (ef_small.h)
     int small_wgs;                  // most workgroups such a launch may have
     int small_span;                 // most tiles of a block in it
     bool has_small;                 // this layout has such launches
-    ef::SmallArgs small;
+    ef::SmallTile *d_small;         // [ntiles] records of the tiles, if it has
+    ef::StartWord *d_small_words;   // [ntiles][TILE_WORDS]
+    ef::SmallTables small;          // both
     bool kernels_auto;              // ef_plan_set_persistent has not been used to pick the kernels
     bool server_pairs[2];           // the server's calls (of up to eight workers, of more) take the whole tiles in pairs, if there are any
 };
@@ -423,7 +424,6 @@ void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
         if (tiles_of_block(p, b) > p->small_span) return;
     out.resize((size_t)ntiles);
     p->has_small = true;
-    int32_t words = 0;
     for (int32_t t = 0; t < ntiles; ++t) {
         const int64_t start = (int64_t)t * ef::TILE, end = start + ef::TILE;
         const int32_t fb = p->fb_host[t], lb = p->lb_host[t];
@@ -431,7 +431,11 @@ void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
         r = ef::SmallTile();
         r.fb = fb;
         r.nseg = lb - fb + 1;
-        r.words = -1;
+        r.whole = fb == lb && end <= d;
+        if (r.nseg <= ef::SMALL_BY_WAVE) {
+            for (int i = 0; i < r.nseg; ++i) r.bound[i] = (int16_t)(o[fb + i] > start ? o[fb + i] - start : 0);
+            r.bound[r.nseg] = (int16_t)((o[lb + 1] < end ? o[lb + 1] : end < d ? end : d) - start);
+        }
         if (o[fb] < start || o[fb + 1] > end) {
             r.flags |= ef::SMALL_HEAD;
             r.head_t0 = (int32_t)(o[fb] / ef::TILE);
@@ -445,7 +449,6 @@ void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
             r.tail_n = (int32_t)tiles_of_block(p, lb);
             r.tail_db = o[lb + 1] - o[lb];
         }
-        if (fb != lb || end > d) r.words = words++;
     }
 }
 
@@ -660,11 +663,10 @@ int build_device(ef_plan *p)
     mem.add(&p->d_qpart, 4 * nt * nv, Arena::LEAVE);
     mem.add(&p->d_qtile, 2 * nt * nv, Arena::LEAVE);
     if (p->has_small) {
-        mem.add(const_cast<ef::SmallTile **>(&p->small.tiles), small.size(), Arena::COPY, small.data());
-        mem.add(&p->small.done, (size_t)(ef::DONE_GROUPS + 1) * ef::DONE_STRIDE, Arena::ZERO);
+        mem.add(&p->d_small, small.size(), Arena::COPY, small.data());
+        mem.add(&p->d_small_words, nt * ef::TILE_WORDS, Arena::LEAVE);
     }
     { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
-    p->small.state = p->d_state;
     p->L.mixed_tiles = p->d_mixed;
     p->L.whole_tiles = p->d_whole;
     p->L.tiles = p->d_tiles;
@@ -693,8 +695,15 @@ int build_device(ef_plan *p)
     p->X.parked = p->d_parked;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
-    if (p->L.n_mixed) {
+    if (p->L.n_mixed && !p->has_small) {
         hipLaunchKernelGGL(ef::k_start_words, dim3((unsigned)p->L.n_mixed), dim3(ef::THREADS), 0, nullptr, p->L, p->d_words);
+        EF_HIP(hipGetLastError());
+    }
+    if (p->has_small) {
+        p->small.tiles = p->d_small;
+        p->small.words = p->d_small_words;
+        hipLaunchKernelGGL(ef::k_small_words, dim3((unsigned)ntiles), dim3(ef::TILE_WORDS), 0, nullptr, p->L, p->d_small_words,
+                           p->d_words);
         EF_HIP(hipGetLastError());
     }
     p->user_fuse_limit = -1;
@@ -774,18 +783,6 @@ bool small_update(const ef_plan *plan)
     return plan->has_small && plan->kernels_auto && 2 * (int64_t)plan->L.ntiles <= plan->small_wgs;
 }
 
-ef::SmallArgs small_args(const ef_plan *plan, int nsets, float *err, int64_t err_stride, float *scales, int64_t scales_stride)
-{
-    ef::SmallArgs Z = plan->small;
-    Z.nsets = nsets;
-    Z.lazy = plan->lazy;
-    Z.err = err;
-    Z.err_stride = err_stride;
-    Z.scales = scales;
-    Z.scales_stride = scales_stride;
-    return Z;
-}
-
 // Scratch argument of one call over the sets [set_base, set_base + nsets).  Everything that
 // differs between two calls of the same kind is read by the kernels from device memory.
 struct CallScratch {
@@ -804,6 +801,16 @@ CallScratch next_call(const ef_plan *plan, int set_base, int nsets)
     return c;
 }
 
+void ends_itself(CallScratch &c, int columns, float *err, int64_t err_stride, float *scales, int64_t scales_stride)
+{
+    c.X.ends = 1;
+    c.X.columns = columns;
+    c.X.err = err;
+    c.X.err_stride = err_stride;
+    c.X.scales = scales;
+    c.X.scales_stride = scales_stride;
+}
+
 // Does the main kernel end the call, with `columns` workgroups to a set (ScratchRef::ends)?  Then nothing may be left for certain to
 // a kernel after it, and what it has to hand on is set here.
 bool main_kernel_ends(const ef_plan *plan, int role, CallScratch &c, int columns, float *err, int64_t err_stride, float *scales,
@@ -811,12 +818,7 @@ bool main_kernel_ends(const ef_plan *plan, int role, CallScratch &c, int columns
 {
     const ef_plan::Role &r = plan->role[role];
     if (role == ROLE_TICKET || r.n_static || r.n_late || (int64_t)columns * c.X.nsets > ef::ENDS_WGS_MAX) return false;
-    c.X.ends = 1;
-    c.X.columns = columns;
-    c.X.err = err;
-    c.X.err_stride = err_stride;
-    c.X.scales = scales;
-    c.X.scales_stride = scales_stride;
+    ends_itself(c, columns, err, err_stride, scales, scales_stride);
     return true;
 }
 
@@ -1219,11 +1221,11 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     CallScratch c = next_call(plan, 0, n_workers);
     if (!quality && small_call(plan, ROLE_TILES, n_workers)) {
         const dim3 grid((unsigned)plan->L.ntiles, (unsigned)n_workers), block(ef::SMALL_THREADS);
-        const ef::SmallArgs Z = small_args(plan, n_workers, err, state_stride, scales, scales_stride);
+        ends_itself(c, plan->L.ntiles, err, state_stride, scales, scales_stride);
         if (has_mom)
-            hipLaunchKernelGGL(ef::k_worker_small<true>, grid, block, 0, s, plan->L, c.X, A, Z);
+            hipLaunchKernelGGL(ef::k_worker_small<true>, grid, block, 0, s, plan->L, c.X, A, plan->small);
         else
-            hipLaunchKernelGGL(ef::k_worker_small<false>, grid, block, 0, s, plan->L, c.X, A, Z);
+            hipLaunchKernelGGL(ef::k_worker_small<false>, grid, block, 0, s, plan->L, c.X, A, plan->small);
         EF_HIP(hipGetLastError());
         return EF_OK;
     }
@@ -1347,9 +1349,9 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
     }
     CallScratch c = next_call(plan, plan->max_workers, 1);
     if (small_call(plan, ROLE_SERVER, 1)) {
-        const ef::SmallArgs Z = small_args(plan, 1, server_err, 0, out_scales, 0);
-        hipLaunchKernelGGL(ef::k_server_small, dim3((unsigned)plan->L.ntiles), dim3(ef::SMALL_THREADS), 0, s, plan->L, c.X, A, Z,
-                           plan->max_workers);
+        ends_itself(c, plan->L.ntiles, server_err, 0, out_scales, 0);
+        hipLaunchKernelGGL(ef::k_server_small, dim3((unsigned)plan->L.ntiles), dim3(ef::SMALL_THREADS), 0, s, plan->L, c.X, A,
+                           plan->small, plan->max_workers);
         EF_HIP(hipGetLastError());
         return EF_OK;
     }

@@ -18,6 +18,19 @@ __device__ __forceinline__ double sure_word(const unsigned long long *at, unsign
     return __longlong_as_double(0x7ff8000000000000ll);
 }
 
+// An entry that is there or on its way (one wavefront).
+__device__ __forceinline__ unsigned long long take_entry(unsigned long long *at)
+{
+    unsigned long long it = 0ull;
+#pragma unroll 1
+    for (int n = 0; n < SURE_POLLS && !it; ++n) {
+        it = uniform_u64(__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (!it) __builtin_amdgcn_s_sleep(8);
+    }
+    if (lane_id() == 0) *at = 0ull;
+    return it;
+}
+
 // A workgroup sees to its own parked segments, the last one to have begun to the `left` entries of others too, which are there or
 // on their way.  Their blocks' partial sums are sure to come.  (Waits run out only where something else holds the GPU, so
 // one wavefront for all of it is enough.)
@@ -29,18 +42,7 @@ __device__ __forceinline__ void end_left_over(unsigned left, const Scratch &X, S
     const int lane = lane_id();
 #pragma unroll 1
     for (unsigned i = 0; i < left + 2u; ++i) {
-        unsigned long long it = 0ull;
-        if (i < 2u) {
-            it = uniform_u64(S.own[i]);
-        } else {
-            unsigned long long *at = R.parked + (i - 2u);
-#pragma unroll 1
-            for (int n = 0; n < SURE_POLLS && !it; ++n) {
-                it = uniform_u64(__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                if (!it) __builtin_amdgcn_s_sleep(8);
-            }
-            if (lane == 0) *at = 0ull;
-        }
+        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u));
         if (!it) continue;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const int set = (int)((it & (PARKED_FORMS - 1ull)) >> 33), w = set - X.set_base;

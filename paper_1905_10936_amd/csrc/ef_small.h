@@ -9,8 +9,8 @@
 //   * all workgroups, or half of them, are resident at once, so all tiles of a block, mixed ones
 //     included, can wait for it in place; and they do not wait for a gatherer's answer, each adds up the block's partial
 //     sums itself (at most SMALL_SPAN of them: one wavefront, four words a lane);
-//   * no kernel follows: the last workgroup to finish steps the call state (and sees to the segments
-//     whose bounded wait ran out, normally none).
+//   * no kernel follows: the last workgroup to begin steps the call state (see arrive), in a wavefront that has nothing else
+//     to do while the others form the block's sum.
 #pragma once
 #include "ef_layout.h"
 #include "ef_tile.h"
@@ -22,17 +22,21 @@ namespace ef {
 
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_WAVES = SMALL_THREADS / 64;
-constexpr int DONE_GROUPS = 8;          // workgroups count themselves out on this many words ...
-constexpr int DONE_STRIDE = 32;         // ... a cache line apart, and these on one more
+constexpr int COUNT_WAVE = SMALL_WAVES - 1;     // the wavefront that counts the workgroup in
+
+// Up to this many segments of a tile get a wavefront each, of more the short ones get a thread each (server, 4 workers,
+// 49 tiles of 64 blocks of 64: 11.4 us a wavefront each, 7.5 a thread each).
+constexpr int SMALL_BY_WAVE = 16;
 
 struct SmallTile {
     int32_t fb, nseg;           // first block and number of segments
-    int32_t words;              // as in TileRec
+    int32_t whole;              // inside one block, and not the ragged end of the vector
     int32_t flags;
     int32_t head_t0, head_n;    // tiles of the first segment's block, if it is open (SMALL_HEAD)
     int32_t tail_n;             // tiles of the last segment's block, if that one is (SMALL_TAIL): it starts in this tile
     int32_t unused;
     int64_t head_db, tail_db;   // elements of those blocks
+    int16_t bound[SMALL_BY_WAVE + 2];   // of up to SMALL_BY_WAVE segments: where they start, and the last one ends
 };
 enum {
     SMALL_HEAD = 1,         // the first segment is open (a whole tile has no other)
@@ -40,22 +44,6 @@ enum {
     SMALL_HEAD_SLOT = 4,    // the head block's partial in its first tile is in slot 1 (it starts inside that tile)
     SMALL_WRITES_HEAD = 8,  // this tile is the head block's last: it writes the block's scale
 };
-
-struct SmallArgs {
-    const SmallTile *tiles;     // [ntiles]
-    unsigned *done;             // [DONE_GROUPS + 1][DONE_STRIDE], zero between calls
-    CallState *state;
-    int nsets;
-    int lazy;
-    float *err;                 // what advance_call and the segments left over need, as in TailArgs
-    int64_t err_stride;
-    float *scales;
-    int64_t scales_stride;
-};
-
-// Up to this many segments of a tile get a wavefront each, of more the short ones get a thread each (server, 4 workers,
-// 49 tiles of 64 blocks of 64: 11.4 us a wavefront each, 7.5 a thread each).
-constexpr int SMALL_BY_WAVE = 16;
 
 struct SmallShared {
     double sum[TILE];           // segment sums; a whole tile: one row sum per thread
@@ -65,23 +53,57 @@ struct SmallShared {
     int long_list[MAX_LONG];    // of more segments: the ones too long for one thread
     int n_long;
     int parked[2];              // head, tail: the wait ran out
-    int left_over;              // this workgroup is the last one, and there is something to see to
+    unsigned park[2];           // as in SyncShared
+    unsigned long long own[2];
+    unsigned left;              // in the last workgroup to begin: entries it has to see to
     double total;
 };
 
-// This thread's four elements among the tile's segments.
+// What a call reads of the plan.  Everything in it is found by the tile's number, so that nothing but the data waits for the
+// record: a scale is two trips to memory away from the kernel's start, not four.
+struct SmallTables {
+    const SmallTile *tiles;     // [ntiles]
+    const StartWord *words;     // [ntiles][TILE_WORDS], whole tiles too; rank: the number of the block in progress before the word, plus 1
+};
+
+// This thread's four elements among the blocks.
 struct SmallPlace {
     unsigned starts;            // bit c: a segment starts at element c
-    int seg;                    // segment in progress before element 0 (-1: none)
+    int block;                  // the block in progress before element 0 (one before the tile's first: none)
 };
-__device__ __forceinline__ SmallPlace small_place(const Layout &L, const SmallTile &T)
+__device__ __forceinline__ SmallPlace small_place(const SmallTables &Z, int32_t tile)
 {
     SmallPlace q;
-    const StartWord w = L.words[T.words * TILE_WORDS + (int)(threadIdx.x >> 3)];
+    const StartWord w = Z.words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
     const unsigned sh = (threadIdx.x & 7u) * 4u;
     q.starts = (w.starts >> sh) & 15u;
-    q.seg = (int)w.rank + __popc(w.starts & ((1u << sh) - 1u)) - 1;
+    q.block = (int)w.rank + __popc(w.starts & ((1u << sh) - 1u)) - 1;
     return q;
+}
+
+// Start words by tile, and those of the mixed tiles (k_start_words) on the way (plan creation).  One workgroup of TILE_WORDS
+// threads per tile.
+__global__ __launch_bounds__(TILE_WORDS) void k_small_words(Layout L, StartWord *words, StartWord *mixed_words)
+{
+    __shared__ unsigned bits[TILE_WORDS];
+    const int32_t tile = blockIdx.x;
+    const int64_t tile_start = (int64_t)tile * TILE;
+    const int32_t fb = L.tile_fb[tile], lb = L.tile_lb[tile], mixed = L.tiles[tile].words;
+    bits[threadIdx.x] = threadIdx.x == 0 ? 1u : 0u;
+    __syncthreads();
+    for (int32_t b = fb + 1 + (int32_t)threadIdx.x; b <= lb; b += TILE_WORDS) {
+        const int j = (int)(L.offs[b] - tile_start);
+        atomicOr(&bits[j >> 5], 1u << (j & 31));
+    }
+    __syncthreads();
+    unsigned before = 0;
+    for (unsigned i = 0; i < threadIdx.x; ++i) before += (unsigned)__popc(bits[i]);
+    StartWord w;
+    w.starts = bits[threadIdx.x];
+    w.rank = before;
+    if (mixed >= 0) mixed_words[(int64_t)mixed * TILE_WORDS + threadIdx.x] = w;
+    w.rank += (unsigned)fb;
+    words[(int64_t)tile * TILE_WORDS + threadIdx.x] = w;
 }
 
 __device__ __forceinline__ float4 small_load4(const float *base, int n_valid)
@@ -172,22 +194,6 @@ __device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double
     return ok;
 }
 
-// One of the block's partial sums, of this call (w: a first look at it).  All of them have been stored by the time the last workgroup looks,
-// but a workgroup that was not parked stores its word and counts itself out with relaxed operations and no
-// release between them (that would write back the L2 of every streaming store), so the count says nothing
-// about the word: the word's own tag does.  The wait is for a store already made; should it never
-// show, the scale is a NaN rather than one formed from the last call's word.
-constexpr int LEFT_OVER_POLLS = 1 << 20;
-__device__ __forceinline__ double left_over_word(const unsigned long long *at, unsigned long long w, unsigned long long tag)
-{
-    for (int it = 0; (w >> 63) != tag; ++it) {
-        if (it == LEFT_OVER_POLLS) return __longlong_as_double(0x7ff8000000000000ll);
-        __builtin_amdgcn_s_sleep(1);
-        w = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    return __longlong_as_double((long long)(w & ~TAG_BIT));
-}
-
 // e <- p - Delta over the elements [lo, hi) of a residual row whose p was parked (one wavefront).
 __device__ __forceinline__ void small_residual(float *e, int64_t lo, int64_t hi, float s)
 {
@@ -212,76 +218,36 @@ __device__ __forceinline__ void small_residual(float *e, int64_t lo, int64_t hi,
     }
 }
 
-// A call that ran out of patience somewhere: scales not written and segments parked as p, seen to by the
-// workgroup that finishes last, a wavefront to an entry of the two lists.  (A call whose every
-// wait gives up, 1000 tiles in blocks of 200: 630 us; one wavefront for all took 26 ms, the kernel that ends the calls of
-// k_worker_tiles takes 150 us of such a call.)
-__device__ __forceinline__ void small_left_over(const Layout &L, const Scratch &X, const SmallArgs &Z)
+// What end_left_over does, a wavefront to an entry.  (A call whose every wait gives up, 1000 tiles in blocks of 200: 497 us.)
+__device__ __forceinline__ void small_left_over(unsigned left, const Layout &L, const Scratch &X, SmallShared &S)
 {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const unsigned n_fin = __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned n_def = __hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (unsigned i = uniform_u32(threadIdx.x >> 6); i < n_fin + n_def; i += SMALL_WAVES) {
-        const bool parked = i >= n_fin;
-        const unsigned long long it = parked ? X.defer_list[i - n_fin] : X.fin_list[i];
-        const int set = parked ? (int)(it >> 33) : (int)(it >> 32);
+    const ScratchRef &R = call_args().R;
+#pragma unroll 1
+    for (unsigned i = uniform_u32(threadIdx.x >> 6); i < left + 2u; i += SMALL_WAVES) {
+        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u));
+        if (!it) continue;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int set = (int)((it & (PARKED_FORMS - 1ull)) >> 33), w = set - X.set_base;
         const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
-        const int which = (int)(it & 1ull);
-        const int64_t b = parked ? (which ? L.tile_lb[tile] : L.tile_fb[tile]) : (int64_t)(it & 0xffffffffull);
+        const int64_t b = (it & 1ull) ? L.tile_lb[tile] : L.tile_fb[tile];
         const BlockSpan sp = block_span(L, b);
         const unsigned long long *part = set_part(X, L, set);
         const unsigned long long tag = set_tag(X, set);
-        unsigned long long word[4];
         double v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)     // past the block: its last word, not used
-            word[q] = __hip_atomic_load(part + part_index(sp.t0 + min(lane_id() + 64 * q, sp.n - 1), sp), __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int j = lane_id() + 64 * q;
-            v[q] = j < sp.n ? left_over_word(part + part_index(sp.t0 + j, sp), word[q], tag) : 0.0;
+            v[q] = j < sp.n ? sure_word(part + part_index(sp.t0 + j, sp), tag) : 0.0;
         }
         const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
-        const int w = set - X.set_base;
-        if (parked)
-            small_residual(Z.err + (int64_t)w * Z.err_stride, max(sp.bs, (int64_t)tile * TILE),
-                           min(sp.be, ((int64_t)tile + 1) * TILE), s);
-        else if (lane_id() == 0)
-            Z.scales[(int64_t)w * Z.scales_stride + b] = s;
+        if ((it & PARKED_FORMS) && lane_id() == 0) R.scales[(int64_t)w * R.scales_stride + b] = s;
+        small_residual(R.err + (int64_t)w * R.err_stride, max(sp.bs, (int64_t)tile * TILE), min(sp.be, ((int64_t)tile + 1) * TILE), s);
     }
-}
-
-// The workgroup is done (called by all of it): the last one to get here ends the call.
-__device__ __forceinline__ void small_finish(const Layout &L, const Scratch &X, const SmallArgs &Z, SmallShared &S)
-{
-    int last = 0;
-    if (threadIdx.x == 0) {
-        const unsigned n = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x, g = me % DONE_GROUPS;
-        const unsigned in_group = (n + DONE_GROUPS - 1 - g) / DONE_GROUPS, groups = min(n, (unsigned)DONE_GROUPS);
-        if (atomicAdd(Z.done + g * DONE_STRIDE, 1u) + 1u == in_group) {
-            Z.done[g * DONE_STRIDE] = 0u;
-            if (atomicAdd(Z.done + DONE_GROUPS * DONE_STRIDE, 1u) + 1u == groups) {
-                Z.done[DONE_GROUPS * DONE_STRIDE] = 0u;
-                last = 1;
-            }
-        }
-        int left = 0;
-        if (last) {
-            left = (__hip_atomic_load(X.defer_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
-                    __hip_atomic_load(X.fin_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0u;
-        }
-        S.left_over = left;
-    }
-    // clears the next call's counters, not this one's
-    if (wave_id() == 0 && uniform_u32((unsigned)last)) advance_call(Z.state, *Z.state, X, Z.nsets, Z.lazy);
-    __syncthreads();
-    if (S.left_over) small_left_over(L, X, Z);
 }
 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
-// of the blocks that end here, e' = p - Delta.  [bs, be): the block of segment threadIdx.x.
-__device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallArgs &Z, const SmallTile &T,
+// of the blocks that end here, e' = p - Delta.  [bs, be): the block of segment threadIdx.x, in a tile of more than SMALL_BY_WAVE.
+__device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallTile &T,
                                                const SmallPlace &at, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
                                                float *err_tile, const Scratch &X, int set, SmallShared &S)
 {
@@ -289,12 +255,16 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     const int lane = lane_id(), wave = wave_id();
     small_signs(p, n_valid, signs, (int64_t)tile * TILE, L.W);
     const int j0 = 4 * (int)threadIdx.x;
-    const bool whole = T.words < 0;
+    const bool whole = T.whole != 0;
+    const unsigned before = arrive<COUNT_WAVE>(X);
     const double a[4] = {j0 + 0 < n_valid ? fabsf(p.x) : 0.f, j0 + 1 < n_valid ? fabsf(p.y) : 0.f,
                          j0 + 2 < n_valid ? fabsf(p.z) : 0.f, j0 + 3 < n_valid ? fabsf(p.w) : 0.f};
     const unsigned long long tag = set_tag(X, set);
     unsigned long long *part = set_part(X, L, set);
-    if (threadIdx.x < 2) S.parked[threadIdx.x] = 0;
+    if (threadIdx.x < 2) {
+        S.parked[threadIdx.x] = 0;
+        S.own[threadIdx.x] = 0ull;
+    }
     if (whole) {
         S.sum[threadIdx.x] = ((a[0] + a[1]) + a[2]) + a[3];
         __syncthreads();
@@ -311,10 +281,6 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         *reinterpret_cast<float4 *>(&S.val[j0]) = make_float4(fabsf(p.x), fabsf(p.y), fabsf(p.z), fabsf(p.w));
         const int64_t start = (int64_t)tile * TILE;
         if (T.nseg <= SMALL_BY_WAVE) {
-            if ((int)threadIdx.x < T.nseg) {
-                S.bound[threadIdx.x] = (int)max(bs - start, (int64_t)0);
-                if ((int)threadIdx.x == T.nseg - 1) S.bound[T.nseg] = (int)min(be - start, (int64_t)n_valid);
-            }
             __syncthreads();
 #pragma unroll 1
             for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < T.nseg; sg += SMALL_WAVES) {
@@ -355,7 +321,9 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     if (tail) store_partial(tail_sum, 1, tile, L, X, set);
     for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
         if ((sg == 0 && head) || (sg == T.nseg - 1 && tail)) continue;
-        const int64_t db = sg < SMALL_THREADS ? be - bs : L.offs[T.fb + sg + 1] - L.offs[T.fb + sg];
+        // a closed segment is all of its block
+        const int64_t db = whole ? (int64_t)TILE : T.nseg <= SMALL_BY_WAVE ? (int64_t)(S.bound[sg + 1] - S.bound[sg])
+                                  : sg < SMALL_THREADS ? be - bs : L.offs[T.fb + sg + 1] - L.offs[T.fb + sg];
         const float sc = (float)((whole ? S.total : S.sum[sg]) / (double)db);
         S.scale[sg] = sc;
         scales_out[T.fb + sg] = sc;
@@ -369,20 +337,23 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
             const float sc = (float)(total / (double)(wave ? T.tail_db : T.head_db));
             S.scale[sg] = sc;
             S.parked[wave] = !ok;
-            if (wave == 0 && (T.flags & SMALL_WRITES_HEAD)) {
-                if (ok)
-                    scales_out[T.fb] = sc;
-                else
-                    X.fin_list[atomicAdd(X.fin_cnt, 1u)] = ((unsigned long long)set << 32) | (unsigned long long)T.fb;
+            const bool writes = wave == 0 && (T.flags & SMALL_WRITES_HEAD);
+            if (ok) {
+                if (writes) scales_out[T.fb] = sc;
+            } else {
+                atomicAdd(X.defer_cnt, 1u);
+                if (writes) atomicAdd(X.fin_cnt, 1u);
+                give_up(X, &S.park[wave], writes ? PARK_FORMS : 0u);
             }
-            if (!ok)
-                X.defer_list[atomicAdd(X.defer_cnt, 1u)] =
-                    ((unsigned long long)set << 33) | ((unsigned long long)tile << 1) | (unsigned)(sg > 0 ? 1 : 0);
         }
+    }
+    if (wave == COUNT_WAVE) {
+        const unsigned left = arrived<COUNT_WAVE>(before, X);
+        if (lane == 0) S.left = left;
     }
     __syncthreads();
     const int park_head = S.parked[0], park_tail = S.parked[1];
-    int seg = at.seg;
+    int seg = at.block - T.fb;
     float v[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -393,25 +364,34 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     }
     small_store4(err_tile, n_valid, make_float4(v[0], v[1], v[2], v[3]));
     if (park_head | park_tail) {
-        // whoever ends the call reads what was parked, and the list entry.  One wavefront releases for all, whose
-        // stores have reached the L2 by then: with a write-back for
-        // each, that call took 1170 us.
+        // One wavefront releases for all, whose stores have reached the L2 by then: with a write-back for
+        // each, a call whose every wait gives up took 1170 us.
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (wave == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (threadIdx.x == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (park_head) leave_entry(S.park[0], 0ull, set, tile, 0, &S.own[0]);
+            if (park_tail) leave_entry(S.park[1], 0ull, set, tile, T.nseg > 1 ? 1 : 0, &S.own[1]);
+        }
+        __syncthreads();
     }
-    small_finish(L, X, Z, S);
+    const unsigned left = uniform_u32(S.left);
+    if (left | (unsigned)(park_head | park_tail)) small_left_over(left, L, X, S);
+}
+
+// What every thread asks for by the tile's number alone, ahead of the record.
+__device__ __forceinline__ void small_bounds(const SmallTables &Z, int32_t tile, SmallShared &S)
+{
+    if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = Z.tiles[tile].bound[threadIdx.x];
 }
 
 template <bool MOM>
 __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
+void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
 {
     __shared__ SmallShared S;
-    const Scratch X = open_call(R);
     const int32_t tile = blockIdx.x;
     const int worker = blockIdx.y;
-    const SmallTile T = Z.tiles[tile];
     const int n_valid = tile_valid(L, tile);
     const int64_t start = (int64_t)tile * TILE;
     float *mt = MOM ? A.mom + (int64_t)worker * A.state_stride + start : nullptr;
@@ -419,100 +399,148 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallArgs Z)
     const float4 g = small_load4(A.grad + (int64_t)worker * A.grad_stride + start, n_valid);
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
-    SmallPlace at = {0u, 0};         // one segment
+    const SmallPlace at = small_place(Z, tile);
+    small_bounds(Z, tile, S);
+    const Scratch X = open_call(R);
+    const SmallTile T = Z.tiles[tile];
     int64_t bs = 0, be = 1;
-    if (T.nseg > 1) at = small_place(L, T);
-    if ((int)threadIdx.x < T.nseg) {
+    if (T.nseg > SMALL_BY_WAVE && (int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
         be = L.offs[T.fb + threadIdx.x + 1];
     }
     worker_values4<MOM>(g, m, e, A.mu, A.r);
     if (MOM) small_store4(mt, n_valid, m);
-    small_compress(e, L, Z, T, at, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+    small_compress(e, L, T, at, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
                    A.scales + (int64_t)worker * A.scales_stride, et, X, worker, S);
 }
 
-constexpr int SMALL_CHUNK = 4;      // workers whose payloads are in flight together
+constexpr int SMALL_CHUNK = 8, SMALL_GROUP = 4;     // workers whose sign words are in flight together, and are added up together
+constexpr int SMALL_STAGE = 2 * TILE;       // scales that fit where the sums will be
 
+// Half-word hw of workers i0 .. i0 + 7 (past M: the last worker's again; of a group without any none).
+__device__ __forceinline__ void small_words(const ServerArgs &A, int i0, unsigned hw, uint32_t (&word)[SMALL_CHUNK])
+{
+#pragma unroll
+    for (int g = 0; g < SMALL_CHUNK; g += SMALL_GROUP)
+        if (g == 0 || i0 + g < A.M)
+#pragma unroll
+            for (int u = g; u < g + SMALL_GROUP; ++u)
+                word[u] = reinterpret_cast<const uint32_t *>(A.signs_in + (int64_t)min(i0 + u, A.M - 1) * A.in_signs_stride)[hw];
+}
+
+// The scales of the tile's segments from all workers come in one trip to memory, a wavefront to a worker, and are looked up
+// in LDS; one segment's are scalars.  (Gathered by element, four workers at a time, each group waited for the one before it, and
+// all of them for the start words, these for the record.  Server call, 16 workers, 322 tiles in blocks of eight
+// 14.1 -> 12.6 us; 4 workers, a bottleneck network of 341 tiles 10.2 -> 9.4; 1 worker, 213 tiles 7.4 -> 7.3.)
 __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallArgs Z, int set)
+void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set)
 {
     __shared__ SmallShared S;
-    const Scratch X = open_call(R);
     const int32_t tile = blockIdx.x;
-    const SmallTile T = Z.tiles[tile];
     const int n_valid = tile_valid(L, tile);
     const int64_t start = (int64_t)tile * TILE;
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
-    SmallPlace at = {0u, 0};         // one segment
+    const SmallPlace at = small_place(Z, tile);
+    small_bounds(Z, tile, S);
+    const Scratch X = open_call(R);
+    const SmallTile T = Z.tiles[tile];
     int64_t bs = 0, be = 1;
-    if (T.nseg > 1) at = small_place(L, T);
-    if ((int)threadIdx.x < T.nseg) {
+    if (T.nseg > SMALL_BY_WAVE && (int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
         be = L.offs[T.fb + threadIdx.x + 1];
     }
-    int seg[4];
-    {
-        int sg = at.seg;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) seg[c] = sg += (int)((at.starts >> c) & 1u);
-    }
-    // this thread's four sign bits are in half-word hw of every payload
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(A.signs_in);
-    const int64_t hw = (start >> 5) + (threadIdx.x >> 3);
-    const bool in = hw < 2 * L.W;
+    // this thread's four sign bits are in one half-word of every payload (past the end: elements that are not stored)
+    const unsigned last = (unsigned)(2 * L.W - 1), hw = min((unsigned)(start >> 5) + (threadIdx.x >> 3), last);
     const unsigned sh = (threadIdx.x & 7u) * 4u;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
-        uint32_t word[SMALL_CHUNK];
-        float sc[SMALL_CHUNK][4];
+    uint32_t word[SMALL_CHUNK];
+    small_words(A, 0, hw, word);
+    if (T.nseg == 1) {
+#pragma unroll 1
+        for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
+            float sc[SMALL_CHUNK];
+            load_scales(A, T.fb, i0, sc);           // past M 0, which changes no sum (one that began with +0 is never -0)
+            if (i0 > 0) small_words(A, i0, hw, word);
 #pragma unroll
-        for (int u = 0; u < SMALL_CHUNK; ++u) {
-            const int i = min(i0 + u, A.M - 1);              // past M: loaded, not used
-            const float *sc_i = A.scales_in + (int64_t)i * A.in_scales_stride + T.fb;
-            word[u] = in ? s32[2 * (int64_t)i * A.in_signs_stride + hw] : 0u;
+            for (int g = 0; g < SMALL_CHUNK; g += SMALL_GROUP)
+                if (g == 0 || i0 + g < A.M)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) sc[u][c] = sc_i[seg[c]];
+                    for (int u = g; u < g + SMALL_GROUP; ++u)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[u], (word[u] >> (sh + c)) & 1u);
         }
+    } else {
+        int seg[4];
+        {
+            int sg = at.block - T.fb;
 #pragma unroll
-        for (int u = 0; u < SMALL_CHUNK; ++u)
-            if (i0 + u < A.M) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[u][c], (word[u] >> (sh + c)) & 1u);
+            for (int c = 0; c < 4; ++c) seg[c] = sg += (int)((at.starts >> c) & 1u);
+        }
+        float *stage = reinterpret_cast<float *>(S.sum);
+        const int rows = (A.M + SMALL_GROUP - 1) / SMALL_GROUP * SMALL_GROUP;
+        if (T.nseg * rows <= SMALL_STAGE) {
+#pragma unroll 1
+            for (int u = wave_id(); u < rows; u += SMALL_WAVES) {
+                const float *sc = A.scales_in + (int64_t)min(u, A.M - 1) * A.in_scales_stride + T.fb;
+#pragma unroll 1
+                for (int j = lane_id(); j < T.nseg; j += 64) stage[u * T.nseg + j] = u < A.M ? sc[j] : 0.0f;
             }
+            __syncthreads();
+#pragma unroll 1
+            for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
+                if (i0 > 0) small_words(A, i0, hw, word);
+#pragma unroll
+                for (int g = 0; g < SMALL_CHUNK; g += SMALL_GROUP)
+                    if (g == 0 || i0 + g < A.M)
+#pragma unroll
+                        for (int u = g; u < g + SMALL_GROUP; ++u)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                acc[c] = acc[c] + signed_scale(stage[seg[c]], (word[u] >> (sh + c)) & 1u);
+                                seg[c] += T.nseg;
+                            }
+            }
+        } else {
+            // more segments than the stage holds: a gather for each element
+#pragma unroll 1
+            for (int i = 0; i < A.M; ++i) {
+                const float *sc = A.scales_in + (int64_t)i * A.in_scales_stride + T.fb;
+                const uint32_t w = reinterpret_cast<const uint32_t *>(A.signs_in + (int64_t)i * A.in_signs_stride)[hw];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[seg[c]], (w >> (sh + c)) & 1u);
+            }
+        }
+        __syncthreads();            // the stage is read no more
     }
     float4 p;
     p.x = mean_of(acc[0], A.Mf, A.Minv) + A.r * te.x;
     p.y = mean_of(acc[1], A.Mf, A.Minv) + A.r * te.y;
     p.z = mean_of(acc[2], A.Mf, A.Minv) + A.r * te.z;
     p.w = mean_of(acc[3], A.Mf, A.Minv) + A.r * te.w;
-    small_compress(p, L, Z, T, at, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
+    small_compress(p, L, T, at, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
 }
 
 // Parameter update (see apply_tile), one workgroup of 1024 threads per tile.
 template <bool WD>
-__global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallArgs Z, float *x, float *mt, const uint64_t *signs,
+__global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallTables Z, float *x, float *mt, const uint64_t *signs,
                                                                const float *scales, float eta, float mu, float lambda)
 {
     const int32_t tile = blockIdx.x;
-    const SmallTile T = Z.tiles[tile];
     const int n_valid = tile_valid(L, tile);
     const int64_t start = (int64_t)tile * TILE;
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(signs);
-    const int64_t hw = (start >> 5) + (threadIdx.x >> 3);
+    const int64_t last = 2 * L.W - 1, hw = (start >> 5) + (threadIdx.x >> 3);
+    const SmallPlace at = small_place(Z, tile);
+    const uint32_t word = reinterpret_cast<const uint32_t *>(signs)[hw < last ? hw : last];
     const float4 x4 = small_load4(x + start, n_valid);
-    const uint32_t word = hw < 2 * L.W ? s32[hw] : 0u;
     float4 m4 = x4;
     if (WD) m4 = small_load4(mt + start, n_valid);
-    SmallPlace at = {0u, 0};         // one segment
-    if (T.nseg > 1) at = small_place(L, T);
     float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
-    int seg = at.seg;
+    int block = at.block;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        seg += (int)((at.starts >> c) & 1u);
-        const float delta = signed_scale(scales[T.fb + seg], (word >> ((threadIdx.x & 7u) * 4u + c)) & 1u);
+        block += (int)((at.starts >> c) & 1u);
+        const float delta = signed_scale(scales[block], (word >> ((threadIdx.x & 7u) * 4u + c)) & 1u);
         update_element<WD>(xv[c], mv[c], delta, eta, mu, lambda);
     }
     small_store4(x + start, n_valid, make_float4(xv[0], xv[1], xv[2], xv[3]));

@@ -683,11 +683,11 @@ __device__ __forceinline__ unsigned *arrive_word(const Scratch &X, unsigned g) {
 // the loads of scales and block offsets would keep the compiler from making them scalar loads, and where many values
 // are still to come it costs the server's pairs 7 spilled registers.  (The lane number, 0 here, keeps the compiler from
 // making one addition of the wavefront's, whose answer it would wait for at once.)
-__device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
+template <int WAVE = 0>
+__device__ __forceinline__ unsigned arrive(const Scratch &X)
 {
     unsigned before = 0u;
-    if (X.ends && threadIdx.x == 0) {
-        S.own[0] = S.own[1] = 0ull;
+    if (X.ends && threadIdx.x == 64 * WAVE) {
         unsigned *at = arrive_word(X, blockIdx.x % ARRIVE_GROUPS) + __builtin_amdgcn_mbcnt_lo(~0u, 0u);
         before = __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -695,11 +695,18 @@ __device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
 }
 __device__ __forceinline__ unsigned arrive_groups(const ScratchRef &R) { return min((unsigned)R.columns, (unsigned)ARRIVE_GROUPS); }
 
-// The last workgroup to have counted itself in steps the call state, its first wavefront alone.  Returns to that one the number
+__device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
+{
+    if (threadIdx.x == 0) S.own[0] = S.own[1] = 0ull;
+    return arrive(X);
+}
+
+// The last workgroup to have counted itself in steps the call state, one wavefront alone.  Returns to that one the number
 // of entries that are left to it, 0 to all others.  Called when the answer is likely to be there: after the wait for a scale.
+template <int WAVE = 0>
 __device__ __forceinline__ unsigned arrived(unsigned before, const Scratch &X)
 {
-    if (!X.ends || uniform_u32(threadIdx.x >> 6) != 0u) return 0u;
+    if (!X.ends || uniform_u32(threadIdx.x >> 6) != WAVE) return 0u;
     const ScratchRef &R = call_args().R;
     const unsigned g = blockIdx.x % ARRIVE_GROUPS;
     if (uniform_u32(before) + 1u != (unsigned)R.nsets * (((unsigned)R.columns + ARRIVE_GROUPS - 1u - g) / ARRIVE_GROUPS)) return 0u;
@@ -717,10 +724,20 @@ __device__ __forceinline__ unsigned arrived(unsigned before, const Scratch &X)
 
 // Thread 0: a wait has run out.  If all workgroups have begun, this one sees to the segment itself at its end, where the sums
 // are sure to come; else the segment gets the number of an entry.
-__device__ __forceinline__ void give_up(const Scratch &X, SyncShared &S, int slot, unsigned forms)
+__device__ __forceinline__ void give_up(const Scratch &X, unsigned *park, unsigned forms)
 {
     const unsigned top = atomicAdd(arrive_word(X, ARRIVE_GROUPS), PARKED_ONE);
-    S.park[slot] = ((top & ARRIVED_MASK) == arrive_groups(call_args().R) ? PARK_OWN : top / PARKED_ONE) | forms;
+    *park = ((top & ARRIVED_MASK) == arrive_groups(call_args().R) ? PARK_OWN : top / PARKED_ONE) | forms;
+}
+// And the segment has been stored as p: an entry, in ScratchRef::parked or the workgroup's own.  One thread, after a release.
+__device__ __forceinline__ void leave_entry(unsigned park, unsigned long long both, int set, int32_t tile, int which, unsigned long long *own)
+{
+    const unsigned long long entry = PARKED_VALID | both | ((park & PARK_FORMS) ? PARKED_FORMS : 0ull) | ((unsigned long long)set << 33) |
+                                     ((unsigned long long)tile << 1) | (unsigned)which;
+    if ((park & ~PARK_FORMS) == PARK_OWN)
+        *own = entry;
+    else
+        __hip_atomic_store(call_args().R.parked + (park & ~PARK_FORMS), entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------ cross-tile block reductions ---
@@ -925,7 +942,7 @@ __device__ __forceinline__ bool finish_block(int64_t b, const BlockSpan &sp, con
             const unsigned k = atomicAdd(X.fin_cnt, 1u);
             if (X.ends) {
                 atomicAdd(X.defer_cnt, 1u);
-                give_up(X, S, slot, PARK_FORMS);
+                give_up(X, &S.park[slot], PARK_FORMS);
             } else {
                 X.fin_list[k] = ((unsigned long long)set << 32) | (unsigned long long)b;
             }
@@ -1002,7 +1019,7 @@ __device__ __forceinline__ bool wait_scale(const unsigned long long *word, const
     if (wait_ready_at(word, 0ull, X, S, scale)) return true;
     if (X.ends && threadIdx.x == 0) {
         atomicAdd(X.defer_cnt, 1u);
-        give_up(X, S, slot, 0u);
+        give_up(X, &S.park[slot], 0u);
     }
     return false;
 }
@@ -1025,15 +1042,8 @@ __device__ __forceinline__ void park_segment(int32_t tile, int which, bool both,
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned at = S.park[which];
-        const unsigned long long entry = PARKED_VALID | (both ? PARKED_BOTH : 0ull) | ((at & PARK_FORMS) ? PARKED_FORMS : 0ull) |
-                                         ((unsigned long long)set << 33) | ((unsigned long long)tile << 1) | (unsigned)which;
-        if ((at & ~PARK_FORMS) == PARK_OWN) {
-            S.own[which] = entry;
-        } else {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __hip_atomic_store(call_args().R.parked + (at & ~PARK_FORMS), entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        leave_entry(S.park[which], both ? PARKED_BOTH : 0ull, set, tile, which, &S.own[which]);
     }
     __syncthreads();
 }
