@@ -9,7 +9,9 @@ Names follow the C ABI: ef_plan_create / ef_worker_step / ef_server_step /
 ef_apply (Algorithm 4 of arxiv 1905.10936).
 """
 import ctypes
+import importlib.util
 import os
+import struct
 
 import numpy as np
 import torch
@@ -50,6 +52,37 @@ class EfError(RuntimeError):
 
 
 _lib = None
+
+
+class _ThroughCtypes:
+    """Stands for csrc/ef_binding.cpp where it is not built: no call is taken there."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_native = _ThroughCtypes()
+_NATIVE_CALLS = ("ef_worker_step", "ef_worker_step_sgd", "ef_server_step", "ef_apply", "ef_apply_wd", "ef_worker_step_fused",
+                 "ef_server_step_fused", "ef_apply_fused", "ef_worker_step_state", "ef_server_step_state",
+                 "ef_compressor_quality")
+
+
+def _load_native(L):
+    """The step calls' marshalling in C++ (csrc/ef_binding.cpp): it takes a call whose arguments are all as they should be
+    and answers None otherwise; the functions below then go through ctypes, which says what is wrong."""
+    global _native
+    if not os.path.exists(_build.BINDING):
+        try:
+            _build.build(lib=_build.BINDING)
+        except Exception as e:          # no compiler or no torch headers: calls take 1 to 3 us longer
+            import warnings
+            warnings.warn("ef_binding.cpp could not be built (%s): calls go through ctypes" % e, RuntimeWarning)
+            return
+    spec = importlib.util.spec_from_file_location("_ef_binding", _build.BINDING)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+    _native = module
 
 
 def lib():
@@ -133,6 +166,7 @@ def lib():
         getattr(L, name).argtypes = [vp, vp, vp, vp, i64, vp, vp]
     L.ef_strerror.restype = ctypes.c_char_p
     L.ef_strerror.argtypes = [c_int]
+    _load_native(L)
     _lib = L
     return L
 
@@ -200,6 +234,8 @@ class Plan:
         self.B = int(lib().ef_plan_blocks(self._h))
         self.W = int(lib().ef_sign_words(self._h))
         self.max_workers = int(max_workers)
+        # what the native calls go by; empty once the plan is closed
+        self._key = struct.pack("Pqqqq", self._h.value, self.d, self.W, self.B, int(lib().ef_payload_bytes(self._h)))
 
     def tune(self, fuse_limit=-1, spin_limit=-1):
         _check(lib().ef_plan_tune(self._h, int(fuse_limit), int(spin_limit)))
@@ -247,6 +283,7 @@ class Plan:
         if getattr(self, "_h", None) is not None and self._h.value:
             lib().ef_plan_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._key = b""
 
     def __del__(self):
         try:
@@ -281,6 +318,9 @@ def ef_plan_destroy(plan):
 def ef_worker_step(plan, grad, mom, err, mu, eta_prev, eta, packed_signs, scales, stream=None):
     """grad/mom/err: float32 [n][>=d] (or [d]); packed_signs int64|uint64 [n][W];
     scales float32 [n][B].  mom, err, packed_signs, scales are written."""
+    rc = _native.worker_step(plan._key, grad, mom, err, mu, eta_prev, eta, packed_signs, scales, stream)
+    if rc is not None:
+        return _check(rc)
     n = 1 if grad.dim() == 1 else grad.shape[0]
     gs, ss = _stride(grad, plan.d, "grad"), _stride(mom, plan.d, "mom")
     if _stride(err, plan.d, "err") != ss or mom.shape != err.shape:
@@ -315,6 +355,9 @@ def ef_worker_step_quality(plan, grad, mom, err, mu, eta_prev, eta, packed_signs
 
 def ef_server_step(plan, M, packed_signs, scales, server_err, eta_prev, eta, out_signs, out_scales,
                    stream=None):
+    rc = _native.server_step(plan._key, M, packed_signs, scales, server_err, eta_prev, eta, out_signs, out_scales, stream)
+    if rc is not None:
+        return _check(rc)
     if packed_signs.numel() != M * plan.W or scales.numel() != M * plan.B:
         raise TypeError("packed_signs must hold M*W words and scales M*B floats")
     if server_err.numel() != plan.d or out_signs.numel() != plan.W or out_scales.numel() != plan.B:
@@ -328,6 +371,9 @@ def ef_server_step(plan, M, packed_signs, scales, server_err, eta_prev, eta, out
 
 
 def ef_apply(plan, params, packed_signs, scales, eta, stream=None):
+    rc = _native.apply(plan._key, params, packed_signs, scales, eta, stream)
+    if rc is not None:
+        return _check(rc)
     if params.numel() != plan.d or packed_signs.numel() != plan.W or scales.numel() != plan.B:
         raise TypeError("params/packed_signs/scales must hold d/W/B entries")
     rc = lib().ef_apply(plan._h, _ptr(params, _f32, "params"),
@@ -337,6 +383,9 @@ def ef_apply(plan, params, packed_signs, scales, eta, stream=None):
 
 
 def ef_apply_wd(plan, params, decay_mom, packed_signs, scales, eta, mu, lam, stream=None):
+    rc = _native.apply_wd(plan._key, params, decay_mom, packed_signs, scales, eta, mu, lam, stream)
+    if rc is not None:
+        return _check(rc)
     if (params.numel() != plan.d or decay_mom.numel() != plan.d or packed_signs.numel() != plan.W
             or scales.numel() != plan.B):
         raise TypeError("params/decay_mom/packed_signs/scales must hold d/d/W/B entries")
@@ -364,6 +413,9 @@ def _messages(t, n, plan, name):
 
 
 def ef_worker_step_fused(plan, grad, mom, err, mu, eta_prev, eta, payloads, stream=None):
+    rc = _native.worker_step_fused(plan._key, grad, mom, err, mu, eta_prev, eta, payloads, stream)
+    if rc is not None:
+        return _check(rc)
     n = 1 if grad.dim() == 1 else grad.shape[0]
     gs, ss = _stride(grad, plan.d, "grad"), _stride(mom, plan.d, "mom")
     if _stride(err, plan.d, "err") != ss or mom.shape != err.shape:
@@ -376,6 +428,9 @@ def ef_worker_step_fused(plan, grad, mom, err, mu, eta_prev, eta, payloads, stre
 
 
 def ef_server_step_fused(plan, M, payloads, server_err, eta_prev, eta, out_payload, stream=None):
+    rc = _native.server_step_fused(plan._key, M, payloads, server_err, eta_prev, eta, out_payload, stream)
+    if rc is not None:
+        return _check(rc)
     if payloads.numel() < M * ef_payload_bytes(plan) or server_err.numel() != plan.d:
         raise TypeError("payloads must hold M messages and server_err d floats")
     rc = lib().ef_server_step_fused(plan._h, int(M), _ptr(payloads, _u8, "payloads"),
@@ -385,6 +440,9 @@ def ef_server_step_fused(plan, M, payloads, server_err, eta_prev, eta, out_paylo
 
 
 def ef_apply_fused(plan, params, payload, eta, stream=None):
+    rc = _native.apply_fused(plan._key, params, payload, eta, stream)
+    if rc is not None:
+        return _check(rc)
     if params.numel() != plan.d:
         raise TypeError("params must hold d floats")
     rc = lib().ef_apply_fused(plan._h, _ptr(params, _f32, "params"), _messages(payload, 1, plan, "payload"),
@@ -394,6 +452,9 @@ def ef_apply_fused(plan, params, payload, eta, stream=None):
 
 def ef_worker_step_sgd(plan, grad, err, eta_prev, eta, packed_signs, scales, stream=None):
     """Algorithm 3 worker (no momentum buffer): shapes as for ef_worker_step."""
+    rc = _native.worker_step_sgd(plan._key, grad, err, eta_prev, eta, packed_signs, scales, stream)
+    if rc is not None:
+        return _check(rc)
     n = 1 if grad.dim() == 1 else grad.shape[0]
     gs, ss = _stride(grad, plan.d, "grad"), _stride(err, plan.d, "err")
     if packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B:
@@ -408,6 +469,9 @@ def ef_worker_step_sgd(plan, grad, err, eta_prev, eta, packed_signs, scales, str
 def ef_compressor_quality(plan, v, out, stream=None, static_scratch=False):
     """v: float32 [n][>=d] (or [d]); out: float64 [n][2] receives (phi, delta) per vector.
     static_scratch: go through ef_compressor_quality_static (allocates nothing, bounded size)."""
+    rc = None if static_scratch else _native.compressor_quality(plan._key, v, out, stream)
+    if rc is not None:
+        return _check(rc)
     n = 1 if v.dim() == 1 else v.shape[0]
     if out.numel() != 2 * n:
         raise TypeError("out must hold 2 doubles per vector")
@@ -429,11 +493,13 @@ class State:
         self.plan, self.n = plan, int(n_workers)
         self._h = ctypes.c_void_p()
         _check(lib().ef_state_create(plan._h, self.n, ctypes.byref(self._h), _stream_ptr(stream)))
+        self._key = struct.pack("Pq", self._h.value, self.n)
 
     def close(self):
         if getattr(self, "_h", None) is not None and self._h.value:
             lib().ef_state_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._key = b""
 
     def __del__(self):
         try:
@@ -451,6 +517,9 @@ def ef_state_destroy(state):
 
 
 def ef_worker_step_state(plan, state, grad, mu, eta_prev, eta, packed_signs, scales, stream=None):
+    rc = _native.worker_step_state(plan._key, state._key, grad, mu, eta_prev, eta, packed_signs, scales, stream)
+    if rc is not None:
+        return _check(rc)
     n = 1 if grad.dim() == 1 else grad.shape[0]
     if n != state.n or packed_signs.numel() != n * plan.W or scales.numel() != n * plan.B:
         raise TypeError("grad must hold the state's workers; packed_signs n*W words, scales n*B floats")
@@ -462,6 +531,9 @@ def ef_worker_step_state(plan, state, grad, mu, eta_prev, eta, packed_signs, sca
 
 
 def ef_server_step_state(plan, state, M, packed_signs, scales, eta_prev, eta, out_signs, out_scales, stream=None):
+    rc = _native.server_step_state(plan._key, state._key, M, packed_signs, scales, eta_prev, eta, out_signs, out_scales, stream)
+    if rc is not None:
+        return _check(rc)
     if packed_signs.numel() != M * plan.W or scales.numel() != M * plan.B:
         raise TypeError("packed_signs must hold M*W words and scales M*B floats")
     if out_signs.numel() != plan.W or out_scales.numel() != plan.B:

@@ -1,14 +1,16 @@
 """Build libef.so (HIP kernels + C ABI) and libef_bench.so (the bandwidth probes bench.py runs
-beside it) for gfx950 with hipcc, in-tree."""
+beside it) for gfx950 with hipcc, and the Python binding's native calls (ef_binding.cpp) with the C++ compiler, in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libef.so")
 BENCH_LIB = os.path.join(HERE, "libef_bench.so")
+BINDING = os.path.join(HERE, "_ef_binding.so")
 # library -> (source, everything it is built from)
 TARGETS = {
     LIB: (os.path.join(CSRC, "ef_api.hip"),
@@ -18,6 +20,7 @@ TARGETS = {
     BENCH_LIB: (os.path.join(CSRC, "ef_bench.hip"),
                 [os.path.join(CSRC, h) for h in ("ef_tile.h", "ef_layout.h", "ef_probe.h")] +
                 [os.path.join(ROOT, "include", h) for h in ("ef.h", "ef_bench.h")]),
+    BINDING: (os.path.join(CSRC, "ef_binding.cpp"), [os.path.join(ROOT, "include", "ef.h")]),
 }
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -35,6 +38,19 @@ FLAGS = [
 ]
 
 
+def binding_command():
+    """The binding sees tensors, so it is built against the torch that is installed; it has no device code."""
+    import torch
+    at = torch.__path__[0]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+             "-isystem", os.path.join(rocm, "include"), "-isystem", os.path.join(at, "include"),
+             "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+             "-isystem", sysconfig.get_paths()["include"]],
+            ["-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"])
+
+
 def stale(lib=LIB):
     if not os.path.exists(lib):
         return True
@@ -50,7 +66,11 @@ def build(force=True, verbose=False, lib=None):
         if not force and not stale(target):
             continue
         tmp = target + ".tmp%d" % os.getpid()
-        cmd = [HIPCC] + FLAGS + ["-o", tmp, TARGETS[target][0]]
+        if target == BINDING:
+            first, last = binding_command()
+            cmd = first + ["-o", tmp, TARGETS[target][0]] + last
+        else:
+            cmd = [HIPCC] + FLAGS + ["-o", tmp, TARGETS[target][0]]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
