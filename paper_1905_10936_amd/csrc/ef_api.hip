@@ -783,6 +783,11 @@ bool small_update(const ef_plan *plan)
     return plan->has_small && plan->kernels_auto && 2 * (int64_t)plan->L.ntiles <= plan->small_wgs;
 }
 
+ef::ApplyTables apply_tables(const ef_plan *plan, bool small)
+{
+    return {plan->L.d, plan->L.W, plan->L.tiles, small ? plan->small.words : plan->L.words};
+}
+
 // Scratch argument of one call over the sets [set_base, set_base + nsets).  Everything that
 // differs between two calls of the same kind is read by the kernels from device memory.
 struct CallScratch {
@@ -1400,10 +1405,10 @@ int ef_apply(const ef_plan *plan, float *params, const uint64_t *packed_signs, c
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
     if (small_update(plan))
-        hipLaunchKernelGGL(ef::k_apply_small<false>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
+        hipLaunchKernelGGL(ef::k_apply_small<false>, grid, dim3(ef::SMALL_THREADS), 0, s, apply_tables(plan, true), params,
                            (float *)nullptr, packed_signs, scales, eta, 0.0f, 0.0f);
     else
-        hipLaunchKernelGGL(ef::k_apply, grid, dim3(ef::THREADS), 0, s, plan->L, params, packed_signs, scales, eta);
+        hipLaunchKernelGGL(ef::k_apply, grid, dim3(ef::THREADS), 0, s, apply_tables(plan, false), params, packed_signs, scales, eta);
     EF_HIP(hipGetLastError());
     return EF_OK;
 }
@@ -1421,10 +1426,10 @@ int ef_apply_wd(const ef_plan *plan, float *params, float *decay_mom, const uint
     hipStream_t s = static_cast<hipStream_t>(stream);
     dim3 grid((unsigned)plan->L.ntiles, 1u);
     if (small_update(plan))
-        hipLaunchKernelGGL(ef::k_apply_small<true>, grid, dim3(ef::SMALL_THREADS), 0, s, plan->L, plan->small, params,
+        hipLaunchKernelGGL(ef::k_apply_small<true>, grid, dim3(ef::SMALL_THREADS), 0, s, apply_tables(plan, true), params,
                            decay_mom, packed_signs, scales, eta, mu, lambda);
     else
-        hipLaunchKernelGGL(ef::k_apply_wd, grid, dim3(ef::THREADS), 0, s, plan->L, params, decay_mom, packed_signs,
+        hipLaunchKernelGGL(ef::k_apply_wd, grid, dim3(ef::THREADS), 0, s, apply_tables(plan, false), params, decay_mom, packed_signs,
                            scales, eta, mu, lambda);
     EF_HIP(hipGetLastError());
     return EF_OK;

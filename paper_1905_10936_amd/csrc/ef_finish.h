@@ -238,15 +238,23 @@ __device__ __forceinline__ void update_element(float &x, float &m, float delta, 
     }
 }
 
+// What an update reads of the plan: its launch copies every byte of its arguments to the device, 1 us for 300 of them, and
+// a small update is over before the next one is enqueued (31 tiles: 5.0 us with all of Layout; see k_apply_small).
+struct ApplyTables {
+    int64_t d, W;
+    const TileRec *tiles;       // k_apply
+    const StartWord *words;     // Layout::words, or for k_apply_small SmallTables::words
+};
+
 // Bound by HBM: 16.125 bytes an element with weight decay, 8.125 without.  Loads that wait for nothing go out first,
 // the sign words ahead of the tile: 354 M elements 474 -> 446 us, with weight decay 987 -> 958, against
 // words loaded where they are used.  The ragged end of one block has nothing more to look up than a whole tile.
 template <bool WD>
-__device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt, const uint64_t *signs,
+__device__ __forceinline__ void apply_tile(const ApplyTables &L, float *x, float *mt, const uint64_t *signs,
                                            const float *scales, float eta, float mu, float lambda)
 {
     const int32_t tile = blockIdx.x;
-    const int n_valid = tile_valid(L, tile);
+    const int n_valid = tile_valid(L.d, tile);
     const int64_t tile_start = (int64_t)tile * TILE;
     float *xt = x + tile_start;
     float *mtt = WD ? mt + tile_start : nullptr;
@@ -266,7 +274,7 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
     if (WD) load_tile(mtt, mv4, n_valid);
     const bool one = abs(T.nseg) == 1;      // a whole tile or the ragged end of one block: nothing else to look up
     TilePlace at;
-    if (!one) at = tile_place(L, T);
+    if (!one) at = tile_place(L.words, T);
     const float first = scales[T.fb];
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
@@ -289,13 +297,13 @@ __device__ __forceinline__ void apply_tile(const Layout &L, float *x, float *mt,
     if (WD) store_tile(mtt, mv4, n_valid);
 }
 
-__global__ __launch_bounds__(THREADS) void k_apply(Layout L, float *x, const uint64_t *signs,
+__global__ __launch_bounds__(THREADS) void k_apply(ApplyTables L, float *x, const uint64_t *signs,
                                                    const float *scales, float eta)
 {
     apply_tile<false>(L, x, nullptr, signs, scales, eta, 0.0f, 0.0f);
 }
 
-__global__ __launch_bounds__(THREADS) void k_apply_wd(Layout L, float *x, float *mt, const uint64_t *signs,
+__global__ __launch_bounds__(THREADS) void k_apply_wd(ApplyTables L, float *x, float *mt, const uint64_t *signs,
                                                       const float *scales, float eta, float mu, float lambda)
 {
     apply_tile<true>(L, x, mt, signs, scales, eta, mu, lambda);

@@ -71,10 +71,10 @@ struct SmallPlace {
     unsigned starts;            // bit c: a segment starts at element c
     int block;                  // the block in progress before element 0 (one before the tile's first: none)
 };
-__device__ __forceinline__ SmallPlace small_place(const SmallTables &Z, int32_t tile)
+__device__ __forceinline__ SmallPlace small_place(const StartWord *words, int32_t tile)
 {
     SmallPlace q;
-    const StartWord w = Z.words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
+    const StartWord w = words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
     const unsigned sh = (threadIdx.x & 7u) * 4u;
     q.starts = (w.starts >> sh) & 15u;
     q.block = (int)w.rank + __popc(w.starts & ((1u << sh) - 1u)) - 1;
@@ -399,7 +399,7 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
     const float4 g = small_load4(A.grad + (int64_t)worker * A.grad_stride + start, n_valid);
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
-    const SmallPlace at = small_place(Z, tile);
+    const SmallPlace at = small_place(Z.words, tile);
     small_bounds(Z, tile, S);
     const Scratch X = open_call(R);
     const SmallTile T = Z.tiles[tile];
@@ -441,7 +441,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
     const int64_t start = (int64_t)tile * TILE;
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
-    const SmallPlace at = small_place(Z, tile);
+    const SmallPlace at = small_place(Z.words, tile);
     small_bounds(Z, tile, S);
     const Scratch X = open_call(R);
     const SmallTile T = Z.tiles[tile];
@@ -523,14 +523,14 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
 
 // Parameter update (see apply_tile), one workgroup of 1024 threads per tile.
 template <bool WD>
-__global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(Layout L, SmallTables Z, float *x, float *mt, const uint64_t *signs,
+__global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(ApplyTables Z, float *x, float *mt, const uint64_t *signs,
                                                                const float *scales, float eta, float mu, float lambda)
 {
     const int32_t tile = blockIdx.x;
-    const int n_valid = tile_valid(L, tile);
+    const int n_valid = tile_valid(Z.d, tile);
     const int64_t start = (int64_t)tile * TILE;
-    const int64_t last = 2 * L.W - 1, hw = (start >> 5) + (threadIdx.x >> 3);
-    const SmallPlace at = small_place(Z, tile);
+    const int64_t last = 2 * Z.W - 1, hw = (start >> 5) + (threadIdx.x >> 3);
+    const SmallPlace at = small_place(Z.words, tile);
     const uint32_t word = reinterpret_cast<const uint32_t *>(signs)[hw < last ? hw : last];
     const float4 x4 = small_load4(x + start, n_valid);
     float4 m4 = x4;

@@ -395,11 +395,12 @@ __device__ __forceinline__ void store_tile(float *base, const float4 (&v)[SUBROW
     }
 }
 
-__device__ __forceinline__ int tile_valid(const Layout &L, int32_t tile)
+__device__ __forceinline__ int tile_valid(int64_t d, int32_t tile)
 {
-    const int64_t left = L.d - (int64_t)tile * TILE;
+    const int64_t left = d - (int64_t)tile * TILE;
     return left >= TILE ? TILE : (int)left;
 }
+__device__ __forceinline__ int tile_valid(const Layout &L, int32_t tile) { return tile_valid(L.d, tile); }
 
 // Data-parallel-primitive moves inside a row of 16 lanes: the value of the lane
 // whose index differs in bit 0 / bit 1, and of the mirror lane within 8 / 16
@@ -1057,13 +1058,13 @@ struct TilePlace {
     __device__ __forceinline__ unsigned starts(int k) const { return row[k] & 15u; }
     __device__ __forceinline__ int seg(int k) const { return (int)(row[k] >> 4) - 1; }
 };
-__device__ __forceinline__ TilePlace tile_place(const Layout &L, const TileRec &T)
+__device__ __forceinline__ TilePlace tile_place(const StartWord *words, const TileRec &T)
 {
     TilePlace q;
     const unsigned sh = (threadIdx.x & 7u) * 4u;
 #pragma unroll
     for (int k = 0; k < SUBROWS; ++k) {
-        const StartWord w = L.words[(int64_t)T.words * TILE_WORDS + (local_base(k) >> 5)];
+        const StartWord w = words[(int64_t)T.words * TILE_WORDS + (local_base(k) >> 5)];
         q.row[k] = ((w.starts >> sh) & 15u) | ((w.rank + (unsigned)__popc(w.starts & ((1u << sh) - 1u))) << 4);
     }
     return q;
