@@ -76,6 +76,8 @@ struct ef_plan {
     int32_t *d_cross;               // blocks that span several tiles
     int32_t n_cross;
     double *d_qtile, *d_qpart;      // [max_workers][ntiles][2], [max_workers][2*ntiles][2]
+    unsigned long long *d_phi;      // [max_workers] see QualityArgs
+    unsigned *d_phi_done;
     // launches that (nearly) fit on the GPU all at once (ef_small.h)
     int small_wgs;                  // most workgroups such a launch may have
     int small_span;                 // most tiles of a block in it
@@ -662,6 +664,9 @@ int build_device(ef_plan *p)
     for (auto &r : p->role) mem.add(&r.d_late_index, (size_t)B, Arena::LEAVE);
     mem.add(&p->d_qpart, 4 * nt * nv, Arena::LEAVE);
     mem.add(&p->d_qtile, 2 * nt * nv, Arena::LEAVE);
+    const std::vector<unsigned long long> ones(nv, 0x3ff0000000000000ull);      // 1.0
+    mem.add(&p->d_phi, nv, Arena::COPY, ones.data());
+    mem.add(&p->d_phi_done, nv, Arena::ZERO);
     if (p->has_small) {
         mem.add(&p->d_small, small.size(), Arena::COPY, small.data());
         mem.add(&p->d_small_words, nt * ef::TILE_WORDS, Arena::LEAVE);
@@ -1239,8 +1244,6 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     const bool ends = main_kernel_ends(plan, role, c, plan->L.n_grid, err, state_stride, scales, scales_stride);
     if (quality) {
         if (!aligned(quality, 8)) return EF_ERR_ALIGN;
-        hipLaunchKernelGGL(ef::k_quality_init, dim3(1), dim3(ef::THREADS), 0, s, quality, n_workers);
-        EF_HIP(hipGetLastError());
     }
     if (role == ROLE_TICKET) {
         // the mixed tiles first, in a kernel of their own, then the persistent kernel
@@ -1269,6 +1272,8 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         Q.tile_sums = plan->d_qtile;
         Q.part_sums = plan->d_qpart;
         Q.out = quality;
+        Q.phi = plan->d_phi;
+        Q.done = plan->d_phi_done;
         const int kind = plan->L.n_dense ? 2 : plan->L.n_mixed ? 1 : 0;
         if (plan->L.n_dense == plan->L.ntiles) {
             if (quality)
@@ -1306,6 +1311,8 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     Q.tile_sums = plan->d_qtile;
     Q.part_sums = plan->d_qpart;
     Q.out = quality;
+    Q.phi = plan->d_phi;
+    Q.done = plan->d_phi_done;
     hipLaunchKernelGGL(ef::k_quality_blocks, dim3((unsigned)plan->n_cross + 1u, (unsigned)n_workers), dim3(ef::THREADS), 0,
                        s, plan->L, Q, (const int32_t *)plan->d_cross, (int)plan->n_cross);
     EF_HIP(hipGetLastError());
@@ -1444,8 +1451,8 @@ static int quality_launch(const ef_plan *plan, int n_vectors, const float *v, in
     Q.tile_sums = tile_sums;
     Q.part_sums = part_sums;
     Q.out = out;
-    hipLaunchKernelGGL(ef::k_quality_init, dim3(1), dim3(ef::THREADS), 0, s, out, n_vectors);
-    EF_HIP(hipGetLastError());
+    Q.phi = plan->d_phi;
+    Q.done = plan->d_phi_done;
     hipLaunchKernelGGL(ef::k_quality_tiles, dim3((unsigned)plan->L.ntiles, (unsigned)n_vectors), dim3(ef::THREADS), 0,
                        s, plan->L, Q);
     EF_HIP(hipGetLastError());
