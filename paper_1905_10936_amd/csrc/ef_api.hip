@@ -654,8 +654,9 @@ int build_device(ef_plan *p)
     // one 128-byte line per tile and set: a block's ready word sits in the line of its gatherer tile
     mem.add(&p->d_ready, (size_t)ef::READY_STRIDE * nt * ns, Arena::ZERO);
     mem.add(&p->d_list_cnt, ef::CALL_WORDS, Arena::ZERO);
-    // at most two entries a workgroup
-    mem.add(&p->d_parked, 2 * (nt * nv < (size_t)ef::ENDS_WGS_MAX ? nt * nv : (size_t)ef::ENDS_WGS_MAX), Arena::ZERO);
+    // an entry for a whole tile or pair, two for a mixed tile, in a call of at most ENDS_WGS_MAX workgroups
+    const size_t max_parked = (whole.size() + 2 * mixed.size()) * nv, most_parked = 2 * (size_t)ef::ENDS_WGS_MAX;
+    mem.add(&p->d_parked, max_parked < most_parked ? max_parked : most_parked, Arena::ZERO);
     mem.add(&p->d_state, 2, Arena::ZERO);
     mem.add(&p->d_lazy_scales, max_cross * ns, Arena::ZERO);
     mem.add(&p->d_defer_list, 2 * nt * ns, Arena::LEAVE);
@@ -669,7 +670,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_phi_done, nv, Arena::ZERO);
     if (p->has_small) {
         mem.add(&p->d_small, small.size(), Arena::COPY, small.data());
-        mem.add(&p->d_small_words, nt * ef::TILE_WORDS, Arena::LEAVE);
+        mem.add(&p->d_small_words, mixed.empty() ? 0 : nt * ef::TILE_WORDS, Arena::LEAVE);
     }
     { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
     p->L.mixed_tiles = p->d_mixed;
@@ -706,10 +707,12 @@ int build_device(ef_plan *p)
     }
     if (p->has_small) {
         p->small.tiles = p->d_small;
-        p->small.words = p->d_small_words;
-        hipLaunchKernelGGL(ef::k_small_words, dim3((unsigned)ntiles), dim3(ef::TILE_WORDS), 0, nullptr, p->L, p->d_small_words,
-                           p->d_words);
-        EF_HIP(hipGetLastError());
+        p->small.words = mixed.empty() ? nullptr : p->d_small_words;
+        if (!mixed.empty()) {
+            hipLaunchKernelGGL(ef::k_small_words, dim3((unsigned)ntiles), dim3(ef::TILE_WORDS), 0, nullptr, p->L, p->d_small_words,
+                               p->d_words);
+            EF_HIP(hipGetLastError());
+        }
     }
     p->user_fuse_limit = -1;
     // Which worker kernel for this layout.  The persistent kernel needs enough tiles per workgroup
@@ -1250,9 +1253,9 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         if (plan->L.n_mixed) {
             const dim3 grid((unsigned)plan->L.n_mixed, (unsigned)n_workers);
             if (has_mom)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
+                hipLaunchKernelGGL((ef::k_worker_mixed<true, false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
             else
-                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
+                hipLaunchKernelGGL((ef::k_worker_mixed<false, false, false>), grid, dim3(ef::THREADS), 0, s, L, c.X, A, ef::QualityArgs());
             EF_HIP(hipGetLastError());
         }
         int64_t wgs = (int64_t)plan->L.n_uniform * n_workers;
@@ -1276,12 +1279,11 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
         Q.done = plan->d_phi_done;
         const int kind = plan->L.n_dense ? 2 : plan->L.n_mixed ? 1 : 0;
         if (plan->L.n_dense == plan->L.ntiles) {
-            if (quality)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, true>), grid, block, 0, s, L, c.X, A, Q);
-            else if (has_mom)
-                hipLaunchKernelGGL((ef::k_worker_mixed<true, false>), grid, block, 0, s, L, c.X, A, Q);
-            else
-                hipLaunchKernelGGL((ef::k_worker_mixed<false, false>), grid, block, 0, s, L, c.X, A, Q);
+            typedef void (*Kernel)(ef::Layout, ef::ScratchRef, ef::WorkerArgs, ef::QualityArgs);
+            static const Kernel kernels[3][2] = {{ef::k_worker_mixed<false, false, false>, ef::k_worker_mixed<false, false, true>},
+                                                 {ef::k_worker_mixed<true, false, false>, ef::k_worker_mixed<true, false, true>},
+                                                 {ef::k_worker_mixed<true, true, false>, ef::k_worker_mixed<true, true, true>}};
+            hipLaunchKernelGGL(kernels[quality ? 2 : has_mom ? 1 : 0][ends], grid, block, 0, s, L, c.X, A, Q);
         } else if (quality && kind == 2)
             hipLaunchKernelGGL((ef::k_worker_tiles<true, ef::DENSE_TILES, true>), grid, block, 0, s, L, c.X, A, Q);
         else if (quality && kind == 1)

@@ -242,7 +242,7 @@ __device__ __forceinline__ void update_element(float &x, float &m, float delta, 
 // a small update is over before the next one is enqueued (31 tiles: 5.0 us with all of Layout; see k_apply_small).
 struct ApplyTables {
     int64_t d, W;
-    const TileRec *tiles;       // k_apply
+    const TileRec *tiles;
     const StartWord *words;     // Layout::words, or for k_apply_small SmallTables::words
 };
 

@@ -301,9 +301,8 @@ void k_server_mixed(Layout L, ScratchRef R, ServerArgs A, int set)
     float *te = A.err + (int64_t)tile * TILE;
     float4 p[SUBROWS];
     server_values_mixed(L, A, tile, T, n_valid, te, p, S);
-    const unsigned before = arrive(X, S);
-    compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
-    end_call(arrived(before, X), R, X, S);      // there may be no whole tiles
+    const unsigned left = compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
+    end_call(left, R, X, S);    // there may be no whole tiles
 }
 
 // p~ of a tile of a few segments (see compress_few): as server_values_whole, with a table of sums for one segment
@@ -735,17 +734,14 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
     } else if constexpr (MIXED) {
         if (TILES == DENSE_TILES && T.nseg < 0) {
             server_values_mixed(L, A, tile, T, n_valid, te, p, S);
-            const unsigned before = arrive(X, S);
-            compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
-            end_call(arrived(before, X), R, X, S);
+            left = compress_mixed(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S);
+            end_call(left, R, X, S);
             return;
         }
         __shared__ FewShared F;
         few_bounds(L, T, tile_start, n_valid, F.bound);
         server_values_few<MANY>(L, A, T, tile_start, te, n_valid, p, lds, F.bound);
-        const unsigned before = arrive(X, S);
-        compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F, lds);
-        left = arrived(before, X);
+        left = compress_few(p, L, T, tile, n_valid, A.signs, A.scales, te, X, set, S, F, lds);
     }
     end_call(left, R, X, S);
 }

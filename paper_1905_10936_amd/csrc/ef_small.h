@@ -63,7 +63,8 @@ struct SmallShared {
 // record: a scale is two trips to memory away from the kernel's start, not four.
 struct SmallTables {
     const SmallTile *tiles;     // [ntiles]
-    const StartWord *words;     // [ntiles][TILE_WORDS], whole tiles too; rank: the number of the block in progress before the word, plus 1
+    const StartWord *words;     // [ntiles][TILE_WORDS], whole tiles too; rank: the number of the block in progress before the word, plus 1.
+                                // Null: the layout has only whole tiles
 };
 
 // This thread's four elements among the blocks.
@@ -73,7 +74,8 @@ struct SmallPlace {
 };
 __device__ __forceinline__ SmallPlace small_place(const StartWord *words, int32_t tile)
 {
-    SmallPlace q;
+    SmallPlace q = {0u, 0};
+    if (!words) return q;
     const StartWord w = words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
     const unsigned sh = (threadIdx.x & 7u) * 4u;
     q.starts = (w.starts >> sh) & 15u;
@@ -353,11 +355,11 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     }
     __syncthreads();
     const int park_head = S.parked[0], park_tail = S.parked[1];
-    int seg = at.block - T.fb;
+    int seg = T.nseg == 1 ? 0 : at.block - T.fb;
     float v[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        seg += (int)((at.starts >> c) & 1u);
+        seg += T.nseg == 1 ? 0 : (int)((at.starts >> c) & 1u);
         const float e = residual(v[c], S.scale[seg]);
         const bool keep = (park_head && seg == 0) || (park_tail && seg == T.nseg - 1);
         v[c] = keep ? v[c] : e;
@@ -536,7 +538,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(ApplyTables Z, fl
     float4 m4 = x4;
     if (WD) m4 = small_load4(mt + start, n_valid);
     float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
-    int block = at.block;
+    int block = Z.words ? at.block : Z.tiles[tile].fb;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         block += (int)((at.starts >> c) & 1u);

@@ -680,9 +680,10 @@ __device__ __forceinline__ void advance_call(CallState *state, const CallState &
 // This call's words of the count (its defer_cnt is the first word of its parity).
 __device__ __forceinline__ unsigned *arrive_word(const Scratch &X, unsigned g) { return X.defer_cnt + ARRIVE_AT + g * ARRIVE_STRIDE; }
 
-// Thread 0 counts its workgroup in; the answer goes to arrived().  Called when the tile's values are there: an atomic ahead of
-// the loads of scales and block offsets would keep the compiler from making them scalar loads, and where many values
-// are still to come it costs the server's pairs 7 spilled registers.  (The lane number, 0 here, keeps the compiler from
+// Thread 0 counts its workgroup in; the answer goes to arrived().  Called when the tile's sums are posted: an atomic ahead of
+// the loads of scales and block offsets would keep the compiler from making them scalar loads (momentum-free worker, 16 workers,
+// 10 606 dense tiles: 1370 -> 1460 us), and where many values are still to come it costs the server's pairs 7
+// spilled registers.  (The lane number, 0 here, keeps the compiler from
 // making one addition of the wavefront's, whose answer it would wait for at once.)
 template <int WAVE = 0>
 __device__ __forceinline__ unsigned arrive(const Scratch &X)
@@ -1076,9 +1077,10 @@ __device__ __forceinline__ TilePlace tile_place(const StartWord *words, const Ti
 // (bounded waits), else their elements stored as p for the kernel that ends the
 // call.  (Section 3.2 and e_{t+1} = p_t - Delta_t of Algorithm 4.)  The sums are those of
 // segment_sum, short segments a thread each.
-__device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
-                                               uint64_t *signs, float *scales_out, float *err_tile,
-                                               const Scratch &X, int set, TileShared &S)
+// Returns what arrived() answers.
+__device__ __forceinline__ unsigned compress_mixed(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
+                                                   uint64_t *signs, float *scales_out, float *err_tile,
+                                                   const Scratch &X, int set, TileShared &S)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
     const int32_t fb = T.fb, lb = T.fb + abs(T.nseg) - 1;
@@ -1137,6 +1139,7 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
     const int tail_begin = tail_open ? (int)(L.offs[lb] - tile_start) : TILE;
     if (head_open) store_partial(S.open_sum[0], 0, tile, L, X, set);
     if (tail_open) store_partial(S.open_sum[1], 1, tile, L, X, set);
+    const unsigned before = arrive(X, S);
     // An open segment whose block has no whole tile is finished in place: all tiles of such a
     // block are mixed ones, handed out before any whole tile and in ascending order.  The first
     // segment's block ends in this tile, which makes this workgroup the one that forms its scale;
@@ -1177,6 +1180,7 @@ __device__ __forceinline__ void compress_mixed(float4 (&p)[SUBROWS], const Layou
     if (park_head) park_segment(tile, 0, false, X, set, S);
     if (park_tail) park_segment(tile, 1, false, X, set, S);
     __syncthreads();            // S.val is free again
+    return arrived(before, X);
 }
 
 // Deferred correction of a uniform tile's residual as loaded (see Scratch::lazy_scales): if the
@@ -1297,10 +1301,11 @@ __device__ __forceinline__ bool few_touches(int k, int lo, int hi)
     return first < hi && first + 256 > lo;
 }
 // val: TILE floats of LDS.
+// Returns what arrived() answers.
 template <bool WORDS = false>
-__device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
-                                             uint64_t *signs, float *scales_out, float *err_tile, const Scratch &X, int set,
-                                             SyncShared &S, FewShared &F, float *val)
+__device__ __forceinline__ unsigned compress_few(float4 (&p)[SUBROWS], const Layout &L, const TileRec &T, int32_t tile, int n_valid,
+                                                 uint64_t *signs, float *scales_out, float *err_tile, const Scratch &X, int set,
+                                                 SyncShared &S, FewShared &F, float *val)
 {
     const int64_t tile_start = (int64_t)tile * TILE;
     const int nseg = T.nseg;
@@ -1320,6 +1325,7 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
     // what others may wait for goes out first
     if (head_open) store_partial(F.sum[0], 0, tile, L, X, set);
     if (tail_open) store_partial(F.sum[nseg - 1], 1, tile, L, X, set);
+    const unsigned before = arrive(X, S);
     if ((int)threadIdx.x < nseg) {
         const int sg = (int)threadIdx.x;
         if (!(sg == 0 && head_open) && !(sg == nseg - 1 && tail_open)) {
@@ -1368,6 +1374,7 @@ __device__ __forceinline__ void compress_few(float4 (&p)[SUBROWS], const Layout 
     store_tile(err_tile, p, n_valid);
     if (park_head) park_segment(tile, 0, false, X, set, S);
     if (park_tail) park_segment(tile, 1, false, X, set, S);
+    return arrived(before, X);
 }
 
 // Writing the residual out in step.  Measured on this machine: workgroups that take consecutive
