@@ -206,7 +206,8 @@ class Run:
         tiles, whole, dense = wl.tile_kinds(w.offsets, w.M)
         quality = "true" if self.variant == "quality" else "false"
         if dense == tiles:
-            return "ef::k_worker_mixed<%s, %s>" % (mom, quality)
+            ends = "true" if tiles * w.M <= 1 << 16 else "false"
+            return "ef::k_worker_mixed<%s, %s, %s>" % (mom, quality, ends)
         return "ef::k_worker_tiles<%s, %d, %s>" % (mom, 2 if dense else 1 if whole < tiles else 0, quality)
 
     def close(self):

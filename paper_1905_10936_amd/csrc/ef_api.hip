@@ -1244,7 +1244,9 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     }
     const int role = quality ? (int)ROLE_TILES : worker_role(plan, has_mom);
     const ef::Layout L = role_layout(plan, role);
-    const bool ends = main_kernel_ends(plan, role, c, plan->L.n_grid, err, state_stride, scales, scales_stride);
+    // the kernels with dense and other tiles do not (server_ends)
+    const bool ends = (!plan->L.n_dense || plan->L.n_dense == plan->L.ntiles) &&
+                      main_kernel_ends(plan, role, c, plan->L.n_grid, err, state_stride, scales, scales_stride);
     if (quality) {
         if (!aligned(quality, 8)) return EF_ERR_ALIGN;
     }
@@ -1373,7 +1375,7 @@ int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, i
     const dim3 block(ef::THREADS);
     const int kind = L.n_dense ? 2 : L.n_mixed ? 1 : 0;
     const bool many = M > ef::SERVER_CHUNK, pairs = takes_pairs(plan, M);
-    const bool ends = ef::server_ends(many, pairs) && main_kernel_ends(plan, ROLE_SERVER, c, pairs ? L.n_paired : L.n_grid, server_err, 0, out_scales, 0);
+    const bool ends = (L.n_dense == L.ntiles || ef::server_ends(kind, many, pairs)) && main_kernel_ends(plan, ROLE_SERVER, c, pairs ? L.n_paired : L.n_grid, server_err, 0, out_scales, 0);
     if (L.n_dense == L.ntiles) {
         hipLaunchKernelGGL(ef::k_server_mixed, dim3((unsigned)L.n_grid), block, 0, s, L, c.X, A, plan->max_workers);
     } else {

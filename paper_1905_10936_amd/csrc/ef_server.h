@@ -682,7 +682,9 @@ constexpr int server_occupancy(int tiles, bool many, bool pairs)
 
 // Pairs of more than eight workers leave the end of their calls to k_tail: the code for it costs the pairs more than that
 // (354 M of a transformer, 14 workers: 730 us without, 783 with it).
-constexpr bool server_ends(bool many, bool pairs) { return !(many && pairs); }
+// Nor do the kernels with dense tiles: blocks with whole tiles leave their segments in those to k_tail anyway, and the code costs
+// them 5 % (a million tiny blocks and four of 8 Mi, 4 workers: 111 -> 117 us).
+constexpr bool server_ends(int tiles, bool many, bool pairs) { return tiles != DENSE_TILES && !(many && pairs); }
 
 template <int TILES, bool MANY, bool PAIRS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(server_occupancy(TILES, MANY, PAIRS), 8)))
@@ -702,7 +704,7 @@ void k_server_tiles(Layout L, ScratchRef R, ServerArgs A, int set)
         __builtin_amdgcn_sched_barrier(0);
     }
     Scratch X = open_call(R);
-    if (!server_ends(MANY, PAIRS)) X.ends = 0;
+    if (!server_ends(TILES, MANY, PAIRS)) X.ends = 0;
     const TileRec T = PAIRS ? L.paired_tiles[blockIdx.x] : MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
     if constexpr (PAIRS) {
         if (T.words == TILE_PAIR) {

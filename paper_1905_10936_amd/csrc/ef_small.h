@@ -250,7 +250,7 @@ __device__ __forceinline__ void small_left_over(unsigned left, const Layout &L, 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
 // of the blocks that end here, e' = p - Delta.  [bs, be): the block of segment threadIdx.x, in a tile of more than SMALL_BY_WAVE.
 __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallTile &T,
-                                               const SmallPlace &at, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
+                                               const SmallPlace &at, int bound, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
                                                float *err_tile, const Scratch &X, int set, SmallShared &S)
 {
     const int32_t tile = blockIdx.x;
@@ -283,6 +283,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         *reinterpret_cast<float4 *>(&S.val[j0]) = make_float4(fabsf(p.x), fabsf(p.y), fabsf(p.z), fabsf(p.w));
         const int64_t start = (int64_t)tile * TILE;
         if (T.nseg <= SMALL_BY_WAVE) {
+            if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = bound;
             __syncthreads();
 #pragma unroll 1
             for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < T.nseg; sg += SMALL_WAVES) {
@@ -349,7 +350,8 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
             }
         }
     }
-    if (wave == COUNT_WAVE) {
+    // while the others gather; where nothing is gathered, at the end
+    if ((head || tail) && wave == COUNT_WAVE) {
         const unsigned left = arrived<COUNT_WAVE>(before, X);
         if (lane == 0) S.left = left;
     }
@@ -377,14 +379,22 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         }
         __syncthreads();
     }
+    if (!(head || tail)) {
+        if (wave == COUNT_WAVE) {
+            const unsigned left = arrived<COUNT_WAVE>(before, X);
+            if (lane == 0) S.left = left;
+        }
+        __syncthreads();
+    }
     const unsigned left = uniform_u32(S.left);
     if (left | (unsigned)(park_head | park_tail)) small_left_over(left, L, X, S);
 }
 
-// What every thread asks for by the tile's number alone, ahead of the record.
-__device__ __forceinline__ void small_bounds(const SmallTables &Z, int32_t tile, SmallShared &S)
+// The bound that this thread puts into SmallShared::bound later: storing it where it is asked for would wait for all that was asked
+// for before it, ahead of the loads of state and record.
+__device__ __forceinline__ int small_bound(const SmallTables &Z, int32_t tile)
 {
-    if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = Z.tiles[tile].bound[threadIdx.x];
+    return Z.tiles[tile].bound[min((int)threadIdx.x, SMALL_BY_WAVE)];
 }
 
 template <bool MOM>
@@ -402,7 +412,7 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
     const SmallPlace at = small_place(Z.words, tile);
-    small_bounds(Z, tile, S);
+    const int bound = small_bound(Z, tile);
     const Scratch X = open_call(R);
     const SmallTile T = Z.tiles[tile];
     int64_t bs = 0, be = 1;
@@ -412,7 +422,7 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
     }
     worker_values4<MOM>(g, m, e, A.mu, A.r);
     if (MOM) small_store4(mt, n_valid, m);
-    small_compress(e, L, T, at, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+    small_compress(e, L, T, at, bound, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
                    A.scales + (int64_t)worker * A.scales_stride, et, X, worker, S);
 }
 
@@ -444,7 +454,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
     const SmallPlace at = small_place(Z.words, tile);
-    small_bounds(Z, tile, S);
+    const int bound = small_bound(Z, tile);
     const Scratch X = open_call(R);
     const SmallTile T = Z.tiles[tile];
     int64_t bs = 0, be = 1;
@@ -520,7 +530,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
     p.y = mean_of(acc[1], A.Mf, A.Minv) + A.r * te.y;
     p.z = mean_of(acc[2], A.Mf, A.Minv) + A.r * te.z;
     p.w = mean_of(acc[3], A.Mf, A.Minv) + A.r * te.w;
-    small_compress(p, L, T, at, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
+    small_compress(p, L, T, at, bound, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
 }
 
 // Parameter update (see apply_tile), one workgroup of 1024 threads per tile.

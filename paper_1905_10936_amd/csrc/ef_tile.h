@@ -51,7 +51,8 @@
 // them get p parked in the residual buffer.  Parked p (those segments, the
 // tiles of blocks larger than fuse_limit but for the last ones (first_kept), any tile whose bounded wait ran out) is finished by one kernel
 // after the main one, which also computes the scales still missing and steps
-// the plan to its next call.
+// the plan to its next call.  Where a layout leaves nothing to that kernel but the last two, the main one sees to them (see
+// ARRIVE_GROUPS).
 //
 // Deferred correction (optional)
 // ------------------------------
@@ -699,7 +700,7 @@ __device__ __forceinline__ unsigned arrive_groups(const ScratchRef &R) { return 
 
 __device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
 {
-    if (threadIdx.x == 0) S.own[0] = S.own[1] = 0ull;
+    if (X.ends && threadIdx.x == 0) S.own[0] = S.own[1] = 0ull;
     return arrive(X);
 }
 

@@ -42,7 +42,7 @@ __device__ __forceinline__ void worker_values(const float4 (&g)[SUBROWS], float4
 // Mixed tiles of all workers, one workgroup per (tile, worker): ahead of the persistent kernel, and layouts that have
 // no others than dense ones.  Bound by its chain of latencies where there are few of them, else by HBM.
 // QUAL: see k_worker_tiles.  ENDS: the kernel may end its call; ahead of the persistent one, and in calls of more than
-// ENDS_WGS_MAX workgroups, the code for it costs more than it gives (momentum-free, 16 workers, 10 606 tiles: 1428 us, 1390).
+// ENDS_WGS_MAX workgroups, the code for it costs more than it gives (momentum-free, 16 workers, 10 606 tiles: 1428 us, 1400 without).
 template <bool MOM, bool QUAL, bool ENDS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_worker_mixed(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
@@ -327,7 +327,8 @@ void k_worker_tiles(Layout L, ScratchRef R, WorkerArgs A, QualityArgs Q)
         load_tile(e + start, pv, TILE);
         __builtin_amdgcn_sched_barrier(0);
     }
-    const Scratch X = open_call(R);
+    Scratch X = open_call(R);
+    if (TILES == DENSE_TILES) X.ends = 0;       // see server_ends
     const TileRec T = MIXED ? L.grid_tiles[blockIdx.x] : L.tiles[blockIdx.x];
     const int32_t tile = MIXED ? T.tile : (int32_t)blockIdx.x;
     const int64_t tile_start = (int64_t)tile * TILE;
