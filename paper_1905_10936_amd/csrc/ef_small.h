@@ -258,7 +258,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     small_signs(p, n_valid, signs, (int64_t)tile * TILE, L.W);
     const int j0 = 4 * (int)threadIdx.x;
     const bool whole = T.whole != 0;
-    const unsigned before = arrive<COUNT_WAVE>(X);
+    unsigned before;            // asked for behind the first barrier (see arrive)
     const double a[4] = {j0 + 0 < n_valid ? fabsf(p.x) : 0.f, j0 + 1 < n_valid ? fabsf(p.y) : 0.f,
                          j0 + 2 < n_valid ? fabsf(p.z) : 0.f, j0 + 3 < n_valid ? fabsf(p.w) : 0.f};
     const unsigned long long tag = set_tag(X, set);
@@ -270,6 +270,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     if (whole) {
         S.sum[threadIdx.x] = ((a[0] + a[1]) + a[2]) + a[3];
         __syncthreads();
+        before = arrive<COUNT_WAVE>(X);
         if (wave == 0) {
             // the order of abs_sum and block_sum: a lane's four rows, the 64 lanes, the four quarters
             double q[4];
@@ -285,6 +286,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         if (T.nseg <= SMALL_BY_WAVE) {
             if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = bound;
             __syncthreads();
+            before = arrive<COUNT_WAVE>(X);
 #pragma unroll 1
             for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < T.nseg; sg += SMALL_WAVES) {
                 const double total = segment_sum(S.val, (int)uniform_u32((unsigned)S.bound[sg]), (int)uniform_u32((unsigned)S.bound[sg + 1]));
@@ -293,6 +295,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         } else {
             if (threadIdx.x == 0) S.n_long = 0;
             __syncthreads();
+            before = arrive<COUNT_WAVE>(X);
             for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
                 const int64_t b = T.fb + sg;
                 const int lo = (int)max((sg < SMALL_THREADS ? bs : L.offs[b]) - start, (int64_t)0);

@@ -681,7 +681,10 @@ __device__ __forceinline__ void advance_call(CallState *state, const CallState &
 // This call's words of the count (its defer_cnt is the first word of its parity).
 __device__ __forceinline__ unsigned *arrive_word(const Scratch &X, unsigned g) { return X.defer_cnt + ARRIVE_AT + g * ARRIVE_STRIDE; }
 
-// Thread 0 counts its workgroup in; the answer goes to arrived().  Called when the tile's sums are posted: an atomic ahead of
+// Thread 0 counts its workgroup in; the answer goes to arrived().  Every wavefront has read the call state for itself, and the
+// last workgroup to be counted changes it: a barrier has to lie between any wavefront's open_call and this, with
+// what it loaded in its registers.  (What is behind a barrier that hands over LDS contents is: the wait ahead of one is for
+// scalar loads, too.)  Called when the tile's sums are posted: an atomic ahead of
 // the loads of scales and block offsets would keep the compiler from making them scalar loads (momentum-free worker, 16 workers,
 // 10 606 dense tiles: 1370 -> 1460 us), and where many values are still to come it costs the server's pairs 7
 // spilled registers.  (The lane number, 0 here, keeps the compiler from
