@@ -18,16 +18,26 @@ __device__ __forceinline__ double sure_word(const unsigned long long *at, unsign
     return __longlong_as_double(0x7ff8000000000000ll);
 }
 
-// An entry that is there or on its way (one wavefront).
-__device__ __forceinline__ unsigned long long take_entry(unsigned long long *at)
+// Nothing that the call has made can be relied on: every scale of it becomes a NaN, which no result that is made from them hides.
+__device__ __forceinline__ void spoil_call(const Layout &L, const ScratchRef &R)
 {
-    unsigned long long it = 0ull;
 #pragma unroll 1
-    for (int n = 0; n < SURE_POLLS && !it; ++n) {
-        it = uniform_u64(__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (!it) __builtin_amdgcn_s_sleep(8);
-    }
-    if (lane_id() == 0) *at = 0ull;
+    for (int w = 0; w < R.nsets; ++w)
+#pragma unroll 1
+        for (int64_t b = lane_id(); b < L.B; b += 64) R.scales[(int64_t)w * R.scales_stride + b] = __uint_as_float(0x7fc00000u);
+}
+
+// An entry that is there or on its way (one wavefront): its workgroup runs, and what it waits for is bounded.  Should it not come, a
+// segment that nobody knows would keep p, and its block's scale not be written: the call is spoiled.  The entry stays, if it
+// does come; it is of this call (parked_in), so no other call takes it.
+__device__ __forceinline__ unsigned long long take_entry(unsigned long long *at, const Layout &L, const Scratch &X)
+{
+    const unsigned long long it = uniform_u64(await_parked([&] { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                                                           [] { __builtin_amdgcn_s_sleep(8); }, X.epoch, SURE_POLLS));
+    if (!it)
+        spoil_call(L, call_args().R);
+    else if (lane_id() == 0)
+        *at = 0ull;
     return it;
 }
 
@@ -42,12 +52,12 @@ __device__ __forceinline__ void end_left_over(unsigned left, const Scratch &X, S
     const int lane = lane_id();
 #pragma unroll 1
     for (unsigned i = 0; i < left + 2u; ++i) {
-        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u));
+        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u), L, X);
         if (!it) continue;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const int set = (int)((it & (PARKED_FORMS - 1ull)) >> 33), w = set - X.set_base;
-        const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
-        const int64_t b = (it & 1ull) ? L.tile_lb[tile] : L.tile_fb[tile], start = (int64_t)tile * TILE;
+        const int set = parked_set(it), w = set - X.set_base;
+        const int32_t tile = parked_tile(it);
+        const int64_t b = parked_slot(it) ? L.tile_lb[tile] : L.tile_fb[tile], start = (int64_t)tile * TILE;
         const BlockSpan sp = block_span(L, b);
         // the order of gather_scale, which has four wavefronts
         const unsigned long long *part = set_part(X, L, set);

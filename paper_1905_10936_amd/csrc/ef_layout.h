@@ -90,4 +90,35 @@ constexpr int64_t group_last(int64_t first, int group, int64_t first_kept)
     return first + group < first_kept ? first + group - 1 : first_kept - 1;
 }
 
+// What a workgroup whose wait ran out leaves for the one that ends the call (ef_tile.h, give_up): which segment, and of which call,
+// so that nobody takes what another call left for its own.
+constexpr unsigned long long PARKED_VALID = 1ull << 63;
+constexpr unsigned long long PARKED_BOTH = 1ull << 62;      // the tile and the next one
+constexpr unsigned long long PARKED_FORMS = 1ull << 61;     // the block's scale is still to be written, too
+constexpr int PARKED_CALL_AT = 40, PARKED_SET_AT = 33;
+constexpr unsigned PARKED_CALLS = 1u << 20, PARKED_SETS = 128u;
+constexpr unsigned long long parked_entry(unsigned call, int set, int32_t tile, int slot, unsigned long long flags)
+{
+    return PARKED_VALID | flags | ((unsigned long long)(call % PARKED_CALLS) << PARKED_CALL_AT) | ((unsigned long long)set << PARKED_SET_AT) |
+           ((unsigned long long)tile << 1) | (unsigned)slot;
+}
+constexpr bool parked_in(unsigned long long entry, unsigned call)
+{
+    return (entry & PARKED_VALID) && (unsigned)(entry >> PARKED_CALL_AT) % PARKED_CALLS == call % PARKED_CALLS;
+}
+constexpr int parked_set(unsigned long long entry) { return (int)((unsigned)(entry >> PARKED_SET_AT) % PARKED_SETS); }
+constexpr int32_t parked_tile(unsigned long long entry) { return (int32_t)((entry >> 1) & 0xffffffffull); }
+constexpr int parked_slot(unsigned long long entry) { return (int)(entry & 1ull); }
+// Looks for the entry of `call` at most `polls` times.  load: what is there now; rest: between two looks.  0: it has not come.
+template <class Load, class Rest>
+constexpr unsigned long long await_parked(Load load, Rest rest, unsigned call, int polls)
+{
+    for (int n = 0; n < polls; ++n) {
+        const unsigned long long entry = load();
+        if (parked_in(entry, call)) return entry;
+        rest();
+    }
+    return 0ull;
+}
+
 }  // namespace ef

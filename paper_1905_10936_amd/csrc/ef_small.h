@@ -226,12 +226,12 @@ __device__ __forceinline__ void small_left_over(unsigned left, const Layout &L, 
     const ScratchRef &R = call_args().R;
 #pragma unroll 1
     for (unsigned i = uniform_u32(threadIdx.x >> 6); i < left + 2u; i += SMALL_WAVES) {
-        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u));
+        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u), L, X);
         if (!it) continue;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const int set = (int)((it & (PARKED_FORMS - 1ull)) >> 33), w = set - X.set_base;
-        const int32_t tile = (int32_t)((it >> 1) & 0xffffffffull);
-        const int64_t b = (it & 1ull) ? L.tile_lb[tile] : L.tile_fb[tile];
+        const int set = parked_set(it), w = set - X.set_base;
+        const int32_t tile = parked_tile(it);
+        const int64_t b = parked_slot(it) ? L.tile_lb[tile] : L.tile_fb[tile];
         const BlockSpan sp = block_span(L, b);
         const unsigned long long *part = set_part(X, L, set);
         const unsigned long long tag = set_tag(X, set);
@@ -377,8 +377,8 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         __syncthreads();
         if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            if (park_head) leave_entry(S.park[0], 0ull, set, tile, 0, &S.own[0]);
-            if (park_tail) leave_entry(S.park[1], 0ull, set, tile, T.nseg > 1 ? 1 : 0, &S.own[1]);
+            if (park_head) leave_entry(S.park[0], 0ull, X, set, tile, 0, &S.own[0]);
+            if (park_tail) leave_entry(S.park[1], 0ull, X, set, tile, T.nseg > 1 ? 1 : 0, &S.own[1]);
         }
         __syncthreads();
     }

@@ -166,9 +166,6 @@ constexpr int ARRIVE_AT = 32;                               // the first of them
 constexpr int CALL_WORDS = ARRIVE_AT + (ARRIVE_GROUPS + 1) * ARRIVE_STRIDE;
 constexpr unsigned ARRIVED_MASK = 255u, PARKED_ONE = 256u;  // on the last word: groups that are complete; parked entries
 constexpr int64_t ENDS_WGS_MAX = 1 << 16;                   // workgroups of such a call: of more, k_tail's 5 us are nothing
-constexpr unsigned long long PARKED_VALID = 1ull << 63;     // entry: | PARKED_BOTH | PARKED_FORMS | (set << 33) | (tile << 1) | slot
-constexpr unsigned long long PARKED_BOTH = 1ull << 62;      // the tile and the next one
-constexpr unsigned long long PARKED_FORMS = 1ull << 61;     // the block's scale is still to be written, too
 constexpr unsigned PARK_FORMS = 1u << 31;                   // the same beside an entry's number (SyncShared::park)
 constexpr unsigned PARK_OWN = PARK_FORMS - 1u;              // in place of the number: the workgroup's own to see to
 
@@ -191,7 +188,7 @@ struct ScratchRef {
     int columns, nsets;                 // workgroups: of a set, and sets
     int lazy;
     CallState *step;
-    unsigned long long *parked;         // entries, all 0 between calls
+    unsigned long long *parked;         // entries (parked_entry), all 0 between calls but for what was lost
     float *err;                         // residual buffers of the call's sets, err_stride apart
     int64_t err_stride;
     float *scales;                      // scale arrays of the call's sets, scales_stride apart
@@ -736,10 +733,10 @@ __device__ __forceinline__ void give_up(const Scratch &X, unsigned *park, unsign
     *park = ((top & ARRIVED_MASK) == arrive_groups(call_args().R) ? PARK_OWN : top / PARKED_ONE) | forms;
 }
 // And the segment has been stored as p: an entry, in ScratchRef::parked or the workgroup's own.  One thread, after a release.
-__device__ __forceinline__ void leave_entry(unsigned park, unsigned long long both, int set, int32_t tile, int which, unsigned long long *own)
+__device__ __forceinline__ void leave_entry(unsigned park, unsigned long long both, const Scratch &X, int set, int32_t tile, int which,
+                                            unsigned long long *own)
 {
-    const unsigned long long entry = PARKED_VALID | both | ((park & PARK_FORMS) ? PARKED_FORMS : 0ull) | ((unsigned long long)set << 33) |
-                                     ((unsigned long long)tile << 1) | (unsigned)which;
+    const unsigned long long entry = parked_entry(X.epoch, set, tile, which, both | ((park & PARK_FORMS) ? PARKED_FORMS : 0ull));
     if ((park & ~PARK_FORMS) == PARK_OWN)
         *own = entry;
     else
@@ -1049,7 +1046,7 @@ __device__ __forceinline__ void park_segment(int32_t tile, int which, bool both,
     __syncthreads();
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        leave_entry(S.park[which], both ? PARKED_BOTH : 0ull, set, tile, which, &S.own[which]);
+        leave_entry(S.park[which], both ? PARKED_BOTH : 0ull, X, set, tile, which, &S.own[which]);
     }
     __syncthreads();
 }

@@ -75,6 +75,26 @@ int main()
                     REQUIRE((g0 - first) % group == 0 && ef::group_first(g1, first, group) == g0);
                 }
         }
+
+    // an entry gives back what was put into it, to its own call alone
+    for (unsigned call : {1u, 2u, 77u, (1u << 20) - 1u, 1u << 20, 0xfffffffeu, 0xffffffffu})
+        for (int set : {0, 1, 63, 64})
+            for (int32_t tile : {0, 1, 65535, 0x7fffffff})
+                for (unsigned long long flags : {0ull, ef::PARKED_BOTH, ef::PARKED_FORMS, ef::PARKED_BOTH | ef::PARKED_FORMS})
+                    for (int slot : {0, 1}) {
+                        const unsigned long long e = ef::parked_entry(call, set, tile, slot, flags);
+                        REQUIRE(ef::parked_in(e, call) && !ef::parked_in(e, call + 1u) && !ef::parked_in(e, call - 1u));
+                        REQUIRE(ef::parked_set(e) == set && ef::parked_tile(e) == tile && ef::parked_slot(e) == slot);
+                        REQUIRE((e & (ef::PARKED_BOTH | ef::PARKED_FORMS)) == flags && !ef::parked_in(0ull, call));
+                    }
+    // what an earlier call left in the place is neither taken nor ends the search; one that does not come ends it with 0
+    {
+        const unsigned long long old = ef::parked_entry(6, 0, 1, 0, 0), mine = ef::parked_entry(7, 0, 2, 1, ef::PARKED_FORMS);
+        int looks = 0, rests = 0;
+        const auto rest = [&] { ++rests; };
+        REQUIRE(ef::await_parked([&] { return ++looks < 5 ? old : mine; }, rest, 7, 100) == mine && looks == 5 && rests == 4);
+        REQUIRE(ef::await_parked([&] { return old; }, rest, 7, 100) == 0ull && rests == 104);
+    }
     std::puts("layout rules ok");
     return 0;
 }
