@@ -376,7 +376,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            release_stores();
             if (park_head) leave_entry(S.park[0], 0ull, X, set, tile, 0, &S.own[0]);
             if (park_tail) leave_entry(S.park[1], 0ull, X, set, tile, T.nseg > 1 ? 1 : 0, &S.own[1]);
         }

@@ -732,6 +732,13 @@ __device__ __forceinline__ void give_up(const Scratch &X, unsigned *park, unsign
     const unsigned top = atomicAdd(arrive_word(X, ARRIVE_GROUPS), PARKED_ONE);
     *park = ((top & ARRIVED_MASK) == arrive_groups(call_args().R) ? PARK_OWN : top / PARKED_ONE) | forms;
 }
+// What the workgroup has stored, and its wavefronts have waited for, is there for all others to see.  One wavefront.  The second wait is the
+// write-back's: the fence's own is dropped by the compiler where it knows of no store on its way, and does not count that.
+__device__ __forceinline__ void release_stores()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_s_waitcnt(0);
+}
 // And the segment has been stored as p: an entry, in ScratchRef::parked or the workgroup's own.  One thread, after a release.
 __device__ __forceinline__ void leave_entry(unsigned park, unsigned long long both, const Scratch &X, int set, int32_t tile, int which,
                                             unsigned long long *own)
@@ -1045,7 +1052,7 @@ __device__ __forceinline__ void park_segment(int32_t tile, int which, bool both,
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        release_stores();
         leave_entry(S.park[which], both ? PARKED_BOTH : 0ull, X, set, tile, which, &S.own[which]);
     }
     __syncthreads();
