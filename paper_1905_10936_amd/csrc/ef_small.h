@@ -55,7 +55,7 @@ struct SmallShared {
     int parked[2];              // head, tail: the wait ran out
     unsigned park[2];           // as in SyncShared
     unsigned long long own[2];
-    unsigned left;              // in the last workgroup to begin: entries it has to see to
+    unsigned left;              // what arrived() answers
     double total;
 };
 
@@ -194,57 +194,6 @@ __device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double
     }
     if (ok) *total = small_total(v);
     return ok;
-}
-
-// e <- p - Delta over the elements [lo, hi) of a residual row whose p was parked (one wavefront).
-__device__ __forceinline__ void small_residual(float *e, int64_t lo, int64_t hi, float s)
-{
-    const int lane = lane_id();
-    const int64_t a = (lo + 3) & ~(int64_t)3, z = hi & ~(int64_t)3;     // whole groups of four
-    if (a >= z) {
-        if (lo + lane < hi) e[lo + lane] = residual(e[lo + lane], s);
-        return;
-    }
-    // the other elements of the first and the last group may be another wavefront's
-    if (lo + lane < a) e[lo + lane] = residual(e[lo + lane], s);
-    if (z + lane < hi) e[z + lane] = residual(e[z + lane], s);
-    for (int64_t j = a + 4 * lane; j < z; j += 4 * 256) {
-        float4 v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const float4 *>(e + min(j + 256 * q, z - 4));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            residual4(v[q], s);
-            if (j + 256 * q < z) *reinterpret_cast<float4 *>(e + j + 256 * q) = v[q];
-        }
-    }
-}
-
-// What end_left_over does, a wavefront to an entry.  (A call whose every wait gives up, 1000 tiles in blocks of 200: 497 us.)
-__device__ __forceinline__ void small_left_over(unsigned left, const Layout &L, const Scratch &X, SmallShared &S)
-{
-    const ScratchRef &R = call_args().R;
-#pragma unroll 1
-    for (unsigned i = uniform_u32(threadIdx.x >> 6); i < left + 2u; i += SMALL_WAVES) {
-        const unsigned long long it = i < 2u ? uniform_u64(S.own[i]) : take_entry(R.parked + (i - 2u), L, X);
-        if (!it) continue;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const int set = parked_set(it), w = set - X.set_base;
-        const int32_t tile = parked_tile(it);
-        const int64_t b = parked_slot(it) ? L.tile_lb[tile] : L.tile_fb[tile];
-        const BlockSpan sp = block_span(L, b);
-        const unsigned long long *part = set_part(X, L, set);
-        const unsigned long long tag = set_tag(X, set);
-        double v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j = lane_id() + 64 * q;
-            v[q] = j < sp.n ? sure_word(part + part_index(sp.t0 + j, sp), tag) : 0.0;
-        }
-        const float s = (float)(small_total(v) / (double)(sp.be - sp.bs));
-        if ((it & PARKED_FORMS) && lane_id() == 0) R.scales[(int64_t)w * R.scales_stride + b] = s;
-        small_residual(R.err + (int64_t)w * R.err_stride, max(sp.bs, (int64_t)tile * TILE), min(sp.be, ((int64_t)tile + 1) * TILE), s);
-    }
 }
 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
@@ -390,7 +339,8 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         __syncthreads();
     }
     const unsigned left = uniform_u32(S.left);
-    if (left | (unsigned)(park_head | park_tail)) small_left_over(left, L, X, S);
+    // see end_call; all wavefronts are at hand here
+    if (left | (unsigned)(park_head | park_tail)) finish_entries(S.own, wave == 0, X);
 }
 
 // The bound that this thread puts into SmallShared::bound later: storing it where it is asked for would wait for all that was asked

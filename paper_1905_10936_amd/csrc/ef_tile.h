@@ -159,11 +159,13 @@ struct alignas(32) CallState {
 // comes back while the workgroup waits for its block's scale, so that it costs no time.  (Counting out at the end does: an atomic's answer takes several us while HBM is saturated.)
 // A wait that runs out goes by the same word.  The workgroup leaves p in the residual buffer.  If all workgroups have begun, all
 // partial sums are sure to come (each posts its own ahead of its waits), and it waits for them at its end and finishes the
-// segment.  Else it is counted there as parked and leaves an entry in ScratchRef::parked, and the last workgroup to begin, which
-// finds the number of entries in its own count's answer, does that for them.
+// segment.  Else it is counted there as parked and leaves an entry in ScratchRef::parked.  The last workgroup to begin finds the
+// number of entries in its own count's answer and sees to them, and others that are at hand with it (finish_entries).
 constexpr int ARRIVE_GROUPS = 32, ARRIVE_STRIDE = 32;       // words
 constexpr int ARRIVE_AT = 32;                               // the first of them, after a parity's counters (ScratchRef::list_cnt)
-constexpr int CALL_WORDS = ARRIVE_AT + (ARRIVE_GROUPS + 1) * ARRIVE_STRIDE;
+constexpr int LEFT = ARRIVE_GROUPS + 1;                     // after the count's words: number of entries and 1, when all have begun
+constexpr int TAKEN = LEFT + 1;                             // and of those that somebody sees to
+constexpr int CALL_WORDS = ARRIVE_AT + (TAKEN + 1) * ARRIVE_STRIDE;
 constexpr unsigned ARRIVED_MASK = 255u, PARKED_ONE = 256u;  // on the last word: groups that are complete; parked entries
 constexpr int64_t ENDS_WGS_MAX = 1 << 16;                   // workgroups of such a call: of more, k_tail's 5 us are nothing
 constexpr unsigned PARK_FORMS = 1u << 31;                   // the same beside an entry's number (SyncShared::park)
@@ -661,7 +663,7 @@ __device__ __forceinline__ void advance_call(CallState *state, const CallState &
 {
     const int lane = lane_id();
     if (lane < 4) X.next_cnt[2 * lane] = 0u;
-    if (lane <= ARRIVE_GROUPS) X.next_cnt[ARRIVE_AT + lane * ARRIVE_STRIDE] = 0u;
+    if (lane <= TAKEN) X.next_cnt[ARRIVE_AT + lane * ARRIVE_STRIDE] = 0u;
     if (lane != 0) return;
     const unsigned long long used = nsets >= 64 ? ~0ull : ((1ull << nsets) - 1ull);
     state->calls = now.calls + 1u;
@@ -705,7 +707,8 @@ __device__ __forceinline__ unsigned arrive(const Scratch &X, SyncShared &S)
 }
 
 // The last workgroup to have counted itself in steps the call state, one wavefront alone.  Returns to that one the number
-// of entries that are left to it, 0 to all others.  Called when the answer is likely to be there: after the wait for a scale.
+// of entries that are left, to the last one of a group how many there are so far, 0 to all others: if it is not 0, that
+// wavefront is to help with them at its end.  Called when the answer is likely to be there: after the wait for a scale.
 template <int WAVE = 0>
 __device__ __forceinline__ unsigned arrived(unsigned before, const Scratch &X)
 {
@@ -720,7 +723,8 @@ __device__ __forceinline__ unsigned arrived(unsigned before, const Scratch &X)
     unsigned top = 0u;
     if (lane_id() == 0) top = atomicAdd(arrive_word(X, ARRIVE_GROUPS), 1u);
     top = uniform_u32(top);
-    if ((top & ARRIVED_MASK) + 1u != arrive_groups(R)) return 0u;
+    if ((top & ARRIVED_MASK) + 1u != arrive_groups(R)) return top / PARKED_ONE;
+    if (lane_id() == 0) __hip_atomic_store(arrive_word(X, LEFT), top / PARKED_ONE + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     advance_call(R.step, now, X, R.nsets, R.lazy);
     return top / PARKED_ONE;
 }

@@ -65,3 +65,24 @@ def test_waits_that_run_out_end_with_the_same_bits(name, M):
         torch.cuda.synchronize()
         for key in a:
             assert torch.equal(a[key].view(torch.int32), b[key].view(torch.int32)), "%s M=%d call %d: %s" % (name, M, k, key)
+
+
+@pytest.mark.parametrize("name", ["whole_tiles", "few_segments", "dense"])
+def test_what_waits_leave_is_finished_by_many(name):
+    """Thousands of waits that run out cost thousands of tiles' second pass, shared out, not one after the other: a workgroup
+    moves a parked tile (32 KiB) in about 10 us, END_WGS = 16 of them in less than 1 us a tile; one wavefront alone takes 28."""
+    offs = np.concatenate([[0], np.cumsum(LAYOUTS[name])])
+    plan = ef.ef_plan_create(offs, 1)
+    plan.set_persistent(False)
+    plan.tune(spin_limit=0)
+    t = _tensors(offs, 1, 3)
+    took, parked = [], 0
+    for _ in range(4):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        ef.ef_worker_step(plan, t["g"], t["m"], t["e"], 0.9, 0.1, 0.05, t["ws"], t["wc"])
+        end.record()
+        parked = plan.last_fallbacks()[0]
+        took.append(begin.elapsed_time(end) * 1e3)
+    assert parked > 900
+    assert min(took) < 300 + 1.0 * parked, (took, parked)

@@ -1,7 +1,8 @@
 """A workgroup may count itself in only once all of its wavefronts have read the call state: the last one to be counted steps the
 state.  That needs a barrier between every wavefront's read and the count, and the read has to be over at the barrier.
 No run can be relied on to show a count that is too early, so this follows the control flow of the built kernels: on no path
-from a kernel's entry to its first atomic in memory may the barrier be missing, nor a scalar load be on its way at it."""
+from a kernel's entry to a count may the barrier be missing, nor a scalar load be on its way at the first one.  A count is an
+atomic whose address has the lane number of a full mask added to it (arrive()): the compiler makes another mask for its own."""
 import os
 import re
 import shutil
@@ -16,6 +17,7 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 # the server's pairs of more than eight workers and the mixed ones built without it, which leave that to k_tail
 ENDING = ("k_worker_small", "k_server_small", "k_worker_tilesILb[01]ELi[01]E", "k_worker_mixedILb[01]ELb[01]ELb1E", "k_server_mixed",
           "k_server_tilesILi[01]ELb0E", "k_server_tilesILi[01]ELb1ELb0E")
+COUNT_SPAN = 24         # instructions ahead of a count's atomic in which its address is formed
 
 
 def _kernels(tmp):
@@ -36,8 +38,14 @@ def _kernels(tmp):
     return kernels
 
 
+def is_count(code, i):
+    if not code[i][1].startswith("global_atomic_add"):
+        return False
+    return any(re.match(r"v_mbcnt_lo_u32_b32\w* v\d+, -1, 0", text) for _, text, _ in code[max(0, i - COUNT_SPAN):i])
+
+
 def early_counts(start, code):
-    """Addresses of atomics that can be reached without a barrier, and of first barriers that a scalar load may be outstanding at."""
+    """Addresses of counts that can be reached without a barrier, and of first barriers that a scalar load may be outstanding at."""
     index = {at: i for i, (at, _, _) in enumerate(code)}
     seen, todo, bad = set(), [(0, False)], []
     while todo:
@@ -52,7 +60,7 @@ def early_counts(start, code):
                 loading = True
             elif op == "s_waitcnt" and "lgkmcnt(0)" in text:
                 loading = False
-            elif op.startswith(("global_atomic", "flat_atomic", "buffer_atomic")):
+            elif is_count(code, i):
                 bad.append((at, text))
                 break
             elif op == "s_barrier":
@@ -79,6 +87,7 @@ def test_no_count_ahead_of_the_barrier(tmp_path):
     for e in ENDING:
         assert any(re.search(e, name) for name in kernels), e
     for name, (start, code) in kernels.items():
+        assert any(is_count(code, i) for i in range(len(code))), name
         assert not early_counts(start, code), name
 
 
@@ -87,10 +96,11 @@ def test_the_check_sees_what_it_is_for():
         code = [(4 * i, text, re.search(r"<\w+(?:\+0x([0-9a-f]+))?>\s*$", text)) for i, text in enumerate(lines)]
         return early_counts(0, code)
 
-    load, wait, count, barrier, end = "s_load_dwordx8 s[4:11], s[0:1], 0x0", "s_waitcnt lgkmcnt(0)", "global_atomic_add v1, v0, v1, s[0:1] sc0", \
-        "s_barrier", "s_endpgm"
-    assert not run(load, wait, barrier, count, end)
-    assert run(load, wait, count, barrier, end)
-    assert run(load, barrier, count, end)
-    assert run(load, wait, "s_cbranch_vccz 1 <k+0x10>", barrier, count, end)        # one of two paths
-    assert not run(load, wait, "s_cbranch_vccz 1 <k+0x14>", barrier, count, end)
+    load, wait, barrier, end = "s_load_dwordx8 s[4:11], s[0:1], 0x0", "s_waitcnt lgkmcnt(0)", "s_barrier", "s_endpgm"
+    lane, count = "v_mbcnt_lo_u32_b32 v1, -1, 0", "global_atomic_add v1, v0, v1, s[0:1] sc0"
+    assert not run(lane, load, wait, barrier, count, end)
+    assert run(lane, load, wait, count, barrier, end)
+    assert run(lane, load, barrier, count, end)
+    assert run(lane, load, wait, "s_cbranch_vccz 1 <k+0x14>", barrier, count, end)      # one of two paths
+    assert not run(lane, load, wait, "s_cbranch_vccz 1 <k+0x18>", barrier, count, end)
+    assert not run(load, wait, count, barrier, end)                                     # an atomic, but no count
