@@ -955,7 +955,6 @@ __device__ __forceinline__ bool finish_block(int64_t b, const BlockSpan &sp, con
         } else {
             const unsigned k = atomicAdd(X.fin_cnt, 1u);
             if (X.ends) {
-                atomicAdd(X.defer_cnt, 1u);
                 give_up(X, &S.park[slot], PARK_FORMS);
             } else {
                 X.fin_list[k] = ((unsigned long long)set << 32) | (unsigned long long)b;
@@ -1031,10 +1030,7 @@ __device__ __forceinline__ void defer_segment(int32_t tile, int which, const Scr
 __device__ __forceinline__ bool wait_scale(const unsigned long long *word, const Scratch &X, SyncShared &S, int slot, float *scale)
 {
     if (wait_ready_at(word, 0ull, X, S, scale)) return true;
-    if (X.ends && threadIdx.x == 0) {
-        atomicAdd(X.defer_cnt, 1u);
-        give_up(X, &S.park[slot], 0u);
-    }
+    if (X.ends && threadIdx.x == 0) give_up(X, &S.park[slot], 0u);
     return false;
 }
 __device__ __forceinline__ bool block_scale(bool forms, int64_t b, const BlockSpan &sp, const Layout &L, const Scratch &X, int set,
@@ -1056,6 +1052,7 @@ __device__ __forceinline__ void park_segment(int32_t tile, int which, bool both,
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
+        atomicAdd(X.defer_cnt, both ? 2u : 1u);
         release_stores();
         leave_entry(S.park[which], both ? PARKED_BOTH : 0ull, X, set, tile, which, &S.own[which]);
     }

@@ -86,3 +86,14 @@ def test_what_waits_leave_is_finished_by_many(name):
         took.append(begin.elapsed_time(end) * 1e3)
     assert parked > 900
     assert min(took) < 300 + 1.0 * parked, (took, parked)
+
+
+@pytest.mark.parametrize("M", [2, 9])
+def test_every_parked_tile_is_counted(M):
+    """ef_plan_last_fallbacks counts tiles, whether a workgroup has one or two of them and whoever ends the call."""
+    offs = np.concatenate([[0], np.cumsum(LAYOUTS["whole_tiles"])])
+    plan, t = ef.ef_plan_create(offs, M), _tensors(offs, M, 7)
+    plan.set_persistent(False)
+    assert plan.server_pairs(M)
+    plan.tune(spin_limit=0)
+    assert _step(plan, t, M, False) == [M * int(offs[-1]) // T, int(offs[-1]) // T]
