@@ -350,8 +350,8 @@ int ef_worker_step_quality(const ef_plan *plan, int n_workers, const float *grad
  * ef_compressor_quality for callers that cannot allocate: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * kernels and the same results, bit for bit, but the per-tile sums go to a
- * fixed array in the library's own device image instead of plan-owned memory,
- * and the call itself calls no hipMalloc, hipFree or other allocating routine
+ * fixed array in the library's own device image instead of plan-owned memory
+ * (of which they use 12 bytes for each vector, ready between calls), and the call itself calls no hipMalloc, hipFree or other allocating routine
  * (plan creation, which happens earlier, still does).
  *
  * Capacity: ceil(d/4096) * n_vectors <= EF_QUALITY_STATIC_MAX_TILE_VECTORS
@@ -363,9 +363,9 @@ int ef_worker_step_quality(const ef_plan *plan, int n_workers, const float *grad
  *
  * All calls on one GPU share the one array, whatever their plan: calls that
  * overlap on the device (different streams, no ordering between them) race on
- * it and give wrong results; order them.  The array keeps the last call's
- * contents; nothing in it has to start at zero, since every word a call reads
- * it has written before.
+ * it and give wrong results; order them, and, like every call, with the others
+ * of their plan.  The array keeps the last call's contents; nothing in it has
+ * to start at zero, since every word of it that a call reads it has written before.
  */
 #define EF_QUALITY_STATIC_MAX_TILE_VECTORS 131072
 int ef_compressor_quality_static(const ef_plan *plan, int n_vectors, const float *v, int64_t stride,

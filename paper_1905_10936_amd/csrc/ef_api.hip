@@ -45,6 +45,7 @@ struct ef_plan {
     // device-side CallState is what the kernels go by; this only catches misuse at the boundary.
     mutable const float *lazy_buf[2];
     mutable int64_t lazy_stride_seen;
+    mutable bool phi_open;          // a diagnostics call has begun that did not come to its last kernel
     mutable int lazy_sets_seen;     // most workers any call since the last full flush has used
     float *d_lazy_scales;           // [nsets][lazy_stride]
     int lazy_stride;
@@ -1181,6 +1182,27 @@ int ef_apply_fused(const ef_plan *plan, float *params, const void *payload, floa
 
 namespace {
 
+// The kernels of a diagnostics call between them keep a word of the plan for each vector (see QualityArgs::phi): from here to
+// quality_end it is theirs.  After a call that has failed in between it has to be set again.
+int quality_begin(const ef_plan *plan, hipStream_t s)
+{
+    if (plan->phi_open) {
+        hipLaunchKernelGGL(ef::k_quality_reset, dim3(1), dim3(ef::THREADS), 0, s, plan->d_phi, plan->d_phi_done, plan->max_workers);
+        EF_HIP(hipGetLastError());
+    }
+    plan->phi_open = true;
+    return EF_OK;
+}
+
+int quality_end(const ef_plan *plan, const ef::QualityArgs &Q, int n_vectors, hipStream_t s)
+{
+    hipLaunchKernelGGL(ef::k_quality_blocks, dim3((unsigned)plan->n_cross + 1u, (unsigned)n_vectors), dim3(ef::THREADS), 0, s,
+                       plan->L, Q, (const int32_t *)plan->d_cross, (int)plan->n_cross);
+    EF_HIP(hipGetLastError());
+    plan->phi_open = false;
+    return EF_OK;
+}
+
 int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int64_t grad_stride, float *mom,
                      float *err, int64_t state_stride, float mu, float eta_prev, float eta, uint64_t *packed_signs,
                      int64_t signs_stride, float *scales, int64_t scales_stride, void *stream, double *quality)
@@ -1249,6 +1271,8 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
                       main_kernel_ends(plan, role, c, plan->L.n_grid, err, state_stride, scales, scales_stride);
     if (quality) {
         if (!aligned(quality, 8)) return EF_ERR_ALIGN;
+        const int rc_begin = quality_begin(plan, s);
+        if (rc_begin) return rc_begin;
     }
     if (role == ROLE_TICKET) {
         // the mixed tiles first, in a kernel of their own, then the persistent kernel
@@ -1317,10 +1341,7 @@ int worker_step_impl(const ef_plan *plan, int n_workers, const float *grad, int6
     Q.out = quality;
     Q.phi = plan->d_phi;
     Q.done = plan->d_phi_done;
-    hipLaunchKernelGGL(ef::k_quality_blocks, dim3((unsigned)plan->n_cross + 1u, (unsigned)n_workers), dim3(ef::THREADS), 0,
-                       s, plan->L, Q, (const int32_t *)plan->d_cross, (int)plan->n_cross);
-    EF_HIP(hipGetLastError());
-    return EF_OK;
+    return quality_end(plan, Q, n_workers, s);
 }
 
 int server_step_impl(const ef_plan *plan, int M, const uint64_t *packed_signs, int64_t in_signs_stride,
@@ -1457,13 +1478,12 @@ static int quality_launch(const ef_plan *plan, int n_vectors, const float *v, in
     Q.out = out;
     Q.phi = plan->d_phi;
     Q.done = plan->d_phi_done;
+    const int rc = quality_begin(plan, s);
+    if (rc) return rc;
     hipLaunchKernelGGL(ef::k_quality_tiles, dim3((unsigned)plan->L.ntiles, (unsigned)n_vectors), dim3(ef::THREADS), 0,
                        s, plan->L, Q);
     EF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(ef::k_quality_blocks, dim3((unsigned)plan->n_cross + 1u, (unsigned)n_vectors),
-                       dim3(ef::THREADS), 0, s, plan->L, Q, (const int32_t *)plan->d_cross, (int)plan->n_cross);
-    EF_HIP(hipGetLastError());
-    return EF_OK;
+    return quality_end(plan, Q, n_vectors, s);
 }
 
 static int quality_args(const ef_plan *plan, int n_vectors, const float *v, int64_t stride, const double *out)
