@@ -71,17 +71,21 @@ def _load_native(L):
     """The step calls' marshalling in C++ (csrc/ef_binding.cpp): it takes a call whose arguments are all as they should be
     and answers None otherwise; the functions below then go through ctypes, which says what is wrong."""
     global _native
-    if not os.path.exists(_build.BINDING):
-        try:
+    try:
+        if not os.path.exists(_build.BINDING):
             _build.build(lib=_build.BINDING)
-        except Exception as e:          # no compiler or no torch headers: calls take 1 to 3 us longer
-            import warnings
-            warnings.warn("ef_binding.cpp could not be built (%s): calls go through ctypes" % e, RuntimeWarning)
-            return
-    spec = importlib.util.spec_from_file_location("_ef_binding", _build.BINDING)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    module.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+        if _build.stale(_build.BINDING):
+            raise RuntimeError("it is older than its sources: run paper_1905_10936_amd/build.py")
+        spec = importlib.util.spec_from_file_location("_ef_binding", _build.BINDING)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        if module.built_for != _build.binding_built_for():
+            raise RuntimeError("it is built for %s, this is %s" % (module.built_for, _build.binding_built_for()))
+        module.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+    except Exception as e:              # no compiler, another torch or Python, an old file: calls take 1 to 3 us longer
+        import warnings
+        warnings.warn("%s cannot be used, calls go through ctypes: %s" % (os.path.basename(_build.BINDING), e), RuntimeWarning)
+        return
     _native = module
 
 

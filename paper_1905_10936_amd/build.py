@@ -1,5 +1,6 @@
 """Build libef.so (HIP kernels + C ABI) and libef_bench.so (the bandwidth probes bench.py runs
 beside it) for gfx950 with hipcc, and the Python binding's native calls (ef_binding.cpp) with the C++ compiler, in-tree."""
+import hashlib
 import os
 import subprocess
 import sys
@@ -38,13 +39,20 @@ FLAGS = [
 ]
 
 
+def binding_built_for():
+    """What the binding has compiled in and its loader compares: the layout of torch's tensors and of the calls' arguments."""
+    import torch
+    with open(os.path.join(ROOT, "include", "ef.h"), "rb") as f:
+        return "torch %s, ef.h %s" % (torch.__version__, hashlib.sha256(f.read()).hexdigest()[:16])
+
+
 def binding_command():
     """The binding sees tensors, so it is built against the torch that is installed; it has no device code."""
     import torch
     at = torch.__path__[0]
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DEF_BUILT_FOR="%s"' % binding_built_for(), "-I", os.path.join(ROOT, "include"),
              "-isystem", os.path.join(rocm, "include"), "-isystem", os.path.join(at, "include"),
              "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
              "-isystem", sysconfig.get_paths()["include"]],

@@ -397,4 +397,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ef_binding", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ef_binding(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__ef_binding(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    // what the loader asks for before it binds any entry point
+    if (m && PyModule_AddStringConstant(m, "built_for", EF_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -1,5 +1,6 @@
 """The native marshalling takes nothing it cannot vouch for: without a GPU every call is left to the path through ctypes."""
 import os
+import shutil
 import struct
 
 import pytest
@@ -26,3 +27,26 @@ def test_calls_it_cannot_vouch_for_are_left_to_ctypes():
         assert getattr(n, name)(key, t, t, t, 0.1, 0.1, 0.1, w, c, None) is None, name
     with pytest.raises(TypeError):
         n.bind(1)
+
+
+@pytest.mark.parametrize("what", ["no library", "old", "another torch or header"])
+def test_a_binding_that_cannot_be_used_leaves_the_library_usable(what, tmp_path, monkeypatch):
+    L = ef.lib()
+    if not os.path.exists(build.BINDING):
+        pytest.skip("ef_binding.cpp could not be built here")
+    place = str(tmp_path / "_ef_binding.so")
+    shutil.copy(build.BINDING, place)
+    monkeypatch.setitem(build.TARGETS, place, build.TARGETS[build.BINDING])
+    monkeypatch.setattr(build, "BINDING", place)
+    monkeypatch.setattr(ef, "_native", ef._ThroughCtypes())
+    if what == "no library":
+        with open(place, "wb") as f:
+            f.write(b"not a library")
+    elif what == "old":
+        os.utime(place, (1, 1))
+    else:
+        monkeypatch.setattr(build, "binding_built_for", lambda: "torch 0.0, ef.h 0")
+    with pytest.warns(RuntimeWarning, match="calls go through ctypes"):
+        ef._load_native(L)
+    assert isinstance(ef._native, ef._ThroughCtypes) and ef._native.apply() is None
+    assert ef.ef_strerror(-3)
