@@ -434,6 +434,7 @@ void small_tables(ef_plan *p, std::vector<ef::SmallTile> &out)
         r = ef::SmallTile();
         r.fb = fb;
         r.nseg = lb - fb + 1;
+        if (r.nseg > 1) p->small.words_of_tile = ef::TILE_WORDS;
         r.whole = fb == lb && end <= d;
         if (r.nseg <= ef::SMALL_BY_WAVE) {
             for (int i = 0; i < r.nseg; ++i) r.bound[i] = (int16_t)(o[fb + i] > start ? o[fb + i] - start : 0);
@@ -671,7 +672,7 @@ int build_device(ef_plan *p)
     mem.add(&p->d_phi_done, nv, Arena::ZERO);
     if (p->has_small) {
         mem.add(&p->d_small, small.size(), Arena::COPY, small.data());
-        mem.add(&p->d_small_words, mixed.empty() ? 0 : nt * ef::TILE_WORDS, Arena::LEAVE);
+        mem.add(&p->d_small_words, p->small.words_of_tile ? nt * ef::TILE_WORDS : ef::TILE_WORDS, Arena::LEAVE);
     }
     { const int rc_mem = mem.make(&p->d_arena); if (rc_mem) return rc_mem; }
     p->L.mixed_tiles = p->d_mixed;
@@ -702,18 +703,17 @@ int build_device(ef_plan *p)
     p->X.parked = p->d_parked;
     p->X.lazy_scales = p->d_lazy_scales;
     p->X.lazy_stride = p->lazy_stride;
-    if (p->L.n_mixed && !p->has_small) {
-        hipLaunchKernelGGL(ef::k_start_words, dim3((unsigned)p->L.n_mixed), dim3(ef::THREADS), 0, nullptr, p->L, p->d_words);
-        EF_HIP(hipGetLastError());
-    }
     if (p->has_small) {
         p->small.tiles = p->d_small;
-        p->small.words = mixed.empty() ? nullptr : p->d_small_words;
-        if (!mixed.empty()) {
-            hipLaunchKernelGGL(ef::k_small_words, dim3((unsigned)ntiles), dim3(ef::TILE_WORDS), 0, nullptr, p->L, p->d_small_words,
-                               p->d_words);
-            EF_HIP(hipGetLastError());
-        }
+        p->small.words = p->d_small_words;
+    }
+    if (p->small.words_of_tile) {
+        hipLaunchKernelGGL(ef::k_small_words, dim3((unsigned)ntiles), dim3(ef::TILE_WORDS), 0, nullptr, p->L, p->d_small_words,
+                           p->d_words);
+        EF_HIP(hipGetLastError());
+    } else if (p->L.n_mixed) {
+        hipLaunchKernelGGL(ef::k_start_words, dim3((unsigned)p->L.n_mixed), dim3(ef::THREADS), 0, nullptr, p->L, p->d_words);
+        EF_HIP(hipGetLastError());
     }
     p->user_fuse_limit = -1;
     // Which worker kernel for this layout.  The persistent kernel needs enough tiles per workgroup
@@ -794,7 +794,7 @@ bool small_update(const ef_plan *plan)
 
 ef::ApplyTables apply_tables(const ef_plan *plan, bool small)
 {
-    return {plan->L.d, plan->L.W, plan->L.tiles, small ? plan->small.words : plan->L.words};
+    return {plan->L.d, plan->L.W, plan->L.tiles, !small ? plan->L.words : plan->small.words_of_tile ? plan->small.words : nullptr};
 }
 
 // Scratch argument of one call over the sets [set_base, set_base + nsets).  Everything that

@@ -63,20 +63,25 @@ struct SmallShared {
 // record: a scale is two trips to memory away from the kernel's start, not four.
 struct SmallTables {
     const SmallTile *tiles;     // [ntiles]
-    const StartWord *words;     // [ntiles][TILE_WORDS], whole tiles too; rank: the number of the block in progress before the word, plus 1.
-                                // Null: the layout has only whole tiles
+    const StartWord *words;     // [ntiles][TILE_WORDS], whole tiles too; rank: the number of the block in progress before the word, plus 1
+    int words_of_tile;          // TILE_WORDS; 0: no tile has two segments, and there is one row of words that nobody looks at
 };
+
+// This thread's start word, as it is loaded: looked at only where the segments are wanted, so that nothing else waits for it (its wait
+// is one for all that was asked for before it).  No branch: it would end with that wait.
+__device__ __forceinline__ StartWord small_word(const SmallTables &Z, int32_t tile)
+{
+    return Z.words[tile * Z.words_of_tile + (int)(threadIdx.x >> 3)];
+}
 
 // This thread's four elements among the blocks.
 struct SmallPlace {
     unsigned starts;            // bit c: a segment starts at element c
     int block;                  // the block in progress before element 0 (one before the tile's first: none)
 };
-__device__ __forceinline__ SmallPlace small_place(const StartWord *words, int32_t tile)
+__device__ __forceinline__ SmallPlace small_place(const StartWord &w)
 {
-    SmallPlace q = {0u, 0};
-    if (!words) return q;
-    const StartWord w = words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
+    SmallPlace q;
     const unsigned sh = (threadIdx.x & 7u) * 4u;
     q.starts = (w.starts >> sh) & 15u;
     q.block = (int)w.rank + __popc(w.starts & ((1u << sh) - 1u)) - 1;
@@ -198,16 +203,17 @@ __device__ __forceinline__ bool small_gather(const SmallSpan &s, int own, double
 
 // Compression of the tile whose values are in p (four consecutive elements a thread): sign words, scales
 // of the blocks that end here, e' = p - Delta.  [bs, be): the block of segment threadIdx.x, in a tile of more than SMALL_BY_WAVE.
+// COUNTED: the workgroup is counted in (small_arrive), and before is the answer.
+template <bool COUNTED>
 __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const SmallTile &T,
-                                               const SmallPlace &at, int bound, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
-                                               float *err_tile, const Scratch &X, int set, SmallShared &S)
+                                               const StartWord &word, int64_t bs, int64_t be, int n_valid, uint64_t *signs, float *scales_out,
+                                               float *err_tile, const Scratch &X, unsigned before, int set, SmallShared &S)
 {
     const int32_t tile = blockIdx.x;
     const int lane = lane_id(), wave = wave_id();
     small_signs(p, n_valid, signs, (int64_t)tile * TILE, L.W);
     const int j0 = 4 * (int)threadIdx.x;
     const bool whole = T.whole != 0;
-    unsigned before;            // asked for behind the first barrier (see arrive)
     const double a[4] = {j0 + 0 < n_valid ? fabsf(p.x) : 0.f, j0 + 1 < n_valid ? fabsf(p.y) : 0.f,
                          j0 + 2 < n_valid ? fabsf(p.z) : 0.f, j0 + 3 < n_valid ? fabsf(p.w) : 0.f};
     const unsigned long long tag = set_tag(X, set);
@@ -219,7 +225,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     if (whole) {
         S.sum[threadIdx.x] = ((a[0] + a[1]) + a[2]) + a[3];
         __syncthreads();
-        before = arrive<COUNT_WAVE>(X);
+        if (!COUNTED) before = arrive<COUNT_WAVE>(X);
         if (wave == 0) {
             // the order of abs_sum and block_sum: a lane's four rows, the 64 lanes, the four quarters
             double q[4];
@@ -233,9 +239,8 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         *reinterpret_cast<float4 *>(&S.val[j0]) = make_float4(fabsf(p.x), fabsf(p.y), fabsf(p.z), fabsf(p.w));
         const int64_t start = (int64_t)tile * TILE;
         if (T.nseg <= SMALL_BY_WAVE) {
-            if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = bound;
             __syncthreads();
-            before = arrive<COUNT_WAVE>(X);
+            if (!COUNTED) before = arrive<COUNT_WAVE>(X);
 #pragma unroll 1
             for (int sg = (int)uniform_u32(threadIdx.x >> 6); sg < T.nseg; sg += SMALL_WAVES) {
                 const double total = segment_sum(S.val, (int)uniform_u32((unsigned)S.bound[sg]), (int)uniform_u32((unsigned)S.bound[sg + 1]));
@@ -244,7 +249,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         } else {
             if (threadIdx.x == 0) S.n_long = 0;
             __syncthreads();
-            before = arrive<COUNT_WAVE>(X);
+            if (!COUNTED) before = arrive<COUNT_WAVE>(X);
             for (int sg = threadIdx.x; sg < T.nseg; sg += SMALL_THREADS) {
                 const int64_t b = T.fb + sg;
                 const int lo = (int)max((sg < SMALL_THREADS ? bs : L.offs[b]) - start, (int64_t)0);
@@ -309,6 +314,7 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
     }
     __syncthreads();
     const int park_head = S.parked[0], park_tail = S.parked[1];
+    const SmallPlace at = small_place(word);
     int seg = T.nseg == 1 ? 0 : at.block - T.fb;
     float v[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
@@ -332,22 +338,35 @@ __device__ __forceinline__ void small_compress(float4 p, const Layout &L, const 
         __syncthreads();
     }
     if (!(head || tail)) {
-        if (wave == COUNT_WAVE) {
-            const unsigned left = arrived<COUNT_WAVE>(before, X);
-            if (lane == 0) S.left = left;
-        }
-        __syncthreads();
+        // nothing of its own is left
+        if (wave == COUNT_WAVE && arrived<COUNT_WAVE>(before, X)) finish_entries(S.own, false, X);
+        return;
     }
     const unsigned left = uniform_u32(S.left);
     // see end_call; all wavefronts are at hand here
     if (left | (unsigned)(park_head | park_tail)) finish_entries(S.own, wave == 0, X);
 }
 
-// The bound that this thread puts into SmallShared::bound later: storing it where it is asked for would wait for all that was asked
-// for before it, ahead of the loads of state and record.
+// The bound that this thread puts into SmallShared::bound ahead of small_compress: storing it where it is asked for would wait for all
+// that was asked for before it.
 __device__ __forceinline__ int small_bound(const SmallTables &Z, int32_t tile)
 {
     return Z.tiles[tile].bound[min((int)threadIdx.x, SMALL_BY_WAVE)];
+}
+
+__device__ __forceinline__ void put_bound(int bound, SmallShared &S)
+{
+    if (threadIdx.x <= SMALL_BY_WAVE) S.bound[threadIdx.x] = bound;
+}
+
+// Counts the workgroup in as soon as all its wavefronts have the call state in registers: one more barrier, while the tile's
+// data are on their way.  Not the server, whose scales wait for the record behind it: it counts behind the first barrier that the sums need
+// anyway.  us, here / there: worker of 65 tiles, 4 workers, 7.2 / 7.5, of ResNet-20 7.5 / 7.6; server of ResNet-20 7.5 / 7.2.
+__device__ __forceinline__ unsigned small_arrive(const Scratch &X)
+{
+    asm volatile("" ::"s"(X.tags), "s"(X.epoch), "s"(X.defer_cnt));
+    __syncthreads();
+    return arrive<COUNT_WAVE>(X);
 }
 
 template <bool MOM>
@@ -364,10 +383,11 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
     const float4 g = small_load4(A.grad + (int64_t)worker * A.grad_stride + start, n_valid);
     float4 m = g, e = small_load4(et, n_valid);
     if (MOM) m = small_load4(mt, n_valid);
-    const SmallPlace at = small_place(Z.words, tile);
+    const StartWord place = small_word(Z, tile);
     const int bound = small_bound(Z, tile);
-    const Scratch X = open_call(R);
     const SmallTile T = Z.tiles[tile];
+    const Scratch X = open_call(R);
+    const unsigned before = small_arrive(X);
     int64_t bs = 0, be = 1;
     if (T.nseg > SMALL_BY_WAVE && (int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
@@ -375,8 +395,9 @@ void k_worker_small(Layout L, ScratchRef R, WorkerArgs A, SmallTables Z)
     }
     worker_values4<MOM>(g, m, e, A.mu, A.r);
     if (MOM) small_store4(mt, n_valid, m);
-    small_compress(e, L, T, at, bound, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
-                   A.scales + (int64_t)worker * A.scales_stride, et, X, worker, S);
+    put_bound(bound, S);
+    small_compress<true>(e, L, T, place, bs, be, n_valid, A.signs + (int64_t)worker * A.signs_stride,
+                   A.scales + (int64_t)worker * A.scales_stride, et, X, before, worker, S);
 }
 
 constexpr int SMALL_CHUNK = 8, SMALL_GROUP = 4;     // workers whose sign words are in flight together, and are added up together
@@ -406,42 +427,53 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
     const int64_t start = (int64_t)tile * TILE;
     float *et = A.err + start;
     const float4 te = small_load4(et, n_valid);
-    const SmallPlace at = small_place(Z.words, tile);
+    const StartWord place = small_word(Z, tile);
     const int bound = small_bound(Z, tile);
-    const Scratch X = open_call(R);
+    // this thread's four sign bits are in one half-word of every payload (past the end: elements that are not stored)
+    const unsigned last = (unsigned)(2 * L.W - 1), hw = min((unsigned)(start >> 5) + (threadIdx.x >> 3), last);
+    const unsigned sh = (threadIdx.x & 7u) * 4u;
+    uint32_t word[SMALL_CHUNK];
+    small_words(A, 0, hw, word);
     const SmallTile T = Z.tiles[tile];
+    const Scratch X = open_call(R);
     int64_t bs = 0, be = 1;
     if (T.nseg > SMALL_BY_WAVE && (int)threadIdx.x < T.nseg) {
         bs = L.offs[T.fb + threadIdx.x];
         be = L.offs[T.fb + threadIdx.x + 1];
     }
-    // this thread's four sign bits are in one half-word of every payload (past the end: elements that are not stored)
-    const unsigned last = (unsigned)(2 * L.W - 1), hw = min((unsigned)(start >> 5) + (threadIdx.x >> 3), last);
-    const unsigned sh = (threadIdx.x & 7u) * 4u;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    uint32_t word[SMALL_CHUNK];
-    small_words(A, 0, hw, word);
     if (T.nseg == 1) {
 #pragma unroll 1
         for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
             float sc[SMALL_CHUNK];
-            load_scales(A, T.fb, i0, sc);           // past M 0, which changes no sum (one that began with +0 is never -0)
+            // vector loads: the eight scalar ones of load_scales took 0.5 us more (server call, 1 worker, 392 tiles 8.6 -> 8.0)
+            unsigned zero = 0u;
+            asm("" : "+v"(zero));
+#pragma unroll
+            for (int g = 0; g < SMALL_CHUNK; g += SMALL_GROUP)
+                if (g == 0 || i0 + g < A.M)
+#pragma unroll
+                    for (int u = g; u < g + SMALL_GROUP; ++u)
+                        sc[u] = A.scales_in[(int64_t)min(i0 + u, A.M - 1) * A.in_scales_stride + T.fb + zero];
             if (i0 > 0) small_words(A, i0, hw, word);
 #pragma unroll
             for (int g = 0; g < SMALL_CHUNK; g += SMALL_GROUP)
                 if (g == 0 || i0 + g < A.M)
 #pragma unroll
                     for (int u = g; u < g + SMALL_GROUP; ++u)
+                        if (i0 + u < A.M)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[u], (word[u] >> (sh + c)) & 1u);
+                            for (int c = 0; c < 4; ++c) acc[c] = acc[c] + signed_scale(sc[u], (word[u] >> (sh + c)) & 1u);
         }
+        put_bound(bound, S);
     } else {
         int seg[4];
-        {
+        const auto segments = [&] {
+            const SmallPlace at = small_place(place);
             int sg = at.block - T.fb;
 #pragma unroll
             for (int c = 0; c < 4; ++c) seg[c] = sg += (int)((at.starts >> c) & 1u);
-        }
+        };
         float *stage = reinterpret_cast<float *>(S.sum);
         const int rows = (A.M + SMALL_GROUP - 1) / SMALL_GROUP * SMALL_GROUP;
         if (T.nseg * rows <= SMALL_STAGE) {
@@ -451,7 +483,9 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
 #pragma unroll 1
                 for (int j = lane_id(); j < T.nseg; j += 64) stage[u * T.nseg + j] = u < A.M ? sc[j] : 0.0f;
             }
+            put_bound(bound, S);
             __syncthreads();
+            segments();
 #pragma unroll 1
             for (int i0 = 0; i0 < A.M; i0 += SMALL_CHUNK) {
                 if (i0 > 0) small_words(A, i0, hw, word);
@@ -468,6 +502,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
             }
         } else {
             // more segments than the stage holds: a gather for each element
+            segments();
 #pragma unroll 1
             for (int i = 0; i < A.M; ++i) {
                 const float *sc = A.scales_in + (int64_t)i * A.in_scales_stride + T.fb;
@@ -483,7 +518,7 @@ void k_server_small(Layout L, ScratchRef R, ServerArgs A, SmallTables Z, int set
     p.y = mean_of(acc[1], A.Mf, A.Minv) + A.r * te.y;
     p.z = mean_of(acc[2], A.Mf, A.Minv) + A.r * te.z;
     p.w = mean_of(acc[3], A.Mf, A.Minv) + A.r * te.w;
-    small_compress(p, L, T, at, bound, bs, be, n_valid, A.signs, A.scales, et, X, set, S);
+    small_compress<false>(p, L, T, place, bs, be, n_valid, A.signs, A.scales, et, X, 0u, set, S);
 }
 
 // Parameter update (see apply_tile), one workgroup of 1024 threads per tile.
@@ -495,12 +530,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_apply_small(ApplyTables Z, fl
     const int n_valid = tile_valid(Z.d, tile);
     const int64_t start = (int64_t)tile * TILE;
     const int64_t last = 2 * Z.W - 1, hw = (start >> 5) + (threadIdx.x >> 3);
-    const SmallPlace at = small_place(Z.words, tile);
+    StartWord place = {0u, 0u};
+    if (Z.words) place = Z.words[tile * TILE_WORDS + (int)(threadIdx.x >> 3)];
     const uint32_t word = reinterpret_cast<const uint32_t *>(signs)[hw < last ? hw : last];
     const float4 x4 = small_load4(x + start, n_valid);
     float4 m4 = x4;
     if (WD) m4 = small_load4(mt + start, n_valid);
     float xv[4] = {x4.x, x4.y, x4.z, x4.w}, mv[4] = {m4.x, m4.y, m4.z, m4.w};
+    const SmallPlace at = small_place(place);
     int block = Z.words ? at.block : Z.tiles[tile].fb;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
