@@ -1,4 +1,5 @@
 """The native marshalling takes nothing it cannot vouch for: without a GPU every call is left to the path through ctypes."""
+import inspect
 import os
 import shutil
 import struct
@@ -22,9 +23,20 @@ def test_calls_it_cannot_vouch_for_are_left_to_ctypes():
     assert n.apply(key, t, w, c, 0.1) is None and n.apply() is None  # another number of arguments
     assert n.apply(key, None, w, c, 0.1, None) is None and n.apply(None, t, w, c, 0.1, None) is None
     assert n.apply(key, t, w, c, 0.1, torch) is None                 # a stream of its own
-    for name in ("worker_step", "worker_step_sgd", "worker_step_fused", "worker_step_state", "server_step", "server_step_state",
-                 "server_step_fused", "apply_wd", "apply_fused", "compressor_quality"):
-        assert getattr(n, name)(key, t, t, t, 0.1, 0.1, 0.1, w, c, None) is None, name
+    # each with a call's own arguments, one of which is not on the GPU
+    f, state, m = 0.1, struct.pack("Pq", 0, 1), torch.zeros(16, dtype=torch.uint8)
+    calls = {"worker_step": (key, t, t, t, f, f, f, w, c), "worker_step_sgd": (key, t, t, f, f, w, c),
+             "worker_step_fused": (key, t, t, t, f, f, f, m), "worker_step_state": (key, state, t, f, f, f, w, c),
+             "server_step": (key, 1, w, c, t, f, f, w, c), "server_step_state": (key, state, 1, w, c, f, f, w, c),
+             "server_step_fused": (key, 1, m, t, f, f, m), "apply": (key, t, w, c, f), "apply_wd": (key, t, t, w, c, f, f, f),
+             "apply_fused": (key, t, m, f), "compressor_quality": (key, t, torch.zeros(2, dtype=torch.float64))}
+    assert len(calls) == len(ef._NATIVE_CALLS)
+    for name, args in calls.items():
+        # the wrapper's own call has as many
+        wrapper = inspect.signature(getattr(ef, "ef_" + name)).parameters
+        expected = [k for k in wrapper if k != "static_scratch"]
+        assert len(args) + 1 == len(expected), name
+        assert getattr(n, name)(*args, None) is None, name
     with pytest.raises(TypeError):
         n.bind(1)
 

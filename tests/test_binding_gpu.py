@@ -28,6 +28,20 @@ def _state(plan, n, pad, seed=1):
     return t
 
 
+class _Recorder:
+    """A native module, and which of its calls answered."""
+
+    def __init__(self, native):
+        self.native, self.answers = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            rc = getattr(self.native, name)(*args)
+            self.answers.append((name, rc is not None))
+            return rc
+        return call
+
+
 def _run(n, pad, number, stream=None):
     plan = ef.ef_plan_create(OFFS, n)
     t = _state(plan, n, pad)
@@ -60,13 +74,21 @@ def test_the_same_bits_as_through_ctypes(n, pad, number, monkeypatch):
     ef.lib()
     native = ef._native
     assert not isinstance(native, ef._ThroughCtypes)
+    recorder = _Recorder(native)
+    monkeypatch.setattr(ef, "_native", recorder)
     got = _run(n, pad, number)
+    # Python's numbers, NumPy's doubles (they are floats) and no stream: taken there, every one of the eleven; anything else: no number taken
+    taken = number in (float, np.float64)
+    assert len({name for name, _ in recorder.answers}) == len(ef._NATIVE_CALLS)
+    assert all(answered == (taken or name == "compressor_quality") for name, answered in recorder.answers)
     monkeypatch.setattr(ef, "_native", ef._ThroughCtypes())
     want = _run(n, pad, number)
     for k in want:
         assert torch.equal(got[k].view(torch.uint8), want[k].view(torch.uint8)), k
-    monkeypatch.setattr(ef, "_native", native)
+    recorder = _Recorder(native)
+    monkeypatch.setattr(ef, "_native", recorder)
     again = _run(n, pad, number, torch.cuda.Stream())       # a stream given: through ctypes
+    assert [answered for _, answered in recorder.answers[:3]] == [False] * 3
     for k in want:
         assert torch.equal(again[k].view(torch.uint8), want[k].view(torch.uint8)), k
 
