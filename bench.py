@@ -419,8 +419,8 @@ def main():
                        d_per_step_Gelem_s=round(d / (ms_per_step * 1e-3) / 1e9, 3)),
         "roofline": {
             "bound": "hbm",
-            "kernel": kernel + ", all M workers in one launch; timed as the whole ef_worker_step call (the short "
-                               "kernel that ends the call included)",
+            "kernel": kernel + ", all M workers in one launch; timed as the whole ef_worker_step call (with the short "
+                               "kernel after it, where one ends the call)",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

@@ -56,11 +56,12 @@ inline int64_t few_place(int64_t tile, int64_t t0, int n, bool first_shared, int
 //   up to eight workers, whole tiles and those of few segments: pairs, for any number of tiles (blocks of 64 tiles, 8 workers,
 //   1200 tiles 12.4 / 12.2, 2400 16.3 / 19.4, 12 000 74.8 / 80.1); with dense ones where not all of it is resident
 //   with one tile to a workgroup anyway (20 000 tiny blocks and four large ones, 1374 tiles 30.3 / 27.7, 2274 32.1 / 33.3)
-//   more, whole tiles alone: one tile to a workgroup (16 workers, blocks of 64, 1200 tiles 17.8 / 14.8, 2400 25.9 / 25.8,
-//   12 000 104 / 92), but where most tiles are in blocks of 1025 to 1536 of them (six of 1100, 72.6 / 78.6)
-//   more, with mixed tiles (9 workers; 16): 1788 29.4 / 26.8; 34.9 / 33.1, 2212 31.0 / 31.6; 37.2 / 37.4, 2680 34.3 / 37.4;
-//   38.5 / 48.5 (bottleneck networks), 19 469 189 / 192; 193 / 214 (a transformer, one tile of 400 mixed), but
-//   blocks of 64 and one ragged end, 5986 56.5 / 52.1; 55.8 / 56.2
+//   more, with mixed tiles (9 workers; 16): 1788 26.0 / 25.3; 33.2 / 31.5, 2680 27.9 / 35.2; 34.4 / 46.4 (bottleneck networks),
+//   19 469 156 / 189; 173 / 211 (a transformer, one tile of 400 mixed)
+//   more, whole tiles alone or all but: one tile to a workgroup, but where most tiles are in blocks of 1025 to 1536 of them (six
+//   of 1100, 54.4 / 75.0; 59.8 / 73.9).  That line is from before pairs had a table of the sums over twelve workers; today it would lie at the
+//   tiles that are resident, too (blocks of 64: 1200 tiles 15.1 / 13.7; 15.6 / 11.9, 2400 19.1 / 21.2; 20.2 / 21.5, 12 000
+//   77.7 / 87.4; 85.1 / 89.1, one ragged end, 5986 43.0 / 49.0; 47.3 / 51.7).
 inline bool server_pairs(bool many, int64_t tiles, int64_t mixed, bool dense, int64_t between, int64_t resident)
 {
     if (!many) return !dense || between > 0 || tiles > resident;

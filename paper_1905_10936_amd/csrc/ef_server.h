@@ -661,7 +661,7 @@ __device__ __forceinline__ unsigned server_pair(const Layout &L, const ServerArg
 // workers, 2^26: 4 us less), and elsewhere by server_pairs (ef_layout.h).  Workgroups per CU:
 //   pairs               seven (72 VGPRs), MANY six (77; 25 KB of LDS); one less: 46.3 us, MANY 916 against 826
 //   whole tiles only    eight (64 VGPRs; 2^28 elements, 8 workers, blocks of 2^20: 457 us against 465 at seven, 491 at six)
-//   tiles of few segments    eight (59 VGPRs), MANY seven (68); MANY on whole tiles only eight (62)
+//   tiles of few segments    eight (61 VGPRs), MANY seven (70); MANY on whole tiles only seven (68)
 //   dense tiles         six (80 VGPRs; 643 965 tiny blocks, 2 workers: 46.3 us against 49.4 at seven, where 6 spill;
 //                       16 workers, 300 000: 51.0 against 52.8)
 // MANY: more than SERVER_CHUNK workers.
