@@ -74,13 +74,12 @@ def _load_native(L):
     try:
         if not os.path.exists(_build.BINDING):
             _build.build(lib=_build.BINDING)
-        if _build.stale(_build.BINDING):
-            raise RuntimeError("it is older than its sources: run paper_1905_10936_amd/build.py")
         spec = importlib.util.spec_from_file_location("_ef_binding", _build.BINDING)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         if module.built_for != _build.binding_built_for():
-            raise RuntimeError("it is built for %s, this is %s" % (module.built_for, _build.binding_built_for()))
+            raise RuntimeError("it is built for %s, this is %s: run paper_1905_10936_amd/build.py" %
+                               (module.built_for, _build.binding_built_for()))
         module.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
     except Exception as e:              # no compiler, another torch or Python, an old file: calls take 1 to 3 us longer
         import warnings

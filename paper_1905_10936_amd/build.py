@@ -40,10 +40,15 @@ FLAGS = [
 
 
 def binding_built_for():
-    """What the binding has compiled in and its loader compares: the layout of torch's tensors and of the calls' arguments."""
+    """What the binding has compiled in and its loader compares: the torch whose tensors it takes, and its sources (their
+    contents: a copied tree's times say nothing)."""
     import torch
-    with open(os.path.join(ROOT, "include", "ef.h"), "rb") as f:
-        return "torch %s, ef.h %s" % (torch.__version__, hashlib.sha256(f.read()).hexdigest()[:16])
+    digest = hashlib.sha256()
+    src, deps = TARGETS[BINDING]
+    for name in [src] + deps:
+        with open(name, "rb") as f:
+            digest.update(f.read())
+    return "torch %s, sources %s" % (torch.__version__, digest.hexdigest()[:16])
 
 
 def binding_command():

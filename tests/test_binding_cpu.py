@@ -41,7 +41,7 @@ def test_calls_it_cannot_vouch_for_are_left_to_ctypes():
         n.bind(1)
 
 
-@pytest.mark.parametrize("what", ["no library", "old", "another torch or header"])
+@pytest.mark.parametrize("what", ["no library", "other sources", "another torch"])
 def test_a_binding_that_cannot_be_used_leaves_the_library_usable(what, tmp_path, monkeypatch):
     L = ef.lib()
     if not os.path.exists(build.BINDING):
@@ -54,10 +54,14 @@ def test_a_binding_that_cannot_be_used_leaves_the_library_usable(what, tmp_path,
     if what == "no library":
         with open(place, "wb") as f:
             f.write(b"not a library")
-    elif what == "old":
-        os.utime(place, (1, 1))
+    elif what == "other sources":
+        header = str(tmp_path / "ef.h")
+        shutil.copy(build.TARGETS[place][1][0], header)
+        with open(header, "a") as f:
+            f.write("int ef_one_more(void);\n")
+        monkeypatch.setitem(build.TARGETS, place, (build.TARGETS[place][0], [header]))
     else:
-        monkeypatch.setattr(build, "binding_built_for", lambda: "torch 0.0, ef.h 0")
+        monkeypatch.setattr(torch, "__version__", "0.0")
     with pytest.warns(RuntimeWarning, match="calls go through ctypes"):
         ef._load_native(L)
     assert isinstance(ef._native, ef._ThroughCtypes) and ef._native.apply() is None
